@@ -280,7 +280,7 @@ const char* isa_strerror(int status);
 int isa_last_hip_error(void);
 
 /* Selects the attention kernels used for bf16 problems with D = 128 and block = 128:
- * 1 (default) = MFMA kernels, 0 = the portable scalar kernels that also serve fp32 and the other shapes.
+ * 1 (default) = MFMA kernels, 0 = the general matrix-core kernel that also serves fp32 and the other shapes.
  * Returns the previous setting.  Process-wide; meant for tests and comparisons. */
 int isa_set_mfma(int enabled);
 

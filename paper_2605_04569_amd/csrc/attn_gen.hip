@@ -1,0 +1,604 @@
+// General matrix-core attention kernel: every dtype, head dimension and block size that the pipelined bf16 D = 128,
+// block = 128 kernels do not cover (and those too when they are switched off): exact online-softmax attention (Alg. 2
+// Part A), block-wise 0-th order Taylor attention with and without exact sets (Sec. 3, Eq. 3-4; Alg. 2 Parts A+B), dense.
+//
+// Precision: everything that a plain fp32 evaluation holds in fp32 keeps its 24 bits here.
+//   fp32 tensors: both products with v_mfma_f32_16x16x4_f32.
+//   bf16 tensors: scores of tokens with v_mfma_f32_16x16x32_bf16 (products of bf16 numbers are exact in fp32); the softmax
+//     weights and the fp32 block means are cut into three bf16 terms whose sum is the fp32 number (8 bits each), and
+//     the product is the sum of the terms' products: 3 matrix instructions for weights x tokens, 3 for queries x means, 8
+//     for weights x means (the term low x low, below 2^-32 of the result, is left out).
+//
+// Shape.  A workgroup of 4 waves owns 64 QT query rows, QT 16-query tiles per wave (QT = 1 when a launch has so few rows
+// that 128 a workgroup would leave compute units idle).  With r = lane % 16, g = lane / 16 the scores are computed
+// transposed (S^T = K Q^T): lane (r, g) holds keys 16 kt + 4 g + i of query 16 qt + r, which is the operand layout of the
+// second product (O^T = V^T P^T), so the weights never leave their registers; V is read transposed out of its row-major
+// tile (ds_read_b64_tr_b16 for bf16; for fp32 a lane's four channels of a row serve four output tiles).  Tiles of 64
+// bf16 (32 fp32) rows go global -> LDS directly, one tile ahead, two stages, 16-byte chunks XOR-swizzled by row.  A stage
+// is 256 D bytes either way, so at least two workgroups share a compute unit and one's softmax runs beside the
+// other's matrix instructions; there is no hand-made interleaving here.
+//
+// What bounds it (measured, 24 heads of 64 channels, 15 600 tokens in blocks of 64, keep 0.5, full 0.25): instruction issue. A weight
+// costs 9.4 vector instructions (5.5 of them the exact cut into three terms; taking the differences with the bf16 dot
+// instruction was slower and not exact) beside 2 matrix instructions; counters of the dense launch: issue port busy
+// 85 % of the cycles, matrix pipe 38 %, no LDS bank conflicts.  Whole call 11.6 -> 0.73 ms against a kernel of one
+// row per four lanes in scalar arithmetic (25 -> 400 TFLOP/s); fp32, 8 heads of 128 channels, 5280 tokens: 1.89 -> 0.40 ms.
+#include <type_traits>
+
+#include "attn_mfma.h"
+
+namespace isa {
+
+#define ISA_GEN_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+namespace {
+
+typedef short short4v __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) short4v* lds_s4_ptr;
+
+struct GenArgs {
+  AttnArgs a;
+  int slots_long, slots_taylor;     // work items per (batch, head) of the exact branch / of the Taylor branch (largest of the batch)
+  int per_xcd_long, per_xcd_taylor; // and per XCD, over all (batch, head)s
+};
+
+__device__ __forceinline__ void dma16(const void* src, uint32_t lds_addr) {      // lane i -> LDS bytes lds_addr + 16 i
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_addr), "v"(src) : "memory", "m0");
+}
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(size_t)(__attribute__((address_space(3))) const void*)p;
+}
+__device__ __forceinline__ f32x4 mfma_bf(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mfma_f(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ float bits_f(uint32_t u) { return __uint_as_float(u); }
+
+// Eight fp32 numbers as three bf16 fragments that add up to them: every term is the leading 8 bits of what the terms before it
+// left over (cut off, not rounded, so the differences are exact and the third term ends at bit 24).
+__device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
+  uint32_t w[3][4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float a = x[2 * e], b = x[2 * e + 1];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+      w[k][e] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);              // high halves: a below, b above
+      if (k < 2) {
+        a -= bits_f(ua & 0xffff0000u);
+        b -= bits_f(ub & 0xffff0000u);
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) t[k] = __builtin_bit_cast(bf16x8, make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]));
+}
+
+// The (batch, head) at position p when they are ordered XCD by XCD (those with the same remainder modulo 8 together).
+__device__ __forceinline__ int head_at(int p, int n) {
+  const int a = n / N_XCD, r = n % N_XCD;
+  if (p < r * (a + 1)) return (p % (a + 1)) * N_XCD + p / (a + 1);
+  p -= r * (a + 1);
+  return (p % a) * N_XCD + r + p / a;
+}
+
+}  // namespace
+
+// One work item: 64 QT rows of one query block (QT = 2, block 64: of two neighbours in the list).  FULL32 evaluates the
+// products of fp32 numbers with fp32 matrix instructions instead of bf16 terms: slower, but infinities go through them
+// as through a multiplication (a term that is zero turns an infinity into NaN).  Returns whether this wave's results are
+// all finite; with FULL32 = false nothing is stored if some wave's are not, and the caller runs the item again.
+template <typename T, int D, int QT, bool FULL32>
+__device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* lds, int bhid, bool taylor, int slot) {
+  constexpr bool BF = sizeof(T) == 2;
+  constexpr int KTOK = BF ? 64 : 32;                   // tokens per tile; tiles of means hold 32
+  constexpr int NT = D / 16;                           // 16-channel tiles
+  constexpr int TILE = 128 * D;                        // bytes of a K (or V) tile, token or mean
+  constexpr int CT = D * (int)sizeof(T) / 16, CM = D / 4;      // 16-byte chunks per row of token / mean tiles
+  constexpr int ST = (CT < 16 ? CT : 16) - 1, SM = 15; // swizzle: chunk c of row r sits at c ^ (r & S)
+  constexpr int NI = D / 32;                           // 1 KB loads per wave, tile and tensor
+  constexpr int ROWS = 64 * QT;
+  const AttnArgs& a = ga.a;
+  float* const wts = reinterpret_cast<float*>(lds + 4 * TILE);         // [stage][block of the item][32]: weights of a mean tile's slots
+
+  const int b = bhid / a.geo.H, h = bhid % a.geo.H;
+  const BatchCounts c = a.cnt.b[b];
+  const int T_max = a.geo.T_max, block = a.geo.block;
+  const long long bh = bhid;
+  const int* const kvl = a.dense ? nullptr : a.kv_list + bh * T_max;
+  const int n_kv = a.dense ? c.T : c.T_new;
+  const int* const bs = a.blk_start + b * T_max;
+  const int* const bn = a.blk_n + b * T_max;
+  const long long tbase = (long long)b * a.geo.stride_b + (long long)h * a.geo.stride_h;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, g = lane >> 4;
+
+  // this wave's query block and rows
+  const bool pair = QT == 2 && block == 64;
+  const int subs = pair ? 1 : block / ROWS;
+  const int n_list = a.dense ? c.T : taylor ? c.n_flat : c.n_full;
+  const int entry0 = pair ? 2 * slot : slot / subs;
+  const int own = pair ? wave >> 1 : 0;                // which of the item's blocks
+  const int entry = entry0 + own;
+  const bool active = entry < n_list;
+  const int e_use = active ? entry : entry0;
+  const int qi = a.dense ? e_use : block_in_range((taylor ? a.flat_list : a.full_list)[bh * T_max + e_use], c.T);
+  const int n_q = active ? bn[qi] : 0, q_start = bs[qi];
+  const int row0 = pair ? (wave & 1) * 32 : (slot % subs) * ROWS + wave * 16 * QT;
+  const bool sets = taylor && a.exact_mask && c.k_exact > 0;
+  const uint32_t* const mrow = sets ? a.exact_mask + (bh * T_max + entry0) * a.cnt.mask_words : nullptr;
+  const int n_sets = pair && entry0 + 1 < n_list ? 2 : 1;              // bit rows of the item
+  auto set_bits = [&](int t) -> int {                  // bit u: kv_list[t] is in the exact set of the item's block u
+    int bits = (mrow[t >> 5] >> (t & 31)) & 1;
+    if (n_sets == 2) bits |= ((mrow[a.cnt.mask_words + (t >> 5)] >> (t & 31)) & 1) << 1;
+    return bits;
+  };
+
+  // Q fragments: bf16 lane (r, g) holds channels 32 ks + 8 g .. + 7 of query 16 qt + r, fp32 channels 16 t + 4 g .. + 3
+  bf16x8 qb[QT][D / 32];
+  f32x4 qf[QT][NT];
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    const int row = row0 + 16 * qt + r16;
+    const T* qp = (const T*)a.q + tbase + (long long)(q_start + (row < n_q ? row : 0)) * a.geo.stride_t;
+    if constexpr (BF) {
+#pragma unroll
+      for (int ks = 0; ks < D / 32; ++ks) qb[qt][ks] = *reinterpret_cast<const bf16x8*>(qp + 32 * ks + 8 * g);
+    } else {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) qf[qt][t] = *reinterpret_cast<const f32x4*>(qp + 16 * t + 4 * g);
+    }
+  }
+
+  // ---- the sequence of tiles: the tokens of the listed blocks (Taylor: of the blocks of the exact sets), then, for
+  // Taylor blocks, the means of the list.  The lanes hold the table rows of 64 list entries at a time.
+  int c_start = 0, c_n = 0, c_bits = 0, cbase = -64;
+  unsigned long long todo = 0ull;
+  struct Tile { int start, nk, bits; bool mean, end; };
+  Tile at = {0, 0, 3, false, false};                   // the tile that was described last
+  int left = 0;                                        // tokens of its block that come after it
+  auto next_tile = [&]() {
+    if (!at.mean) {
+      if (left > 0) {
+        at.start += KTOK;
+        at.nk = min(KTOK, left);
+        left -= KTOK;
+        return;
+      }
+      while (todo == 0ull && (!taylor || sets) && cbase + 64 < n_kv) {
+        cbase += 64;
+        const int t = cbase + lane;
+        const int j = t < n_kv ? (kvl ? block_in_range(kvl[t], c.T) : t) : 0;
+        c_bits = t < n_kv ? (taylor ? set_bits(t) : 3) : 0;
+        c_start = bs[j];
+        c_n = bn[j];
+        todo = __ballot(c_bits != 0);
+      }
+      if (todo != 0ull) {
+        const int l = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        at.start = __builtin_amdgcn_readlane(c_start, l);
+        at.bits = __builtin_amdgcn_readlane(c_bits, l);
+        const int n = __builtin_amdgcn_readlane(c_n, l);
+        at.nk = min(KTOK, n);
+        left = n - KTOK;
+        return;
+      }
+      at.start = -32;
+      at.mean = taylor;
+      at.end = !taylor;
+    }
+    at.start += 32;                                    // mean tiles: position in kv_list
+    at.nk = min(32, n_kv - at.start);
+    at.bits = 3;
+    if (at.nk <= 0) at.end = true;
+  };
+  auto issue = [&](const Tile& t, int stage) {
+    unsigned char* const kdst = lds + stage * 2 * TILE;
+    int li = lane;
+    asm volatile("" : "+v"(li));                       // worked out for every tile, not kept in registers
+    if (!t.mean) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int p = (wave * NI + i) * 64 + li, row = p / CT, ch = (p % CT) ^ (row & ST);
+        const long long off = tbase + (long long)(t.start + min(row, t.nk - 1)) * a.geo.stride_t + ch * (16 / (int)sizeof(T));
+        const uint32_t dst = lds_addr(kdst) + (wave * NI + i) * 1024;
+        dma16((const T*)a.k + off, dst);
+        dma16((const T*)a.v + off, dst + TILE);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int p = (wave * NI + i) * 64 + li, row = p / CM, ch = (p % CM) ^ (row & SM);
+        const int j = block_in_range(kvl[t.start + min(row, t.nk - 1)], c.T);
+        const long long off = (bh * T_max + j) * D + ch * 4;
+        const uint32_t dst = lds_addr(kdst) + (wave * NI + i) * 1024;
+        dma16(a.kc + off, dst);
+        dma16(a.vc + off, dst + TILE);
+      }
+      if (tid < 64) {                                  // slot tid % 32 as block tid / 32 of the item sees it: n_j, or 0
+        const int s = t.start + (tid & 31);
+        float w = 0.f;
+        if ((tid & 31) < t.nk && !(sets && ((set_bits(s) >> (tid >> 5)) & 1))) w = (float)bn[block_in_range(kvl[s], c.T)];
+        wts[stage * 64 + tid] = w;
+      }
+    }
+  };
+
+  f32x4 acc[NT][QT];                                   // element i: bf16: channel 16 ct + 4 g + i; fp32: see the store
+  float neg_m[QT], l_run[QT];                          // minus the running maximum (log2 domain, scaled); sums per lane
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    neg_m[qt] = -M_INIT;
+    l_run[qt] = 0.f;
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const float cscale = 1.4426950408889634f / sqrtf((float)D);
+
+  // ---- a half tile: 32 keys from row `r0` of the stage; `nk` of them real; wt: weights of a mean tile's 32 slots
+  auto half = [&](const unsigned char* kb, const unsigned char* vb, const int r0, const int nk, const auto mean_c, const float* wt)
+      __attribute__((always_inline)) {
+    constexpr bool mean = decltype(mean_c)::value;
+    // the lane's coordinates for the reads of mean tiles: opaque, so that their many LDS addresses are worked out where they
+    // are used instead of being kept in registers through the loop
+    int rm = r16, gm = g;
+    if (BF) asm volatile("" : "+v"(rm), "+v"(gm));
+    f32x4 s[2][QT];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) s[kt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (!BF) {
+      f32x4 k4[2][2];                                  // [t % 2][kt]: the fragments of a step are read a step ahead
+      auto k_load = [&](int t) {
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+          k4[t & 1][kt] = *reinterpret_cast<const f32x4*>(kb + ((16 * kt + r16) * CM + ((4 * t + g) ^ r16)) * 16);
+      };
+      k_load(0);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        ISA_GEN_FENCE();
+        if (t + 1 < NT) k_load(t + 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt) s[kt][qt] = mfma_f(k4[t & 1][kt][i], qf[qt][t][i], s[kt][qt]);
+      }
+    } else if constexpr (!mean) {
+#pragma unroll
+      for (int ks = 0; ks < D / 32; ++ks)
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+          const bf16x8 k8 = *reinterpret_cast<const bf16x8*>(kb + ((r0 + 16 * kt + r16) * CT + ((4 * ks + g) ^ (r16 & ST))) * 16);
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt) s[kt][qt] = mfma_bf(k8, qb[qt][ks], s[kt][qt]);
+        }
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < D / 32; ++ks)
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+          ISA_GEN_FENCE();
+          float x[8];
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const f32x4 k4 = *reinterpret_cast<const f32x4*>(kb + ((16 * kt + rm) * CM + ((8 * ks + 2 * gm + u) ^ rm)) * 16);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[4 * u + i] = k4[i];
+          }
+          if constexpr (FULL32) {
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt) {
+              uint4 qw = __builtin_bit_cast(uint4, qb[qt][ks]);          // converted here, not kept as fp32
+              asm volatile("" : "+v"(qw.x), "+v"(qw.y), "+v"(qw.z), "+v"(qw.w));
+              const uint32_t q2[4] = {qw.x, qw.y, qw.z, qw.w};
+#pragma unroll
+              for (int e = 0; e < 8; ++e)
+                s[kt][qt] = mfma_f(x[e], bits_f(e & 1 ? q2[e >> 1] & 0xffff0000u : q2[e >> 1] << 16), s[kt][qt]);
+            }
+          } else {
+            bf16x8 k3[3];
+            split3(x, k3);
+#pragma unroll
+            for (int u = 2; u >= 0; --u)
+#pragma unroll
+              for (int qt = 0; qt < QT; ++qt) s[kt][qt] = mfma_bf(k3[u], qb[qt][ks], s[kt][qt]);
+          }
+        }
+    }
+    // masks: slots past the end, mean slots with weight 0
+    f32x4 w4[2];
+    if constexpr (mean) {
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+        w4[kt] = *reinterpret_cast<const f32x4*>(wt + 16 * kt + 4 * g);
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[kt][qt][i] = w4[kt][i] > 0.f ? s[kt][qt][i] : -INFINITY;
+      }
+    } else if (nk < 32) {
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[kt][qt][i] = 16 * kt + 4 * g + i < nk ? s[kt][qt][i] : -INFINITY;
+      asm volatile("");                                // a branch around all of it, not selects in every full tile
+    }
+    // running maxima, raised only when a score exceeds one by more than 2^tau
+    float mx[QT];
+    unsigned long long raise = 0ull;
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      mx[qt] = s[0][qt][0];
+#pragma unroll
+      for (int e = 1; e < 7; e += 2) mx[qt] = fmaxf(fmaxf(mx[qt], s[e >> 2][qt][e & 3]), s[(e + 1) >> 2][qt][(e + 1) & 3]);
+      mx[qt] = fmaxf(mx[qt], s[1][qt][3]) * cscale;
+      raise |= __ballot(mx[qt] + neg_m[qt] > RESCALE_TAU);
+    }
+    if (raise != 0ull) {
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        float m = fmaxf(mx[qt], __shfl_xor(mx[qt], 16, 64));
+        m = fmaxf(m, __shfl_xor(m, 32, 64));
+        m = fmaxf(m, -neg_m[qt]);
+        const float alpha = __builtin_amdgcn_exp2f(-neg_m[qt] - m);
+        neg_m[qt] = -m;
+        l_run[qt] *= alpha;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) acc[ct][qt] *= alpha;
+      }
+    }
+    float p[QT][8];                                    // element 4 kt + i
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          p[qt][4 * kt + i] = __builtin_amdgcn_exp2f(fmaf(s[kt][qt][i], cscale, neg_m[qt]));
+    if constexpr (mean) {                              // Eq. 4: a mean key weighs its block's token count
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[qt][e] *= w4[e >> 2][e & 3];
+    }
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) l_run[qt] += p[qt][e];
+    // O^T += V^T P^T
+    if constexpr (!BF) {
+      f32x4 v4[2][NT / 4];                             // tiles 4 u + e: output row m is channel 64 u + 4 m + e
+      auto v_load = [&](int n) {                       // key slot 16 kt + 4 g + i, n = 4 kt + i
+        const int row = 4 * (n & 4) + 4 * g + (n & 3);
+#pragma unroll
+        for (int u = 0; u < NT / 4; ++u) {
+          v4[n & 1][u] = *reinterpret_cast<const f32x4*>(vb + (row * CM + ((16 * u + r16) ^ (row & SM))) * 16);
+          if (mean ? w4[n >> 2][n & 3] == 0.f : nk < 32 && row >= nk) v4[n & 1][u] = f32x4{0.f, 0.f, 0.f, 0.f};      // what is masked may hold anything
+        }
+      };
+      v_load(0);
+#pragma unroll
+      for (int n = 0; n < 8; ++n) {
+        ISA_GEN_FENCE();
+        if (n + 1 < 8) v_load(n + 1);
+#pragma unroll
+        for (int u = 0; u < NT / 4; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt) acc[4 * u + e][qt] = mfma_f(v4[n & 1][u][e], p[qt][n], acc[4 * u + e][qt]);
+      }
+    } else if constexpr (FULL32) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        asm volatile("" : "+v"(rm), "+v"(gm));
+        const int row = (e & 4) * 4 + 4 * gm + (e & 3);
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+          ISA_GEN_FENCE();
+          float v;
+          if constexpr (mean) v = *reinterpret_cast<const float*>(vb + (row * CM + ((4 * ct + (rm >> 2)) ^ (row & SM))) * 16 + (rm & 3) * 4);
+          else v = bits_f((uint32_t)*reinterpret_cast<const uint16_t*>(vb + ((r0 + row) * CT + ((2 * ct + (rm >> 3)) ^ (row & ST))) * 16 + (rm & 7) * 2) << 16);
+          if (mean ? w4[e >> 2][e & 3] == 0.f : row >= nk) v = 0.f;
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt) acc[ct][qt] = mfma_f(v, p[qt][e], acc[ct][qt]);
+        }
+      }
+    } else {
+      bf16x8 p3[QT][3];
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) split3(p[qt], p3[qt]);
+      if constexpr (!mean) {
+        const int tr_row = 4 * g + (r16 >> 2);         // see the transposed reads of the backward kernel
+        constexpr int GR = 4;                          // output tiles whose V^T fragments are held at a time
+#pragma unroll
+        for (int c0 = 0; c0 < NT; c0 += GR) {
+          bf16x8 v8[GR];
+#pragma unroll
+          for (int n = 0; n < GR; ++n) {
+            const unsigned char* src = vb + ((r0 + tr_row) * CT + ((2 * (c0 + n) + ((r16 & 3) >> 1)) ^ (tr_row & ST))) * 16 + (r16 & 1) * 8;
+            const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src));
+            const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src + 16 * CT * 16));
+            v8[n] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+          }
+#pragma unroll
+          for (int u = 2; u >= 0; --u)                 // the small terms first
+#pragma unroll
+            for (int n = 0; n < GR; ++n)
+#pragma unroll
+              for (int qt = 0; qt < QT; ++qt) acc[c0 + n][qt] = mfma_bf(v8[n], p3[qt][u], acc[c0 + n][qt]);
+        }
+      } else {
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+          ISA_GEN_FENCE();
+          float x[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int row = (e & 4) * 4 + 4 * gm + (e & 3);
+            x[e] = *reinterpret_cast<const float*>(vb + (row * CM + ((4 * ct + (rm >> 2)) ^ (row & SM))) * 16 + (rm & 3) * 4);
+          }
+          bf16x8 v3[3];
+          split3(x, v3);
+#pragma unroll
+          for (int u = 2; u >= 0; --u)
+#pragma unroll
+            for (int w = 2; w >= 0; --w)
+              if (u + w < 4) {
+#pragma unroll
+                for (int qt = 0; qt < QT; ++qt) acc[ct][qt] = mfma_bf(v3[u], p3[qt][w], acc[ct][qt]);
+              }
+        }
+      }
+    }
+  };
+
+  // ---- the loop: the loads of tile n + 1 fly while tile n is multiplied
+  next_tile();
+  Tile cur = at;
+  if (!cur.end) issue(cur, 0);
+  int stage = 0;
+  auto tiles = [&](const auto mean_c) __attribute__((always_inline)) {
+    constexpr bool mean = decltype(mean_c)::value;
+    for (; !cur.end && cur.mean == mean; stage ^= 1) {
+      next_tile();                                     // its table reads wait together with the tile loads
+      const Tile nxt = at;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();                                 // tile n is complete; everybody has left tile n - 1, whose stage is filled next
+      if (!nxt.end) issue(nxt, stage ^ 1);
+      const unsigned char* kb = lds + stage * 2 * TILE;
+      if ((cur.bits >> own) & 1) {                     // wave-uniform
+#pragma unroll 1
+        for (int r0 = 0; r0 < cur.nk; r0 += 32) half(kb, kb + TILE, r0, cur.nk - r0, mean_c, wts + stage * 64 + own * 32);
+      }
+      cur = nxt;
+    }
+  };
+  // two loops: the kinds of tile share no code path through which the accumulators would have to be moved
+  tiles(std::false_type{});
+  tiles(std::true_type{});
+  __syncthreads();                                     // nobody reads LDS any more: the caller may start another pass
+
+  // ---- normalise, check, store
+  float inv[QT];
+  bool ok = true;
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    float l = l_run[qt];
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    inv[qt] = 1.0f / l;
+    if (row0 + 16 * qt + r16 < n_q)
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ok = ok && fabsf(acc[ct][qt][i] * inv[qt]) < INFINITY;
+  }
+  if constexpr (BF && !FULL32)
+    if (__syncthreads_or(!ok)) return false;
+  // coarse residual (Alg. 1 Stage 5): the block's row of O_coarse, the same for all of its tokens
+  const float* const oc = (a.ocoarse && !a.dense) ? a.ocoarse + (bh * T_max + qi) * D : nullptr;
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    const int row = row0 + 16 * qt + r16;
+    if (row >= n_q) continue;
+    T* op = (T*)a.out + tbase + (long long)(q_start + row) * a.geo.stride_t;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {                     // four consecutive channels at a time
+      float r[4];
+      const int ch = BF ? 16 * n + 4 * g : 64 * (n >> 2) + 16 * g + 4 * (n & 3);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        r[i] = (BF ? acc[n][qt][i] : acc[4 * (n >> 2) + i][qt][n & 3]) * inv[qt];
+        if (oc) r[i] = fmaf(a.gamma, oc[ch + i], r[i]);
+      }
+      if constexpr (BF) {
+        *reinterpret_cast<uint2*>(op + ch) = make_uint2(f2bf(r[0]) | ((uint32_t)f2bf(r[1]) << 16), f2bf(r[2]) | ((uint32_t)f2bf(r[3]) << 16));
+      } else {
+        *reinterpret_cast<float4*>(op + ch) = make_float4(r[0], r[1], r[2], r[3]);
+      }
+    }
+  }
+  return true;
+}
+
+// D = 128: 66 KB of LDS, two workgroups per compute unit; D = 64: registers for three (QT = 2) or four
+template <typename T, int D, int QT>
+__global__ __launch_bounds__(256, D == 128 ? 2 : QT == 1 ? 4 : 3) void k_attn_gen(GenArgs ga) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[512 * D + 2 * 64 * 4];
+  // Workgroup ids go round-robin over the 8 XCDs.  The items of all (batch, head)s, ordered XCD by XCD (every 8th head) and
+  // head after head, are cut into 8 equal ranges, one per XCD: with a multiple of 8 heads an XCD works through whole heads
+  // of its own, whose keys and values its L2 then holds, and with any other number no XCD is left idle.  The long items
+  // (exact branch) come first.
+  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+  const bool taylor = j >= ga.per_xcd_long;
+  const int n_bh = ga.a.geo.B * ga.a.geo.H;
+  const int slots = taylor ? ga.slots_taylor : ga.slots_long, per = taylor ? ga.per_xcd_taylor : ga.per_xcd_long;
+  const long long idx = (long long)xcd * per + (taylor ? j - ga.per_xcd_long : j);
+  if (idx >= (long long)n_bh * slots) return;
+  const int bhid = head_at((int)(idx / slots), n_bh), slot = (int)(idx % slots);
+  const BatchCounts c = ga.a.cnt.b[bhid / ga.a.geo.H];
+  const int n_list = ga.a.dense ? c.T : taylor ? c.n_flat : c.n_full;
+  // QT-tile slot n of a list: rows 64 QT n .. of a 128-row block's sequence of rows, or block n / blocks 2 n, 2 n + 1 of 64 rows
+  auto first_entry = [&](int qt, int n) { return ga.a.geo.block == 64 ? qt * n : n * qt / 2; };
+  if (first_entry(QT, slot) >= n_list) return;         // a shorter batch item
+  if (attn_gen_item<T, D, QT, false>(ga, lds, bhid, taylor, slot)) return;
+  if constexpr (sizeof(T) == 2) {                      // again, 64 rows at a time
+#pragma unroll 1
+    for (int n = QT * slot; n < QT * (slot + 1); ++n)
+      if (first_entry(1, n) < n_list) attn_gen_item<T, D, 1, true>(ga, lds, bhid, taylor, n);
+  }
+}
+
+hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st) {
+  GenArgs ga;
+  ga.a = a;
+  int n_long = 0, n_taylor = 0;
+  for (int b = 0; b < pr.p.B; ++b) {
+    const BatchCounts& c = pr.cnt.b[b];
+    const int f = a.dense ? c.T : c.n_full, t = a.dense ? 0 : c.n_flat;
+    n_long = f > n_long ? f : n_long;
+    n_taylor = t > n_taylor ? t : n_taylor;
+  }
+  const long long bh = (long long)pr.p.B * pr.p.H;
+  // bf16: 128 rows per workgroup read every LDS fragment once for two query tiles, but need the chip full of them: measured
+  // at 15 600 tokens, keep 0.5, full 0.25, blocks of 64, QT = 2 / 1: D = 64: 24 heads (744 long items of 128 rows) 728 /
+  // 833 us, dense over half as many tokens, 8 heads (488) 318 / 343, 12 heads (372) 538 / 480, 2 heads (62) 412 / 315; D = 128:
+  // 24 heads 1288 / 1597, 12 heads (372) 755 / 816, 8 heads (248) 576 / 569, 2 heads 553 / 408.  fp32: a fragment feeds
+  // four times as many matrix instructions of twice the length, and more waves always won.
+  const long long long128 = bh * (pr.p.block == 128 ? n_long : (n_long + 1) / 2);
+  const bool two = pr.p.dtype == ISA_BF16 && long128 >= (long long)N_XCD * cus_per_xcd() * (pr.p.D == 64 ? 7 : 5) / 4;
+  const int rows = two ? 128 : 64;
+  auto slots = [&](int n) { return pr.p.block >= rows ? n * (pr.p.block / rows) : (n + 1) / 2; };
+  ga.slots_long = slots(n_long);
+  ga.slots_taylor = slots(n_taylor);
+  ga.per_xcd_long = (int)((bh * ga.slots_long + N_XCD - 1) / N_XCD);
+  ga.per_xcd_taylor = (int)((bh * ga.slots_taylor + N_XCD - 1) / N_XCD);
+  if (ga.slots_long == 0) ga.slots_long = 1;           // divisors in the kernel; a branch without work gets no workgroups
+  if (ga.slots_taylor == 0) ga.slots_taylor = 1;
+  const dim3 grid((unsigned)(N_XCD * (ga.per_xcd_long + ga.per_xcd_taylor))), blk(256);
+  if (pr.p.dtype == ISA_BF16) {
+    if (pr.p.D == 128 && two) hipLaunchKernelGGL((k_attn_gen<uint16_t, 128, 2>), grid, blk, 0, st, ga);
+    else if (pr.p.D == 128) hipLaunchKernelGGL((k_attn_gen<uint16_t, 128, 1>), grid, blk, 0, st, ga);
+    else if (two) hipLaunchKernelGGL((k_attn_gen<uint16_t, 64, 2>), grid, blk, 0, st, ga);
+    else hipLaunchKernelGGL((k_attn_gen<uint16_t, 64, 1>), grid, blk, 0, st, ga);
+  } else {
+    if (pr.p.D == 128) hipLaunchKernelGGL((k_attn_gen<float, 128, 1>), grid, blk, 0, st, ga);
+    else hipLaunchKernelGGL((k_attn_gen<float, 64, 1>), grid, blk, 0, st, ga);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace isa

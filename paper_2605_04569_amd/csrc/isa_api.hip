@@ -91,7 +91,7 @@ int validate(const isa_problem* p, Problem* out) {
   pr.S_max = (int)S_max;
   pr.mfma_shape = p->dtype == ISA_BF16 && p->D == 128 && p->block == 128;
   if (pr.mfma_shape && (unsigned long long)S_max * (unsigned long long)p->stride_t * 2ull >= (1ull << 32)) {
-    // Not a silent drop to the portable kernels (50 times slower, and no backward pass): the caller is told, and can
+    // Not a silent drop to the portable kernels (slower, and no backward pass): the caller is told, and can
     // still ask for those kernels explicitly with isa_set_mfma(0).
     if (g_use_mfma.load()) return ISA_ERR_UNSUPPORTED;
     pr.mfma_shape = false;
@@ -257,7 +257,7 @@ static int run_attend(const Problem& pr, const Workspace& ws, const AttnArgs& a,
                       hipStream_t st) {
   const bool mfma = pr.mfma_shape && g_use_mfma.load();
   if (!mfma) {
-    ISA_STAGE(launch_attn_simt(pr, a, st));
+    ISA_STAGE(launch_attn_gen(pr, a, st));
     return ISA_OK;
   }
   if (!vt_ready) ISA_STAGE(launch_pack_vt(pr, ws, v, nullptr, st));

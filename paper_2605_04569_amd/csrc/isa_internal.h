@@ -132,7 +132,7 @@ hipError_t launch_coarse(const Problem& pr, const Workspace& ws, const float* qc
                          float* s_ctx, float* sharp, float* z, const float* vc, float* ocoarse, hipStream_t st);
 hipError_t launch_select(const Problem& pr, const Workspace& ws, const float* s_ctx, const float* sharp, const float* z,
                          int* kv_list, int* full_list, int* flat_list, uint32_t* exact_mask, hipStream_t st);
-hipError_t launch_attn_simt(const Problem& pr, const AttnArgs& a, hipStream_t st);
+hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st);
 
 // MFMA path (bf16, D = 128, block = 128)
 // vc (may be null): also writes the fp32 block means of V, [B,H,T_max,D]

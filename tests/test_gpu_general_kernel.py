@@ -1,0 +1,100 @@
+"""The general matrix-core kernel (csrc/attn_gen.hip: fp32, D = 64, blocks of 64, and the pipelined kernels' shape when
+they are switched off) at the sizes where its tiles, pairs and splits can go wrong, against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import isa_oracle as O
+from util import err_stats, f64, problem_of
+from test_gpu_parity import TOL, check_end_to_end, gen
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [("bf16", 64, 64), ("bf16", 64, 128), ("bf16", 128, 64), ("f32", 64, 64), ("f32", 128, 128), ("f32", 64, 128)]
+SHAPE_IDS = ["%s_d%d_b%d" % s for s in SHAPES]
+
+
+@pytest.fixture(scope="module")
+def I():
+    import paper_2605_04569_amd as isa
+    isa.lib()
+    return isa
+
+
+def _wl(shape, H, src, ctx, **kw):
+    dtype, D, block = shape
+    return W.CONFIGS["cfg1"].with_(name="general", H=H, D=D, dtype=dtype, block=block, src_grid=src, ctx_grids=ctx, **kw)
+
+
+# tails of 1, 31, 32, 33, 63, 64 and 65 tokens: a tile's half, both halves, one past
+@pytest.mark.parametrize("tail", [1, 31, 32, 33, 63, 64, 65])
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_tails(I, shape, tail):
+    wl = _wl(shape, 2, (1, 1, 256 + tail), (((1, 1, 128 + tail), (1, 1, tail)),), keep_ratio=0.7, full_frac=0.4,
+             exact_frac=0.3 if tail % 2 else 0.0, gamma=0.5 if tail == 33 else 0.0, seed=700 + tail)
+    check_end_to_end(I, wl, *gen(wl))
+
+
+# enough heads for 128-row workgroups: odd lists (a pair with one block), exact sets of both blocks of a pair, a ragged batch
+@pytest.mark.parametrize("exact_frac", [0.0, 0.25])
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] == "bf16"], ids=[i for i in SHAPE_IDS if i[:4] == "bf16"])
+def test_wide_workgroups(I, shape, exact_frac):
+    dtype, D, block = shape
+    src, ctx = (1, 1, 5 * block + 40), (((1, 1, 5 * block),), ((1, 1, 2 * block + 9),))
+    wl = _wl(shape, 300, src, ctx, B=2, keep_ratio=0.6, full_frac=0.6, exact_frac=exact_frac, seed=731)
+    n_full = [I.isa_get_counts(problem_of(wl), b)["n_full"] for b in range(2)]
+    assert max(n_full) % 2 == 1 and 600 * (max(n_full) + 1) // 2 >= 448            # the premise: odd list, enough items
+    check_end_to_end(I, wl, *gen(wl), heads=[0, 7, 150, 299])
+
+
+@pytest.mark.parametrize("H", [1, 3, 5, 9, 20])
+def test_head_counts_over_the_xcds(I, H):
+    wl = _wl(("bf16", 64, 64), H, (2, 10, 33), (((1, 10, 33),),), keep_ratio=0.5, full_frac=0.4, seed=750 + H)
+    check_end_to_end(I, wl, *gen(wl))
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_no_further_from_64_bits_than_the_storage_type(I, shape):
+    # fp32: a softmax average of unit values in fp32 sums of 500 terms, scores up to about 30: 30 * 2^-24 per weight; bf16: the
+    # rounding of the result alone, uniform in half a step: 2^-9 / sqrt(3) of the value in the 2-norm, times 1.5
+    wl = _wl(shape, 2, (1, 10, 33), (((1, 5, 33),),), seed=761)
+    Q, K, V, q, k, v = gen(wl)
+    pr = problem_of(wl)
+    out = torch.empty_like(q)
+    I.isa_dense_attention(pr, q, k, v, out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    want = np.stack([O.dense_attention(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h])) for h in range(2)])
+    rel = np.linalg.norm(f64(out[0]) - want) / np.linalg.norm(want)
+    assert rel <= (30 * 2.0 ** -24 if shape[0] == "f32" else 1.5 * 2.0 ** -9 / 3 ** 0.5), rel
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+@pytest.mark.parametrize("H", [2, 520], ids=["narrow", "wide"])
+def test_infinities_pass_as_in_plain_arithmetic(I, shape, H):
+    if H == 520 and shape[0] == "f32":
+        pytest.skip("fp32 always takes 64-row workgroups")
+    wl = _wl(shape, H, (1, 1, 4 * shape[2] + 17), (((1, 1, shape[2]),),), keep_ratio=1.0, full_frac=0.5, seed=771)
+    Q, K, V, q, k, v = gen(wl)
+    n = wl.tokens(0)
+    # moderate scores, so that no weight underflows; one +inf value in the last token of a short block (whose row the tile loads
+    # repeat past the block's end), and one key that no query may see: channel 0 of every query is positive
+    q, k = q * 0.25, k * 0.25
+    q[..., 0] = q[..., 0].abs() + 0.125
+    v[:, :, 4 * shape[2] + 16, 3] = float("inf")
+    k[:, :, 5, 0] = float("-inf")
+    pr = problem_of(wl)
+    ws = I.new_workspace(pr)
+    out = torch.empty_like(q)
+    I.isa_dense_attention(pr, q, k, v, out, ws)
+    torch.cuda.synchronize()
+    tol_max, tol_mean = TOL[wl.dtype]
+    for h in sorted({0, H - 1}):
+        got, kk, vv = f64(out[0, h, :n]), f64(k[0, h, :n]), f64(v[0, h, :n])
+        assert np.isposinf(got[:, 3]).all()
+        seen = np.arange(n) != 5
+        vv[:, 3] = 0.0
+        want = O.dense_attention(f64(q[0, h, :n]), kk[seen], vv[seen])
+        got[:, 3] = want[:, 3]
+        emax, emean = err_stats(got, want)
+        assert emax <= tol_max and emean <= tol_mean, (h, emax, emean)
