@@ -104,8 +104,8 @@ struct BwdArgs {
   // mean rows only: every item runs as `parts` workgroups, each over its share of the streamed entries, and writes its
   // partial sums to out_f32 + part * part_stride (k_bwd_sum_parts adds them up)
   int parts; long long part_stride;
-  // token rows, one phase only: the last tail_items items of every XCD (its last, incomplete round over the compute
-  // units) run as tail_parts workgroups each, every one over its share of the streamed entries; they leave their
+  // token rows: the last tail_items items of every XCD (its last, incomplete round over the compute
+  // units) run as tail_parts workgroups each, every one over its share of the streamed entries of each phase; they leave their
   // unscaled fp32 sums in tail_scratch [XCD][tail item][part][256 rows][128] and k_bwd_tail_merge writes the rows
   int items_xcd, tail_items, tail_parts;
   float* tail_scratch;
@@ -123,14 +123,19 @@ template <bool SM, bool T2, int EX, bool YD>
 __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
   constexpr int STG = EX == 2 ? STAGE + K_TILE : STAGE;      // EX == 2: a third tile per stage (see BwdStream::y3)
   __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * STG + 2 * SIDE_BYTES / 2];
-  // Workgroup ids go round-robin over the 8 XCDs: XCD x gets every 8th (batch, head) and works through its items one
-  // head after the other, so that the workgroups that run together on an XCD (and share its L2) stream the same rows.
+  // Workgroup ids go round-robin over the 8 XCDs: XCD x has its range of the items of all (batch, head)s (xcd_first, head_at) and
+  // works through it one head after the other, so that the workgroups that run together on an XCD (and share its L2)
+  // stream the same rows.
   const int xcd = blockIdx.x & 7, jj = blockIdx.x >> 3;
+  const int n_bh = a.geo.B * a.geo.H;
   int parts = 1, part = 0, item, bhid, tail_slot = -1;
   if (SM) {
     parts = a.parts;
-    const int item_all = jj % (a.items * parts);
-    bhid = (jj / (a.items * parts)) * 8 + xcd;
+    const int per_head = a.items * parts;
+    const int idx = xcd_first((long long)n_bh * per_head, xcd) + jj;
+    if (idx >= xcd_first((long long)n_bh * per_head, xcd + 1)) return;
+    const int item_all = idx % per_head;
+    bhid = head_at(idx / per_head, n_bh);
     item = item_all / parts;
     part = item_all - item * parts;
   } else {
@@ -139,11 +144,11 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
       if (threadIdx.x == 0) taken = atomicAdd(a.dyn_ctr, 1);
       __syncthreads();
       const int idx = __builtin_amdgcn_readfirstlane(taken);
-      if (idx >= a.items * a.geo.B * a.geo.H) return;     // the launch has more workgroups than items
+      if (idx >= a.items * n_bh) return;                  // the launch has more workgroups than items
       item = idx % a.items;
       bhid = idx / a.items;
     } else {
-      const int n_reg = a.items_xcd - a.tail_items;       // items_xcd = items x heads of an XCD; no tail: jj itself
+      const int n_reg = a.items_xcd - a.tail_items;       // items_xcd = items of an XCD (some have one fewer); no tail: jj itself
       int idx = jj;
       if (jj >= n_reg) {
         const int u = jj - n_reg;
@@ -152,11 +157,12 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
         parts = a.tail_parts;
         idx = n_reg + tail_slot;
       }
+      idx += xcd_first((long long)n_bh * a.items, xcd);
+      if (idx >= xcd_first((long long)n_bh * a.items, xcd + 1)) return;
       item = idx % a.items;
-      bhid = (idx / a.items) * 8 + xcd;
+      bhid = head_at(idx / a.items, n_bh);
     }
   }
-  if (bhid >= a.geo.B * a.geo.H) return;
   const int h = bhid % a.geo.H, b = bhid / a.geo.H;
   const int T_new = a.cnt.b[b].T_new, n_full = a.cnt.b[b].n_full, n_flat = a.cnt.b[b].n_flat;
   const int T_max = a.geo.T_max;
@@ -261,10 +267,14 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
   const int ph_ent1 = a.s[1].kind == 0 ? T_new : a.s[1].kind == 1 ? n_full : n_flat;
   const int4* const ph_tab0 = a.s[0].tab;
   const int4* const ph_tab1 = a.s[1].tab;
-  const int ent_lo = parts > 1 ? (int)((long long)part * ph_ent0 / parts) : 0;        // this part's share of the entries
-  const int ent_hi = parts > 1 ? (int)((long long)(part + 1) * ph_ent0 / parts) : ph_ent0;
-  const int ph_tiles0 = ph_tab0 ? 2 * ent_hi : (T_new + KT - 1) / KT;
-  const int ph_tiles1 = ph_tab1 ? 2 * ph_ent1 : (T_new + KT - 1) / KT;
+  // this part's share of each phase: tiles [lo, hi), cut between entries (token tiles) or between tiles of means
+  auto share = [&](bool tokens, int entries, int p) __attribute__((always_inline)) -> int {
+    const int units = tokens ? entries : (T_new + KT - 1) / KT;
+    const int u = parts > 1 ? (int)((long long)p * units / parts) : p * units;
+    return tokens ? 2 * u : u;
+  };
+  const int ph_lo0 = share(ph_tab0 != nullptr, ph_ent0, part), ph_tiles0 = share(ph_tab0 != nullptr, ph_ent0, part + 1);
+  const int ph_lo1 = share(ph_tab1 != nullptr, ph_ent1, part), ph_tiles1 = share(ph_tab1 != nullptr, ph_ent1, part + 1);
   const int ph_masked0 = a.s[0].masked, ph_masked1 = a.s[1].masked;
   const uint16_t* const ph_y1_0 = a.s[0].y1; const uint16_t* const ph_y1_1 = a.s[1].y1;
   const uint16_t* const ph_y2_0 = a.s[0].y2; const uint16_t* const ph_y2_1 = a.s[1].y2;
@@ -289,7 +299,7 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
       if (EX && !SM && PH(c.p, ph_masked0, ph_masked1) == 1 && (c.T & 1) == 0 && c.T < nt) c.T = 2 * next_linked(c.T >> 1, nt >> 1);
       if (c.T < nt) break;
       c.p += 1;
-      c.T = 0;
+      c.T = ph_lo1;
     }
     return c;
   };
@@ -385,7 +395,7 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
   }
 
   // cur: tile being multiplied; nxt: tile whose loads are in flight; nn: tile whose table row is being fetched
-  Cursor cur = settle(Cursor{0, 2 * ent_lo});
+  Cursor cur = settle(Cursor{0, ph_lo0});
   Cursor nxt = cur.p < n_phases ? advance(cur) : cur;
   int4 ent_nxt = row_of(cur);
   if (cur.p < n_phases) issue_tile(cur, 0, ent_nxt);
@@ -859,9 +869,10 @@ __global__ __launch_bounds__(128) void k_bwd_sum_parts(float* __restrict__ g, in
 __global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
   const int rows8 = blockIdx.x & 15, grp = (blockIdx.x >> 4) & 1;
   const int r = (blockIdx.x >> 5) % a.tail_items, xcd = (blockIdx.x >> 5) / a.tail_items;
-  const int idx = a.items_xcd - a.tail_items + r;
-  const int item = idx % a.items, bhid = (idx / a.items) * 8 + xcd;
-  if (bhid >= a.geo.B * a.geo.H) return;
+  const long long n_items = (long long)a.items * a.geo.B * a.geo.H;
+  const int idx = xcd_first(n_items, xcd) + a.items_xcd - a.tail_items + r;
+  if (idx >= xcd_first(n_items, xcd + 1)) return;
+  const int item = idx % a.items, bhid = head_at(idx / a.items, a.geo.B * a.geo.H);
   const int h = bhid % a.geo.H, b = bhid / a.geo.H;
   const long long bh = bhid;
   const int T_max = a.geo.T_max;
@@ -897,19 +908,22 @@ __global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
 
 // YD (the streamed rows are queries, which carry deltas; the stationary rows then must not: a.dx == nullptr) is implied
 // by what the launch streams.
+// split_units: into how many parts the streamed side can be cut (list entries or tiles of means; 0: not to be cut).
 template <bool SM, bool T2, bool YD>
-static hipError_t launch_one(BwdArgs a, int ex, int B, int H, hipStream_t st, bool split_tail = false, int* dyn_ctr = nullptr) {
+static hipError_t launch_one(BwdArgs a, int ex, int B, int H, hipStream_t st, int split_units = 0, int* dyn_ctr = nullptr) {
   if (a.items <= 0) return hipSuccess;
   if (YD && a.dx != nullptr) return hipErrorInvalidValue;
-  const int hpx = (B * H + 7) / 8;                // (batch, head)s per XCD
-  a.items_xcd = a.items * hpx;
+  const int cus = cus_per_xcd();
+  a.items_xcd = (int)(((long long)a.items * B * H + N_XCD - 1) / N_XCD);
   a.tail_items = 0; a.tail_parts = 1;
-  a.dyn_ctr = SM ? nullptr : dyn_ctr;
-  if (!SM && !a.dyn_ctr && split_tail && a.n_phases == 1 && ex == 0 && a.tail_scratch) {
+  // items from a counter only where there is more than half a round of them: fewer are cut into parts instead
+  a.dyn_ctr = SM || (split_units > 1 && a.items_xcd <= cus / 2) ? nullptr : dyn_ctr;
+  if (!SM && !a.dyn_ctr && split_units > 1 && a.tail_scratch) {
     // the last round of an XCD's 32 compute units: if at most half of them would have an item, cut those items
-    const int cus = cus_per_xcd(), t = a.items_xcd % cus;
+    const int t = a.items_xcd % cus;
     if (t > 0 && t <= cus / 2) {
       int parts = cus / t > 8 ? 8 : cus / t;
+      if (parts > split_units) parts = split_units;
       while (parts > 1 && N_XCD * t * parts > SPLIT_MAX_SUB) --parts;       // the partial-result area holds SPLIT_MAX_SUB sub-items
       if (parts > 1) { a.tail_items = t; a.tail_parts = parts; }
     }
@@ -918,7 +932,7 @@ static hipError_t launch_one(BwdArgs a, int ex, int B, int H, hipStream_t st, bo
   // of workgroups before the items run out
   const long long n_dyn = (long long)a.items * B * H;
   const long long dyn_wgs = ((n_dyn + n_dyn / 8) / N_XCD + cus_per_xcd() + 1) * N_XCD;
-  const dim3 grid((unsigned)(SM ? a.items * a.parts * hpx * 8
+  const dim3 grid((unsigned)(SM ? ((long long)a.items * a.parts * B * H + N_XCD - 1) / N_XCD * N_XCD
                                 : a.dyn_ctr ? dyn_wgs : (a.items_xcd - a.tail_items + a.tail_items * a.tail_parts) * 8));
   if (ex == 2) {                                // position bits only occur with token rows as stationary rows and dS
     if (SM || !T2 || YD) return hipErrorInvalidValue;
@@ -940,18 +954,18 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   const float gamma = (float)pr.p.gamma;
   const bool resid = pr.p.gamma != 0.0;               // ws.ocoarse holds O_coarse (recomputed by the caller of this function)
   const int B = pr.p.B, H = pr.p.H, T_max = pr.cnt.T_max;
-  int S_max = pr.S_max, sf = 0, sl = 0, sk = 0, kx = 0;
+  int S_max = pr.S_max, sf = 0, sl = 0, sk = 0, min_kept = 1 << 30, min_full = 1 << 30;
   for (int b = 0; b < B; ++b) {
     const BatchCounts& c = pr.cnt.b[b];
     sf = c.n_full > sf ? c.n_full : sf;
     sl = c.n_flat > sl ? c.n_flat : sl;
     sk = c.T_new > sk ? c.T_new : sk;
-    kx = c.k_exact > kx ? c.k_exact : kx;
+    min_kept = c.T_new < min_kept ? c.T_new : min_kept;
+    min_full = c.n_full < min_full ? c.n_full : min_full;
   }
   // The forward ran its 4-wave kernel (exact sets, possibly empty ones when exact_frac is too small for the list): token
   // keys and mean keys in one softmax, the mean keys stored minus Kc_0 and q . Kc_0 kept per Taylor row (ws.rq).
   const bool ex = pr.p.exact_frac > 0.0 && sl > 0 && exact_mask != nullptr;
-  (void)kx;
 #define ISA_BWD_CHECK()                           \
   do {                                            \
     hipError_t e__ = hipGetLastError();           \
@@ -1017,7 +1031,7 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   a.add_rows = resid ? ws.cdq : nullptr; a.add_by_block = 1;       // every query block's share of dQc
   a.stat_list = full_list; a.stat_kind = 0; a.items = (sf + 1) / 2;
   a.s[0] = kept_tokens; a.s[1] = none; a.n_phases = 1; a.bits = nullptr;
-  if ((e = launch_one<false, true, false>(a, 0, B, H, st, true)) != hipSuccess) return e;
+  if ((e = launch_one<false, true, false>(a, 0, B, H, st, min_kept)) != hipSuccess) return e;
   a.stat_list = flat_list; a.stat_kind = 1; a.items = (sl + 1) / 2;
   if (ex) {
     a.s[0] = kept_tokens; a.s[0].masked = 1;
@@ -1027,7 +1041,7 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   } else {
     a.s[0] = kept_means; a.n_phases = 1;
   }
-  if ((e = launch_one<false, true, false>(a, ex ? 2 : 0, B, H, st, false, ws.bwd_ctr + 0)) != hipSuccess) return e;
+  if ((e = launch_one<false, true, false>(a, ex ? 2 : 0, B, H, st, (min_kept + KT - 1) / KT, ws.bwd_ctr + 0)) != hipSuccess) return e;
 
   // ---- dKc and dK (streamed Q, dO)
   const int n_mean_pairs = ((sk + 127) / 128 + 1) / 2;
@@ -1077,8 +1091,8 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
     a.out_bf = (uint16_t*)(pass == 0 ? dk : dv); a.out_f32 = nullptr;
     a.add_rows = (sl > 0 || resid) ? mean_grad : nullptr; a.add_by_block = 0;
     a.oscale = osc; a.items = (sk + 1) / 2;
-    e = pass == 0 ? launch_one<false, true, true>(a, ex ? 1 : 0, B, H, st, true, ws.bwd_ctr + 1)
-                  : launch_one<false, false, false>(a, ex ? 1 : 0, B, H, st, true, ws.bwd_ctr + 2);
+    e = pass == 0 ? launch_one<false, true, true>(a, ex ? 1 : 0, B, H, st, min_full, ws.bwd_ctr + 1)
+                  : launch_one<false, false, false>(a, ex ? 1 : 0, B, H, st, min_full, ws.bwd_ctr + 2);
     if (e != hipSuccess) return e;
   }
 #undef ISA_BWD_CHECK

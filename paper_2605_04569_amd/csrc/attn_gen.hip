@@ -77,14 +77,6 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
   for (int k = 0; k < 3; ++k) t[k] = __builtin_bit_cast(bf16x8, make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]));
 }
 
-// The (batch, head) at position p when they are ordered XCD by XCD (those with the same remainder modulo 8 together).
-__device__ __forceinline__ int head_at(int p, int n) {
-  const int a = n / N_XCD, r = n % N_XCD;
-  if (p < r * (a + 1)) return (p % (a + 1)) * N_XCD + p / (a + 1);
-  p -= r * (a + 1);
-  return (p % a) * N_XCD + r + p / a;
-}
-
 }  // namespace
 
 // One work item: 64 QT rows of one query block (QT = 2, block 64: of two neighbours in the list).  FULL32 evaluates the
@@ -538,17 +530,16 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 template <typename T, int D, int QT>
 __global__ __launch_bounds__(256, D == 128 ? 2 : QT == 1 ? 4 : 3) void k_attn_gen(GenArgs ga) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[512 * D + 2 * 64 * 4];
-  // Workgroup ids go round-robin over the 8 XCDs.  The items of all (batch, head)s, ordered XCD by XCD (every 8th head) and
-  // head after head, are cut into 8 equal ranges, one per XCD: with a multiple of 8 heads an XCD works through whole heads
-  // of its own, whose keys and values its L2 then holds, and with any other number no XCD is left idle.  The long items
-  // (exact branch) come first.
+  // Workgroup ids go round-robin over the 8 XCDs; each has its range of the items of all (batch, head)s, the long ones
+  // (exact branch) first.
   const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
   const bool taylor = j >= ga.per_xcd_long;
   const int n_bh = ga.a.geo.B * ga.a.geo.H;
-  const int slots = taylor ? ga.slots_taylor : ga.slots_long, per = taylor ? ga.per_xcd_taylor : ga.per_xcd_long;
-  const long long idx = (long long)xcd * per + (taylor ? j - ga.per_xcd_long : j);
-  if (idx >= (long long)n_bh * slots) return;
-  const int bhid = head_at((int)(idx / slots), n_bh), slot = (int)(idx % slots);
+  const int slots = taylor ? ga.slots_taylor : ga.slots_long;
+  const long long total = (long long)n_bh * slots;
+  const int idx = xcd_first(total, xcd) + (taylor ? j - ga.per_xcd_long : j);
+  if (idx >= xcd_first(total, xcd + 1)) return;
+  const int bhid = head_at(idx / slots, n_bh), slot = idx % slots;
   const BatchCounts c = ga.a.cnt.b[bhid / ga.a.geo.H];
   const int n_list = ga.a.dense ? c.T : taylor ? c.n_flat : c.n_full;
   // QT-tile slot n of a list: rows 64 QT n .. of a 128-row block's sequence of rows, or block n / blocks 2 n, 2 n + 1 of 64 rows

@@ -250,8 +250,8 @@ __device__ __forceinline__ void attn_sp_item(const MfmaArgs& a, uint16_t* lds, c
   uint16_t* ldsQ = lds + NBUF * K_TILE + NBUF * V_TILE;       // 2 x 128 query rows of a Taylor group's next pair
 
   // ---- which work item.  Workgroup ids go round-robin over the 8 XCDs, so XCD x sees ids x, x + 8, ... in
-  // order.  Each XCD owns every 8th (batch, head) (`hpx` of them: batch items of different lengths are spread
-  // evenly over the XCDs), and works through their exact-branch pairs (the long items) one head after the other, so
+  // order.  Each XCD has its range of the exact-branch pairs (the long items) of all (batch, head)s (xcd_first, head_at) and
+  // works through them one head after the other, so
   // that the workgroups that run together on it (and share its L2) read the same head's keys and values.  The Taylor
   // groups (short items) belong to no XCD: the workgroups that come after an XCD's long items take them from one
   // counter (`taken`), so they fill the compute units that the last, incomplete round of long items leaves
@@ -270,10 +270,14 @@ __device__ __forceinline__ void attn_sp_item(const MfmaArgs& a, uint16_t* lds, c
   const int part = split ? (j - n_whole) % a.parts : 0;
   // A Taylor work item is a group of up to `tgroup` consecutive pairs of one head, handled one after the other (all of
   // them read the same sequence of mean tiles); an exact-branch item is one pair.
-  const int hl = taylor ? item / a.groups_second : item / a.slots_first;
-  int slot = taylor ? (item % a.groups_second) * a.tgroup : item % a.slots_first;   // (first) pair index inside its branch
-  const int bhid = counted ? hl : hl * 8 + xcd;                // counted items are numbered over all (batch, head)s
-  if ((!counted && hl >= a.hpx) || bhid >= a.geo.B * a.geo.H) return;
+  const int n_bh = a.geo.B * a.geo.H;
+  const long long n_long_items = (long long)n_bh * a.slots_first;
+  const int numbered = counted ? item : xcd_first(n_long_items, xcd) + item;   // counted items are numbered over all (batch, head)s
+  if (!counted && numbered >= xcd_first(n_long_items, xcd + 1)) return;
+  const int hl = numbered / (taylor ? a.groups_second : a.slots_first);
+  int slot = taylor ? (item % a.groups_second) * a.tgroup : numbered % a.slots_first;   // (first) pair index inside its branch
+  if (hl >= n_bh) return;
+  const int bhid = counted ? hl : head_at(hl, n_bh);
   const int h = bhid % a.geo.H, b = bhid / a.geo.H;
   const BatchCounts c = a.cnt.b[b];
   const int T_max = a.geo.T_max;
@@ -726,10 +730,10 @@ __global__ __launch_bounds__(512, 1) void k_attn_sp(MfmaArgs a) {
 __global__ __launch_bounds__(256) void k_split_merge(MfmaArgs a) {
   const int rows8 = blockIdx.x & 15, grp = (blockIdx.x >> 4) & 1;
   const int r = (blockIdx.x >> 5) % a.n_split, xcd = (blockIdx.x >> 5) / a.n_split;
-  const int item = a.n_long - a.n_split + r;
-  const int hl = item / a.slots_first, slot = item % a.slots_first;
-  const int bhid = hl * 8 + xcd;
-  if (hl >= a.hpx || bhid >= a.geo.B * a.geo.H) return;
+  const long long n_items = (long long)a.geo.B * a.geo.H * a.slots_first;
+  const int item = xcd_first(n_items, xcd) + a.n_long - a.n_split + r;
+  if (item >= xcd_first(n_items, xcd + 1)) return;
+  const int slot = item % a.slots_first, bhid = head_at(item / a.slots_first, a.geo.B * a.geo.H);
   const int h = bhid % a.geo.H, b = bhid / a.geo.H;
   const BatchCounts c = a.cnt.b[b];
   const int T_max = a.geo.T_max;
@@ -809,27 +813,32 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
   if (sf + ss > 0) {
     m.slots_first = sf > 0 ? sf : 1;        // divisors in the kernel; a branch with no work gets no workgroups
     m.slots_second = ss > 0 ? ss : 1;
-    m.hpx = (pr.p.B * pr.p.H + 7) / 8;
-    m.n_long = m.hpx * sf;
+    m.n_long = (int)(((long long)pr.p.B * pr.p.H * sf + N_XCD - 1) / N_XCD);
     // An XCD runs one workgroup per compute unit, so its long items go in rounds of `cus`; when the last round is at
-    // most half full, its items are cut into as many key ranges as fill it (each at least 8 key blocks long).
+    // most half full, its items are cut into as many key ranges as fill it.  A sub-item costs about five iterations beside those
+    // of its tiles (set-up, pipeline drain, its share of the merge), so a range is at least two key blocks (four tiles) long;
+    // this matters to launches of less than a round (5 heads, 990 tokens, 7 key blocks: 31.9 us for the kernel before, 21.0 + 4.5
+    // with the merge).
     m.n_split = 0; m.parts = 1;
     m.split_o = ws.split_o; m.split_ml = ws.split_ml;
     const int cus = cus_per_xcd(), rem = m.n_long % cus;
-    if (rem > 0 && rem <= cus / 2 && rem <= sf && ws.split_o) {
+    if (rem > 0 && rem <= cus / 2 && ws.split_o) {
       int min_list = 1 << 30;
       for (int b = 0; b < pr.p.B; ++b) {
         const int nl = a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new;
         min_list = nl < min_list ? nl : min_list;
       }
       int parts = cus / rem;
-      if (parts > min_list / 8) parts = min_list / 8;
+      if (parts > min_list / 2) parts = min_list / 2;
       while (parts >= 2 && N_XCD * rem * parts > SPLIT_MAX_SUB) --parts;      // the partial-result area holds SPLIT_MAX_SUB sub-items
       if (parts >= 2) { m.n_split = rem; m.parts = parts; }
     }
     // Taylor pairs go in groups of up to TAYLOR_GROUP consecutive pairs of a head per workgroup
-    m.tgroup = TAYLOR_GROUP;
-    m.groups_second = ss > 0 ? (ss + TAYLOR_GROUP - 1) / TAYLOR_GROUP : 1;
+    // (fewer when there are not enough pairs for a group per compute unit: then the pairs of a group would only wait for
+    // each other)
+    const long long pairs = (long long)pr.p.B * pr.p.H * ss / (N_XCD * cus_per_xcd());
+    m.tgroup = pairs < 1 ? 1 : pairs < TAYLOR_GROUP ? (int)pairs : TAYLOR_GROUP;
+    m.groups_second = ss > 0 ? (ss + m.tgroup - 1) / m.tgroup : 1;
     // one such workgroup per compute unit (they stay until the groups run out), fewer if there are fewer groups
     const long long n_groups = ss > 0 ? (long long)pr.p.B * pr.p.H * m.groups_second : 0;
     m.n_taylor_wg = (int)((n_groups + N_XCD - 1) / N_XCD < cus_per_xcd() ? (n_groups + N_XCD - 1) / N_XCD : cus_per_xcd());

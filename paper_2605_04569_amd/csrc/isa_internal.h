@@ -108,6 +108,18 @@ extern int g_prof_on, g_prof_recorded;
 int cus_per_xcd();
 constexpr int N_XCD = 8;
 
+// Work items of all (batch, head)s over the XCDs.  The (batch, head)s are ordered by their number modulo 8 (batch items of
+// different lengths are spread evenly), their items head after head, and the sequence is cut into 8 equal ranges, one per XCD: with
+// a multiple of 8 heads an XCD works through whole heads of its own, whose keys and values its L2 then holds, and with any
+// other number (40 heads over 8 devices leave 5) no XCD gets a head more than another.
+__host__ __device__ inline int xcd_first(long long total, int xcd) { return (int)((total * xcd) / N_XCD); }
+__device__ __forceinline__ int head_at(int p, int n) {            // the (batch, head) at position p of the order above
+  const int a = n / N_XCD, r = n % N_XCD;
+  if (p < r * (a + 1)) return (p % (a + 1)) * N_XCD + p / (a + 1);
+  p -= r * (a + 1);
+  return (p % a) * N_XCD + r + p / a;
+}
+
 int validate(const isa_problem* p, Problem* out);
 // forward_only: without the arrays that the forward pass leaves for, and that are scratch of, the backward pass
 void carve(const Problem& pr, void* base, Workspace* ws, bool forward_only = false);
