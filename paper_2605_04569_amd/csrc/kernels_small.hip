@@ -366,23 +366,36 @@ hipError_t launch_coarse(const Problem& pr, const Workspace& ws, const float* qc
 __device__ inline bool beats(float sa, int ia, float sb, int ib) { return sa > sb || (sa == sb && ia < ib); }
 
 constexpr int SEL_THREADS = 1024;
-constexpr int SEL_PARTS = 16;        // lanes that share the count of one entry's rank (each counts 1/16 of the peers)
+constexpr int SEL_PARTS = 16;        // lanes that share the count of an entry's rank, each over every 16th of the peers
+constexpr int SEL_EACH = 4;          // entries whose ranks a lane counts at once, against the same peers
 
 // flags[j] = 1 for the entries of sc[0..n) that fewer than k others beat.  Integer counts: the result does not depend
-// on how the peers are divided among the lanes.
+// on how the peers are divided among the lanes.  The 16 lanes of an entry read 16 consecutive peers (a contiguous 16th of
+// the peers each put them on few LDS banks, on one where n / 16 is a multiple of 32: 40 heads of 512 blocks 68 -> 17 us).
 __device__ void rank_flags(const float* sc, int n, int k, int* flags) {
-  const int part = threadIdx.x % SEL_PARTS;
-  const int per = (n + SEL_PARTS - 1) / SEL_PARTS, lo = min(n, part * per), hi = min(n, lo + per);
-  for (int j0 = 0; j0 < n; j0 += SEL_THREADS / SEL_PARTS) {          // the same trip count for every thread
-    const int j = j0 + threadIdx.x / SEL_PARTS;
-    int rank = 0;
-    if (j < n) {
-      const float s = sc[j];
-      for (int x = lo; x < hi; ++x) rank += beats(sc[x], x, s, j) ? 1 : 0;
+  const int part = threadIdx.x % SEL_PARTS, first = threadIdx.x / SEL_PARTS;
+  constexpr int GROUPS = SEL_THREADS / SEL_PARTS;
+  for (int j0 = 0; j0 < n; j0 += GROUPS * SEL_EACH) {                // the same trip count for every thread
+    int rank[SEL_EACH];
+    float s[SEL_EACH];
+#pragma unroll
+    for (int u = 0; u < SEL_EACH; ++u) {
+      rank[u] = 0;
+      s[u] = sc[min(j0 + first + u * GROUPS, n - 1)];
+    }
+#pragma unroll 4
+    for (int x = part; x < n; x += SEL_PARTS) {
+      const float v = sc[x];
+#pragma unroll
+      for (int u = 0; u < SEL_EACH; ++u) rank[u] += beats(v, x, s[u], j0 + first + u * GROUPS) ? 1 : 0;
     }
 #pragma unroll
-    for (int o = SEL_PARTS / 2; o > 0; o >>= 1) rank += __shfl_xor(rank, o, 64);
-    if (j < n && part == 0) flags[j] = rank < k ? 1 : 0;
+    for (int u = 0; u < SEL_EACH; ++u) {
+      const int j = j0 + first + u * GROUPS;
+#pragma unroll
+      for (int o = SEL_PARTS / 2; o > 0; o >>= 1) rank[u] += __shfl_xor(rank[u], o, 64);
+      if (j < n && part == 0) flags[j] = rank[u] < k ? 1 : 0;
+    }
   }
 }
 
@@ -444,36 +457,57 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const float* __restrict_
   }
 }
 
-// Alg. 2 Stage 2: for the Taylor query block at position r of flat_list, mark the k_exact positions of
-// kv_list with the largest coarse logit.
+// Alg. 2 Stage 2: for the Taylor query block at position r of flat_list, mark the k_exact positions of kv_list with the
+// largest coarse logit (ties to the lower position): every entry that fewer than k_exact others beat.
+//
+// One wave per row, NV entries of the list per lane (position lane + 64 u) as unsigned keys that order like the logits.
+// The k-th largest key is found bit by bit, counting with ballots the keys that are not below a candidate: 32 steps of NV
+// compares, where counting every entry's rank against all others takes T_new of them.  40 heads of 256 Taylor blocks, 288 kept
+// blocks: 133 -> 26 us.  A NaN beats nothing and nothing beats it: it is marked whenever k_exact > 0 and takes nobody's place.
+template <int NV>
 __global__ __launch_bounds__(256) void k_exact_sets(const float* __restrict__ z, const int* __restrict__ kv_list,
                                                     const int* __restrict__ flat_list, uint32_t* __restrict__ mask,
                                                     Counts cnt, int H) {
-  extern __shared__ float sm[];                      // [T_max]
-  const int r = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, h = blockIdx.y, b = blockIdx.z;
   const BatchCounts c = cnt.b[b];
-  if (r >= c.n_flat) return;
+  if (r >= c.n_flat) return;                         // uniform over the wave; nothing below synchronises waves
   const long long bh = (long long)b * H + h;
   const int i = block_in_range(flat_list[bh * cnt.T_max + r], c.T);
   const float* zr = z + (bh * cnt.T_max + i) * cnt.T_max;
-  for (int t = threadIdx.x; t < c.T_new; t += 256) sm[t] = zr[block_in_range(kv_list[bh * cnt.T_max + t], c.T)];
-  __syncthreads();
+  uint32_t key[NV];                                  // 0: past the list, or NaN (every number's key is larger)
+  unsigned long long nan[NV];
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    const int t = lane + 64 * u;
+    const int j = t < c.T_new ? block_in_range(kv_list[bh * cnt.T_max + t], c.T) : -1;
+    const float x = j >= 0 ? zr[j] + 0.0f : 0.f;     // -0 and 0 tie
+    const uint32_t bits = __float_as_uint(x);
+    const bool is_nan = x != x;
+    key[u] = j < 0 || is_nan ? 0u : (bits & 0x80000000u) ? ~bits : bits | 0x80000000u;
+    nan[u] = __ballot(is_nan);
+  }
+  auto count = [&](uint32_t at_least) {
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) n += __popcll(__ballot(key[u] >= at_least));
+    return n;
+  };
+  uint32_t kth = 0u;                                 // the k_exact-th largest key (0: there are fewer numbers)
+  for (uint32_t bit = 0x80000000u; bit != 0u; bit >>= 1)
+    if (count(kth | bit) >= c.k_exact) kth |= bit;
+  // all larger keys, and the first of the equal ones
+  int equal = c.k_exact - (kth == 0xffffffffu ? 0 : count(kth + 1u));
   uint32_t* mrow = mask + (bh * cnt.T_max + r) * cnt.mask_words;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int base = wave * 64; base < cnt.mask_words * 32; base += 256) {
-    const int t = base + lane;
-    bool bit = false;
-    if (t < c.T_new) {
-      const float s = sm[t];
-      int rank = 0;
-      for (int x = 0; x < c.T_new; ++x) rank += beats(sm[x], x, s, t) ? 1 : 0;
-      bit = rank < c.k_exact;
-    }
-    const unsigned long long bal = __ballot(bit);
-    if (lane == 0) {
-      mrow[base / 32] = (uint32_t)bal;
-      if (base / 32 + 1 < cnt.mask_words) mrow[base / 32 + 1] = (uint32_t)(bal >> 32);
-    }
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    if (2 * u >= cnt.mask_words) break;
+    const unsigned long long eq = __ballot(kth != 0u && key[u] == kth);
+    const int before = __popcll(eq & ((1ull << lane) - 1ull));
+    unsigned long long set = __ballot(key[u] > kth || (kth != 0u && key[u] == kth && before < equal));
+    equal -= __popcll(eq);
+    if (c.k_exact > 0) set |= nan[u];
+    if (lane == 0) mrow[2 * u] = (uint32_t)set;
+    if (lane == 1 && 2 * u + 1 < cnt.mask_words) mrow[2 * u + 1] = (uint32_t)(set >> 32);
   }
 }
 
@@ -487,8 +521,15 @@ hipError_t launch_select(const Problem& pr, const Workspace& ws, const float* s_
   int nflat_max = 0;
   for (int b = 0; b < pr.p.B; ++b) nflat_max = pr.cnt.b[b].n_flat > nflat_max ? pr.cnt.b[b].n_flat : nflat_max;
   if (nflat_max == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_exact_sets, dim3(nflat_max, pr.p.H, pr.p.B), dim3(256), (size_t)pr.cnt.T_max * 4, st, z, kv_list,
-                     flat_list, exact_mask, pr.cnt, pr.p.H);
+  const dim3 grid((nflat_max + 3) / 4, pr.p.H, pr.p.B);
+  // the list entries a lane holds: enough for T_max, which bounds the mask row as well
+#define ISA_SETS(NV) hipLaunchKernelGGL((k_exact_sets<NV>), grid, dim3(256), 0, st, z, kv_list, flat_list, exact_mask, pr.cnt, pr.p.H)
+  if (pr.cnt.T_max <= 256) ISA_SETS(4);
+  else if (pr.cnt.T_max <= 512) ISA_SETS(8);
+  else if (pr.cnt.T_max <= 1024) ISA_SETS(16);
+  else if (pr.cnt.T_max <= 2048) ISA_SETS(32);
+  else ISA_SETS(64);
+#undef ISA_SETS
   return hipGetLastError();
 }
 
