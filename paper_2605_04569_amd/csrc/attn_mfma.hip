@@ -26,41 +26,93 @@ namespace isa {
 // ------------------------------------------------------------------------------------------
 // V^T copies: vt[((bh*T_max + j)*2 + half)][d][pos]; keys past n_j are zero.  `vt` is in the key order of the
 // 16x16x32 kernel (position p holds key key_of_pos16(p)); `vt4`, written only when given, in that of the 4-wave
-// 32x32x16 kernel (position p holds key swap23(p)).  With `vc` the block's mean value (fp32, Alg. 1 Stage 1) is written
-// as well: the tile is in LDS anyway, and the block-mean kernel then need not read V a second time.
+// 32x32x16 kernel (position p holds key swap23(p)).
+//
+// ALL: the first kernel of the whole call.  The same workgroup also takes the block means of its block of V, Q and K
+// (fp32, Alg. 1 Stage 1), and finds its block's place from the segment lengths instead of reading it from the block
+// table, which the workgroups of head 0 write for the kernels that follow.  One launch instead of three, and a thread
+// has its 16-byte loads of all three tensors in flight at once.  HBM-bound at the rate of a copy: 5.1 TB/s for
+// 117 000 tokens of 40 heads (940 us as before); short calls gain: 40 heads of 15 600 tokens 157 -> 126 us, 5 heads of 990
+// tokens 12.7 us in three launches -> 6.8.
+template <bool ALL>
 __global__ __launch_bounds__(256) void k_pack_vt(const uint16_t* __restrict__ v, uint16_t* __restrict__ vt,
-                                                 uint16_t* __restrict__ vt4, const int* __restrict__ blk_start,
-                                                 const int* __restrict__ blk_n, uint16_t* __restrict__ zero_tile,
-                                                 float* __restrict__ vc, int* __restrict__ long_ctr, Geometry g) {
+                                                 uint16_t* __restrict__ vt4, int* __restrict__ blk_start,
+                                                 int* __restrict__ blk_n, int4* __restrict__ btab, uint16_t* __restrict__ zero_tile,
+                                                 int* __restrict__ long_ctr, Geometry g, SegDesc seg,
+                                                 const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                                 float* __restrict__ qc, float* __restrict__ kc, float* __restrict__ vc) {
   __shared__ uint16_t tile[128][MD + 2];
-  __shared__ float colsum[MD];
+  __shared__ float red[ALL ? 2 : 1][16][MD];
   const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   if (j == 0 && h == 0 && b == 0) {                               // the all-zero V^T tile the attention kernel pads with
     for (int x = threadIdx.x; x < MD * KT / 8; x += 256) reinterpret_cast<uint4*>(zero_tile)[x] = make_uint4(0, 0, 0, 0);
     if (threadIdx.x == 0) *long_ctr = 0;                          // the counter a dense launch may take its items from
   }
-  const int n = blk_n[b * g.T_max + j];
+  int start, n;
+  if (ALL) {
+    block_place(seg, 128, b, j, start, n);
+    if (h == 0 && threadIdx.x == 0) {
+      blk_start[b * g.T_max + j] = start;
+      blk_n[b * g.T_max + j] = n;
+      btab[b * g.T_max + j] = make_int4(start, n, j, 0);
+    }
+  } else {
+    start = blk_start[b * g.T_max + j];
+    n = blk_n[b * g.T_max + j];
+  }
   if (n == 0) return;
-  const int start = blk_start[b * g.T_max + j];
-  const long long base = (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)start * g.stride_t;
-  for (int x = threadIdx.x; x < 128 * 16; x += 256) {          // 16-byte chunks
-    const int r = x >> 4, c = x & 15;
-    uint4 val = make_uint4(0, 0, 0, 0);
-    if (r < n) val = *reinterpret_cast<const uint4*>(v + base + (long long)r * g.stride_t + c * 8);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[r][c * 8]);
-    dst[0] = val.x; dst[1] = val.y; dst[2] = val.z; dst[3] = val.w;
+  const int c = threadIdx.x & 15, rg = threadIdx.x >> 4;          // 16-byte chunk c of rows rg, rg + 16, ..
+  const long long base = (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)start * g.stride_t + c * 8;
+  constexpr int NX = ALL ? 3 : 1;
+  const uint16_t* const src[3] = {v, q, k};
+  uint4 val[NX][8];
+#pragma unroll
+  for (int t = 0; t < NX; ++t)
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      val[t][i] = rg + 16 * i < n ? *reinterpret_cast<const uint4*>(src[t] + base + (long long)(rg + 16 * i) * g.stride_t) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[rg + 16 * i][c * 8]);
+    dst[0] = val[0][i].x; dst[1] = val[0][i].y; dst[2] = val[0][i].z; dst[3] = val[0][i].w;
+  }
+  if (ALL) {                                // column sums of Q and K over the thread's rows, in the order of k_block_means
+#pragma unroll
+    for (int t = 1; t < NX; ++t) {
+      float acc[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t w[4] = {val[t][i].x, val[t][i].y, val[t][i].z, val[t][i].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[2 * e] += __uint_as_float(w[e] << 16);
+          acc[2 * e + 1] += __uint_as_float(w[e] & 0xffff0000u);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; e += 4) *reinterpret_cast<float4*>(&red[t - 1][rg][c * 8 + e]) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
+    }
   }
   __syncthreads();
-  if (vc) {                                 // rows past n are zero: both halves of the threads add 64 rows of a channel
-    const int d = threadIdx.x & (MD - 1), r0 = (threadIdx.x >> 7) * 64;
+  if (ALL) {
+    const long long mean = (((long long)b * g.H + h) * g.T_max + j) * MD;
+    const int d = threadIdx.x & (MD - 1), t = threadIdx.x >> 7;
     float s = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s += red[t][r][d];
+    (t ? kc : qc)[mean + d] = s / (float)n;
+    float sv = 0.f;                          // V: rows past n are zero; each half of the threads adds 64 rows of a channel
 #pragma unroll 8
-    for (int r = 0; r < 64; ++r) s += __uint_as_float((uint32_t)tile[r0 + r][d] << 16);
-    if (r0) colsum[d] = s;
+    for (int r = 0; r < 64; ++r) sv += __uint_as_float((uint32_t)tile[t * 64 + r][d] << 16);
     __syncthreads();
-    if (!r0) vc[(((long long)b * g.H + h) * g.T_max + j) * MD + d] = (s + colsum[d]) / (float)n;
+    if (t) red[0][0][d] = sv;
+    __syncthreads();
+    if (!t) vc[mean + d] = (sv + red[0][0][d]) / (float)n;
   }
   const long long tile_off = (((long long)b * g.H + h) * g.T_max + j) * (2 * MD * KT);
+#pragma unroll 2
   for (int x = threadIdx.x; x < 2 * MD * 8; x += 256) {         // one 16-byte chunk = 8 key positions of one channel
     const int half = x / (MD * 8), rem = x % (MD * 8);
     const int d = rem >> 3, pc = rem & 7;
@@ -81,9 +133,16 @@ __global__ __launch_bounds__(256) void k_pack_vt(const uint16_t* __restrict__ v,
   }
 }
 
-hipError_t launch_pack_vt(const Problem& pr, const Workspace& ws, const void* v, float* vc, hipStream_t st) {
-  hipLaunchKernelGGL(k_pack_vt, dim3(pr.cnt.T_max, pr.p.H, pr.p.B), dim3(256), 0, st, (const uint16_t*)v, ws.vt,
-                     ws.vt4, ws.blk_start, ws.blk_n, ws.zero_tile, vc, ws.taylor_ctr + 1, pr.geo);
+hipError_t launch_pack_vt(const Problem& pr, const Workspace& ws, const void* v, hipStream_t st) {
+  hipLaunchKernelGGL((k_pack_vt<false>), dim3(pr.cnt.T_max, pr.p.H, pr.p.B), dim3(256), 0, st, (const uint16_t*)v, ws.vt,
+                     ws.vt4, ws.blk_start, ws.blk_n, ws.btab, ws.zero_tile, ws.taylor_ctr + 1, pr.geo, pr.seg, (const uint16_t*)nullptr,
+                     (const uint16_t*)nullptr, (float*)nullptr, (float*)nullptr, (float*)nullptr);
+  return hipGetLastError();
+}
+hipError_t launch_front(const Problem& pr, const Workspace& ws, const void* q, const void* k, const void* v, hipStream_t st) {
+  hipLaunchKernelGGL((k_pack_vt<true>), dim3(pr.cnt.T_max, pr.p.H, pr.p.B), dim3(256), 0, st, (const uint16_t*)v, ws.vt, ws.vt4,
+                     ws.blk_start, ws.blk_n, ws.btab, ws.zero_tile, ws.taylor_ctr + 1, pr.geo, pr.seg, (const uint16_t*)q,
+                     (const uint16_t*)k, ws.qc, ws.kc, ws.vc);
   return hipGetLastError();
 }
 

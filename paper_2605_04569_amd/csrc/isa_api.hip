@@ -260,7 +260,7 @@ static int run_attend(const Problem& pr, const Workspace& ws, const AttnArgs& a,
     ISA_STAGE(launch_attn_gen(pr, a, st));
     return ISA_OK;
   }
-  if (!vt_ready) ISA_STAGE(launch_pack_vt(pr, ws, v, nullptr, st));
+  if (!vt_ready) ISA_STAGE(launch_pack_vt(pr, ws, v, st));
   if (!a.dense) ISA_STAGE(launch_gather_means(pr, ws, a.kc, a.vc, a.kv_list, st));
   ISA_STAGE(launch_attn_mfma(pr, ws, a, st));
   return ISA_OK;
@@ -390,12 +390,14 @@ int isa_attend(const isa_problem* p, const void* q, const void* k, const void* v
 // Alg. 1, all stages, on a carved workspace (the body of isa_attention and of its allocation-free twin).
 static int run_attention(const Problem& pr, const Workspace& ws, const void* q, const void* k, const void* v, void* out,
                          hipStream_t st) {
-  ISA_STAGE(launch_layout(pr, ws, st));
-  // the matrix-core kernels want a packed V^T copy: the kernel that writes it has every block of V in LDS and writes the
-  // block's mean value too, so the block-mean kernel reads Q and K only
+  // the pipelined kernels want a packed V^T copy: the kernel that writes it takes the block table and the block means along
   const bool pack_first = pr.mfma_shape && g_use_mfma.load();
-  if (pack_first) ISA_STAGE(launch_pack_vt(pr, ws, v, ws.vc, st));
-  ISA_STAGE(launch_block_means(pr, ws, q, k, pack_first ? nullptr : v, ws.qc, ws.kc, ws.vc, st));
+  if (pack_first) {
+    ISA_STAGE(launch_front(pr, ws, q, k, v, st));
+  } else {
+    ISA_STAGE(launch_layout(pr, ws, st));
+    ISA_STAGE(launch_block_means(pr, ws, q, k, v, ws.qc, ws.kc, ws.vc, st));
+  }
   ISA_STAGE(launch_coarse(pr, ws, ws.qc, ws.kc, ws.s_ctx, ws.sharp, ws.z, ws.vc, ws.ocoarse, st));
   ISA_STAGE(launch_select(pr, ws, ws.s_ctx, ws.sharp, ws.z, ws.kv_list, ws.full_list, ws.flat_list, ws.exact_mask, st));
   AttnArgs a = attn_args(pr, ws, q, k, v, out, ws.kc, ws.vc, ws.kv_list, ws.full_list, ws.flat_list, ws.exact_mask, ws.ocoarse, 0);

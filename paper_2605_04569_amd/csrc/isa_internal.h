@@ -16,6 +16,21 @@ struct SegDesc {
   int seg_len[ISA_MAX_SEGMENTS];
 };
 
+// Place of block j of batch item b: token offset and real tokens (0 past the batch item's last block).
+__device__ __forceinline__ void block_place(const SegDesc& seg, int block, int b, int j, int& start, int& n) {
+  int first = 0, off = 0;
+  start = n = 0;
+  for (int s = seg.seg_ptr[b]; s < seg.seg_ptr[b + 1]; ++s) {
+    const int len = seg.seg_len[s], nb = (len + block - 1) / block;
+    if (j >= first && j < first + nb) {
+      start = off + (j - first) * block;
+      n = min(block, len - (j - first) * block);
+    }
+    first += nb;
+    off += len;
+  }
+}
+
 // Per-batch counts derived on the host (see isa_counts), passed to kernels by value.
 struct BatchCounts {
   int S, T, T_src, T_ctx, k_keep, T_new, n_flat, n_full, k_exact;
@@ -147,8 +162,9 @@ hipError_t launch_select(const Problem& pr, const Workspace& ws, const float* s_
 hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st);
 
 // MFMA path (bf16, D = 128, block = 128)
-// vc (may be null): also writes the fp32 block means of V, [B,H,T_max,D]
-hipError_t launch_pack_vt(const Problem& pr, const Workspace& ws, const void* v, float* vc, hipStream_t st);
+hipError_t launch_pack_vt(const Problem& pr, const Workspace& ws, const void* v, hipStream_t st);
+// the block table, the block means of q, k, v (into the workspace) and the packed V^T copy, in one launch
+hipError_t launch_front(const Problem& pr, const Workspace& ws, const void* q, const void* k, const void* v, hipStream_t st);
 hipError_t launch_gather_means(const Problem& pr, const Workspace& ws, const float* kc, const float* vc,
                                const int* kv_list, hipStream_t st);
 hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnArgs& a, hipStream_t st);

@@ -52,19 +52,9 @@ __device__ inline float bf16_bits_to_float(uint16_t b) { return __uint_as_float(
 __global__ void k_layout(SegDesc seg, int block, int T_max, int* blk_start, int* blk_n, int4* btab) {
   const int b = blockIdx.x;
   for (int j = threadIdx.x; j < T_max; j += blockDim.x) {
-    int start = 0, n = 0, first = 0, off = 0;
-    for (int s = seg.seg_ptr[b]; s < seg.seg_ptr[b + 1]; ++s) {
-      const int len = seg.seg_len[s];
-      const int nb = (len + block - 1) / block;
-      if (j >= first && j < first + nb) {
-        const int local = j - first;
-        start = off + local * block;
-        n = min(block, len - local * block);
-      }
-      first += nb;
-      off += len;
-    }
-    blk_start[b * T_max + j] = start;   // blocks past the batch item's T get n = 0
+    int start, n;
+    block_place(seg, block, b, j, start, n);
+    blk_start[b * T_max + j] = start;
     blk_n[b * T_max + j] = n;
     btab[b * T_max + j] = make_int4(start, n, j, 0);
   }
@@ -119,8 +109,7 @@ __global__ __launch_bounds__(256) void k_block_means(const T* __restrict__ q, co
   const long long obase = (((long long)b * g.H + h) * g.T_max + j) * D;
   const T* src[3] = {q, k, v};
   float* dst[3] = {qc, kc, vc};
-  const int n_tensors = v ? 3 : 2;        // without v: its means come from the kernel that packs V^T
-  for (int t = 0; t < n_tensors; ++t) {
+  for (int t = 0; t < 3; ++t) {
     float acc[VEC];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
