@@ -36,7 +36,6 @@ __device__ __forceinline__ void split_bf16x4(const float4 r, uint2& hi, uint2& l
   hi = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
   lo = make_uint2(l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16));
 }
-__device__ inline int swap23(int k) { return (k & ~12) | ((k & 4) << 1) | ((k & 8) >> 1); }
 // Key stored at position p of a 64-key V^T row in the layout of the 16x16x32 kernel: inside each 32-key group,
 // position 8 q + 4 kt + i holds key 16 kt + 4 q + i (the order in which a lane's score registers list its keys).
 __device__ inline int key_of_pos16(int p) { return (p & 32) | ((p & 4) << 2) | ((p >> 1) & 12) | (p & 3); }

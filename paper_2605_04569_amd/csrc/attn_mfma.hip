@@ -11,8 +11,10 @@
 // layout of the second product O^T = V^T P^T: P never leaves registers, and the row maximum / row sum of
 // the online softmax (Alg. 2 Part A) need one cross-lane exchange only.  The A operand of the second
 // product wants, per lane, 8 consecutive keys of one channel; V is therefore read from a copy that the
-// pack kernel stores transposed per 64-key half block, with key positions permuted to the accumulator's
-// key order (bits 2 and 3 of the key index swapped).
+// pack kernel stores transposed per 64-key half block in the key order of the 16x16x32 kernel, which serves
+// this kernel as well: 16 bytes of a channel hold keys 4 c + i and 16 + 4 c + i of a 32-key group, two groups of four
+// that a lane's accumulators hold too (elements 4 j + i: keys 8 j + 4 g + i), so the weights of j and j + 2 go together.
+// (A second copy in this kernel's natural order cost 0.67 GB of stores per 480p call, 0.13 ms of 22.5.)
 //
 // The Taylor branch (Sec. 3, Eq. 4; Alg. 2 Part B) runs through the same tile code: its "keys" are the
 // block means gathered in kv_list order, its "values" the gathered mean values, and the token count n_j
@@ -25,8 +27,7 @@ namespace isa {
 // Pack kernels
 // ------------------------------------------------------------------------------------------
 // V^T copies: vt[((bh*T_max + j)*2 + half)][d][pos]; keys past n_j are zero.  `vt` is in the key order of the
-// 16x16x32 kernel (position p holds key key_of_pos16(p)); `vt4`, written only when given, in that of the 4-wave
-// 32x32x16 kernel (position p holds key swap23(p)).
+// 16x16x32 kernel (position p holds key key_of_pos16(p)).
 //
 // ALL: the first kernel of the whole call.  The same workgroup also takes the block means of its block of V, Q and K
 // (fp32, Alg. 1 Stage 1), and finds its block's place from the segment lengths instead of reading it from the block
@@ -36,8 +37,8 @@ namespace isa {
 // tokens 12.7 us in three launches -> 6.8.
 template <bool ALL>
 __global__ __launch_bounds__(256) void k_pack_vt(const uint16_t* __restrict__ v, uint16_t* __restrict__ vt,
-                                                 uint16_t* __restrict__ vt4, int* __restrict__ blk_start,
-                                                 int* __restrict__ blk_n, int4* __restrict__ btab, uint16_t* __restrict__ zero_tile,
+                                                 int* __restrict__ blk_start, int* __restrict__ blk_n,
+                                                 int4* __restrict__ btab, uint16_t* __restrict__ zero_tile,
                                                  int* __restrict__ long_ctr, Geometry g, SegDesc seg,
                                                  const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                  float* __restrict__ qc, float* __restrict__ kc, float* __restrict__ vc) {
@@ -123,24 +124,17 @@ __global__ __launch_bounds__(256) void k_pack_vt(const uint16_t* __restrict__ v,
     o.x = e[0] | ((uint32_t)e[1] << 16); o.y = e[2] | ((uint32_t)e[3] << 16);
     o.z = e[4] | ((uint32_t)e[5] << 16); o.w = e[6] | ((uint32_t)e[7] << 16);
     *reinterpret_cast<uint4*>(vt + tile_off + (half * MD + d) * KT + pc * 8) = o;
-    if (vt4) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) e[i] = tile[half * 64 + swap23(pc * 8 + i)][d];    // swap23 is an involution
-      o.x = e[0] | ((uint32_t)e[1] << 16); o.y = e[2] | ((uint32_t)e[3] << 16);
-      o.z = e[4] | ((uint32_t)e[5] << 16); o.w = e[6] | ((uint32_t)e[7] << 16);
-      *reinterpret_cast<uint4*>(vt4 + tile_off + (half * MD + d) * KT + pc * 8) = o;
-    }
   }
 }
 
 hipError_t launch_pack_vt(const Problem& pr, const Workspace& ws, const void* v, hipStream_t st) {
   hipLaunchKernelGGL((k_pack_vt<false>), dim3(pr.cnt.T_max, pr.p.H, pr.p.B), dim3(256), 0, st, (const uint16_t*)v, ws.vt,
-                     ws.vt4, ws.blk_start, ws.blk_n, ws.btab, ws.zero_tile, ws.taylor_ctr + 1, pr.geo, pr.seg, (const uint16_t*)nullptr,
+                     ws.blk_start, ws.blk_n, ws.btab, ws.zero_tile, ws.taylor_ctr + 1, pr.geo, pr.seg, (const uint16_t*)nullptr,
                      (const uint16_t*)nullptr, (float*)nullptr, (float*)nullptr, (float*)nullptr);
   return hipGetLastError();
 }
 hipError_t launch_front(const Problem& pr, const Workspace& ws, const void* q, const void* k, const void* v, hipStream_t st) {
-  hipLaunchKernelGGL((k_pack_vt<true>), dim3(pr.cnt.T_max, pr.p.H, pr.p.B), dim3(256), 0, st, (const uint16_t*)v, ws.vt, ws.vt4,
+  hipLaunchKernelGGL((k_pack_vt<true>), dim3(pr.cnt.T_max, pr.p.H, pr.p.B), dim3(256), 0, st, (const uint16_t*)v, ws.vt,
                      ws.blk_start, ws.blk_n, ws.btab, ws.zero_tile, ws.taylor_ctr + 1, pr.geo, pr.seg, (const uint16_t*)q,
                      (const uint16_t*)k, ws.qc, ws.kc, ws.vc);
   return hipGetLastError();
@@ -148,13 +142,12 @@ hipError_t launch_front(const Problem& pr, const Workspace& ws, const void* q, c
 
 // Mean keys (without exact sets: minus the mean key of block 0) / values gathered in kv_list order, rounded to bf16, in the
 // layouts the attention kernel reads:
-// kcn[bh][t][d], vcn[bh][t][d]; vcnt[bh][t/64][d][pos] with the list position t%64 = key_of_pos16(pos) (and vcnt4, when given, with
-// t%64 = swap23(pos), for the 4-wave kernel); biasn[bh][t] = ln(n_j) sqrt(D), -inf past T_new.
+// kcn[bh][t][d], vcn[bh][t][d]; vcnt[bh][t/64][d][pos] with the list position t%64 = key_of_pos16(pos); biasn[bh][t] = ln(n_j) sqrt(D), -inf past T_new.
 __global__ __launch_bounds__(256) void k_gather_means(const float* __restrict__ kc, const float* __restrict__ vc,
                                                       const int* __restrict__ kv_list,
                                                       const int4* __restrict__ btab, uint16_t* __restrict__ kcn,
                                                       uint16_t* __restrict__ kcnb, uint16_t* __restrict__ vcn, uint16_t* __restrict__ vcnt,
-                                                      uint16_t* __restrict__ vcnt4,
+                                                      bool sets,
                                                       float* __restrict__ biasn, int* __restrict__ tflag,
                                                       int4* __restrict__ ktab, int* __restrict__ taylor_ctr, Counts cnt, int H,
                                                       int Tn_pad, int block) {
@@ -162,7 +155,6 @@ __global__ __launch_bounds__(256) void k_gather_means(const float* __restrict__ 
   __shared__ int ids[KT];
   // the attention launch that follows hands out its Taylor groups by counting this up from zero
   if (threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) *taylor_ctr = 0;
-  const bool sets = vcnt4 != nullptr;
   const int tile = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int T_new = cnt.b[b].T_new, T_max = cnt.T_max;
   const long long bh = (long long)b * H + h;
@@ -236,21 +228,17 @@ __global__ __launch_bounds__(256) void k_gather_means(const float* __restrict__ 
 #pragma unroll
   for (int x = threadIdx.x; x < MD * 8; x += 256) {                // 16 bytes: 8 positions of one channel
     const int d = x >> 3, p8 = (x & 7) * 8;
-    auto positions = [&](auto key_of) {
-      uint32_t w[4];
+    uint32_t w[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = vtile[key_of(p8 + 2 * e)][d] | ((uint32_t)vtile[key_of(p8 + 2 * e + 1)][d] << 16);
-      return make_uint4(w[0], w[1], w[2], w[3]);
-    };
-    *reinterpret_cast<uint4*>(vcnt + out_off + d * KT + p8) = positions([](int p) { return key_of_pos16(p); });
-    if (vcnt4) *reinterpret_cast<uint4*>(vcnt4 + out_off + d * KT + p8) = positions([](int p) { return swap23(p); });
+    for (int e = 0; e < 4; ++e) w[e] = vtile[key_of_pos16(p8 + 2 * e)][d] | ((uint32_t)vtile[key_of_pos16(p8 + 2 * e + 1)][d] << 16);
+    *reinterpret_cast<uint4*>(vcnt + out_off + d * KT + p8) = make_uint4(w[0], w[1], w[2], w[3]);
   }
 }
 
 hipError_t launch_gather_means(const Problem& pr, const Workspace& ws, const float* kc, const float* vc,
                                const int* kv_list, hipStream_t st) {
   hipLaunchKernelGGL(k_gather_means, dim3(pr.Tn_pad / KT, pr.p.H, pr.p.B), dim3(256), 0, st, kc, vc, kv_list,
-                     ws.btab, ws.kcn, ws.kcnb, ws.vcn, ws.vcnt, ws.vcnt4, ws.biasn, ws.tflag, ws.ktab, ws.taylor_ctr, pr.cnt, pr.p.H,
+                     ws.btab, ws.kcn, ws.kcnb, ws.vcn, ws.vcnt, pr.p.exact_frac > 0.0, ws.biasn, ws.tflag, ws.ktab, ws.taylor_ctr, pr.cnt, pr.p.H,
                      pr.Tn_pad, pr.p.block);
   return hipGetLastError();
 }
@@ -351,8 +339,9 @@ __device__ __forceinline__ void tile_body(const uint16_t* __restrict__ kbase, co
       const float p1 = __builtin_amdgcn_exp2f(fmaf(sacc[kb][e + 1], cscale, neg_m));
       const bf16x2 pp = {(__bf16)p0, (__bf16)p1};
       l_run = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, l_run, false);   // sum of the rounded weights
-      pf[kb * 2 + (e >> 3)][e & 7] = pp[0];
-      pf[kb * 2 + (e >> 3)][(e & 7) + 1] = pp[1];
+      const int j = e >> 2;                          // keys 8 j + 4 g + i of the 32-key group: chunk 2 (j % 2) + g of the packed V^T
+      pf[kb * 2 + (j & 1)][4 * (j >> 1) + (e & 3)] = pp[0];
+      pf[kb * 2 + (j & 1)][4 * (j >> 1) + (e & 3) + 1] = pp[1];
     }
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {

@@ -133,8 +133,6 @@ void carve(const Problem& pr, void* base, Workspace* ws, bool forward_only) {
     ws->vcnt = (uint16_t*)take(B * H * (size_t)pr.Tn_pad * D * 2);
     ws->biasn = (float*)take(B * H * (size_t)pr.Tn_pad * 4);
     ws->tflag = (int*)take(B * H * (size_t)(pr.Tn_pad / 64) * 4);
-    ws->vt4 = pr.p.exact_frac > 0.0 ? (uint16_t*)take(B * H * T * D * 128 * 2) : nullptr;
-    ws->vcnt4 = pr.p.exact_frac > 0.0 ? (uint16_t*)take(B * H * (size_t)pr.Tn_pad * D * 2) : nullptr;
     ws->zero_tile = (uint16_t*)take(128 * 64 * 2);
     ws->taylor_ctr = (int*)take(256);
     ws->ktab = (int4*)take(B * H * T * 16);
@@ -185,7 +183,7 @@ void carve(const Problem& pr, void* base, Workspace* ws, bool forward_only) {
     ws->cstats = nullptr;
   }
   if (!pr.mfma_shape) {
-    ws->vt = ws->kcn = ws->vcnt = ws->vt4 = ws->vcnt4 = nullptr;
+    ws->vt = ws->kcn = ws->vcnt = nullptr;
     ws->biasn = nullptr;
     ws->tflag = nullptr;
     ws->zero_tile = nullptr;

@@ -72,7 +72,6 @@ struct Workspace {
   uint16_t* vcnt;        // [B,H,Tn_pad/128][D][128]: mean values gathered, transposed, key-permuted
   float* biasn;          // [B,H,Tn_pad]: ln(n_j) sqrt(D) per gathered mean key (without exact sets: ln(n_j / block) sqrt(D)), -inf for padding
   int* tflag;            // [B,H,Tn_pad/64]: 1 if a tile of mean keys needs its bias or masks (padding, a short block, exact sets)
-  uint16_t* vt4; uint16_t* vcnt4;   // the same two arrays in the key order of the 4-wave kernel (only with exact sets)
   uint16_t* zero_tile;   // 16 KB of zeros, written by the V^T pack kernel
   int* taylor_ctr;       // the next Taylor group of the attention launch (zeroed by the mean gather, counted up by the launch)
   int* bwd_ctr;          // backward: the next work item of each launch that hands its items out dynamically (8 counters, zeroed by k_bwd_delta)
