@@ -619,16 +619,23 @@ __global__ __launch_bounds__(256) void k_bwd_delta(const uint16_t* __restrict__ 
 // queries (term = minus the row's log-sum-exp in the log2 domain, delta of the row); with `rq` (Taylor blocks under exact
 // sets, for scores against the gathered means, which are stored minus Kc_0) the row's q . Kc_0, scaled to the log2
 // domain, is added to the term.
-__global__ __launch_bounds__(128) void k_bwd_rows(const int* __restrict__ list, int kind, const int4* __restrict__ btab,
-                                                  const float* __restrict__ nlse, const float* __restrict__ rq, float rq_scale,
-                                                  const float* __restrict__ delta,
-                                                  int4* __restrict__ tab, float2* __restrict__ ybd,
+struct RowLists {                             // what k_bwd_rows does, list by list (blockIdx.z = list * B + batch item)
+  const int* list[4]; int kind[4]; const float* rq[4]; int4* tab[4]; float2* ybd[4];
+};
+__global__ __launch_bounds__(128) void k_bwd_rows(RowLists ls, int B, const int4* __restrict__ btab, const float* __restrict__ nlse,
+                                                  float rq_scale, const float* __restrict__ delta,
                                                   float2* __restrict__ ybd_mean, float* __restrict__ bx_mean, Counts cnt,
                                                   int H, int Tn_pad, int S_max) {
-  const int e = blockIdx.x, h = blockIdx.y, b = blockIdx.z, r = threadIdx.x;
+  const int which = blockIdx.z / B;
+  const int e = blockIdx.x, h = blockIdx.y, b = blockIdx.z % B, r = threadIdx.x;
+  const int* const list = ls.list[which];
+  const int kind = ls.kind[which];
+  const float* const rq = ls.rq[which];
+  int4* const tab = ls.tab[which];
+  float2* const ybd = ls.ybd[which];
   const int T_max = cnt.T_max;
   const long long bh = (long long)b * H + h;
-  const int n_list = kind == 0 ? cnt.b[b].T_new : kind == 1 ? cnt.b[b].n_full : cnt.b[b].n_flat;      // kinds 2, 3: Taylor blocks
+  const int n_list = kind == 0 ? cnt.b[b].T_new : kind == 1 ? cnt.b[b].n_full : cnt.b[b].n_flat;
   if (kind == 0 && e < Tn_pad && r == 0) {
     float l2 = -INFINITY;
     if (e < n_list) l2 = log2f((float)btab[b * T_max + block_in_range(list[bh * T_max + e], cnt.b[b].T)].y);
@@ -653,26 +660,36 @@ __global__ __launch_bounds__(128) void k_bwd_rows(const int* __restrict__ list, 
   yf[(pos >> 6) * 128 + 64 + (pos & 63)] = v.y;
 }
 
-// Rows of a token tensor that no later launch writes (keys and values of context blocks that were not kept): zero, or,
-// with the coarse residual, the block's share `rows[block] / n` of the gradient of its mean.  Written for every block;
-// the launches over the kept blocks overwrite theirs.
-__global__ __launch_bounds__(256) void k_bwd_fill(uint16_t* __restrict__ x, const float* __restrict__ rows,
-                                                  const int4* __restrict__ btab, Geometry g, Counts cnt) {
+// Rows of dK and dV that no later launch writes (keys and values of blocks that were not kept): zero, or, with the
+// coarse residual, the block's share `rows[block] / n` of the gradient of its mean.  The launches over the kept blocks write
+// theirs, so those are left alone (480p at the paper's ratios, half the blocks kept: 220 us for all rows of both -> 79).
+__global__ __launch_bounds__(256) void k_bwd_fill(uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
+                                                  const float* __restrict__ rows_k, const float* __restrict__ rows_v,
+                                                  const int* __restrict__ kv_list, const int4* __restrict__ btab, Geometry g, Counts cnt) {
   const int blk = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  if (blk >= cnt.b[b].T) return;
+  const int T = cnt.b[b].T, T_new = cnt.b[b].T_new;
+  if (blk >= T) return;
+  const long long bh = (long long)b * g.H + h;
+  int kept = 0;
+  for (int t = threadIdx.x; t < T_new; t += 256) kept |= block_in_range(kv_list[bh * cnt.T_max + t], T) == blk ? 1 : 0;
+  if (__syncthreads_or(kept)) return;
   const int4 ent = btab[b * cnt.T_max + blk];
   const int c16 = threadIdx.x & 15;
-  uint4 val = make_uint4(0, 0, 0, 0);
-  if (rows) {
-    const float inv = 1.0f / (float)ent.y;
-    const float* rp = rows + (((long long)b * g.H + h) * cnt.T_max + blk) * MD + 8 * c16;
-    uint32_t w[4];
+  const float inv = 1.0f / (float)ent.y;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = f2bf(rp[2 * i] * inv) | ((uint32_t)f2bf(rp[2 * i + 1] * inv) << 16);
-    val = make_uint4(w[0], w[1], w[2], w[3]);
+  for (int t = 0; t < 2; ++t) {
+    const float* rows = t ? rows_v : rows_k;
+    uint4 val = make_uint4(0, 0, 0, 0);
+    if (rows) {
+      const float* rp = rows + (bh * cnt.T_max + blk) * MD + 8 * c16;
+      uint32_t w[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = f2bf(rp[2 * i] * inv) | ((uint32_t)f2bf(rp[2 * i + 1] * inv) << 16);
+      val = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+    uint16_t* x = (t ? dv : dk) + (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)ent.x * g.stride_t + 8 * c16;
+    for (int r = threadIdx.x >> 4; r < ent.y; r += 16) *reinterpret_cast<uint4*>(x + (long long)r * g.stride_t) = val;
   }
-  for (int r = threadIdx.x >> 4; r < ent.y; r += 16)
-    *reinterpret_cast<uint4*>(x + (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)(ent.x + r) * g.stride_t + 8 * c16) = val;
 }
 
 // ---- coarse residual (Alg. 1 Stage 1 and Stage 5): out += gamma * O_coarse[block], O_coarse = softmax(Qc Kc^T / sqrt D) Vc.
@@ -987,23 +1004,17 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
                        ws.kc, ws.vc, ws.doc, ws.cstats, ws.cdk, ws.cdv, pr.cnt, H);
     ISA_BWD_CHECK();
   }
-  hipLaunchKernelGGL(k_bwd_fill, dim3(T_max, H, B), dim3(256), 0, st, (uint16_t*)dk, resid ? ws.cdk : nullptr, ws.btab,
-                     pr.geo, pr.cnt);
-  hipLaunchKernelGGL(k_bwd_fill, dim3(T_max, H, B), dim3(256), 0, st, (uint16_t*)dv, resid ? ws.cdv : nullptr, ws.btab,
-                     pr.geo, pr.cnt);
+  hipLaunchKernelGGL(k_bwd_fill, dim3(T_max, H, B), dim3(256), 0, st, (uint16_t*)dk, (uint16_t*)dv, resid ? ws.cdk : nullptr,
+                     resid ? ws.cdv : nullptr, kv_list, ws.btab, pr.geo, pr.cnt);
   ISA_BWD_CHECK();
   const int gx = T_max > pr.Tn_pad ? T_max : pr.Tn_pad;
-  const float* no_rq = nullptr;
   const float cs = 1.4426950408889634f / sqrtf((float)MD);      // raw score -> log2 domain
-  hipLaunchKernelGGL(k_bwd_rows, dim3(gx, H, B), dim3(128), 0, st, kv_list, 0, ws.btab, ws.nlse, no_rq, 0.f, ws.delta, ws.ktab,
-                     ws.ybd_kv, ws.ybd_mean, ws.bx_mean, pr.cnt, H, pr.Tn_pad, S_max);
-  hipLaunchKernelGGL(k_bwd_rows, dim3(gx, H, B), dim3(128), 0, st, full_list, 1, ws.btab, ws.nlse, no_rq, 0.f, ws.delta, ws.ftab,
-                     ws.ybd_full, ws.ybd_mean, ws.bx_mean, pr.cnt, H, pr.Tn_pad, S_max);
-  hipLaunchKernelGGL(k_bwd_rows, dim3(gx, H, B), dim3(128), 0, st, flat_list, 2, ws.btab, ws.nlse, no_rq, 0.f, ws.delta, ws.ltab,
-                     ws.ybd_flat, ws.ybd_mean, ws.bx_mean, pr.cnt, H, pr.Tn_pad, S_max);
-  if (ex)             // the same rows with q . Kc_0 in their exponent terms, for the launches that score them against gathered means
-    hipLaunchKernelGGL(k_bwd_rows, dim3(gx, H, B), dim3(128), 0, st, flat_list, 2, ws.btab, ws.nlse, (const float*)ws.rq, cs, ws.delta,
-                       ws.ltab, ws.ybd_flatm, ws.ybd_mean, ws.bx_mean, pr.cnt, H, pr.Tn_pad, S_max);
+  RowLists ls = {{kv_list, full_list, flat_list, flat_list}, {0, 1, 2, 2}, {nullptr, nullptr, nullptr, ws.rq},
+                 {ws.ktab, ws.ftab, ws.ltab, ws.ltab}, {ws.ybd_kv, ws.ybd_full, ws.ybd_flat, ws.ybd_flatm}};
+  // with exact sets the Taylor rows a second time, with q . Kc_0 in their exponent terms, for the launches that score them
+  // against gathered means
+  hipLaunchKernelGGL(k_bwd_rows, dim3(gx, H, B * (ex ? 4 : 3)), dim3(128), 0, st, ls, B, ws.btab, ws.nlse, cs, ws.delta,
+                     ws.ybd_mean, ws.bx_mean, pr.cnt, H, pr.Tn_pad, S_max);
   ISA_BWD_CHECK();
   if (ex) {
     hipLaunchKernelGGL(k_bwd_tmask, dim3(T_max, H, B), dim3(128), 0, st, exact_mask, ws.mask_t, pr.cnt, H);
