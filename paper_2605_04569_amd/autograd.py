@@ -10,12 +10,19 @@ import torch
 from . import binding as B
 
 
+def _zero_past_the_end(x, problem):
+    """The library writes every row of a batch item's tokens; the rows past its end are zeroed here."""
+    for b, lengths in enumerate(problem.seg_len):
+        n = sum(lengths)
+        if n < x.shape[2]:
+            x[b, :, n:].zero_()
+    return x
+
+
 class _IsaAttentionFunction(torch.autograd.Function):
     @staticmethod
     def forward(ctx, q, k, v, problem, workspace):
-        out = torch.empty_like(q)
-        if q.shape[0] > 1 or problem.S_max < q.shape[2]:
-            out.zero_()                          # rows past a batch item's end are not written by the library
+        out = _zero_past_the_end(torch.empty_like(q), problem)
         B.isa_attention(problem, q, k, v, out, workspace)
         ctx.save_for_backward(q, k, v, out)
         ctx.problem, ctx.workspace = problem, workspace
@@ -28,7 +35,7 @@ class _IsaAttentionFunction(torch.autograd.Function):
             g = torch.empty_like(q)
             g.copy_(d_out)
             d_out = g
-        dq, dk, dv = (torch.zeros_like(q) for _ in range(3))
+        dq, dk, dv = (_zero_past_the_end(torch.empty_like(q), ctx.problem) for _ in range(3))
         B.isa_attention_backward(ctx.problem, q, k, v, out, d_out, dq, dk, dv, ctx.workspace)
         return dq, dk, dv, None, None
 
