@@ -8,9 +8,14 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libisa_hip.so")
-SOURCES = ["isa_api.hip", "kernels_small.hip", "attn_gen.hip", "attn_mfma.hip", "attn_sp.hip", "attn_bwd.hip", "prologue.hip"]
+SOURCES = ["isa_api.hip", "kernels_small.hip", "attn_gen.hip", "attn_mfma.hip", "attn_sp.hip", "attn_bwd.hip", "attn_bwd_kv.hip", "prologue.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+
+
+# attn_bwd_kv.hip keeps its accumulators in accumulation registers by hand; every other matrix instruction of the file is to
+# write ordinary registers, which its vector instructions read next
+FILE_FLAGS = {"attn_bwd_kv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _hipcc():
@@ -28,7 +33,7 @@ def build(verbose=False, extra_flags=(), out=None, objdir=None):
 
     def compile_one(src):
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
-        cmd = [hipcc, *FLAGS, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc, *FLAGS, *FILE_FLAGS.get(src, ()), *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError("hipcc failed on %s:\n%s\n%s" % (src, " ".join(cmd), r.stderr[-8000:]))

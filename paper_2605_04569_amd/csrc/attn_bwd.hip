@@ -927,7 +927,7 @@ __global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
 // by what the launch streams.
 // split_units: into how many parts the streamed side can be cut (list entries or tiles of means; 0: not to be cut).
 template <bool SM, bool T2, bool YD>
-static hipError_t launch_one(BwdArgs a, int ex, int B, int H, hipStream_t st, int split_units = 0, int* dyn_ctr = nullptr) {
+static hipError_t launch_one(BwdArgs a, bool ex, int B, int H, hipStream_t st, int split_units = 0, int* dyn_ctr = nullptr) {
   if (a.items <= 0) return hipSuccess;
   if (YD && a.dx != nullptr) return hipErrorInvalidValue;
   const int cus = cus_per_xcd();
@@ -951,14 +951,9 @@ static hipError_t launch_one(BwdArgs a, int ex, int B, int H, hipStream_t st, in
   const long long dyn_wgs = ((n_dyn + n_dyn / 8) / N_XCD + cus_per_xcd() + 1) * N_XCD;
   const dim3 grid((unsigned)(SM ? ((long long)a.items * a.parts * B * H + N_XCD - 1) / N_XCD * N_XCD
                                 : a.dyn_ctr ? dyn_wgs : (a.items_xcd - a.tail_items + a.tail_items * a.tail_parts) * 8));
-  if (ex == 2) {                                // position bits only occur with token rows as stationary rows and dS
-    if (SM || !T2 || YD) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_attn_bwd<false, true, 2, false>), grid, dim3(512), 0, st, a);
-  } else if (ex == 1) {
-    hipLaunchKernelGGL((k_attn_bwd<SM, T2, 1, YD>), grid, dim3(512), 0, st, a);
-  } else {
-    hipLaunchKernelGGL((k_attn_bwd<SM, T2, 0, YD>), grid, dim3(512), 0, st, a);
-  }
+  constexpr int EX = SM ? 1 : 2;                  // mean rows mask whole tiles per lane, token rows (dQ) also single positions
+  if (ex) hipLaunchKernelGGL((k_attn_bwd<SM, T2, EX, YD>), grid, dim3(512), 0, st, a);
+  else hipLaunchKernelGGL((k_attn_bwd<SM, T2, 0, YD>), grid, dim3(512), 0, st, a);
   if (a.tail_items > 0)
     hipLaunchKernelGGL(k_bwd_tail_merge, dim3((unsigned)(8 * a.tail_items * 32)), dim3(256), 0, st, a);
   return hipGetLastError();
@@ -971,14 +966,13 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   const float gamma = (float)pr.p.gamma;
   const bool resid = pr.p.gamma != 0.0;               // ws.ocoarse holds O_coarse (recomputed by the caller of this function)
   const int B = pr.p.B, H = pr.p.H, T_max = pr.cnt.T_max;
-  int S_max = pr.S_max, sf = 0, sl = 0, sk = 0, min_kept = 1 << 30, min_full = 1 << 30;
+  int S_max = pr.S_max, sf = 0, sl = 0, sk = 0, min_kept = 1 << 30;
   for (int b = 0; b < B; ++b) {
     const BatchCounts& c = pr.cnt.b[b];
     sf = c.n_full > sf ? c.n_full : sf;
     sl = c.n_flat > sl ? c.n_flat : sl;
     sk = c.T_new > sk ? c.T_new : sk;
     min_kept = c.T_new < min_kept ? c.T_new : min_kept;
-    min_full = c.n_full < min_full ? c.n_full : min_full;
   }
   // The forward ran its 4-wave kernel (exact sets, possibly empty ones when exact_frac is too small for the list): token
   // keys and mean keys in one softmax, the mean keys stored minus Kc_0 and q . Kc_0 kept per Taylor row (ws.rq).
@@ -1042,7 +1036,7 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   a.add_rows = resid ? ws.cdq : nullptr; a.add_by_block = 1;       // every query block's share of dQc
   a.stat_list = full_list; a.stat_kind = 0; a.items = (sf + 1) / 2;
   a.s[0] = kept_tokens; a.s[1] = none; a.n_phases = 1; a.bits = nullptr;
-  if ((e = launch_one<false, true, false>(a, 0, B, H, st, min_kept)) != hipSuccess) return e;
+  if ((e = launch_one<false, true, false>(a, false, B, H, st, min_kept)) != hipSuccess) return e;
   a.stat_list = flat_list; a.stat_kind = 1; a.items = (sl + 1) / 2;
   if (ex) {
     a.s[0] = kept_tokens; a.s[0].masked = 1;
@@ -1052,9 +1046,9 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   } else {
     a.s[0] = kept_means; a.n_phases = 1;
   }
-  if ((e = launch_one<false, true, false>(a, ex ? 2 : 0, B, H, st, (min_kept + KT - 1) / KT, ws.bwd_ctr + 0)) != hipSuccess) return e;
+  if ((e = launch_one<false, true, false>(a, ex, B, H, st, (min_kept + KT - 1) / KT, ws.bwd_ctr + 0)) != hipSuccess) return e;
 
-  // ---- dKc and dK (streamed Q, dO)
+  // ---- dKc, dVc (streamed Q, dO of the Taylor blocks)
   const int n_mean_pairs = ((sk + 127) / 128 + 1) / 2;
   // The mean-row launches have few items (one per 256 gathered means and head): each is cut into up to BWD_MEAN_PARTS
   // parts along the streamed entries, as many as make the launch's rounds over the 256 compute units shortest.
@@ -1068,44 +1062,32 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
       if (rounds < best - 1e-9) { best = rounds; mean_parts = p; }
     }
   }
-  const BwdStream full_q = {Q, DO, nullptr, ws.ftab, ws.ybd_full, 1, 0};
-  const BwdStream flat_q = {Q, DO, nullptr, ws.ltab, ws.ybd_flat, 2, 0};
   const BwdStream flat_q_means = {Q, DO, nullptr, ws.ltab, ex ? ws.ybd_flatm : ws.ybd_flat, 2, 0};     // scored against gathered means
   a.dx = nullptr; a.rx = nullptr;
-  for (int pass = 0; pass < 2; ++pass) {          // pass 0: dKc, dK (W = dS, read Q transposed); pass 1: dVc, dV (W = P, dO transposed)
+  for (int pass = 0; pass < 2; ++pass) {          // pass 0: dKc (W = dS, read Q transposed); pass 1: dVc (W = P, dO transposed)
     float* mean_grad = pass == 0 ? ws.dkc : ws.dvc;
-    const float osc = pass == 0 ? scale : 1.0f;
     if (sl > 0) {                                 // gradients of the gathered means: every Taylor block, minus its exact set
       a.x1 = mean_keys; a.x2 = pass == 0 ? ws.vcn : nullptr; a.stat_list = nullptr; a.stat_kind = 2; a.bx = ws.bx_mean;
       a.s[0] = flat_q_means; a.s[0].masked = ex ? 3 : 0; a.s[1] = none; a.n_phases = 1; a.bits = ws.mask_t;
-      a.out_bf = nullptr; a.out_f32 = mean_grad; a.add_rows = nullptr; a.add_by_block = 0; a.oscale = osc; a.items = n_mean_pairs;
+      a.out_bf = nullptr; a.out_f32 = mean_grad; a.add_rows = nullptr; a.oscale = pass == 0 ? scale : 1.0f; a.items = n_mean_pairs;
       a.parts = mean_parts; a.part_stride = (long long)B * H * pr.Tn_pad * MD;
-      e = pass == 0 ? launch_one<true, true, true>(a, ex ? 1 : 0, B, H, st) : launch_one<true, false, false>(a, ex ? 1 : 0, B, H, st);
+      e = pass == 0 ? launch_one<true, true, true>(a, ex, B, H, st) : launch_one<true, false, false>(a, ex, B, H, st);
       if (e != hipSuccess) return e;
       if (mean_parts > 1) {
         hipLaunchKernelGGL(k_bwd_sum_parts, dim3(sk, H, B), dim3(128), 0, st, mean_grad, mean_parts, a.part_stride, pr.cnt, H,
                            pr.Tn_pad);
         ISA_BWD_CHECK();
       }
-      a.parts = 1;
     }
     if (resid) {                                  // the coarse residual's gradient of the same means joins the Taylor branch's
       hipLaunchKernelGGL(k_bwd_add_coarse, dim3(sk, H, B), dim3(128), 0, st, mean_grad, pass == 0 ? ws.cdk : ws.cdv,
                          kv_list, sl > 0 ? 0 : 1, pr.cnt, H, pr.Tn_pad);
       ISA_BWD_CHECK();
     }
-    // gradients of the kept tokens: every full-attention block, the Taylor blocks whose exact set holds the block, and
-    // the block's share of its mean's gradient
-    a.x1 = K; a.x2 = pass == 0 ? V : nullptr; a.stat_list = kv_list; a.stat_kind = 2; a.bx = nullptr;
-    a.s[0] = full_q; a.s[1] = none; a.n_phases = 1; a.bits = nullptr;
-    if (ex) { a.s[1] = flat_q; a.s[1].masked = 1; a.n_phases = 2; a.bits = ws.mask_t; }
-    a.out_bf = (uint16_t*)(pass == 0 ? dk : dv); a.out_f32 = nullptr;
-    a.add_rows = (sl > 0 || resid) ? mean_grad : nullptr; a.add_by_block = 0;
-    a.oscale = osc; a.items = (sk + 1) / 2;
-    e = pass == 0 ? launch_one<false, true, true>(a, ex ? 1 : 0, B, H, st, min_full, ws.bwd_ctr + 1)
-                  : launch_one<false, false, false>(a, ex ? 1 : 0, B, H, st, min_full, ws.bwd_ctr + 2);
-    if (e != hipSuccess) return e;
   }
+  // ---- dK, dV of the kept tokens: every full-attention block, the Taylor blocks whose exact set holds the block, and
+  // the block's share of its mean's gradient
+  if ((e = launch_bwd_kv(pr, ws, q, k, v, d_out, ex, sl > 0 || resid, dk, dv, st)) != hipSuccess) return e;
 #undef ISA_BWD_CHECK
   return hipSuccess;
 }

@@ -171,6 +171,9 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
                            const void* out, const void* d_out, const int* kv_list, const int* full_list,
                            const int* flat_list, const uint32_t* exact_mask, void* dq, void* dk, void* dv,
                            hipStream_t st);
+// dK and dV of the kept blocks (attn_bwd_kv.hip), after the gradients of the gathered means
+hipError_t launch_bwd_kv(const Problem& pr, const Workspace& ws, const void* q, const void* k, const void* v, const void* d_out,
+                         bool exact_sets, bool mean_grads, void* dk, void* dv, hipStream_t st);
 
 // prologue (prologue.hip): tile order, rotary embedding and block means in one pass (inverse: its transpose, no means);
 // the inverse reordering of one tensor
