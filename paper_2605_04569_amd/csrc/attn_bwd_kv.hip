@@ -5,10 +5,16 @@
 // Shape.  A workgroup is one kept block and 4 waves, one per SIMD: a wave keeps its 32 rows of K and V (64 registers) and
 // both accumulators (128) beside a tile's state, which takes the 512 registers a wave has when it is alone on its SIMD
 // (two waves per SIMD have 256 each: with them dK and dV were two launches of five products).  The streamed tiles, 64 rows of
-// Q and dO, come global -> LDS, PD tiles ahead, in PD + 1 stages.  An iteration of a wave is 128 MFMAs (2048 cycles of the
+// Q and dO, come global -> LDS two tiles ahead, in four stages.  An iteration of a wave is 128 MFMAs (2048 cycles of the
 // matrix pipe); each of its 64 KB of fragments feeds two of them, so the four waves together read at the LDS's full rate
 // meanwhile, and the 32 weights per lane (fma, exp2, two products' roundings) are issued between the MFMAs of the next
-// sub-tile.  XX
+// sub-tile.
+//
+// Measured at 480p with the paper's ratios (40 heads, 288 kept and 256 full-attention blocks each): 56.0 ms in two launches of 8
+// waves -> 47.2 in this one, 45.1 with the tile set-up, the barrier and the first fragments of the next tile moved into the
+// shadows of matrix instructions.  Matrix pipe busy 52 % of 4000 cycles an iteration at 2.2 GHz; a wave waits 20 % of
+// them for LDS or the barrier and 28 % for the pipe.  Without effect (within 1 %): fragments 5 or 7 steps ahead instead of 3, vector
+// instructions placed one by one behind every matrix instruction, another chunk swizzle.
 //
 // Layouts as in attn_bwd.hip: with r = lane % 16, q = lane / 16, T1 = Q K^T and T2 = dO V^T - delta of a 16-row sub-tile give lane
 // (r, q) streamed rows 4 q + i of key 16 qt + r; the weights P and dS of two sub-tiles are the B operands of dV^T += dO^T P
@@ -21,8 +27,7 @@ namespace isa {
 
 namespace {
 
-constexpr int PD = 3;                                 // tiles in flight
-constexpr int NST = PD + 1;                           // LDS stages
+constexpr int NST = 4;                                // LDS stages; two tiles are in flight (see the loop)
 constexpr int STAGE_B = 2 * K_TILE * 2 + 1024;        // bytes of a stage: the Q and dO tiles, then 64 exponent terms and 64 minus-deltas
 constexpr int TILE_LOADS = 9;                         // load instructions of a wave per tile
 
@@ -142,8 +147,9 @@ __global__ __launch_bounds__(256, 1) void k_bwd_kv(KvArgs a) {
   int phase = 0, cbase = cut(c.n_full, part) - 64, hi = cut(c.n_full, part + 1);
   int c_start = 0, c_n = 0;
   unsigned long long todo = 0ull;
-  struct Tile { int start, nk, pos; bool end; };        // first row, rows, list position of the first row (entries are 128 apart)
-  Tile at = {0, 0, 0, false};
+  struct Tile { int start, nk, pos; };                  // first row, rows, list position of the first row (entries are 128 apart)
+  Tile at = {0, 1, 0};                                  // (an empty sequence loads row 0 and multiplies nothing)
+  bool end = false;                                     // `at` was the last one
   int rest = 0;                                         // rows of its block behind the tile described last
   auto next_tile = [&]() __attribute__((always_inline)) {
     if (rest > 0) {
@@ -155,7 +161,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_kv(KvArgs a) {
     }
     while (todo == 0ull) {
       if (cbase + 64 >= hi) {
-        if (phase == 1 || !bits) { at.end = true; return; }
+        if (phase == 1 || !bits) { end = true; return; }
         phase = 1;
         cbase = cut(c.n_flat, part) - 64;
         hi = cut(c.n_flat, part + 1);
@@ -183,22 +189,45 @@ __global__ __launch_bounds__(256, 1) void k_bwd_kv(KvArgs a) {
   const char* const q_head = reinterpret_cast<const char*>(a.q + tbase);
   const char* const o_head = reinterpret_cast<const char*>(a.d_o + tbase);
   const int l16 = lane >> 4;
-  auto issue = [&](const Tile& t, int ph, int stage) __attribute__((always_inline)) {
-    const uint32_t off = (uint32_t)t.start * stride_b;
-    const char* const q_tile = uniform_ptr(q_head + off);
-    const char* const o_tile = uniform_ptr(o_head + off);
-    const char* const side = uniform_ptr(reinterpret_cast<const char*>((ph == 0 ? a.qside[0] : a.qside[1]) + bh * T_max * 128 + t.pos));
-    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_addr(lds) + (uint32_t)stage * STAGE_B + (uint32_t)wave * 4096u);
+  // The loads of a tile in four slices: 0 describes the tile and works its addresses out, 1 to 3 issue the loads.  A
+  // sequence that has ended loads its last tile again: the number of loads in flight stays the same.
+  uint32_t row_off[4];                                  // bytes from the tile's first row: row 16 wave + 4 i + lane / 16, swizzled chunk
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = 16 * wave + 4 * i + l16;         // chunk ch of row r sits at ch ^ (r & 15); rows past the end repeat the last one
-      const uint32_t ro = (uint32_t)min(row, t.nk - 1) * stride_b + (uint32_t)(((lane & 15) ^ (row & 15)) * 16);
-      dma16(q_tile, ro, dst + i * 1024);
-      dma16(o_tile, ro, dst + K_TILE * 2 + i * 1024);
+  for (int i = 0; i < 4; ++i) {
+    const int row = 16 * wave + 4 * i + l16;            // chunk ch of row r sits at ch ^ (r & 15)
+    row_off[i] = (uint32_t)row * stride_b + (uint32_t)(((lane & 15) ^ (row & 15)) * 16);
+  }
+  const char *q_tile = nullptr, *o_tile = nullptr, *side_tile = nullptr;
+  uint32_t dst = 0, ro[4];
+  int in_stage = 0;                                     // where the next tile goes
+  auto issue_slice = [&](int f) __attribute__((always_inline)) {
+    if (f == 0) {
+      next_tile();
+      const uint32_t off = (uint32_t)at.start * stride_b;
+      q_tile = uniform_ptr(q_head + off);
+      o_tile = uniform_ptr(o_head + off);
+      side_tile = uniform_ptr(reinterpret_cast<const char*>((phase == 0 ? a.qside[0] : a.qside[1]) + bh * T_max * 128 + at.pos));
+      dst = __builtin_amdgcn_readfirstlane(lds_addr(lds) + (uint32_t)in_stage * STAGE_B);
+      in_stage = (in_stage + 1) & (NST - 1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ro[i] = row_off[i];
+      if (__builtin_expect(at.nk < KT, 0)) {            // rows past the end repeat the last one
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = 16 * wave + 4 * i + l16;
+          ro[i] = (uint32_t)min(row, at.nk - 1) * stride_b + (uint32_t)(((lane & 15) ^ (row & 15)) * 16);
+        }
+      }
+    } else if (f < 3) {
+#pragma unroll
+      for (int i = 2 * (f - 1); i < 2 * f; ++i) {
+        dma16(q_tile, ro[i], dst + (uint32_t)wave * 4096u + i * 1024);
+        dma16(o_tile, ro[i], dst + (uint32_t)wave * 4096u + K_TILE * 2 + i * 1024);
+      }
+    } else {
+      // 512 B, lanes 32..63 repeat lanes 0..31; every wave loads them, so that all waves have the same number of loads in flight
+      dma16(side_tile, (uint32_t)(lane & 31) * 16u, dst + 4u * K_TILE);
     }
-    // 512 B, lanes 32..63 repeat lanes 0..31; every wave loads them, so that all waves have the same number of loads in flight
-    dma16(side, (uint32_t)(lane & 31) * 16u,
-          __builtin_amdgcn_readfirstlane(lds_addr(lds) + (uint32_t)stage * STAGE_B + 4u * K_TILE));
   };
 
   // per-lane fragment offsets in bytes (attn_bwd.hip has the layouts)
@@ -219,56 +248,59 @@ __global__ __launch_bounds__(256, 1) void k_bwd_kv(KvArgs a) {
   const float cscale = 1.4426950408889634f / sqrtf((float)MD);       // log2(e) / sqrt(D)
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
 
-  // ---- loop: `ahead` tiles behind the current one are in flight
-  int ahead = 0, in_stage = 0;                          // in_stage: where the next tile to be issued goes
-  auto issue_next = [&]() __attribute__((always_inline)) -> bool {
-    if (at.end) return false;
-    next_tile();
-    if (at.end) return false;
-    issue(at, phase, in_stage);
-    in_stage = in_stage == NST - 1 ? 0 : in_stage + 1;
-    return true;
+  constexpr int PF = 3, NB = 4;                         // fragments are requested PF steps ahead, in NB rotating sets
+  bf16x8 fa[NB], fb[NB];                                // T steps: Q, dO rows; C steps: Q^T, dO^T
+  f32x4 nd[2], bt[2];                                   // minus deltas / exponent terms of the rows of a sub-tile, [kt]
+  // steps 0..15 of a tile: T (sub-tile n / 4, k-slice n % 4); 16..31: C (half, channel tile)
+  auto load = [&](const unsigned char* sb, int n) __attribute__((always_inline)) {
+    if (n < 16) {
+      const unsigned char* p = sb + (n >> 2) * 16 * MD * 2 + koff[n & 3];
+      fa[n % NB] = *reinterpret_cast<const bf16x8*>(p);
+      fb[n % NB] = *reinterpret_cast<const bf16x8*>(p + K_TILE * 2);
+    } else {
+      const unsigned char* p = sb + ((n - 16) >> 3) * 32 * MD * 2 + tr_pos[n & 7];
+      auto tr = [](const unsigned char* x) __attribute__((always_inline)) {
+        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)x);
+        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(x + 16 * MD * 2));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      };
+      fa[n % NB] = tr(p);
+      fb[n % NB] = tr(p + K_TILE * 2);
+    }
   };
-  bool live = issue_next();
-#pragma unroll 1
-  for (int i = 1; i < PD; ++i) ahead += issue_next() ? 1 : 0;
-  for (int stage = 0; live;) {
-    // this wave's loads of the current tile have landed (loads complete in the order of their issue); after the barrier
-    // everybody's have, and everybody has finished reading the stage that is filled next
-    if (ahead == 2) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * TILE_LOADS) : "memory");
-    else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(TILE_LOADS) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    const unsigned char* const sb = lds + stage * STAGE_B;
-    const float* const side = reinterpret_cast<const float*>(sb + 4 * K_TILE);
+  auto load_delta = [&](const unsigned char* sb, int s) __attribute__((always_inline)) {
+    nd[s & 1] = *reinterpret_cast<const f32x4*>(sb + 4 * K_TILE + 256 + (16 * s + 4 * q) * 4);
+  };
+  auto load_term = [&](const unsigned char* sb, int s) __attribute__((always_inline)) {
+    bt[s & 1] = *reinterpret_cast<const f32x4*>(sb + 4 * K_TILE + (16 * s + 4 * q) * 4);
+  };
 
-    constexpr int PF = 2, NB = PF + 1;                  // fragments are requested PF steps ahead, in PF + 1 rotating sets
-    bf16x8 fa[NB], fb[NB];                              // T steps: Q, dO rows; C steps: Q^T, dO^T
-    auto load = [&](int n) __attribute__((always_inline)) {        // steps 0..15: T (sub-tile n / 4, k-slice n % 4); 16..31: C
-      if (n < 16) {
-        const unsigned char* p = sb + (n >> 2) * 16 * MD * 2 + koff[n & 3];
-        fa[n % NB] = *reinterpret_cast<const bf16x8*>(p);
-        fb[n % NB] = *reinterpret_cast<const bf16x8*>(p + K_TILE * 2);
-      } else {
-        const unsigned char* p = sb + ((n - 16) >> 3) * 32 * MD * 2 + tr_pos[n & 7];
-        auto tr = [](const unsigned char* x) __attribute__((always_inline)) {
-          const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)x);
-          const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(x + 16 * MD * 2));
-          return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-        };
-        fa[n % NB] = tr(p);
-        fb[n % NB] = tr(p + K_TILE * 2);
-      }
-    };
-    f32x4 nd[2], bt[2];                                 // minus deltas / exponent terms of the rows of a sub-tile, [kt]
-    auto load_delta = [&](int s) __attribute__((always_inline)) { nd[s & 1] = *reinterpret_cast<const f32x4*>(side + 64 + 16 * s + 4 * q); };
-    auto load_term = [&](int s) __attribute__((always_inline)) { bt[s & 1] = *reinterpret_cast<const f32x4*>(side + 16 * s + 4 * q); };
+  // ---- loop over the tiles; iteration n:
+  //   T products of tile n, with the set-up and the loads of tile n + 2 in the shadows of its first four steps (which have no weights
+  //   to issue); the first half's C products;
+  //   wait for this wave's loads of tile n + 1 (all but the last tile's, loads complete in the order of their issue); barrier:
+  //   tile n + 1 is complete for everybody, and everybody is through tile n - 1, whose stage tile n + 3 will fill;
+  //   the second half's C products, with the first fragments of tile n + 1 requested in their shadows.
+  // A wave is alone on its SIMD: what it waits for, or works out with no matrix instruction in flight, nothing hides.
+  int live = 0;                                         // tiles described and not yet multiplied
+  auto describe = [&](int f) __attribute__((always_inline)) {
+    issue_slice(f);
+    if (f == 0) live += end ? 0 : 1;
+  };
 #pragma unroll
-    for (int n = 0; n < PF; ++n) load(n);
-    load_delta(0);
-    // the first fragments are on their way from LDS while the next tile's loads are set up and issued
-    const bool more = issue_next();
-
+  for (int f = 0; f < 4; ++f) describe(f);
+  if (live > 0) {
+#pragma unroll
+  for (int f = 0; f < 4; ++f) describe(f);
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"(TILE_LOADS) : "memory");
+  __syncthreads();
+#pragma unroll
+  for (int n = 0; n < PF; ++n) load(lds, n);
+  load_delta(lds, 0);
+  for (int stage = 0;;) {
+    const unsigned char* const sb = lds + stage * STAGE_B;
+    stage = (stage + 1) & (NST - 1);
+    const unsigned char* const sb_next = lds + stage * STAGE_B;
     f32x4 t1[2][2], t2[2][2];                           // [kt][qt]
     bf16x8 wp[2][2], ws[2][2];                          // [half][qt]: P and dS; element 4 kt + i = streamed row 32 half + 16 kt + 4 q + i
     auto weight2 = [&](int s, int tp) __attribute__((always_inline)) {      // weights 2 tp, 2 tp + 1 of sub-tile s: key tile tp / 2
@@ -287,40 +319,48 @@ __global__ __launch_bounds__(256, 1) void k_bwd_kv(KvArgs a) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int kt = s & 1;
-      if (s > 0) load_term(s - 1);
-      if (s < 3) load_delta(s + 1);
+      if (s > 0) load_term(sb, s - 1);
+      if (s < 3) load_delta(sb, s + 1);
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         const int n = 4 * s + ks, cb = n % NB;
         ISA_KV_FENCE();
-        load(n + PF);
+        load(sb, n + PF);
         t1[kt][0] = mfma16(fa[cb], kf[0][ks], ks == 0 ? zero4 : t1[kt][0]);
         t1[kt][1] = mfma16(fa[cb], kf[1][ks], ks == 0 ? zero4 : t1[kt][1]);
         t2[kt][0] = mfma16(fb[cb], vf[0][ks], ks == 0 ? nd[kt] : t2[kt][0]);
         t2[kt][1] = mfma16(fb[cb], vf[1][ks], ks == 0 ? nd[kt] : t2[kt][1]);
         if (s > 0) weight2(s - 1, ks);
+        else describe(ks);
       }
     }
-    load_term(3);
+    load_term(sb, 3);
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh)
+    for (int hh = 0; hh < 2; ++hh) {
+      if (hh == 1) {
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(TILE_LOADS) : "memory");
+        __builtin_amdgcn_s_barrier();                   // the fragments in flight are of this tile, whose stage nobody fills yet
+        asm volatile("" ::: "memory");
+      }
 #pragma unroll
       for (int ct = 0; ct < 8; ++ct) {
         const int n = 16 + 8 * hh + ct, cb = n % NB;
         ISA_KV_FENCE();
-        if (n + PF < 32) load(n + PF);
+        load(n + PF < 32 ? sb : sb_next, (n + PF) % 32);
+        if (n == 31) load_delta(sb_next, 0);
         mfma16_acc(fa[cb], ws[hh][0], ak[ct][0]);
         mfma16_acc(fa[cb], ws[hh][1], ak[ct][1]);
         mfma16_acc(fb[cb], wp[hh][0], av[ct][0]);
         mfma16_acc(fb[cb], wp[hh][1], av[ct][1]);
         if (hh == 0 && ct < 7 && !(ct & 1)) weight2(3, ct >> 1);
       }
+    }
     ISA_KV_FENCE();
-    stage = stage == NST - 1 ? 0 : stage + 1;
-    live = ahead > 0 || more;
-    ahead += (more ? 1 : 0) - 1;
+    if (--live == 0) break;
   }
-
+  }
+  // the loads past the end still target this workgroup's LDS: let them land before the waves end
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
   for (int ct = 0; ct < 8; ++ct)
 #pragma unroll
