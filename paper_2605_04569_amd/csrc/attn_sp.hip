@@ -814,25 +814,6 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
     m.slots_first = sf > 0 ? sf : 1;        // divisors in the kernel; a branch with no work gets no workgroups
     m.slots_second = ss > 0 ? ss : 1;
     m.n_long = (int)(((long long)pr.p.B * pr.p.H * sf + N_XCD - 1) / N_XCD);
-    // An XCD runs one workgroup per compute unit, so its long items go in rounds of `cus`; when the last round is at
-    // most half full, its items are cut into as many key ranges as fill it.  A sub-item costs about five iterations beside those
-    // of its tiles (set-up, pipeline drain, its share of the merge), so a range is at least two key blocks (four tiles) long;
-    // this matters to launches of less than a round (5 heads, 990 tokens, 7 key blocks: 31.9 us for the kernel before, 21.0 + 4.5
-    // with the merge).
-    m.n_split = 0; m.parts = 1;
-    m.split_o = ws.split_o; m.split_ml = ws.split_ml;
-    const int cus = cus_per_xcd(), rem = m.n_long % cus;
-    if (rem > 0 && rem <= cus / 2 && ws.split_o) {
-      int min_list = 1 << 30;
-      for (int b = 0; b < pr.p.B; ++b) {
-        const int nl = a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new;
-        min_list = nl < min_list ? nl : min_list;
-      }
-      int parts = cus / rem;
-      if (parts > min_list / 2) parts = min_list / 2;
-      while (parts >= 2 && N_XCD * rem * parts > SPLIT_MAX_SUB) --parts;      // the partial-result area holds SPLIT_MAX_SUB sub-items
-      if (parts >= 2) { m.n_split = rem; m.parts = parts; }
-    }
     // Taylor pairs go in groups of up to TAYLOR_GROUP consecutive pairs of a head per workgroup
     // (fewer when there are not enough pairs for a group per compute unit: then the pairs of a group would only wait for
     // each other)
@@ -843,6 +824,29 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
     const long long n_groups = ss > 0 ? (long long)pr.p.B * pr.p.H * m.groups_second : 0;
     m.n_taylor_wg = (int)((n_groups + N_XCD - 1) / N_XCD < cus_per_xcd() ? (n_groups + N_XCD - 1) / N_XCD : cus_per_xcd());
     m.taylor_ctr = ws.taylor_ctr;
+    // An XCD runs one workgroup per compute unit, so its long items go in rounds of `cus`; when the last round is at
+    // most half full, its items are cut into as many key ranges as fill it, of two blocks or more, or of one block in up to 8
+    // ranges (a merge reads every range).  Where that round is the only one and the ranges would be as short as the work of a
+    // Taylor group (less than four blocks), the workgroups of the groups need their compute units too.  Measured, 5 heads of 990
+    // tokens (7 key blocks), kernel + merge: whole items 31.9 us, ranges of two blocks 25.5, of one 23.5; whole call, 8 heads
+    // of 3200 tokens without / with room for the groups 73 / 65 us, 12 heads of 1564 66 / 60; 2 heads of 9360 tokens (ranges of 5
+    // blocks) 77 / 79.
+    m.n_split = 0; m.parts = 1;
+    m.split_o = ws.split_o; m.split_ml = ws.split_ml;
+    const int cus = cus_per_xcd(), rem = m.n_long % cus;
+    if (rem > 0 && rem <= cus / 2 && ws.split_o) {
+      int min_list = 1 << 30;
+      for (int b = 0; b < pr.p.B; ++b) {
+        const int nl = a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new;
+        min_list = nl < min_list ? nl : min_list;
+      }
+      int parts = cus / rem;
+      if (m.n_long < cus && 4 * parts > min_list) parts = (cus - (m.n_taylor_wg < cus / 2 ? m.n_taylor_wg : cus / 2)) / rem;
+      const int most = min_list / 2 > 8 ? min_list / 2 : (min_list < 8 ? min_list : 8);
+      if (parts > most) parts = most;
+      while (parts >= 2 && N_XCD * rem * parts > SPLIT_MAX_SUB) --parts;      // the partial-result area holds SPLIT_MAX_SUB sub-items
+      if (parts >= 2) { m.n_split = rem; m.parts = parts; }
+    }
     // Dense attention over a long sequence: nothing but long items, 64 rounds of them or more.  The XCDs of a chip differ
     // in speed by several per cent, and with equal shares the launch ends with the slowest; there are no short items to
     // level with, so the long items themselves are taken from a counter (zeroed by the V^T pack, which precedes every
