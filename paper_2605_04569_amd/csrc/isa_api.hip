@@ -252,14 +252,14 @@ static AttnArgs attn_args(const Problem& pr, const Workspace& ws, const void* q,
 }
 
 static int run_attend(const Problem& pr, const Workspace& ws, const AttnArgs& a, const void* v, bool vt_ready,
-                      hipStream_t st) {
+                      hipStream_t st, bool means_ready = false) {
   const bool mfma = pr.mfma_shape && g_use_mfma.load();
   if (!mfma) {
     ISA_STAGE(launch_attn_gen(pr, a, st));
     return ISA_OK;
   }
   if (!vt_ready) ISA_STAGE(launch_pack_vt(pr, ws, v, st));
-  if (!a.dense) ISA_STAGE(launch_gather_means(pr, ws, a.kc, a.vc, a.kv_list, st));
+  if (!a.dense && !means_ready) ISA_STAGE(launch_gather_means(pr, ws, a.kc, a.vc, a.kv_list, st));
   ISA_STAGE(launch_attn_mfma(pr, ws, a, st));
   return ISA_OK;
 }
@@ -396,10 +396,11 @@ static int run_attention(const Problem& pr, const Workspace& ws, const void* q, 
     ISA_STAGE(launch_layout(pr, ws, st));
     ISA_STAGE(launch_block_means(pr, ws, q, k, v, ws.qc, ws.kc, ws.vc, st));
   }
-  ISA_STAGE(launch_coarse(pr, ws, ws.qc, ws.kc, ws.s_ctx, ws.sharp, ws.z, ws.vc, ws.ocoarse, st));
-  ISA_STAGE(launch_select(pr, ws, ws.s_ctx, ws.sharp, ws.z, ws.kv_list, ws.full_list, ws.flat_list, ws.exact_mask, st));
+  const bool small = pack_first && select_is_small(pr);
+  ISA_STAGE(launch_coarse(pr, ws, ws.qc, ws.kc, ws.s_ctx, ws.sharp, ws.z, ws.vc, ws.ocoarse, st, !small));
+  ISA_STAGE(launch_select(pr, ws, ws.s_ctx, ws.sharp, ws.z, ws.kv_list, ws.full_list, ws.flat_list, ws.exact_mask, st, small));
   AttnArgs a = attn_args(pr, ws, q, k, v, out, ws.kc, ws.vc, ws.kv_list, ws.full_list, ws.flat_list, ws.exact_mask, ws.ocoarse, 0);
-  return run_attend(pr, ws, a, v, pack_first, st);
+  return run_attend(pr, ws, a, v, pack_first, st, small);
 }
 
 int isa_attention(const isa_problem* p, const void* q, const void* k, const void* v, void* out, void* workspace,

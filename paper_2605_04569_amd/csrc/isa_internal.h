@@ -155,9 +155,13 @@ hipError_t launch_layout(const Problem& pr, const Workspace& ws, hipStream_t st)
 hipError_t launch_block_means(const Problem& pr, const Workspace& ws, const void* q, const void* k, const void* v,
                               float* qc, float* kc, float* vc, hipStream_t st);
 hipError_t launch_coarse(const Problem& pr, const Workspace& ws, const float* qc, const float* kc,
-                         float* s_ctx, float* sharp, float* z, const float* vc, float* ocoarse, hipStream_t st);
+                         float* s_ctx, float* sharp, float* z, const float* vc, float* ocoarse, hipStream_t st,
+                         bool columns = true);          // columns: also the column means (s_ctx)
+// small: the selection of a short problem takes the column means before and the mean gather after along (whole call on the
+// workspace's own arrays, problems for which select_is_small holds)
+bool select_is_small(const Problem& pr);
 hipError_t launch_select(const Problem& pr, const Workspace& ws, const float* s_ctx, const float* sharp, const float* z,
-                         int* kv_list, int* full_list, int* flat_list, uint32_t* exact_mask, hipStream_t st);
+                         int* kv_list, int* full_list, int* flat_list, uint32_t* exact_mask, hipStream_t st, bool small = false);
 hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st);
 
 // MFMA path (bf16, D = 128, block = 128)

@@ -4,7 +4,7 @@
 // are reproducible from run to run.
 #include <hip/hip_bf16.h>
 
-#include "isa_internal.h"
+#include "gather.h"
 
 namespace isa {
 
@@ -331,7 +331,7 @@ static hipError_t launch_coarse_rows(const Problem& pr, const Workspace& ws, con
 }
 
 hipError_t launch_coarse(const Problem& pr, const Workspace& ws, const float* qc, const float* kc, float* s_ctx,
-                         float* sharp, float* z, const float* vc, float* ocoarse, hipStream_t st) {
+                         float* sharp, float* z, const float* vc, float* ocoarse, hipStream_t st, bool columns) {
   // 16 rows per workgroup (every column of the matrix instruction's B operand in use) while two such workgroups fit
   // a compute unit's LDS; 8 rows for longer rows (up to ISA_MAX_BLOCKS columns: 131 KB)
   const bool wide = (size_t)16 * (((pr.cnt.T_max + 15) / 16) * 16 + 4) * sizeof(float) <= 80 * 1024;
@@ -340,7 +340,7 @@ hipError_t launch_coarse(const Problem& pr, const Workspace& ws, const float* qc
                               : launch_coarse_rows<128, 8>(pr, ws, qc, kc, sharp, z, vc, ocoarse, st);
   else e = wide ? launch_coarse_rows<64, 16>(pr, ws, qc, kc, sharp, z, vc, ocoarse, st)
                 : launch_coarse_rows<64, 8>(pr, ws, qc, kc, sharp, z, vc, ocoarse, st);
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || !columns) return e;
   hipLaunchKernelGGL(k_colmean, dim3((pr.Tctx_max + 63) / 64, pr.p.H, pr.p.B), dim3(256), 0, st, ws.pctx, s_ctx, pr.cnt,
                      pr.p.H, pr.Tsrc_max, pr.Tctx_max);
   return hipGetLastError();
@@ -415,24 +415,61 @@ __device__ void compact(const int* flags, int n, int add, int* out_yes, int* out
   __syncthreads();
 }
 
+// Short problems (SMALL: at most 256 source and 256 context blocks, 256 kept ones): the workgroup of the context blocks also
+// takes the column means of Eq. 1 from pctx (in the order of k_colmean) before it selects, and gathers the means of the
+// blocks it kept (four tiles, 256 threads each) afterwards.  One launch instead of three, each of which is all latency there: 5 heads of
+// 9 blocks 2.1 + 4.9 + 6.5 us and two launches -> 9.9.
+constexpr int SMALL_BLOCKS = 256;
+struct SelectSmall {
+  const float* pctx; float* s_ctx; int Tsrc_max, Tctx_max;
+  int* taylor_ctr;
+  GatherArgs g;
+};
+
+template <bool SMALL>
 __global__ __launch_bounds__(SEL_THREADS) void k_select(const float* __restrict__ s_ctx, const float* __restrict__ sharp,
                                                         int* __restrict__ kv_list, int* __restrict__ full_list,
-                                                        int* __restrict__ flat_list, Counts cnt, int H) {
+                                                        int* __restrict__ flat_list, Counts cnt, int H, SelectSmall x) {
   extern __shared__ float sm[];
   float* sc = sm;                                   // [T_max]
   int* flags = reinterpret_cast<int*>(sm + cnt.T_max);   // [T_max]
   __shared__ int wsum[SEL_THREADS / 64];
   const int h = blockIdx.x, b = blockIdx.y;
   const BatchCounts c = cnt.b[b];
-  const long long off = ((long long)b * H + h) * cnt.T_max;
+  const long long bh = (long long)b * H + h, off = bh * cnt.T_max;
 
   if (blockIdx.z == 0) {       // context blocks by saliency: kv_list = all source blocks, then the kept context blocks
-    for (int j = threadIdx.x; j < c.T_ctx; j += SEL_THREADS) sc[j] = s_ctx[off + j];
+    if constexpr (SMALL) {
+      __shared__ double sums[4][SMALL_BLOCKS];
+      const int j = threadIdx.x % SMALL_BLOCKS, quarter = threadIdx.x / SMALL_BLOCKS;
+      const int per = (c.T_src + 3) / 4, i_lo = quarter * per, i_hi = min(c.T_src, i_lo + per);
+      double acc = 0.0;
+      if (j < c.T_ctx) {
+#pragma unroll 8
+        for (int i = i_lo; i < i_hi; ++i) acc += (double)x.pctx[(bh * x.Tsrc_max + i) * x.Tctx_max + j];
+      }
+      sums[quarter][j] = acc;
+      __syncthreads();
+      if (quarter == 0 && j < c.T_ctx) {
+        sc[j] = (float)((((sums[0][j] + sums[1][j]) + sums[2][j]) + sums[3][j]) / (double)c.T_src);
+        x.s_ctx[off + j] = sc[j];
+      }
+      if (threadIdx.x == 0 && h == 0 && b == 0) *x.taylor_ctr = 0;     // see k_gather_means
+    } else {
+      for (int j = threadIdx.x; j < c.T_ctx; j += SEL_THREADS) sc[j] = s_ctx[off + j];
+    }
     for (int j = threadIdx.x; j < cnt.T_max; j += SEL_THREADS) kv_list[off + j] = j < c.T_src ? j : -1;
     __syncthreads();
     rank_flags(sc, c.T_ctx, c.k_keep, flags);
     __syncthreads();
     compact(flags, c.T_ctx, c.T_src, kv_list + off + c.T_src, nullptr, wsum);
+    if constexpr (SMALL) {
+      __shared__ GatherLds tiles[SMALL_BLOCKS / KT];
+      __threadfence_block();                         // the list as the other threads of this workgroup have just written it
+      __syncthreads();
+      const int tile = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+      gather_tile(x.g, tiles[tile], threadIdx.x & 255, tile, h, b, tile < x.g.Tn_pad / KT);
+    }
   } else {                     // query blocks by sharpness
     for (int i = threadIdx.x; i < c.T; i += SEL_THREADS) sc[i] = sharp[off + i];
     for (int i = threadIdx.x; i < cnt.T_max; i += SEL_THREADS) {
@@ -444,6 +481,10 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const float* __restrict_
     __syncthreads();
     compact(flags, c.T, 0, full_list + off, flat_list + off, wsum);
   }
+}
+
+bool select_is_small(const Problem& pr) {
+  return pr.mfma_shape && pr.Tsrc_max <= SMALL_BLOCKS && pr.Tctx_max <= SMALL_BLOCKS && pr.Tn_pad <= SMALL_BLOCKS;
 }
 
 // Alg. 2 Stage 2: for the Taylor query block at position r of flat_list, mark the k_exact positions of kv_list with the
@@ -501,10 +542,17 @@ __global__ __launch_bounds__(256) void k_exact_sets(const float* __restrict__ z,
 }
 
 hipError_t launch_select(const Problem& pr, const Workspace& ws, const float* s_ctx, const float* sharp, const float* z,
-                         int* kv_list, int* full_list, int* flat_list, uint32_t* exact_mask, hipStream_t st) {
+                         int* kv_list, int* full_list, int* flat_list, uint32_t* exact_mask, hipStream_t st, bool small) {
   const size_t lds = (size_t)pr.cnt.T_max * 8;
-  hipLaunchKernelGGL(k_select, dim3(pr.p.H, pr.p.B, 2), dim3(SEL_THREADS), lds, st, s_ctx, sharp, kv_list, full_list,
-                     flat_list, pr.cnt, pr.p.H);
+  const dim3 sel_grid(pr.p.H, pr.p.B, 2);
+  if (small) {
+    const SelectSmall x = {ws.pctx, ws.s_ctx, pr.Tsrc_max, pr.Tctx_max, ws.taylor_ctr, gather_args(pr, ws, ws.kc, ws.vc, kv_list)};
+    hipLaunchKernelGGL(k_select<true>, sel_grid, dim3(SEL_THREADS), lds, st, s_ctx, sharp, kv_list, full_list, flat_list, pr.cnt,
+                       pr.p.H, x);
+  } else {
+    hipLaunchKernelGGL(k_select<false>, sel_grid, dim3(SEL_THREADS), lds, st, s_ctx, sharp, kv_list, full_list, flat_list, pr.cnt,
+                       pr.p.H, SelectSmall{});
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !(pr.p.exact_frac > 0.0)) return e;
   int nflat_max = 0;
