@@ -696,149 +696,217 @@ __global__ __launch_bounds__(256) void k_bwd_fill(uint16_t* __restrict__ dk, uin
 // Its gradient: dOc[i] = gamma * (sum of dO over block i); dVc = S^T dOc; dS = dOc Vc^T; dZ = S * (dS - rowsum(dS * S));
 // dQc = dZ Kc / sqrt D; dKc = dZ^T Qc / sqrt D; each mean's gradient is spread evenly over its block's tokens.
 
-// One workgroup per (block, head): doc[block] = gamma * column sums of the block's dO rows, and the residual's share is
-// taken out of delta (the attention branches' delta is rowsum(dO * (out - gamma * O_coarse[block]))).
-__global__ __launch_bounds__(128) void k_bwd_docoarse(const uint16_t* __restrict__ d_o, const float* __restrict__ ocoarse,
-                                                      float gamma, float* __restrict__ delta, float* __restrict__ doc,
-                                                      const int4* __restrict__ btab, Geometry g, Counts cnt, int S_max) {
-  __shared__ uint16_t tile[128][MD + 2];
-  __shared__ float oc[MD];
-  const int blk = blockIdx.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+// One workgroup per (block, head), in place of k_bwd_delta: delta without the residual's share (the attention branches' delta
+// is rowsum(dO * (out - gamma * O_coarse[block]))), and doc[block] = gamma * column sums of the block's dO rows, from one
+// read of dO.  HBM-bound: 40 heads of 15 600 tokens 97 + 60 us in two kernels -> 114.
+__global__ __launch_bounds__(256) void k_bwd_delta_residual(const uint16_t* __restrict__ o, const uint16_t* __restrict__ olo,
+                                                            const uint16_t* __restrict__ d_o, const float* __restrict__ ocoarse,
+                                                            float gamma, float* __restrict__ delta, float* __restrict__ doc,
+                                                            int* __restrict__ ctr, const int4* __restrict__ btab, Geometry g,
+                                                            Counts cnt, int S_max) {
+  __shared__ float red[16][MD];
+  const int blk = blockIdx.x, h = blockIdx.y, b = blockIdx.z, c16 = threadIdx.x & 15, rg = threadIdx.x >> 4;
+  if (blk == 0 && h == 0 && b == 0 && threadIdx.x < 8) ctr[threadIdx.x] = 0;      // as in k_bwd_delta
   if (blk >= cnt.b[b].T) return;
   const int4 ent = btab[b * cnt.T_max + blk];
   const long long bh = (long long)b * g.H + h;
-  const long long base = (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)ent.x * g.stride_t;
-  oc[tid] = ocoarse[(bh * cnt.T_max + blk) * MD + tid];
-  for (int x = tid; x < 128 * 16; x += 128) {
-    const int r = x >> 4, c = x & 15;
-    uint4 val = make_uint4(0, 0, 0, 0);
-    if (r < ent.y) val = *reinterpret_cast<const uint4*>(d_o + base + (long long)r * g.stride_t + c * 8);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[r][c * 8]);
-    dst[0] = val.x; dst[1] = val.y; dst[2] = val.z; dst[3] = val.w;
+  const long long base = (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)ent.x * g.stride_t + 8 * c16;
+  const float* op = ocoarse + (bh * cnt.T_max + blk) * MD + 8 * c16;
+  const float4 oc0 = *reinterpret_cast<const float4*>(op), oc1 = *reinterpret_cast<const float4*>(op + 4);
+  const float oc[8] = {oc0.x, oc0.y, oc0.z, oc0.w, oc1.x, oc1.y, oc1.z, oc1.w};
+  uint4 uo[8], ud[8], ul[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = rg + 16 * i;
+    uo[i] = ud[i] = ul[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (r < ent.y) {
+      uo[i] = *reinterpret_cast<const uint4*>(o + base + (long long)r * g.stride_t);
+      ud[i] = *reinterpret_cast<const uint4*>(d_o + base + (long long)r * g.stride_t);
+      if (olo) ul[i] = *reinterpret_cast<const uint4*>(olo + (bh * S_max + ent.x + r) * MD + 8 * c16);
+    }
   }
+  float col[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = rg + 16 * i;
+    const uint32_t wo[4] = {uo[i].x, uo[i].y, uo[i].z, uo[i].w}, wd[4] = {ud[i].x, ud[i].y, ud[i].z, ud[i].w},
+                   wl[4] = {ul[i].x, ul[i].y, ul[i].z, ul[i].w};
+    float s = 0.f, dot = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float d0 = __uint_as_float(wd[e] << 16), d1 = __uint_as_float(wd[e] & 0xffff0000u);
+      s += (__uint_as_float(wo[e] << 16) + __uint_as_float(wl[e] << 16)) * d0 +
+           (__uint_as_float(wo[e] & 0xffff0000u) + __uint_as_float(wl[e] & 0xffff0000u)) * d1;
+      dot = fmaf(d1, oc[2 * e + 1], fmaf(d0, oc[2 * e], dot));
+      col[2 * e] += d0;
+      col[2 * e + 1] += d1;
+    }
+#pragma unroll
+    for (int m = 8; m >= 1; m >>= 1) {
+      s += __shfl_xor(s, m, 64);
+      dot += __shfl_xor(dot, m, 64);
+    }
+    if (r < ent.y && c16 == 0) delta[bh * S_max + ent.x + r] = fmaf(-gamma, dot, s);
+  }
+#pragma unroll
+  for (int e = 0; e < 8; e += 4) *reinterpret_cast<float4*>(&red[rg][8 * c16 + e]) = make_float4(col[e], col[e + 1], col[e + 2], col[e + 3]);
   __syncthreads();
-  float sum = 0.f;
-  for (int r = 0; r < ent.y; ++r) sum += __uint_as_float((uint32_t)tile[r][tid] << 16);
-  doc[(bh * cnt.T_max + blk) * MD + tid] = gamma * sum;
-  if (tid < ent.y) {
-    float dot = 0.f;
-    for (int d = 0; d < MD; ++d) dot += __uint_as_float((uint32_t)tile[tid][d] << 16) * oc[d];
-    delta[bh * S_max + ent.x + tid] -= gamma * dot;
+  if (threadIdx.x < MD) {
+    float sum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sum += red[r][threadIdx.x];
+    doc[(bh * cnt.T_max + blk) * MD + threadIdx.x] = gamma * sum;
   }
 }
 
-// Row i of the pooled map: softmax statistics {max, sum, rowsum(dS * S)} and dQc[i].  LDS: qc_i, doc_i, T values.
-__global__ __launch_bounds__(256) void k_bwd_coarse_rows(const float* __restrict__ qc, const float* __restrict__ kc,
-                                                         const float* __restrict__ vc, const float* __restrict__ doc,
-                                                         float4* __restrict__ stats, float* __restrict__ dqc, Counts cnt,
-                                                         int H) {
-  extern __shared__ float sm[];
-  float* qi = sm; float* di = sm + MD; float* val = sm + 2 * MD;        // val[T]
-  __shared__ float red[256];
-  const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
-  const int T = cnt.b[b].T, T_max = cnt.T_max;
-  if (i >= T) return;
-  const long long row0 = ((long long)b * H + h) * T_max;
+// ROWS rows of the pooled map (COLS: ROWS columns): with x the rows' own means and y the other side's,
+//     Z = x1 . y1 / sqrt D and dS = x2 . y2 of all pairs, then
+//   rows    (x = Qc, dOc; y = Kc, Vc): softmax statistics {max, sum, rowsum(dS * S)} of every row, out1 = dQc = dZ Kc / sqrt D;
+//   columns (x = Kc, Vc; y = Qc, dOc): S and dZ from the rows' statistics, out1 = dKc = dZ^T Qc / sqrt D, out2 = dVc = S^T dOc.
+// All products on fp32 matrix instructions (v_mfma_f32_16x16x4_f32, operands as in k_coarse): one thread per pair, each
+// walking its own row of 512 bytes, took 137 + 111 us for 40 heads of 122 blocks; this takes 22 + 23.  Both T-wide arrays of the
+// workgroup's rows sit in LDS: 16 rows up to 1088 blocks, 4 above.
+template <int ROWS, bool COLS>
+__global__ __launch_bounds__(256) void k_bwd_coarse(const float* __restrict__ x1, const float* __restrict__ x2,
+                                                    const float* __restrict__ y1, const float* __restrict__ y2,
+                                                    float4* __restrict__ stats, float* __restrict__ out1, float* __restrict__ out2,
+                                                    Counts cnt, int n_bh, int H, int stride, int row_tiles) {
+  extern __shared__ __attribute__((aligned(16))) float sm[];
+  float* const zs = sm;                                 // [ROWS][stride]: Z, in the end S
+  float* const ds = sm + ROWS * stride;                 // [ROWS][stride]: dS, in the end dZ
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;             // an XCD works through one head after the other (see k_coarse)
+  const int bhid = (slot / row_tiles) * 8 + xcd;
+  if (bhid >= n_bh) return;
+  const int T = cnt.b[bhid / H].T, i0 = (slot % row_tiles) * ROWS;
+  if (i0 >= T) return;
+  const long long row0 = (long long)bhid * cnt.T_max;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
   const float scale = 1.0f / sqrtf((float)MD);
-  if (tid < MD) { qi[tid] = qc[(row0 + i) * MD + tid]; di[tid] = doc[(row0 + i) * MD + tid]; }
-  __syncthreads();
-  auto reduce = [&](float x, bool take_max) -> float {
-    red[tid] = x;
-    __syncthreads();
-    for (int s2 = 128; s2 > 0; s2 >>= 1) {
-      if (tid < s2) red[tid] = take_max ? fmaxf(red[tid], red[tid + s2]) : red[tid] + red[tid + s2];
-      __syncthreads();
+  const int n_ct = (T + 15) / 16;
+  {
+    float4 bx1[8], bx2[8];
+    const long long xr = (row0 + min(i0 + l16, T - 1)) * MD + 4 * g;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      bx1[t] = *reinterpret_cast<const float4*>(x1 + xr + 16 * t);
+      bx2[t] = *reinterpret_cast<const float4*>(x2 + xr + 16 * t);
     }
-    const float r = red[0];
-    __syncthreads();
-    return r;
-  };
-  float mloc = -INFINITY;
-  for (int j = tid; j < T; j += 256) {
-    const float4* kp = reinterpret_cast<const float4*>(kc + (row0 + j) * MD);
-    float z = 0.f;
-    for (int d4 = 0; d4 < MD / 4; ++d4) {
-      const float4 k4 = kp[d4];
-      z += qi[4 * d4] * k4.x + qi[4 * d4 + 1] * k4.y + qi[4 * d4 + 2] * k4.z + qi[4 * d4 + 3] * k4.w;
+    for (int jt = wave; jt < n_ct; jt += 4) {
+      const long long yr = (row0 + min(jt * 16 + l16, T - 1)) * MD + 4 * g;
+      float4 a1[8], a2[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        a1[t] = *reinterpret_cast<const float4*>(y1 + yr + 16 * t);
+        a2[t] = *reinterpret_cast<const float4*>(y2 + yr + 16 * t);
+      }
+      f32x4 z = {0.f, 0.f, 0.f, 0.f}, d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        z = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[t].x, bx1[t].x, z, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(a2[t].x, bx2[t].x, d, 0, 0, 0);
+        z = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[t].y, bx1[t].y, z, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(a2[t].y, bx2[t].y, d, 0, 0, 0);
+        z = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[t].z, bx1[t].z, z, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(a2[t].z, bx2[t].z, d, 0, 0, 0);
+        z = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[t].w, bx1[t].w, z, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(a2[t].w, bx2[t].w, d, 0, 0, 0);
+      }
+      // lane (l16, g) holds y = 16 jt + 4 g .. + 3 of x row l16
+      float zv[4], dv[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int y = jt * 16 + 4 * g + i;
+        zv[i] = z[i] * scale;
+        dv[i] = d[i];
+        if (COLS) {
+          const float4 st = stats[row0 + min(y, T - 1)];
+          zv[i] = __expf(zv[i] - st.x) / st.y;
+          dv[i] = zv[i] * (dv[i] - st.z);
+        }
+        if (y >= T) zv[i] = dv[i] = 0.f;
+      }
+      if (l16 < ROWS) {
+        *reinterpret_cast<float4*>(zs + l16 * stride + jt * 16 + 4 * g) = make_float4(zv[0], zv[1], zv[2], zv[3]);
+        *reinterpret_cast<float4*>(ds + l16 * stride + jt * 16 + 4 * g) = make_float4(dv[0], dv[1], dv[2], dv[3]);
+      }
     }
-    val[j] = z * scale;
-    mloc = fmaxf(mloc, z * scale);
-  }
-  const float m = reduce(mloc, true);
-  float lloc = 0.f;
-  for (int j = tid; j < T; j += 256) lloc += __expf(val[j] - m);
-  const float l = reduce(lloc, false);
-  float rloc = 0.f;
-  for (int j = tid; j < T; j += 256) {                  // val[j] <- dZ_ij needs rowdot first: keep S in val, dS in registers twice
-    const float4* vp = reinterpret_cast<const float4*>(vc + (row0 + j) * MD);
-    float ds = 0.f;
-    for (int d4 = 0; d4 < MD / 4; ++d4) {
-      const float4 v4 = vp[d4];
-      ds += di[4 * d4] * v4.x + di[4 * d4 + 1] * v4.y + di[4 * d4 + 2] * v4.z + di[4 * d4 + 3] * v4.w;
-    }
-    const float sj = __expf(val[j] - m) / l;
-    rloc += sj * ds;
-    val[j] = sj * ds;                                   // S * dS for now; turned into dZ below
-  }
-  const float rowdot = reduce(rloc, false);
-  if (tid == 0) stats[row0 + i] = make_float4(m, l, rowdot, 0.f);
-  // dZ_ij = S_ij dS_ij - S_ij rowdot; S_ij is recomputed from the logit, which val no longer holds: recompute it
-  for (int j = tid; j < T; j += 256) {
-    const float4* kp = reinterpret_cast<const float4*>(kc + (row0 + j) * MD);
-    float z = 0.f;
-    for (int d4 = 0; d4 < MD / 4; ++d4) {
-      const float4 k4 = kp[d4];
-      z += qi[4 * d4] * k4.x + qi[4 * d4 + 1] * k4.y + qi[4 * d4 + 2] * k4.z + qi[4 * d4 + 3] * k4.w;
-    }
-    val[j] -= __expf(z * scale - m) / l * rowdot;
   }
   __syncthreads();
-  if (tid < MD) {
-    float acc = 0.f;
-    for (int j = 0; j < T; ++j) acc += val[j] * kc[(row0 + j) * MD + tid];
-    dqc[(row0 + i) * MD + tid] = acc * scale;
+  if (!COLS) {
+    auto all = [](float x, bool take_max) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const float y = __shfl_xor(x, o, 64);
+        x = take_max ? fmaxf(x, y) : x + y;
+      }
+      return x;
+    };
+    for (int r = wave; r < ROWS; r += 4) {              // one wave per row: nothing to synchronise between the passes
+      if (i0 + r >= T) break;
+      float* const zr = zs + r * stride;
+      float* const dr = ds + r * stride;
+      float m = -INFINITY, l = 0.f, rd = 0.f;
+      for (int j = lane; j < T; j += 64) m = fmaxf(m, zr[j]);
+      m = all(m, true);
+      for (int j = lane; j < T; j += 64) l += (zr[j] = __expf(zr[j] - m));
+      l = all(l, false);
+      for (int j = lane; j < T; j += 64) rd += (zr[j] /= l) * dr[j];
+      rd = all(rd, false);
+      for (int j = lane; j < T; j += 64) dr[j] = zr[j] * (dr[j] - rd);
+      if (lane == 0) stats[row0 + i0 + r] = make_float4(m, l, rd, 0.f);
+    }
+    __syncthreads();
+  }
+  // out^T[channel][row] += y^T[channel][j] dZ[row][j]: a wave takes two tiles of 16 channels, 16 j at a time
+  f32x4 acc1[2], acc2[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) acc1[u] = acc2[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int lr = l16 < ROWS ? l16 : 0;
+  for (int jt = 0; jt < n_ct; ++jt) {
+    float a1[4][2], a2[4][2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const long long yr = (row0 + min(jt * 16 + 4 * k + g, T - 1)) * MD + 32 * wave + l16;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        a1[k][u] = y1[yr + 16 * u];
+        if (COLS) a2[k][u] = y2[yr + 16 * u];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float bd = ds[lr * stride + jt * 16 + 4 * k + g];
+      const float bs = COLS ? zs[lr * stride + jt * 16 + 4 * k + g] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        acc1[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[k][u], bd, acc1[u], 0, 0, 0);
+        if (COLS) acc2[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a2[k][u], bs, acc2[u], 0, 0, 0);
+      }
+    }
+  }
+  if (l16 < ROWS && i0 + l16 < T) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const long long to = (row0 + i0 + l16) * MD + 32 * wave + 16 * u + 4 * g;
+      *reinterpret_cast<float4*>(out1 + to) = make_float4(acc1[u][0] * scale, acc1[u][1] * scale, acc1[u][2] * scale, acc1[u][3] * scale);
+      if (COLS) *reinterpret_cast<float4*>(out2 + to) = make_float4(acc2[u][0], acc2[u][1], acc2[u][2], acc2[u][3]);
+    }
   }
 }
 
-// Column j of the pooled map: dKc[j] = sum_i dZ_ij Qc_i / sqrt D, dVc[j] = sum_i S_ij dOc_i, with S and dZ recomputed from the
-// row statistics.  LDS: kc_j, vc_j, 2 T values.
-__global__ __launch_bounds__(256) void k_bwd_coarse_cols(const float* __restrict__ qc, const float* __restrict__ kc,
-                                                         const float* __restrict__ vc, const float* __restrict__ doc,
-                                                         const float4* __restrict__ stats, float* __restrict__ dkc,
-                                                         float* __restrict__ dvc, Counts cnt, int H) {
-  extern __shared__ float sm[];
-  float* kj = sm; float* vj = sm + MD; float* sv = sm + 2 * MD; float* dz = sv + cnt.T_max;
-  const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
-  const int T = cnt.b[b].T, T_max = cnt.T_max;
-  if (j >= T) return;
-  const long long row0 = ((long long)b * H + h) * T_max;
-  const float scale = 1.0f / sqrtf((float)MD);
-  if (tid < MD) { kj[tid] = kc[(row0 + j) * MD + tid]; vj[tid] = vc[(row0 + j) * MD + tid]; }
-  __syncthreads();
-  for (int i = tid; i < T; i += 256) {
-    const float4* qp = reinterpret_cast<const float4*>(qc + (row0 + i) * MD);
-    const float4* dp = reinterpret_cast<const float4*>(doc + (row0 + i) * MD);
-    float z = 0.f, ds = 0.f;
-    for (int d4 = 0; d4 < MD / 4; ++d4) {
-      const float4 q4 = qp[d4], o4 = dp[d4];
-      z += q4.x * kj[4 * d4] + q4.y * kj[4 * d4 + 1] + q4.z * kj[4 * d4 + 2] + q4.w * kj[4 * d4 + 3];
-      ds += o4.x * vj[4 * d4] + o4.y * vj[4 * d4 + 1] + o4.z * vj[4 * d4 + 2] + o4.w * vj[4 * d4 + 3];
-    }
-    const float4 st = stats[row0 + i];
-    const float sij = __expf(z * scale - st.x) / st.y;
-    sv[i] = sij;
-    dz[i] = sij * (ds - st.z);
+template <int ROWS, bool COLS>
+static hipError_t launch_bwd_coarse(const Problem& pr, const Workspace& ws, hipStream_t st) {
+  const int T_max = pr.cnt.T_max, n_bh = pr.p.B * pr.p.H;
+  const int stride = (T_max + 15) / 16 * 16 + 4, row_tiles = (T_max + ROWS - 1) / ROWS;      // + 4 spreads the rows over the banks
+  const size_t lds = (size_t)2 * ROWS * stride * sizeof(float);
+  if (lds > 64 * 1024) {                                // beyond the default limit of dynamic LDS: ask for it
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bwd_coarse<ROWS, COLS>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
   }
-  __syncthreads();
-  if (tid < MD) {
-    float ak = 0.f, av = 0.f;
-    for (int i = 0; i < T; ++i) {
-      ak += dz[i] * qc[(row0 + i) * MD + tid];
-      av += sv[i] * doc[(row0 + i) * MD + tid];
-    }
-    dkc[(row0 + j) * MD + tid] = ak * scale;
-    dvc[(row0 + j) * MD + tid] = av;
-  }
+  hipLaunchKernelGGL((k_bwd_coarse<ROWS, COLS>), dim3((unsigned)(N_XCD * ((n_bh + N_XCD - 1) / N_XCD) * row_tiles)), dim3(256), lds, st,
+                     COLS ? ws.kc : ws.qc, COLS ? ws.vc : ws.doc, COLS ? ws.qc : ws.kc, COLS ? ws.doc : ws.vc, ws.cstats,
+                     COLS ? ws.cdk : ws.cdq, COLS ? ws.cdv : (float*)nullptr, pr.cnt, n_bh, pr.p.H, stride, row_tiles);
+  return hipGetLastError();
 }
 
 // mean_grad[bh][e] (gradient of the gathered mean of kv_list[e], or nothing yet if `fresh`) += coarse[bh][kv_list[e]]
@@ -902,9 +970,15 @@ __global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
   if (row >= n_x) return;
   const float* src = a.tail_scratch + ((((long long)xcd * a.tail_items + r) * a.tail_parts) * 256 + grp * 128 + row) * MD + ch;
   float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int p = 0; p < a.tail_parts; ++p) {
-    const float4 o = *reinterpret_cast<const float4*>(src + (long long)p * 256 * MD);
-    sum.x += o.x; sum.y += o.y; sum.z += o.z; sum.w += o.w;
+  for (int p0 = 0; p0 < a.tail_parts; p0 += 4) {        // four parts' loads in flight
+    float4 o[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o[u] = *reinterpret_cast<const float4*>(src + (long long)min(p0 + u, a.tail_parts - 1) * 256 * MD);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (p0 + u >= a.tail_parts) break;
+      sum.x += o[u].x; sum.y += o[u].y; sum.z += o[u].z; sum.w += o[u].w;
+    }
   }
   sum.x *= a.oscale; sum.y *= a.oscale; sum.z *= a.oscale; sum.w *= a.oscale;
   if (a.add_rows) {
@@ -983,19 +1057,19 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
     if (e__ != hipSuccess) return e__;            \
   } while (0)
   // delta, zero fill, per-list tables and row terms
-  hipLaunchKernelGGL(k_bwd_delta, dim3((S_max + 15) / 16, H, B), dim3(256), 0, st, (const uint16_t*)out,
-                     ws.olo, (const uint16_t*)d_out, ws.delta, ws.bwd_ctr, pr.geo, pr.cnt, S_max);
-  ISA_BWD_CHECK();
   if (resid) {
-    // gradient of the coarse residual with respect to the block means (all blocks, by block id), and delta without
-    // the residual's share
-    hipLaunchKernelGGL(k_bwd_docoarse, dim3(T_max, H, B), dim3(128), 0, st, (const uint16_t*)d_out, ws.ocoarse, gamma,
-                       ws.delta, ws.doc, ws.btab, pr.geo, pr.cnt, S_max);
+    // delta without the residual's share; gradient of the coarse residual with respect to the block means (all blocks, by
+    // block id)
+    hipLaunchKernelGGL(k_bwd_delta_residual, dim3(T_max, H, B), dim3(256), 0, st, (const uint16_t*)out, ws.olo, (const uint16_t*)d_out,
+                       ws.ocoarse, gamma, ws.delta, ws.doc, ws.bwd_ctr, ws.btab, pr.geo, pr.cnt, S_max);
     ISA_BWD_CHECK();
-    hipLaunchKernelGGL(k_bwd_coarse_rows, dim3(T_max, H, B), dim3(256), (size_t)(2 * MD + T_max) * 4, st, ws.qc, ws.kc,
-                       ws.vc, ws.doc, ws.cstats, ws.cdq, pr.cnt, H);
-    hipLaunchKernelGGL(k_bwd_coarse_cols, dim3(T_max, H, B), dim3(256), (size_t)(2 * MD + 2 * T_max) * 4, st, ws.qc,
-                       ws.kc, ws.vc, ws.doc, ws.cstats, ws.cdk, ws.cdv, pr.cnt, H);
+    const bool wide = T_max <= 1088;
+    hipError_t ec = wide ? launch_bwd_coarse<16, false>(pr, ws, st) : launch_bwd_coarse<4, false>(pr, ws, st);
+    if (ec == hipSuccess) ec = wide ? launch_bwd_coarse<16, true>(pr, ws, st) : launch_bwd_coarse<4, true>(pr, ws, st);
+    if (ec != hipSuccess) return ec;
+  } else {
+    hipLaunchKernelGGL(k_bwd_delta, dim3((S_max + 15) / 16, H, B), dim3(256), 0, st, (const uint16_t*)out,
+                       ws.olo, (const uint16_t*)d_out, ws.delta, ws.bwd_ctr, pr.geo, pr.cnt, S_max);
     ISA_BWD_CHECK();
   }
   hipLaunchKernelGGL(k_bwd_fill, dim3(T_max, H, B), dim3(256), 0, st, (uint16_t*)dk, (uint16_t*)dv, resid ? ws.cdk : nullptr,

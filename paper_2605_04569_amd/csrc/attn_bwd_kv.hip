@@ -418,9 +418,15 @@ __global__ __launch_bounds__(256) void k_bwd_kv_merge(KvArgs a) {
   if (row >= own.y) return;
   const float* src = a.tail_scratch + (((long long)xcd * a.tail_items + r) * a.tail_parts * 2 + which) * 128 * MD + row * MD + ch;
   float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int p = 0; p < a.tail_parts; ++p) {
-    const float4 o = *reinterpret_cast<const float4*>(src + (long long)p * 2 * 128 * MD);
-    sum.x += o.x; sum.y += o.y; sum.z += o.z; sum.w += o.w;
+  for (int p0 = 0; p0 < a.tail_parts; p0 += 4) {        // four parts' loads in flight
+    float4 o[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o[u] = *reinterpret_cast<const float4*>(src + (long long)min(p0 + u, a.tail_parts - 1) * 2 * 128 * MD);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (p0 + u >= a.tail_parts) break;
+      sum.x += o[u].x; sum.y += o[u].y; sum.z += o[u].z; sum.w += o[u].w;
+    }
   }
   if (!which) { sum.x *= a.scale; sum.y *= a.scale; sum.z *= a.scale; sum.w *= a.scale; }
   if (a.mean_k) {
