@@ -244,7 +244,7 @@ __device__ __forceinline__ void rescale(const float (&alpha)[2], f32x4 (&l_run)[
 // One work item.  `taylor` is a template parameter so that the tile set-up inside the loop carries no selects or
 // branches between the two kinds of key sequence (token tiles of kept blocks / tiles of gathered block means).
 template <bool taylor>
-__device__ __forceinline__ void attn_sp_item(const MfmaArgs& a, uint16_t* lds, const int taken) {
+__device__ __forceinline__ void attn_sp_item(const MfmaArgs& a, uint16_t* lds, const int taken, const int taken_part = -1) {
   uint16_t* ldsK = lds;                     // K tile T lives in buffer T % NBUF
   uint16_t* ldsV = lds + NBUF * K_TILE;     // V^T tile T lives in buffer T % NBUF
   uint16_t* ldsQ = lds + NBUF * K_TILE + NBUF * V_TILE;       // 2 x 128 query rows of a Taylor group's next pair
@@ -265,9 +265,11 @@ __device__ __forceinline__ void attn_sp_item(const MfmaArgs& a, uint16_t* lds, c
   // results afterwards.
   const int n_whole = a.n_long - a.n_split;
   const bool counted = taylor || taken >= 0;                    // the item's number comes from a counter
-  const bool split = !counted && j >= n_whole;
+  const bool split = counted ? taken_part >= 0 : j >= n_whole;
   const int item = counted ? taken : split ? n_whole + (j - n_whole) / a.parts : j;
-  const int part = split ? (j - n_whole) % a.parts : 0;
+  const int part = !split ? 0 : counted ? taken_part : (j - n_whole) % a.parts;
+  // the item's place in the partial-result area
+  const int split_slot = counted ? taken - a.ctr_whole : xcd * a.n_split + (item - n_whole);
   // A Taylor work item is a group of up to `tgroup` consecutive pairs of one head, handled one after the other (all of
   // them read the same sequence of mean tiles); an exact-branch item is one pair.
   const int n_bh = a.geo.B * a.geo.H;
@@ -589,7 +591,7 @@ __device__ __forceinline__ void attn_sp_item(const MfmaArgs& a, uint16_t* lds, c
       const int row = rowq[qt];
       if (split) {
         // partial result of a sub-item: unnormalised fp32 outputs and the {maximum, sum} they refer to
-        const long long sid = (((long long)xcd * a.n_split + (item - n_whole)) * a.parts + part) * 2 + grp;
+        const long long sid = ((long long)split_slot * a.parts + part) * 2 + grp;
         float* op = a.split_o + (sid * 128 + row) * MD + 4 * q;
 #pragma unroll
         for (int c = 0; c < 8; ++c)
@@ -718,7 +720,8 @@ __global__ __launch_bounds__(512, 1) void k_attn_sp(MfmaArgs a) {
     __syncthreads();
     const int g = __builtin_amdgcn_readfirstlane(*slot);
     if (g >= a.n_long_all) return;
-    attn_sp_item<false>(a, lds, g);
+    if (g < a.ctr_whole) attn_sp_item<false>(a, lds, g);
+    else attn_sp_item<false>(a, lds, a.ctr_whole + (g - a.ctr_whole) / a.parts, (g - a.ctr_whole) % a.parts);
   } else {
     attn_sp_item<false>(a, lds, -1);
   }
@@ -729,11 +732,20 @@ __global__ __launch_bounds__(512, 1) void k_attn_sp(MfmaArgs a) {
 // pair, 8 query rows); 32 threads per row, 4 channels each.
 __global__ __launch_bounds__(256) void k_split_merge(MfmaArgs a) {
   const int rows8 = blockIdx.x & 15, grp = (blockIdx.x >> 4) & 1;
-  const int r = (blockIdx.x >> 5) % a.n_split, xcd = (blockIdx.x >> 5) / a.n_split;
-  const long long n_items = (long long)a.geo.B * a.geo.H * a.slots_first;
-  const int item = xcd_first(n_items, xcd) + a.n_long - a.n_split + r;
-  if (item >= xcd_first(n_items, xcd + 1)) return;
-  const int slot = item % a.slots_first, bhid = head_at(item / a.slots_first, a.geo.B * a.geo.H);
+  const int split_slot = blockIdx.x >> 5, n_bh = a.geo.B * a.geo.H;
+  int slot, bhid;
+  if (a.long_ctr) {
+    const int item = a.ctr_whole + split_slot;
+    slot = item % a.slots_first;
+    bhid = item / a.slots_first;
+  } else {
+    const int r = split_slot % a.n_split, xcd = split_slot / a.n_split;
+    const long long n_items = (long long)n_bh * a.slots_first;
+    const int item = xcd_first(n_items, xcd) + a.n_long - a.n_split + r;
+    if (item >= xcd_first(n_items, xcd + 1)) return;
+    slot = item % a.slots_first;
+    bhid = head_at(item / a.slots_first, n_bh);
+  }
   const int h = bhid % a.geo.H, b = bhid / a.geo.H;
   const BatchCounts c = a.cnt.b[b];
   const int T_max = a.geo.T_max;
@@ -744,17 +756,31 @@ __global__ __launch_bounds__(256) void k_split_merge(MfmaArgs a) {
   const int n_q = a.blk_n[b * T_max + qi], q_start = a.blk_start[b * T_max + qi];
   const int row = rows8 * 8 + (threadIdx.x >> 5), ch = (threadIdx.x & 31) * 4;
   if (row >= n_q) return;
-  const long long sid0 = (((long long)xcd * a.n_split + r) * a.parts) * 2 + grp;       // part p is at sid0 + 2p
+  const long long sid0 = (long long)split_slot * a.parts * 2 + grp;                    // part p is at sid0 + 2p
+  // four parts' loads at a time in flight (a part past the last repeats it, with weight 0)
   float m = M_INIT;
-  for (int p = 0; p < a.parts; ++p) m = fmaxf(m, a.split_ml[((sid0 + 2 * p) * 128 + row) * 2]);
+  for (int p0 = 0; p0 < a.parts; p0 += 4) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m = fmaxf(m, a.split_ml[((sid0 + 2 * min(p0 + u, a.parts - 1)) * 128 + row) * 2]);
+  }
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   float l = 0.f;
-  for (int p = 0; p < a.parts; ++p) {
-    const float2 ml = *reinterpret_cast<const float2*>(a.split_ml + ((sid0 + 2 * p) * 128 + row) * 2);
-    const float w = __builtin_amdgcn_exp2f(ml.x - m);
-    const float4 o = *reinterpret_cast<const float4*>(a.split_o + ((sid0 + 2 * p) * 128 + row) * MD + ch);
-    acc.x += w * o.x; acc.y += w * o.y; acc.z += w * o.z; acc.w += w * o.w;
-    l += w * ml.y;
+  for (int p0 = 0; p0 < a.parts; p0 += 4) {
+    float2 ml[4];
+    float4 o[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const long long at = (sid0 + 2 * min(p0 + u, a.parts - 1)) * 128 + row;
+      ml[u] = *reinterpret_cast<const float2*>(a.split_ml + at * 2);
+      o[u] = *reinterpret_cast<const float4*>(a.split_o + at * MD + ch);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (p0 + u >= a.parts) break;
+      const float w = __builtin_amdgcn_exp2f(ml[u].x - m);
+      acc.x += w * o[u].x; acc.y += w * o[u].y; acc.z += w * o[u].z; acc.w += w * o[u].w;
+      l += w * ml[u].y;
+    }
   }
   const float inv = 1.0f / l;
   const long long tbase = (long long)b * a.geo.stride_b + (long long)h * a.geo.stride_h;
@@ -834,12 +860,12 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
     m.n_split = 0; m.parts = 1;
     m.split_o = ws.split_o; m.split_ml = ws.split_ml;
     const int cus = cus_per_xcd(), rem = m.n_long % cus;
+    int min_list = 1 << 30;
+    for (int b = 0; b < pr.p.B; ++b) {
+      const int nl = a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new;
+      min_list = nl < min_list ? nl : min_list;
+    }
     if (rem > 0 && rem <= cus / 2 && ws.split_o) {
-      int min_list = 1 << 30;
-      for (int b = 0; b < pr.p.B; ++b) {
-        const int nl = a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new;
-        min_list = nl < min_list ? nl : min_list;
-      }
       int parts = cus / rem;
       if (m.n_long < cus && 4 * parts > min_list) parts = (cus - (m.n_taylor_wg < cus / 2 ? m.n_taylor_wg : cus / 2)) / rem;
       const int most = min_list / 2 > 8 ? min_list / 2 : (min_list < 8 ? min_list : 8);
@@ -847,25 +873,31 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
       while (parts >= 2 && N_XCD * rem * parts > SPLIT_MAX_SUB) --parts;      // the partial-result area holds SPLIT_MAX_SUB sub-items
       if (parts >= 2) { m.n_split = rem; m.parts = parts; }
     }
-    // Dense attention over a long sequence: nothing but long items, 64 rounds of them or more.  The XCDs of a chip differ
-    // in speed by several per cent, and with equal shares the launch ends with the slowest; there are no short items to
-    // level with, so the long items themselves are taken from a counter (zeroed by the V^T pack, which precedes every
-    // such launch), one per workgroup, with an eighth more workgroups than items and one round of the chip to spare.  With
-    // fewer rounds the last, ragged round of such a launch would cost what the levelling gains.
-    m.long_ctr = nullptr; m.n_long_all = 0;
-    if (a.dense && ss == 0 && m.n_long >= 64 * cus) {
-      const long long all = (long long)pr.p.B * pr.p.H * sf;
+    // A launch of nothing but long items (dense attention; the exact branch beside exact sets), 8 rounds of them or more.  The
+    // XCDs of a chip differ in speed by several per cent, and with equal shares the launch ends with the slowest; there are
+    // no short items to level with, so the long items themselves are taken from a counter (zeroed by the V^T pack, which precedes
+    // every such launch), one per workgroup, with an eighth more workgroups than items and one round of the chip to spare.  The
+    // last 64 items run as four key ranges each, so that the launch ends within a quarter of an item of the ideal (whole items to
+    // the end: as much lost in the last round as gained, at 40 rounds).  Dense attention at
+    // 480p (40 rounds) 71.1 -> 68.9 ms, 480p at the paper's ratios (20 rounds of the exact branch) 22.7 -> 22.25.
+    m.long_ctr = nullptr; m.n_long_all = 0; m.ctr_whole = 0;
+    int n_merge = N_XCD * m.n_split;
+    if (ss == 0 && m.n_long >= 8 * cus && min_list >= 16) {
+      const int all = (int)((long long)pr.p.B * pr.p.H * sf);
       m.long_ctr = ws.taylor_ctr + 1;
-      m.n_long_all = (int)all;
-      m.n_split = 0; m.parts = 1;
-      m.n_long = (int)((all + all / 8) / N_XCD + cus + 1);      // workgroups per XCD
+      m.parts = 4;
+      n_merge = SPLIT_MAX_SUB / m.parts;
+      m.ctr_whole = all - n_merge;
+      m.n_long_all = all + n_merge * (m.parts - 1);
+      m.n_split = 0;
+      m.n_long = (m.n_long_all + m.n_long_all / 8) / N_XCD + cus + 1;      // workgroups per XCD
     }
     const long long per_xcd = (long long)m.n_long - m.n_split + (long long)m.n_split * m.parts + m.n_taylor_wg;
     m.slots = 0; m.total = 0;
     hipLaunchKernelGGL(k_attn_sp, dim3((unsigned)(per_xcd * 8)), dim3(512), 0, st, m);
     e = hipGetLastError();
-    if (e == hipSuccess && m.n_split > 0) {
-      hipLaunchKernelGGL(k_split_merge, dim3((unsigned)(8 * m.n_split * 32)), dim3(256), 0, st, m);
+    if (e == hipSuccess && n_merge > 0) {
+      hipLaunchKernelGGL(k_split_merge, dim3((unsigned)(n_merge * 32)), dim3(256), 0, st, m);
       e = hipGetLastError();
     }
   }
