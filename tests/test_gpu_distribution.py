@@ -49,3 +49,32 @@ def test_backward(I, H, exact_frac):
 def test_backward_few_streamed_entries(I, full_frac):
     wl = _wl(3, (1, 10, 60), (((1, 10, 33),), ((1, 1, 40),)), B=2, keep_ratio=1.0, full_frac=full_frac, exact_frac=0.3, seed=870)
     backward_matches_the_oracle(I, wl)
+
+
+# launches of nothing but long items, 8 rounds or more: items from a counter, the last 64 as four key ranges each (the last heads);
+# 16 key blocks is the shortest list that may be cut so, 17 makes the ranges unequal
+@pytest.mark.parametrize("blocks", [16, 17])
+def test_counted_items_dense(I, blocks):
+    import numpy as np
+    import torch
+    from oracle import isa_oracle as O
+    from test_gpu_parity import TOL
+    from util import err_stats, f64, problem_of
+    H = 300
+    wl = _wl(H, (1, 1, 128 * (blocks - 1) + 5), ((),), seed=880 + blocks)
+    assert H * ((blocks + 1) // 2) // 8 >= 8 * 32                                       # the premise: 8 rounds of an XCD's 32 units
+    Q, K, V, q, k, v = gen(wl)
+    pr = problem_of(wl)
+    out = torch.full_like(q, float("nan"))
+    I.isa_dense_attention(pr, q, k, v, out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    assert torch.isfinite(out.float()).all()
+    for h in (0, 100, 290, 292, 295, 299):
+        emax, emean = err_stats(f64(out[0, h]), O.dense_attention(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h])))
+        assert emax <= TOL["bf16"][0] and emean <= TOL["bf16"][1], (h, emax, emean)
+
+
+def test_counted_items_beside_exact_sets(I):
+    wl = _wl(200, (1, 1, 128 * 17 + 5), (((1, 1, 500),), ((1, 1, 70),)), B=2, keep_ratio=0.5, full_frac=0.6, exact_frac=0.2, gamma=0.5,
+             seed=890)
+    check_end_to_end(I, wl, *gen(wl), heads=[0, 77, 192, 199])
