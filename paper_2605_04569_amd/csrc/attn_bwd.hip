@@ -113,6 +113,7 @@ struct BwdArgs {
   // numbered over all (batch, head)s: the launch then has more workgroups than items, and an XCD that gets through its
   // workgroups sooner takes more of the items (the XCDs of a chip are not equally fast)
   int* dyn_ctr;
+  int dyn_whole, dyn_total;                   // the first dyn_whole of them are whole items, the others tail_parts parts of an item each
 };
 
 // SM: stationary rows are block means; T2: W = P * (T2 - delta), else W = P; EX: exact-set bits are in play (1: whole
@@ -143,8 +144,14 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
       __shared__ int taken;
       if (threadIdx.x == 0) taken = atomicAdd(a.dyn_ctr, 1);
       __syncthreads();
-      const int idx = __builtin_amdgcn_readfirstlane(taken);
-      if (idx >= a.items * n_bh) return;                  // the launch has more workgroups than items
+      int idx = __builtin_amdgcn_readfirstlane(taken);
+      if (idx >= a.dyn_total) return;                     // the launch has more workgroups than items
+      if (idx >= a.dyn_whole) {
+        tail_slot = (idx - a.dyn_whole) / a.tail_parts;
+        part = (idx - a.dyn_whole) % a.tail_parts;
+        parts = a.tail_parts;
+        idx = a.dyn_whole + tail_slot;
+      }
       item = idx % a.items;
       bhid = idx / a.items;
     } else {
@@ -544,7 +551,7 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
 
 #undef PH
   if (!SM && tail_slot >= 0) {                // a part of a tail item: unscaled sums to scratch, the merge kernel does the rest
-    float* dst = a.tail_scratch + ((((long long)xcd * a.tail_items + tail_slot) * parts + part) * 256 + grp * 128) * MD;
+    float* dst = a.tail_scratch + (((long long)((a.dyn_ctr ? 0 : xcd * a.tail_items) + tail_slot) * parts + part) * 256 + grp * 128) * MD;
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
@@ -953,11 +960,19 @@ __global__ __launch_bounds__(128) void k_bwd_sum_parts(float* __restrict__ g, in
 // does for whole items.  One workgroup per (XCD, tail item, block of the pair, 8 rows); 32 threads per row, 4 channels each.
 __global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
   const int rows8 = blockIdx.x & 15, grp = (blockIdx.x >> 4) & 1;
-  const int r = (blockIdx.x >> 5) % a.tail_items, xcd = (blockIdx.x >> 5) / a.tail_items;
-  const long long n_items = (long long)a.items * a.geo.B * a.geo.H;
-  const int idx = xcd_first(n_items, xcd) + a.items_xcd - a.tail_items + r;
-  if (idx >= xcd_first(n_items, xcd + 1)) return;
-  const int item = idx % a.items, bhid = head_at(idx / a.items, a.geo.B * a.geo.H);
+  const int slot = blockIdx.x >> 5, n_bh = a.geo.B * a.geo.H;
+  int item, bhid;
+  if (a.dyn_ctr) {
+    item = (a.dyn_whole + slot) % a.items;
+    bhid = (a.dyn_whole + slot) / a.items;
+  } else {
+    const int xcd = slot / a.tail_items;
+    const long long n_items = (long long)a.items * n_bh;
+    const int idx = xcd_first(n_items, xcd) + a.items_xcd - a.tail_items + slot % a.tail_items;
+    if (idx >= xcd_first(n_items, xcd + 1)) return;
+    item = idx % a.items;
+    bhid = head_at(idx / a.items, n_bh);
+  }
   const int h = bhid % a.geo.H, b = bhid / a.geo.H;
   const long long bh = bhid;
   const int T_max = a.geo.T_max;
@@ -968,7 +983,7 @@ __global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
   const int n_x = a.blk_n[b * T_max + blk], x_start = a.blk_start[b * T_max + blk];
   const int row = rows8 * 8 + (threadIdx.x >> 5), ch = (threadIdx.x & 31) * 4;
   if (row >= n_x) return;
-  const float* src = a.tail_scratch + ((((long long)xcd * a.tail_items + r) * a.tail_parts) * 256 + grp * 128 + row) * MD + ch;
+  const float* src = a.tail_scratch + ((long long)slot * a.tail_parts * 256 + grp * 128 + row) * MD + ch;
   float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int p0 = 0; p0 < a.tail_parts; p0 += 4) {        // four parts' loads in flight
     float4 o[4];
@@ -1001,14 +1016,14 @@ __global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
 // by what the launch streams.
 // split_units: into how many parts the streamed side can be cut (list entries or tiles of means; 0: not to be cut).
 template <bool SM, bool T2, bool YD>
-static hipError_t launch_one(BwdArgs a, bool ex, int B, int H, hipStream_t st, int split_units = 0, int* dyn_ctr = nullptr) {
+static hipError_t launch_one(BwdArgs a, bool ex, int B, int H, hipStream_t st, int split_units = 0, int* dyn_ctr = nullptr, int min_dyn = 0) {
   if (a.items <= 0) return hipSuccess;
   if (YD && a.dx != nullptr) return hipErrorInvalidValue;
   const int cus = cus_per_xcd();
   a.items_xcd = (int)(((long long)a.items * B * H + N_XCD - 1) / N_XCD);
   a.tail_items = 0; a.tail_parts = 1;
-  // items from a counter only where there is more than half a round of them: fewer are cut into parts instead
-  a.dyn_ctr = SM || (split_units > 1 && a.items_xcd <= cus / 2) ? nullptr : dyn_ctr;
+  // items from a counter only where an XCD has min_dyn of them: fewer are cut into parts instead
+  a.dyn_ctr = SM || a.items_xcd < min_dyn ? nullptr : dyn_ctr;
   if (!SM && !a.dyn_ctr && split_units > 1 && a.tail_scratch) {
     // the last round of an XCD's 32 compute units: if at most half of them would have an item, cut those items
     const int t = a.items_xcd % cus;
@@ -1019,17 +1034,29 @@ static hipError_t launch_one(BwdArgs a, bool ex, int B, int H, hipStream_t st, i
       if (parts > 1) { a.tail_items = t; a.tail_parts = parts; }
     }
   }
+  // A counted launch of 8 rounds or more runs its last 32 items in 8 parts each, so that it ends within an eighth of an item of
+  // the ideal.  dQ of the exact branch at 480p with the paper's ratios, 20 rounds, and dK / dV
+  // likewise: training step 101.35 -> 100.85 ms, at keep 0.5, full 0.2 52.3 -> 51.9.
+  a.dyn_whole = a.items * B * H;
+  a.dyn_total = a.dyn_whole;
+  int n_merge = N_XCD * a.tail_items;
+  if (a.dyn_ctr && a.items_xcd >= 8 * cus && split_units >= 16 && a.tail_scratch) {
+    a.tail_parts = 8;
+    n_merge = SPLIT_MAX_SUB / a.tail_parts;
+    a.dyn_whole -= n_merge;
+    a.dyn_total += n_merge * (a.tail_parts - 1);
+  }
   // dynamic items: an eighth more workgroups than items and one round of the chip, so that the faster XCDs do not run out
   // of workgroups before the items run out
-  const long long n_dyn = (long long)a.items * B * H;
+  const long long n_dyn = a.dyn_total;
   const long long dyn_wgs = ((n_dyn + n_dyn / 8) / N_XCD + cus_per_xcd() + 1) * N_XCD;
   const dim3 grid((unsigned)(SM ? ((long long)a.items * a.parts * B * H + N_XCD - 1) / N_XCD * N_XCD
                                 : a.dyn_ctr ? dyn_wgs : (a.items_xcd - a.tail_items + a.tail_items * a.tail_parts) * 8));
   constexpr int EX = SM ? 1 : 2;                  // mean rows mask whole tiles per lane, token rows (dQ) also single positions
   if (ex) hipLaunchKernelGGL((k_attn_bwd<SM, T2, EX, YD>), grid, dim3(512), 0, st, a);
   else hipLaunchKernelGGL((k_attn_bwd<SM, T2, 0, YD>), grid, dim3(512), 0, st, a);
-  if (a.tail_items > 0)
-    hipLaunchKernelGGL(k_bwd_tail_merge, dim3((unsigned)(8 * a.tail_items * 32)), dim3(256), 0, st, a);
+  if (n_merge > 0)
+    hipLaunchKernelGGL(k_bwd_tail_merge, dim3((unsigned)(n_merge * 32)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1110,7 +1137,7 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   a.add_rows = resid ? ws.cdq : nullptr; a.add_by_block = 1;       // every query block's share of dQc
   a.stat_list = full_list; a.stat_kind = 0; a.items = (sf + 1) / 2;
   a.s[0] = kept_tokens; a.s[1] = none; a.n_phases = 1; a.bits = nullptr;
-  if ((e = launch_one<false, true, false>(a, false, B, H, st, min_kept)) != hipSuccess) return e;
+  if ((e = launch_one<false, true, false>(a, false, B, H, st, min_kept, ws.bwd_ctr + 2, 8 * cus_per_xcd())) != hipSuccess) return e;
   a.stat_list = flat_list; a.stat_kind = 1; a.items = (sl + 1) / 2;
   if (ex) {
     a.s[0] = kept_tokens; a.s[0].masked = 1;
@@ -1120,7 +1147,8 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   } else {
     a.s[0] = kept_means; a.n_phases = 1;
   }
-  if ((e = launch_one<false, true, false>(a, ex, B, H, st, (min_kept + KT - 1) / KT, ws.bwd_ctr + 0)) != hipSuccess) return e;
+  if ((e = launch_one<false, true, false>(a, ex, B, H, st, (min_kept + KT - 1) / KT, ws.bwd_ctr + 0,
+                                           min_kept > KT ? cus_per_xcd() / 2 + 1 : 0)) != hipSuccess) return e;
 
   // ---- dKc, dVc (streamed Q, dO of the Taylor blocks)
   const int n_mean_pairs = ((sk + 127) / 128 + 1) / 2;

@@ -72,6 +72,7 @@ struct KvArgs {
   int items;                                 // kept blocks per (batch, head) (largest of the batch)
   // distribution as in k_attn_bwd: a counter, or equal ranges per XCD whose last tail_items run as tail_parts parts each
   int* dyn_ctr;
+  int dyn_whole, dyn_total;
   int items_xcd, tail_items, tail_parts;
   float* tail_scratch;                       // [XCD][tail item][part][dK, dV][128][128]
 };
@@ -93,7 +94,13 @@ __global__ __launch_bounds__(256, 1) void k_bwd_kv(KvArgs a) {
     if (threadIdx.x == 0) taken = atomicAdd(a.dyn_ctr, 1);
     __syncthreads();
     idx = __builtin_amdgcn_readfirstlane(taken);
-    if (idx >= a.items * n_bh) return;                 // the launch has more workgroups than items
+    if (idx >= a.dyn_total) return;                    // the launch has more workgroups than items
+    if (idx >= a.dyn_whole) {
+      tail_slot = (idx - a.dyn_whole) / a.tail_parts;
+      part = (idx - a.dyn_whole) % a.tail_parts;
+      parts = a.tail_parts;
+      idx = a.dyn_whole + tail_slot;
+    }
   } else {
     const int n_reg = a.items_xcd - a.tail_items;
     idx = jj;
@@ -367,7 +374,7 @@ __global__ __launch_bounds__(256, 1) void k_bwd_kv(KvArgs a) {
     for (int qt = 0; qt < 2; ++qt) { settle(ak[ct][qt]); settle(av[ct][qt]); }
   // ---- element i of ak / av[ct][qt] is channel 16 ct + 4 q + i of row 16 qt + r
   if (tail_slot >= 0) {                                 // a part: unscaled sums, k_bwd_kv_merge does the rest
-    float* dst = a.tail_scratch + (((long long)xcd * a.tail_items + tail_slot) * parts + part) * 2 * 128 * MD;
+    float* dst = a.tail_scratch + ((long long)((a.dyn_ctr ? 0 : xcd * a.tail_items) + tail_slot) * parts + part) * 2 * 128 * MD;
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
@@ -405,18 +412,25 @@ __global__ __launch_bounds__(256, 1) void k_bwd_kv(KvArgs a) {
 // 32 threads per row, 4 channels each.
 __global__ __launch_bounds__(256) void k_bwd_kv_merge(KvArgs a) {
   const int rows8 = blockIdx.x & 15, which = (blockIdx.x >> 4) & 1;
-  const int r = (blockIdx.x >> 5) % a.tail_items, xcd = (blockIdx.x >> 5) / a.tail_items;
-  const int n_bh = a.geo.B * a.geo.H;
-  const long long n_items = (long long)a.items * n_bh;
-  const int idx = xcd_first(n_items, xcd) + a.items_xcd - a.tail_items + r;
-  if (idx >= xcd_first(n_items, xcd + 1)) return;
-  const int entry = idx % a.items, bhid = head_at(idx / a.items, n_bh);
+  const int slot = blockIdx.x >> 5, n_bh = a.geo.B * a.geo.H;
+  int entry, bhid;
+  if (a.dyn_ctr) {
+    entry = (a.dyn_whole + slot) % a.items;
+    bhid = (a.dyn_whole + slot) / a.items;
+  } else {
+    const int xcd = slot / a.tail_items;
+    const long long n_items = (long long)a.items * n_bh;
+    const int idx = xcd_first(n_items, xcd) + a.items_xcd - a.tail_items + slot % a.tail_items;
+    if (idx >= xcd_first(n_items, xcd + 1)) return;
+    entry = idx % a.items;
+    bhid = head_at(idx / a.items, n_bh);
+  }
   const int h = bhid % a.geo.H, b = bhid / a.geo.H;
   if (entry >= a.cnt.b[b].T_new) return;
   const int4 own = a.ktab[(long long)bhid * a.geo.T_max + entry];
   const int row = rows8 * 8 + (threadIdx.x >> 5), ch = (threadIdx.x & 31) * 4;
   if (row >= own.y) return;
-  const float* src = a.tail_scratch + (((long long)xcd * a.tail_items + r) * a.tail_parts * 2 + which) * 128 * MD + row * MD + ch;
+  const float* src = a.tail_scratch + ((long long)slot * a.tail_parts * 2 + which) * 128 * MD + row * MD + ch;
   float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int p0 = 0; p0 < a.tail_parts; p0 += 4) {        // four parts' loads in flight
     float4 o[4];
@@ -469,11 +483,21 @@ hipError_t launch_bwd_kv(const Problem& pr, const Workspace& ws, const void* q, 
     while (parts > 1 && N_XCD * a.items_xcd * parts > SPLIT_MAX_SUB) --parts;       // the partial-result area holds SPLIT_MAX_SUB sub-items
     if (parts > 1) { a.dyn_ctr = nullptr; a.tail_items = a.items_xcd; a.tail_parts = parts; }
   }
+  // 8 rounds or more: the last 32 items run in 8 parts each, so that the launch ends within an eighth of an item of the ideal.
+  a.dyn_whole = sk * B * H;
+  a.dyn_total = a.dyn_whole;
+  int n_merge = N_XCD * a.tail_items;
+  if (a.dyn_ctr && a.items_xcd >= 8 * cus && min_full >= 16) {
+    a.tail_parts = 8;
+    n_merge = SPLIT_MAX_SUB / a.tail_parts;
+    a.dyn_whole -= n_merge;
+    a.dyn_total += n_merge * (a.tail_parts - 1);
+  }
   // an eighth more workgroups than items and one round of the chip, so that the faster XCDs do not run out of workgroups
-  const long long n_dyn = (long long)sk * B * H;
+  const long long n_dyn = a.dyn_total;
   const long long wgs = a.dyn_ctr ? (n_dyn + n_dyn / 8) / N_XCD + cus + 1 : (long long)a.tail_items * a.tail_parts;
   hipLaunchKernelGGL(k_bwd_kv, dim3((unsigned)(wgs * N_XCD)), dim3(256), 0, st, a);
-  if (a.tail_items > 0) hipLaunchKernelGGL(k_bwd_kv_merge, dim3((unsigned)(N_XCD * a.tail_items * 32)), dim3(256), 0, st, a);
+  if (n_merge > 0) hipLaunchKernelGGL(k_bwd_kv_merge, dim3((unsigned)(n_merge * 32)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

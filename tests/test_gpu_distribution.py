@@ -78,3 +78,31 @@ def test_counted_items_beside_exact_sets(I):
     wl = _wl(200, (1, 1, 128 * 17 + 5), (((1, 1, 500),), ((1, 1, 70),)), B=2, keep_ratio=0.5, full_frac=0.6, exact_frac=0.2, gamma=0.5,
              seed=890)
     check_end_to_end(I, wl, *gen(wl), heads=[0, 77, 192, 199])
+
+
+def test_counted_items_backward(I):
+    """Backward of 8 rounds or more: the last 32 items of the dQ and of the dK / dV launch run in 8 parts each (the last heads).
+    Everything kept and exact: the gradient of dense attention, whatever the scores."""
+    import numpy as np
+    import torch
+    from oracle import isa_oracle_bwd as OB
+    from test_gpu_backward import TOL_MAX_REL, TOL_MEAN_REL, _inputs
+    from util import f64, problem_of
+    H = 240
+    wl = _wl(H, (1, 1, 128 * 9 + 5), (((1, 1, 128 * 7 + 60),),), keep_ratio=1.0, full_frac=1.0, seed=895)
+    pr = problem_of(wl)
+    c = I.isa_get_counts(pr, 0)
+    assert c["n_full"] >= 16 and H * ((c["n_full"] + 1) // 2) // 8 >= 8 * 32 and c["n_flat"] == 0          # the premise
+    Q, K, V, dO = _inputs(wl)
+    q, k, v, g = (t.cuda() for t in (Q, K, V, dO))
+    ws = I.new_workspace(pr)
+    out = torch.empty_like(q)
+    grads = [torch.full_like(q, float("nan")) for _ in range(3)]
+    I.isa_attention(pr, q, k, v, out, ws)
+    I.isa_attention_backward(pr, q, k, v, out, g, *grads, ws)
+    torch.cuda.synchronize()
+    assert all(torch.isfinite(x.float()).all() for x in grads)
+    for h in (0, 120, 236, 237, 238, 239):
+        for got, want in zip(grads, OB.dense_attention_bwd(*(f64(t[0, h]) for t in (Q, K, V, dO)))):
+            d = np.abs(f64(got[0, h]) - want) / np.abs(want).max()
+            assert d.max() <= TOL_MAX_REL and d.mean() <= TOL_MEAN_REL, (h, d.max(), d.mean())
