@@ -22,7 +22,7 @@
 // costs 9.4 vector instructions (5.5 of them the exact cut into three terms; taking the differences with the bf16 dot
 // instruction was slower and not exact) beside 2 matrix instructions; counters of the dense launch: issue port busy
 // 85 % of the cycles, matrix pipe 38 %, no LDS bank conflicts.  Whole call 11.6 -> 0.73 ms against a kernel of one
-// row per four lanes in scalar arithmetic (25 -> 400 TFLOP/s); fp32, 8 heads of 128 channels, 5280 tokens: 1.89 -> 0.40 ms.
+// row per four lanes in scalar arithmetic (25 -> 400 TFLOP/s); fp32, 8 heads of 128 channels, 5280 tokens: 1.89 -> 0.39 ms.
 #include <type_traits>
 
 #include "attn_mfma.h"
@@ -32,6 +32,8 @@ namespace isa {
 #define ISA_GEN_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 namespace {
+
+template <int D> constexpr int GROUP_LDS = 512 * D + 2 * 64 * 4;         // two stages of a K and a V tile, weights of mean tiles
 
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4v* lds_s4_ptr;
@@ -83,8 +85,11 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 // products of fp32 numbers with fp32 matrix instructions instead of bf16 terms: slower, but infinities go through them
 // as through a multiplication (a term that is zero turns an infinity into NaN).  Returns whether this wave's results are
 // all finite; with FULL32 = false nothing is stored if some wave's are not, and the caller runs the item again.
-template <typename T, int D, int QT, bool FULL32>
-__device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* lds, int bhid, bool taylor, int slot) {
+//
+// NG = 2: two groups of 4 waves work on the same rows, each with stages of its own, and take the tiles of the sequence in turn;
+// the second group hands its running maxima, sums and outputs to the first through LDS at the end.
+template <typename T, int D, int QT, bool FULL32, int NG>
+__device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* const lds_all, int bhid, bool taylor, int slot) {
   constexpr bool BF = sizeof(T) == 2;
   constexpr int KTOK = BF ? 64 : 32;                   // tokens per tile; tiles of means hold 32
   constexpr int NT = D / 16;                           // 16-channel tiles
@@ -93,6 +98,8 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   constexpr int ST = (CT < 16 ? CT : 16) - 1, SM = 15; // swizzle: chunk c of row r sits at c ^ (r & S)
   constexpr int NI = D / 32;                           // 1 KB loads per wave, tile and tensor
   constexpr int ROWS = 64 * QT;
+  const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
+  unsigned char* const lds = lds_all + grp * GROUP_LDS<D>;
   const AttnArgs& a = ga.a;
   float* const wts = reinterpret_cast<float*>(lds + 4 * TILE);         // [stage][block of the item][32]: weights of a mean tile's slots
 
@@ -106,7 +113,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   const int* const bn = a.blk_n + b * T_max;
   const long long tbase = (long long)b * a.geo.stride_b + (long long)h * a.geo.stride_h;
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = NG > 1 ? threadIdx.x & 255 : threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, g = lane >> 4;
 
@@ -457,18 +464,27 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     }
   };
 
-  // ---- the loop: the loads of tile n + 1 fly while tile n is multiplied
-  next_tile();
-  Tile cur = at;
+  // ---- the loop: the loads of a group's next tile fly while its current one is multiplied
+  int n_first = 0, n_mine = 0;                         // tiles of the first group / of this one among those described
+  auto next_mine = [&]() -> Tile {
+    Tile mine = at;
+#pragma unroll
+    for (int u = 0; u < NG; ++u) {
+      if (!at.end) next_tile();
+      if (u == 0) n_first += at.end ? 0 : 1;
+      if (u == grp) mine = at;
+    }
+    return mine;
+  };
+  Tile cur = next_mine();
   if (!cur.end) issue(cur, 0);
   int stage = 0;
   auto tiles = [&](const auto mean_c) __attribute__((always_inline)) {
     constexpr bool mean = decltype(mean_c)::value;
     for (; !cur.end && cur.mean == mean; stage ^= 1) {
-      next_tile();                                     // its table reads wait together with the tile loads
-      const Tile nxt = at;
+      const Tile nxt = next_mine();                    // its table reads wait together with the tile loads
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();                                 // tile n is complete; everybody has left tile n - 1, whose stage is filled next
+      __syncthreads();                                 // the tile is complete; everybody has left the one before, whose stage is filled next
       if (!nxt.end) issue(nxt, stage ^ 1);
       const unsigned char* kb = lds + stage * 2 * TILE;
       if ((cur.bits >> own) & 1) {                     // wave-uniform
@@ -476,12 +492,46 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         for (int r0 = 0; r0 < cur.nk; r0 += 32) half(kb, kb + TILE, r0, cur.nk - r0, mean_c, wts + stage * 64 + own * 32);
       }
       cur = nxt;
+      ++n_mine;
     }
   };
   // two loops: the kinds of tile share no code path through which the accumulators would have to be moved
   tiles(std::false_type{});
   tiles(std::true_type{});
+  if (NG > 1 && n_mine < n_first) __syncthreads();     // the first group has had one tile, and one barrier, more
   __syncthreads();                                     // nobody reads LDS any more: the caller may start another pass
+
+  // ---- the second group's part (the merge step of the online softmax)
+  if constexpr (NG > 1) {
+    constexpr int W = QT * (4 * NT + 2);               // floats of a lane
+    float* const part = reinterpret_cast<float*>(lds_all + GROUP_LDS<D>) + wave * W * 64 + lane;
+    if (grp == 1) {
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        part[(qt * (4 * NT + 2)) * 64] = neg_m[qt];
+        part[(qt * (4 * NT + 2) + 1) * 64] = l_run[qt];
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) part[(qt * (4 * NT + 2) + 2 + 4 * ct + i) * 64] = acc[ct][qt][i];
+      }
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        const float other = part[(qt * (4 * NT + 2)) * 64];
+        const float nm = fminf(neg_m[qt], other);      // minus the larger maximum
+        const float mine = __builtin_amdgcn_exp2f(nm - neg_m[qt]), theirs = __builtin_amdgcn_exp2f(nm - other);
+        l_run[qt] = l_run[qt] * mine + part[(qt * (4 * NT + 2) + 1) * 64] * theirs;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[ct][qt][i] = acc[ct][qt][i] * mine + part[(qt * (4 * NT + 2) + 2 + 4 * ct + i) * 64] * theirs;
+      }
+    }
+    __syncthreads();                                   // read before the caller's next pass fills the stages again
+  }
 
   // ---- normalise, check, store
   float inv[QT];
@@ -492,7 +542,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     inv[qt] = 1.0f / l;
-    if (row0 + 16 * qt + r16 < n_q)
+    if (grp == 0 && row0 + 16 * qt + r16 < n_q)
 #pragma unroll
       for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
@@ -500,6 +550,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   }
   if constexpr (BF && !FULL32)
     if (__syncthreads_or(!ok)) return false;
+  if (grp != 0) return true;
   // coarse residual (Alg. 1 Stage 5): the block's row of O_coarse, the same for all of its tokens
   const float* const oc = (a.ocoarse && !a.dense) ? a.ocoarse + (bh * T_max + qi) * D : nullptr;
 #pragma unroll
@@ -526,10 +577,10 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   return true;
 }
 
-// D = 128: 66 KB of LDS, two workgroups per compute unit; D = 64: registers for three (QT = 2) or four
-template <typename T, int D, int QT>
-__global__ __launch_bounds__(256, D == 128 ? 2 : QT == 1 ? 4 : 3) void k_attn_gen(GenArgs ga) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[512 * D + 2 * 64 * 4];
+// D = 128: 66 KB of LDS a group, two groups per compute unit; D = 64: registers for three workgroups (QT = 2) or four groups
+template <typename T, int D, int QT, int NG>
+__global__ __launch_bounds__(256 * NG, D == 128 ? 2 : QT == 1 ? 4 : 3) void k_attn_gen(GenArgs ga) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[NG * GROUP_LDS<D>];
   // Workgroup ids go round-robin over the 8 XCDs; each has its range of the items of all (batch, head)s, the long ones
   // (exact branch) first.
   const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
@@ -545,11 +596,11 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : QT == 1 ? 4 : 3) void k_attn_ge
   // QT-tile slot n of a list: rows 64 QT n .. of a 128-row block's sequence of rows, or block n / blocks 2 n, 2 n + 1 of 64 rows
   auto first_entry = [&](int qt, int n) { return ga.a.geo.block == 64 ? qt * n : n * qt / 2; };
   if (first_entry(QT, slot) >= n_list) return;         // a shorter batch item
-  if (attn_gen_item<T, D, QT, false>(ga, lds, bhid, taylor, slot)) return;
+  if (attn_gen_item<T, D, QT, false, NG>(ga, lds, bhid, taylor, slot)) return;
   if constexpr (sizeof(T) == 2) {                      // again, 64 rows at a time
 #pragma unroll 1
     for (int n = QT * slot; n < QT * (slot + 1); ++n)
-      if (first_entry(1, n) < n_list) attn_gen_item<T, D, 1, true>(ga, lds, bhid, taylor, n);
+      if (first_entry(1, n) < n_list) attn_gen_item<T, D, 1, true, NG>(ga, lds, bhid, taylor, n);
   }
 }
 
@@ -579,16 +630,21 @@ hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st)
   ga.per_xcd_taylor = (int)((bh * ga.slots_taylor + N_XCD - 1) / N_XCD);
   if (ga.slots_long == 0) ga.slots_long = 1;           // divisors in the kernel; a branch without work gets no workgroups
   if (ga.slots_taylor == 0) ga.slots_taylor = 1;
-  const dim3 grid((unsigned)(N_XCD * (ga.per_xcd_long + ga.per_xcd_taylor))), blk(256);
+  const dim3 grid((unsigned)(N_XCD * (ga.per_xcd_long + ga.per_xcd_taylor)));
+  // Two groups per workgroup while the long items leave most SIMDs with one or two waves.  Measured, one / two groups, whole call: D = 64
+  // (two such workgroups fit a compute unit), 2, 4, 6, 8 heads of 15 600 tokens (122, 244, 366, 488 long items) 311 / 238, 317 / 243,
+  // 341 / 315, 347 / 349 us; D = 128 (one fits), 2, 4 heads (122, 244) 404 / 317, 420 / 397, fp32, 12 heads of 5280 tokens (264)
+  // 668 / 733; 5 heads of 990 tokens, D = 64: 44.5 / 41.3.
+  const bool groups = !two && bh * ga.slots_long <= (long long)N_XCD * cus_per_xcd() * (pr.p.D == 64 ? 7 : 4) / 4;
+#define ISA_GEN(T, D, QT, NG) hipLaunchKernelGGL((k_attn_gen<T, D, QT, NG>), grid, dim3(256 * NG), 0, st, ga)
   if (pr.p.dtype == ISA_BF16) {
-    if (pr.p.D == 128 && two) hipLaunchKernelGGL((k_attn_gen<uint16_t, 128, 2>), grid, blk, 0, st, ga);
-    else if (pr.p.D == 128) hipLaunchKernelGGL((k_attn_gen<uint16_t, 128, 1>), grid, blk, 0, st, ga);
-    else if (two) hipLaunchKernelGGL((k_attn_gen<uint16_t, 64, 2>), grid, blk, 0, st, ga);
-    else hipLaunchKernelGGL((k_attn_gen<uint16_t, 64, 1>), grid, blk, 0, st, ga);
+    if (pr.p.D == 128) { if (two) ISA_GEN(uint16_t, 128, 2, 1); else if (groups) ISA_GEN(uint16_t, 128, 1, 2); else ISA_GEN(uint16_t, 128, 1, 1); }
+    else { if (two) ISA_GEN(uint16_t, 64, 2, 1); else if (groups) ISA_GEN(uint16_t, 64, 1, 2); else ISA_GEN(uint16_t, 64, 1, 1); }
   } else {
-    if (pr.p.D == 128) hipLaunchKernelGGL((k_attn_gen<float, 128, 1>), grid, blk, 0, st, ga);
-    else hipLaunchKernelGGL((k_attn_gen<float, 64, 1>), grid, blk, 0, st, ga);
+    if (pr.p.D == 128) { if (groups) ISA_GEN(float, 128, 1, 2); else ISA_GEN(float, 128, 1, 1); }
+    else { if (groups) ISA_GEN(float, 64, 1, 2); else ISA_GEN(float, 64, 1, 1); }
   }
+#undef ISA_GEN
   return hipGetLastError();
 }
 

@@ -48,6 +48,22 @@ def test_wide_workgroups(I, shape, exact_frac):
     check_end_to_end(I, wl, *gen(wl), heads=[0, 7, 150, 299])
 
 
+# 1, 2 and 3 tiles for the two groups of a workgroup to share (fp32: 32 tokens each), token tiles followed by tiles of means
+@pytest.mark.parametrize("tokens", [32, 33, 64, 65, 96])
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_few_tiles_for_two_groups(I, shape, tokens):
+    wl = _wl(shape, 2, (1, 1, tokens), (((1, 1, 40),),), keep_ratio=1.0, full_frac=0.5, exact_frac=0.5, seed=740 + tokens)
+    check_end_to_end(I, wl, *gen(wl))
+
+
+# a long list with fewer than 256 long items (two groups) and with more (one group): the same answers
+@pytest.mark.parametrize("H", [2, 60])
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_one_and_two_groups(I, shape, H):
+    wl = _wl(shape, H, (1, 1, 1500), (((1, 1, 900),),), keep_ratio=0.5, full_frac=0.5, exact_frac=0.2, gamma=0.5, seed=745 + H)
+    check_end_to_end(I, wl, *gen(wl), heads=[0, H // 2, H - 1])
+
+
 @pytest.mark.parametrize("H", [1, 3, 5, 9, 20])
 def test_head_counts_over_the_xcds(I, H):
     wl = _wl(("bf16", 64, 64), H, (2, 10, 33), (((1, 10, 33),),), keep_ratio=0.5, full_frac=0.4, seed=750 + H)
