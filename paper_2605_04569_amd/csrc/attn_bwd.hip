@@ -10,18 +10,16 @@
 // The coarse residual gamma * O_coarse (Stages 1 and 5) adds the gradient of a small T x T attention over the block
 // means (kernels at the end of this file), which enters the big launches through their epilogues.
 //
-// One kernel does all six products.  A workgroup (8 waves) keeps 2 x 128 "stationary" rows in registers and streams
-// 64-row tiles of the other side through LDS; per tile it forms T1 = Y1 X1^T (the scores) and, where dS is needed,
+// One kernel body does these products (dK and dV have a kernel of their own, attn_bwd_kv.hip).  A workgroup (8 waves)
+// keeps 2 x 128 "stationary" rows in registers and streams 64-row tiles of the other side through LDS; per tile it forms T1 = Y1 X1^T (the scores) and, where dS is needed,
 // T2 = Y2 X2^T (dP), turns them into W = P or dS in registers and accumulates acc^T += Yt W^T, where Yt is the
 // transpose of a streamed tile: its fragments are read out of the row-major tile in LDS with ds_read_b64_tr_b16, in the
-// key order of the 16x16x32 accumulators, so no transposed copy of any tensor exists.  The six launches:
+// key order of the 16x16x32 accumulators, so no transposed copy of any tensor exists.  The three launches:
 //     dQ, exact branch : stationary (Q, dO) of the full-attention blocks,  streamed K, V of the kept tokens (Yt = K^T)
 //     dQ, Taylor branch: stationary (Q, dO) of the Taylor blocks,          streamed Kc, Vc (block means), after the
 //                        K, V tiles of the blocks' exact sets
-//     dKc, dVc         : stationary (Kc, Vc) / Kc rows,                    streamed Q, dO of the Taylor blocks (Yt = Q^T / dO^T)
-//     dK, dV           : stationary (K, V) / K of the kept blocks,         streamed Q, dO of the full-attention
-//                        blocks and of the Taylor blocks whose exact set holds the block; the epilogue adds the block's
-//                        dKc / n_j (dVc / n_j) and writes bf16
+//     dKc, dVc         : stationary (Kc, Vc) / Kc rows,                    streamed Q, dO of the Taylor blocks (Yt = Q^T / dO^T),
+//                        half of the workgroups each
 // Every output element is written by exactly one workgroup: no atomics, results are reproducible.
 //
 // The additive terms of a weight ride in the MFMA accumulators: T1 starts at b_x / c (minus the log-sum-exp of a
@@ -102,7 +100,7 @@ struct BwdArgs {
   int stat_kind;                              // token rows: 0 full-attention blocks, 1 Taylor blocks, 2 kept blocks
   int items;                                  // work items (pairs of stationary blocks) per (batch, head) in this launch
   // mean rows only: every item runs as `parts` workgroups, each over its share of the streamed entries, and writes its
-  // partial sums to out_f32 + part * part_stride (k_bwd_sum_parts adds them up)
+  // partial sums to out_f32 + part * part_stride (k_bwd_mean_sums adds them up)
   int parts; long long part_stride;
   // token rows: the last tail_items items of every XCD (its last, incomplete round over the compute
   // units) run as tail_parts workgroups each, every one over its share of the streamed entries of each phase; they leave their
@@ -121,13 +119,12 @@ struct BwdArgs {
 // YD: the streamed rows carry deltas of their own (they are queries) and the stationary rows none; otherwise the other
 // way round.
 template <bool SM, bool T2, int EX, bool YD>
-__global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
+__device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, const int wg, float* const out_f32, const float oscale) {
   constexpr int STG = EX == 2 ? STAGE + K_TILE : STAGE;      // EX == 2: a third tile per stage (see BwdStream::y3)
-  __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * STG + 2 * SIDE_BYTES / 2];
   // Workgroup ids go round-robin over the 8 XCDs: XCD x has its range of the items of all (batch, head)s (xcd_first, head_at) and
   // works through it one head after the other, so that the workgroups that run together on an XCD (and share its L2)
   // stream the same rows.
-  const int xcd = blockIdx.x & 7, jj = blockIdx.x >> 3;
+  const int xcd = wg & 7, jj = wg >> 3;
   const int n_bh = a.geo.B * a.geo.H;
   int parts = 1, part = 0, item, bhid, tail_slot = -1;
   if (SM) {
@@ -570,15 +567,15 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
     const int row = rowq[qt];
 #pragma unroll
     for (int ct = 0; ct < 8; ++ct) {
-      float4 r = make_float4(acc[ct][qt][0] * a.oscale, acc[ct][qt][1] * a.oscale, acc[ct][qt][2] * a.oscale,
-                             acc[ct][qt][3] * a.oscale);
+      float4 r = make_float4(acc[ct][qt][0] * oscale, acc[ct][qt][1] * oscale, acc[ct][qt][2] * oscale,
+                             acc[ct][qt][3] * oscale);
       if (addp) {
         const float4 m4 = *reinterpret_cast<const float4*>(addp + 16 * ct);
         r.x = fmaf(m4.x, inv_n, r.x); r.y = fmaf(m4.y, inv_n, r.y);
         r.z = fmaf(m4.z, inv_n, r.z); r.w = fmaf(m4.w, inv_n, r.w);
       }
       if (SM) {
-        *reinterpret_cast<float4*>(a.out_f32 + part * a.part_stride + (bh * a.Tn_pad + (long long)entry * 128 + row) * MD + 16 * ct + 4 * q) = r;
+        *reinterpret_cast<float4*>(out_f32 + part * a.part_stride + (bh * a.Tn_pad + (long long)entry * 128 + row) * MD + 16 * ct + 4 * q) = r;
       } else {
         bf16x2 lo = {(__bf16)r.x, (__bf16)r.y};
         bf16x2 hi = {(__bf16)r.z, (__bf16)r.w};
@@ -589,6 +586,24 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
       }
     }
   }
+}
+
+// dQ: stationary token rows
+template <int EX>
+__global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * (EX == 2 ? STAGE + K_TILE : STAGE) + 2 * SIDE_BYTES / 2];
+  attn_bwd<false, true, EX, false>(a, lds, blockIdx.x, nullptr, a.oscale);
+}
+
+// dKc (the first half of the workgroups) and dVc, stationary gathered means, in one launch: either alone leaves most of the chip
+// idle (measured, a training step, two launches / one: 12 heads of 1564 tokens with exact sets 233 / 219 us, 40 heads of 15 600
+// tokens with the residual 4490 / 4435)
+template <int EX>
+__global__ __launch_bounds__(512, 1) void k_attn_bwd_means(BwdArgs a, float* dvc) {
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * STAGE + 2 * SIDE_BYTES / 2];
+  const int half = gridDim.x / 2;                      // a multiple of the XCDs
+  if ((int)blockIdx.x < half) attn_bwd<true, true, EX, true>(a, lds, blockIdx.x, a.out_f32, a.oscale);
+  else attn_bwd<true, false, EX, false>(a, lds, (int)blockIdx.x - half, dvc, 1.0f);
 }
 
 // delta[bh][token] = sum_d dO * O (fp32); 16 lanes per token row, 16 bytes per lane and tensor.  O is taken as out + olo:
@@ -916,18 +931,6 @@ static hipError_t launch_bwd_coarse(const Problem& pr, const Workspace& ws, hipS
   return hipGetLastError();
 }
 
-// mean_grad[bh][e] (gradient of the gathered mean of kv_list[e], or nothing yet if `fresh`) += coarse[bh][kv_list[e]]
-__global__ __launch_bounds__(128) void k_bwd_add_coarse(float* __restrict__ mean_grad, const float* __restrict__ coarse,
-                                                        const int* __restrict__ kv_list, int fresh, Counts cnt, int H,
-                                                        int Tn_pad) {
-  const int e = blockIdx.x, h = blockIdx.y, b = blockIdx.z, d = threadIdx.x;
-  if (e >= cnt.b[b].T_new) return;
-  const long long bh = (long long)b * H + h;
-  const int blk = block_in_range(kv_list[bh * cnt.T_max + e], cnt.b[b].T);
-  const float prev = fresh ? 0.f : mean_grad[(bh * Tn_pad + e) * MD + d];
-  mean_grad[(bh * Tn_pad + e) * MD + d] = prev + coarse[(bh * cnt.T_max + blk) * MD + d];
-}
-
 // Transposed exact-set bits: bit r of word r / 32 of row t is bit t of row r of `mask` (r: position in the Taylor list,
 // t: position in the kept list), so that a kept block finds the Taylor blocks that attend to its tokens.
 __global__ __launch_bounds__(128) void k_bwd_tmask(const uint32_t* __restrict__ mask, uint32_t* __restrict__ mask_t,
@@ -945,14 +948,20 @@ __global__ __launch_bounds__(128) void k_bwd_tmask(const uint32_t* __restrict__ 
   mask_t[(bh * T_max + t) * mw + w] = out;
 }
 
-// Adds the partial sums of the parts of a mean-row launch into part 0: one workgroup per gathered mean row.
-__global__ __launch_bounds__(128) void k_bwd_sum_parts(float* __restrict__ g, int parts, long long part_stride, Counts cnt,
-                                                       int H, int Tn_pad) {
-  const int e = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+// Gradients of the gathered means, dKc and dVc (blockIdx.z = 2 * batch item + which): the partial sums of the `parts` parts of the
+// launch over the mean rows (0: there was none) plus, with the coarse residual, its gradient of the same mean (coarse, by
+// block id), into part 0.  One workgroup per gathered mean row.
+__global__ __launch_bounds__(128) void k_bwd_mean_sums(float* __restrict__ dkc, float* __restrict__ dvc, int parts, long long part_stride,
+                                                       const float* __restrict__ coarse_k, const float* __restrict__ coarse_v,
+                                                       const int* __restrict__ kv_list, Counts cnt, int H, int Tn_pad) {
+  const int e = blockIdx.x, h = blockIdx.y, b = blockIdx.z >> 1, d = threadIdx.x;
   if (e >= cnt.b[b].T_new) return;
-  const long long i = (((long long)b * H + h) * Tn_pad + e) * MD + threadIdx.x;
-  float sum = g[i];
+  float* const g = blockIdx.z & 1 ? dvc : dkc;
+  const float* const coarse = blockIdx.z & 1 ? coarse_v : coarse_k;
+  const long long bh = (long long)b * H + h, i = (bh * Tn_pad + e) * MD + d;
+  float sum = parts > 0 ? g[i] : 0.f;
   for (int p = 1; p < parts; ++p) sum += g[p * part_stride + i];
+  if (coarse) sum += coarse[(bh * cnt.T_max + block_in_range(kv_list[bh * cnt.T_max + e], cnt.b[b].T)) * MD + d];
   g[i] = sum;
 }
 
@@ -1012,19 +1021,15 @@ __global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
   *reinterpret_cast<uint2*>(a.out_bf + tbase + (long long)(x_start + row) * a.geo.stride_t + ch) = o;
 }
 
-// YD (the streamed rows are queries, which carry deltas; the stationary rows then must not: a.dx == nullptr) is implied
-// by what the launch streams.
-// split_units: into how many parts the streamed side can be cut (list entries or tiles of means; 0: not to be cut).
-template <bool SM, bool T2, bool YD>
-static hipError_t launch_one(BwdArgs a, bool ex, int B, int H, hipStream_t st, int split_units = 0, int* dyn_ctr = nullptr, int min_dyn = 0) {
+// A dQ launch.  split_units: into how many parts the streamed side can be cut (list entries or tiles of means).
+static hipError_t launch_dq(BwdArgs a, bool ex, int B, int H, hipStream_t st, int split_units, int* dyn_ctr, int min_dyn) {
   if (a.items <= 0) return hipSuccess;
-  if (YD && a.dx != nullptr) return hipErrorInvalidValue;
   const int cus = cus_per_xcd();
   a.items_xcd = (int)(((long long)a.items * B * H + N_XCD - 1) / N_XCD);
   a.tail_items = 0; a.tail_parts = 1;
   // items from a counter only where an XCD has min_dyn of them: fewer are cut into parts instead
-  a.dyn_ctr = SM || a.items_xcd < min_dyn ? nullptr : dyn_ctr;
-  if (!SM && !a.dyn_ctr && split_units > 1 && a.tail_scratch) {
+  a.dyn_ctr = a.items_xcd < min_dyn ? nullptr : dyn_ctr;
+  if (!a.dyn_ctr && split_units > 1 && a.tail_scratch) {
     // the last round of an XCD's 32 compute units: if at most half of them would have an item, cut those items
     const int t = a.items_xcd % cus;
     if (t > 0 && t <= cus / 2) {
@@ -1050,11 +1055,9 @@ static hipError_t launch_one(BwdArgs a, bool ex, int B, int H, hipStream_t st, i
   // of workgroups before the items run out
   const long long n_dyn = a.dyn_total;
   const long long dyn_wgs = ((n_dyn + n_dyn / 8) / N_XCD + cus_per_xcd() + 1) * N_XCD;
-  const dim3 grid((unsigned)(SM ? ((long long)a.items * a.parts * B * H + N_XCD - 1) / N_XCD * N_XCD
-                                : a.dyn_ctr ? dyn_wgs : (a.items_xcd - a.tail_items + a.tail_items * a.tail_parts) * 8));
-  constexpr int EX = SM ? 1 : 2;                  // mean rows mask whole tiles per lane, token rows (dQ) also single positions
-  if (ex) hipLaunchKernelGGL((k_attn_bwd<SM, T2, EX, YD>), grid, dim3(512), 0, st, a);
-  else hipLaunchKernelGGL((k_attn_bwd<SM, T2, 0, YD>), grid, dim3(512), 0, st, a);
+  const dim3 grid((unsigned)(a.dyn_ctr ? dyn_wgs : (a.items_xcd - a.tail_items + a.tail_items * a.tail_parts) * 8));
+  if (ex) hipLaunchKernelGGL((k_attn_bwd<2>), grid, dim3(512), 0, st, a);
+  else hipLaunchKernelGGL((k_attn_bwd<0>), grid, dim3(512), 0, st, a);
   if (n_merge > 0)
     hipLaunchKernelGGL(k_bwd_tail_merge, dim3((unsigned)(n_merge * 32)), dim3(256), 0, st, a);
   return hipGetLastError();
@@ -1137,7 +1140,7 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   a.add_rows = resid ? ws.cdq : nullptr; a.add_by_block = 1;       // every query block's share of dQc
   a.stat_list = full_list; a.stat_kind = 0; a.items = (sf + 1) / 2;
   a.s[0] = kept_tokens; a.s[1] = none; a.n_phases = 1; a.bits = nullptr;
-  if ((e = launch_one<false, true, false>(a, false, B, H, st, min_kept, ws.bwd_ctr + 2, 8 * cus_per_xcd())) != hipSuccess) return e;
+  if ((e = launch_dq(a, false, B, H, st, min_kept, ws.bwd_ctr + 2, 8 * cus_per_xcd())) != hipSuccess) return e;
   a.stat_list = flat_list; a.stat_kind = 1; a.items = (sl + 1) / 2;
   if (ex) {
     a.s[0] = kept_tokens; a.s[0].masked = 1;
@@ -1147,45 +1150,37 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   } else {
     a.s[0] = kept_means; a.n_phases = 1;
   }
-  if ((e = launch_one<false, true, false>(a, ex, B, H, st, (min_kept + KT - 1) / KT, ws.bwd_ctr + 0,
+  if ((e = launch_dq(a, ex, B, H, st, (min_kept + KT - 1) / KT, ws.bwd_ctr + 0,
                                            min_kept > KT ? cus_per_xcd() / 2 + 1 : 0)) != hipSuccess) return e;
 
-  // ---- dKc, dVc (streamed Q, dO of the Taylor blocks)
-  const int n_mean_pairs = ((sk + 127) / 128 + 1) / 2;
-  // The mean-row launches have few items (one per 256 gathered means and head): each is cut into up to BWD_MEAN_PARTS
-  // parts along the streamed entries, as many as make the launch's rounds over the 256 compute units shortest.
-  int mean_parts = 1;
-  {
-    const long long wgs = (long long)n_mean_pairs * B * H;
+  // ---- dKc, dVc: gradients of the gathered means (streamed Q, dO of every Taylor block, minus its exact set)
+  // dKc: W = dS, read Q transposed; dVc: W = P, dO transposed.  The launch has few items (two per 256 gathered means and head):
+  // each is cut into up to BWD_MEAN_PARTS parts along the streamed entries, as many as make the launch's rounds over the 256
+  // compute units shortest.
+  int mean_parts = 0;
+  if (sl > 0 && sk > 0) {
+    const int n_mean_pairs = ((sk + 127) / 128 + 1) / 2;
     double best = 1e30;
     for (int p = 1; p <= BWD_MEAN_PARTS; ++p) {
-      const long long chip = (long long)cus_per_xcd() * N_XCD;
-      const double rounds = (double)((wgs * p + chip - 1) / chip) / p;
+      const long long chip = (long long)cus_per_xcd() * N_XCD, wgs = 2ll * n_mean_pairs * B * H * p;
+      const double rounds = (double)((wgs + chip - 1) / chip) / p;
       if (rounds < best - 1e-9) { best = rounds; mean_parts = p; }
     }
+    a.x1 = mean_keys; a.x2 = ws.vcn; a.stat_list = nullptr; a.stat_kind = 2; a.bx = ws.bx_mean; a.dx = nullptr; a.rx = nullptr;
+    a.s[0] = {Q, DO, nullptr, ws.ltab, ex ? ws.ybd_flatm : ws.ybd_flat, 2, ex ? 3 : 0};      // scored against gathered means
+    a.s[1] = none; a.n_phases = 1; a.bits = ws.mask_t;
+    a.out_bf = nullptr; a.out_f32 = ws.dkc; a.add_rows = nullptr; a.items = n_mean_pairs;
+    a.parts = mean_parts; a.part_stride = (long long)B * H * pr.Tn_pad * MD;
+    a.dyn_ctr = nullptr;
+    const dim3 grid((unsigned)(2 * (((long long)n_mean_pairs * mean_parts * B * H + N_XCD - 1) / N_XCD * N_XCD)));
+    if (ex) hipLaunchKernelGGL((k_attn_bwd_means<1>), grid, dim3(512), 0, st, a, ws.dvc);
+    else hipLaunchKernelGGL((k_attn_bwd_means<0>), grid, dim3(512), 0, st, a, ws.dvc);
+    ISA_BWD_CHECK();
   }
-  const BwdStream flat_q_means = {Q, DO, nullptr, ws.ltab, ex ? ws.ybd_flatm : ws.ybd_flat, 2, 0};     // scored against gathered means
-  a.dx = nullptr; a.rx = nullptr;
-  for (int pass = 0; pass < 2; ++pass) {          // pass 0: dKc (W = dS, read Q transposed); pass 1: dVc (W = P, dO transposed)
-    float* mean_grad = pass == 0 ? ws.dkc : ws.dvc;
-    if (sl > 0) {                                 // gradients of the gathered means: every Taylor block, minus its exact set
-      a.x1 = mean_keys; a.x2 = pass == 0 ? ws.vcn : nullptr; a.stat_list = nullptr; a.stat_kind = 2; a.bx = ws.bx_mean;
-      a.s[0] = flat_q_means; a.s[0].masked = ex ? 3 : 0; a.s[1] = none; a.n_phases = 1; a.bits = ws.mask_t;
-      a.out_bf = nullptr; a.out_f32 = mean_grad; a.add_rows = nullptr; a.oscale = pass == 0 ? scale : 1.0f; a.items = n_mean_pairs;
-      a.parts = mean_parts; a.part_stride = (long long)B * H * pr.Tn_pad * MD;
-      e = pass == 0 ? launch_one<true, true, true>(a, ex, B, H, st) : launch_one<true, false, false>(a, ex, B, H, st);
-      if (e != hipSuccess) return e;
-      if (mean_parts > 1) {
-        hipLaunchKernelGGL(k_bwd_sum_parts, dim3(sk, H, B), dim3(128), 0, st, mean_grad, mean_parts, a.part_stride, pr.cnt, H,
-                           pr.Tn_pad);
-        ISA_BWD_CHECK();
-      }
-    }
-    if (resid) {                                  // the coarse residual's gradient of the same means joins the Taylor branch's
-      hipLaunchKernelGGL(k_bwd_add_coarse, dim3(sk, H, B), dim3(128), 0, st, mean_grad, pass == 0 ? ws.cdk : ws.cdv,
-                         kv_list, sl > 0 ? 0 : 1, pr.cnt, H, pr.Tn_pad);
-      ISA_BWD_CHECK();
-    }
+  if (sk > 0 && (mean_parts > 1 || resid)) {
+    hipLaunchKernelGGL(k_bwd_mean_sums, dim3(sk, H, 2 * B), dim3(128), 0, st, ws.dkc, ws.dvc, mean_parts,
+                       (long long)B * H * pr.Tn_pad * MD, resid ? ws.cdk : nullptr, resid ? ws.cdv : nullptr, kv_list, pr.cnt, H, pr.Tn_pad);
+    ISA_BWD_CHECK();
   }
   // ---- dK, dV of the kept tokens: every full-attention block, the Taylor blocks whose exact set holds the block, and
   // the block's share of its mean's gradient
