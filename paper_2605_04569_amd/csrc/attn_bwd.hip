@@ -641,15 +641,13 @@ __global__ __launch_bounds__(256) void k_bwd_delta(const uint16_t* __restrict__ 
 // queries (term = minus the row's log-sum-exp in the log2 domain, delta of the row); with `rq` (Taylor blocks under exact
 // sets, for scores against the gathered means, which are stored minus Kc_0) the row's q . Kc_0, scaled to the log2
 // domain, is added to the term.
-struct RowLists {                             // what k_bwd_rows does, list by list (blockIdx.z = list * B + batch item)
+struct RowLists {
   const int* list[4]; int kind[4]; const float* rq[4]; int4* tab[4]; float2* ybd[4];
 };
-__global__ __launch_bounds__(128) void k_bwd_rows(RowLists ls, int B, const int4* __restrict__ btab, const float* __restrict__ nlse,
-                                                  float rq_scale, const float* __restrict__ delta,
-                                                  float2* __restrict__ ybd_mean, float* __restrict__ bx_mean, Counts cnt,
-                                                  int H, int Tn_pad, int S_max) {
-  const int which = blockIdx.z / B;
-  const int e = blockIdx.x, h = blockIdx.y, b = blockIdx.z % B, r = threadIdx.x;
+__device__ __forceinline__ void bwd_rows(const RowLists& ls, int which, int b, const int4* __restrict__ btab, const float* __restrict__ nlse,
+                                         float rq_scale, const float* __restrict__ delta, float2* __restrict__ ybd_mean,
+                                         float* __restrict__ bx_mean, const Counts& cnt, int H, int Tn_pad, int S_max) {
+  const int e = blockIdx.x, h = blockIdx.y, r = threadIdx.x;
   const int* const list = ls.list[which];
   const int kind = ls.kind[which];
   const float* const rq = ls.rq[which];
@@ -685,15 +683,15 @@ __global__ __launch_bounds__(128) void k_bwd_rows(RowLists ls, int B, const int4
 // Rows of dK and dV that no later launch writes (keys and values of blocks that were not kept): zero, or, with the
 // coarse residual, the block's share `rows[block] / n` of the gradient of its mean.  The launches over the kept blocks write
 // theirs, so those are left alone (480p at the paper's ratios, half the blocks kept: 220 us for all rows of both -> 79).
-__global__ __launch_bounds__(256) void k_bwd_fill(uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
-                                                  const float* __restrict__ rows_k, const float* __restrict__ rows_v,
-                                                  const int* __restrict__ kv_list, const int4* __restrict__ btab, Geometry g, Counts cnt) {
-  const int blk = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+__device__ __forceinline__ void bwd_fill(uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int b,
+                                         const float* __restrict__ rows_k, const float* __restrict__ rows_v,
+                                         const int* __restrict__ kv_list, const int4* __restrict__ btab, const Geometry& g, const Counts& cnt) {
+  const int blk = blockIdx.x, h = blockIdx.y;
   const int T = cnt.b[b].T, T_new = cnt.b[b].T_new;
   if (blk >= T) return;
   const long long bh = (long long)b * g.H + h;
   int kept = 0;
-  for (int t = threadIdx.x; t < T_new; t += 256) kept |= block_in_range(kv_list[bh * cnt.T_max + t], T) == blk ? 1 : 0;
+  for (int t = threadIdx.x; t < T_new; t += 128) kept |= block_in_range(kv_list[bh * cnt.T_max + t], T) == blk ? 1 : 0;
   if (__syncthreads_or(kept)) return;
   const int4 ent = btab[b * cnt.T_max + blk];
   const int c16 = threadIdx.x & 15;
@@ -710,8 +708,42 @@ __global__ __launch_bounds__(256) void k_bwd_fill(uint16_t* __restrict__ dk, uin
       val = make_uint4(w[0], w[1], w[2], w[3]);
     }
     uint16_t* x = (t ? dv : dk) + (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)ent.x * g.stride_t + 8 * c16;
-    for (int r = threadIdx.x >> 4; r < ent.y; r += 16) *reinterpret_cast<uint4*>(x + (long long)r * g.stride_t) = val;
+    for (int r = threadIdx.x >> 4; r < ent.y; r += 8) *reinterpret_cast<uint4*>(x + (long long)r * g.stride_t) = val;
   }
+}
+
+// Transposed exact-set bits: bit r of word r / 32 of row t is bit t of row r of `mask` (r: position in the Taylor list,
+// t: position in the kept list), so that a kept block finds the Taylor blocks that attend to its tokens.
+__device__ __forceinline__ void bwd_tmask(const uint32_t* __restrict__ mask, uint32_t* __restrict__ mask_t, int b, const Counts& cnt, int H) {
+  const int t = blockIdx.x, h = blockIdx.y, w = threadIdx.x;
+  const int T_max = cnt.T_max, mw = cnt.mask_words;
+  if (w >= mw || t >= T_max) return;
+  const long long bh = (long long)b * H + h;
+  uint32_t out = 0u;
+  if (t < cnt.b[b].T_new)
+    for (int i = 0; i < 32; ++i) {
+      const int r = 32 * w + i;
+      if (r < cnt.b[b].n_flat) out |= ((mask[(bh * T_max + r) * mw + (t >> 5)] >> (t & 31)) & 1u) << i;
+    }
+  mask_t[(bh * T_max + t) * mw + w] = out;
+}
+
+// The three in one launch, blockIdx.z = task * B + batch item, task: the n_lists lists of `ls`, then the fill, then (mask != null)
+// the transposed bits: none reads what another writes, and one after the other each waits for a nearly idle chip
+// (measured, a training step of 12 heads of 1564 tokens, three launches / one: 218 / 212 us).
+struct PrepArgs {
+  RowLists ls; int n_lists, B, H, Tn_pad, S_max;
+  const int4* btab; const float* nlse; const float* delta; float rq_scale;
+  float2* ybd_mean; float* bx_mean;
+  uint16_t* dk; uint16_t* dv; const float* rows_k; const float* rows_v; const int* kv_list;
+  const uint32_t* mask; uint32_t* mask_t;
+  Geometry geo; Counts cnt;
+};
+__global__ __launch_bounds__(128) void k_bwd_prepare(PrepArgs p) {
+  const int task = blockIdx.z / p.B, b = blockIdx.z % p.B;
+  if (task < p.n_lists) bwd_rows(p.ls, task, b, p.btab, p.nlse, p.rq_scale, p.delta, p.ybd_mean, p.bx_mean, p.cnt, p.H, p.Tn_pad, p.S_max);
+  else if (task == p.n_lists) bwd_fill(p.dk, p.dv, b, p.rows_k, p.rows_v, p.kv_list, p.btab, p.geo, p.cnt);
+  else bwd_tmask(p.mask, p.mask_t, b, p.cnt, p.H);
 }
 
 // ---- coarse residual (Alg. 1 Stage 1 and Stage 5): out += gamma * O_coarse[block], O_coarse = softmax(Qc Kc^T / sqrt D) Vc.
@@ -931,23 +963,6 @@ static hipError_t launch_bwd_coarse(const Problem& pr, const Workspace& ws, hipS
   return hipGetLastError();
 }
 
-// Transposed exact-set bits: bit r of word r / 32 of row t is bit t of row r of `mask` (r: position in the Taylor list,
-// t: position in the kept list), so that a kept block finds the Taylor blocks that attend to its tokens.
-__global__ __launch_bounds__(128) void k_bwd_tmask(const uint32_t* __restrict__ mask, uint32_t* __restrict__ mask_t,
-                                                  Counts cnt, int H) {
-  const int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z, w = threadIdx.x;
-  const int T_max = cnt.T_max, mw = cnt.mask_words;
-  if (w >= mw) return;
-  const long long bh = (long long)b * H + h;
-  uint32_t out = 0u;
-  if (t < cnt.b[b].T_new)
-    for (int i = 0; i < 32; ++i) {
-      const int r = 32 * w + i;
-      if (r < cnt.b[b].n_flat) out |= ((mask[(bh * T_max + r) * mw + (t >> 5)] >> (t & 31)) & 1u) << i;
-    }
-  mask_t[(bh * T_max + t) * mw + w] = out;
-}
-
 // Gradients of the gathered means, dKc and dVc (blockIdx.z = 2 * batch item + which): the partial sums of the `parts` parts of the
 // launch over the mean rows (0: there was none) plus, with the coarse residual, its gradient of the same mean (coarse, by
 // block id), into part 0.  One workgroup per gathered mean row.
@@ -1102,22 +1117,16 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
                        ws.olo, (const uint16_t*)d_out, ws.delta, ws.bwd_ctr, pr.geo, pr.cnt, S_max);
     ISA_BWD_CHECK();
   }
-  hipLaunchKernelGGL(k_bwd_fill, dim3(T_max, H, B), dim3(256), 0, st, (uint16_t*)dk, (uint16_t*)dv, resid ? ws.cdk : nullptr,
-                     resid ? ws.cdv : nullptr, kv_list, ws.btab, pr.geo, pr.cnt);
-  ISA_BWD_CHECK();
   const int gx = T_max > pr.Tn_pad ? T_max : pr.Tn_pad;
   const float cs = 1.4426950408889634f / sqrtf((float)MD);      // raw score -> log2 domain
   RowLists ls = {{kv_list, full_list, flat_list, flat_list}, {0, 1, 2, 2}, {nullptr, nullptr, nullptr, ws.rq},
                  {ws.ktab, ws.ftab, ws.ltab, ws.ltab}, {ws.ybd_kv, ws.ybd_full, ws.ybd_flat, ws.ybd_flatm}};
   // with exact sets the Taylor rows a second time, with q . Kc_0 in their exponent terms, for the launches that score them
   // against gathered means
-  hipLaunchKernelGGL(k_bwd_rows, dim3(gx, H, B * (ex ? 4 : 3)), dim3(128), 0, st, ls, B, ws.btab, ws.nlse, cs, ws.delta,
-                     ws.ybd_mean, ws.bx_mean, pr.cnt, H, pr.Tn_pad, S_max);
+  const PrepArgs pa = {ls, ex ? 4 : 3, B, H, pr.Tn_pad, S_max, ws.btab, ws.nlse, ws.delta, cs, ws.ybd_mean, ws.bx_mean, (uint16_t*)dk,
+                       (uint16_t*)dv, resid ? ws.cdk : nullptr, resid ? ws.cdv : nullptr, kv_list, exact_mask, ws.mask_t, pr.geo, pr.cnt};
+  hipLaunchKernelGGL(k_bwd_prepare, dim3(gx, H, B * (ex ? 6 : 4)), dim3(128), 0, st, pa);
   ISA_BWD_CHECK();
-  if (ex) {
-    hipLaunchKernelGGL(k_bwd_tmask, dim3(T_max, H, B), dim3(128), 0, st, exact_mask, ws.mask_t, pr.cnt, H);
-    ISA_BWD_CHECK();
-  }
 
   BwdArgs a;
   a.blk_start = ws.blk_start; a.blk_n = ws.blk_n;
