@@ -33,6 +33,8 @@ namespace isa {
 
 namespace {
 
+constexpr float FAST_MAX = 16777216.f;    // 2^24, log2 domain: a maximum below is rounded by half at most
+
 template <int D> constexpr int GROUP_LDS = 512 * D + 2 * 64 * 4;         // two stages of a K and a V tile, weights of mean tiles
 
 typedef short short4v __attribute__((ext_vector_type(4)));
@@ -84,13 +86,21 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 // One work item: 64 QT rows of one query block (QT = 2, block 64: of two neighbours in the list).  FULL32 evaluates the
 // products of fp32 numbers with fp32 matrix instructions instead of bf16 terms: slower, but infinities go through them
 // as through a multiplication (a term that is zero turns an infinity into NaN).  Returns whether this wave's results are
-// all finite; with FULL32 = false nothing is stored if some wave's are not, and the caller runs the item again.
+// all finite and its maxima in the range of the fast weights; with FULL32 = false nothing is stored if some wave's are not, and the
+// caller runs the item again.
+//
+// A weight is exp2 of the scaled score minus the scaled running maximum.  The fast form of bf16 tensors is one fma, whose
+// product is not rounded while the maximum is: all weights of a row share a factor of 2^r with |r| up to half a unit in the
+// last place of the maximum, which cancels in the result as long as it is a small number.  From FAST_MAX on the row is left to the
+// second pass; it and fp32 tensors (WIDE) keep the maximum unscaled and multiply the difference, so that the largest key's
+// exponent is 0 whatever the scores are (one more instruction per weight: clip of 8 heads of 128 channels, 5280 tokens, fp32,
+// 392 -> 394 us; the fast form of bf16 is bound by instruction issue).
 //
 // NG = 2: two groups of 4 waves work on the same rows, each with stages of its own, and take the tiles of the sequence in turn;
 // the second group hands its running maxima, sums and outputs to the first through LDS at the end.
 template <typename T, int D, int QT, bool FULL32, int NG>
 __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* const lds_all, int bhid, bool taylor, int slot) {
-  constexpr bool BF = sizeof(T) == 2;
+  constexpr bool BF = sizeof(T) == 2, WIDE = !BF || FULL32;
   constexpr int KTOK = BF ? 64 : 32;                   // tokens per tile; tiles of means hold 32
   constexpr int NT = D / 16;                           // 16-channel tiles
   constexpr int TILE = 128 * D;                        // bytes of a K (or V) tile, token or mean
@@ -230,7 +240,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   };
 
   f32x4 acc[NT][QT];                                   // element i: bf16: channel 16 ct + 4 g + i; fp32: see the store
-  float neg_m[QT], l_run[QT];                          // minus the running maximum (log2 domain, scaled); sums per lane
+  float neg_m[QT], l_run[QT];                          // minus the running maximum (scaled, log2 domain; WIDE: as the score is); sums per lane
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     neg_m[qt] = -M_INIT;
@@ -239,6 +249,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     for (int ct = 0; ct < NT; ++ct) acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   const float cscale = 1.4426950408889634f / sqrtf((float)D);
+  auto weight = [&](float diff) { return __builtin_amdgcn_exp2f(WIDE ? diff * cscale : diff); };      // of a difference in the unit of neg_m
 
   // ---- a half tile: 32 keys from row `r0` of the stage; `nk` of them real; wt: weights of a mean tile's 32 slots
   auto half = [&](const unsigned char* kb, const unsigned char* vb, const int r0, const int nk, const auto mean_c, const float* wt)
@@ -342,8 +353,8 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       mx[qt] = s[0][qt][0];
 #pragma unroll
       for (int e = 1; e < 7; e += 2) mx[qt] = fmaxf(fmaxf(mx[qt], s[e >> 2][qt][e & 3]), s[(e + 1) >> 2][qt][(e + 1) & 3]);
-      mx[qt] = fmaxf(mx[qt], s[1][qt][3]) * cscale;
-      raise |= __ballot(mx[qt] + neg_m[qt] > RESCALE_TAU);
+      mx[qt] = fmaxf(mx[qt], s[1][qt][3]) * (WIDE ? 1.f : cscale);
+      raise |= __ballot((mx[qt] + neg_m[qt]) * (WIDE ? cscale : 1.f) > RESCALE_TAU);
     }
     if (raise != 0ull) {
 #pragma unroll
@@ -351,7 +362,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         float m = fmaxf(mx[qt], __shfl_xor(mx[qt], 16, 64));
         m = fmaxf(m, __shfl_xor(m, 32, 64));
         m = fmaxf(m, -neg_m[qt]);
-        const float alpha = __builtin_amdgcn_exp2f(-neg_m[qt] - m);
+        const float alpha = weight(-neg_m[qt] - m);
         neg_m[qt] = -m;
         l_run[qt] *= alpha;
 #pragma unroll
@@ -365,7 +376,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          p[qt][4 * kt + i] = __builtin_amdgcn_exp2f(fmaf(s[kt][qt][i], cscale, neg_m[qt]));
+          p[qt][4 * kt + i] = weight(WIDE ? s[kt][qt][i] + neg_m[qt] : fmaf(s[kt][qt][i], cscale, neg_m[qt]));
     if constexpr (mean) {                              // Eq. 4: a mean key weighs its block's token count
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt)
@@ -522,7 +533,8 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       for (int qt = 0; qt < QT; ++qt) {
         const float other = part[(qt * (4 * NT + 2)) * 64];
         const float nm = fminf(neg_m[qt], other);      // minus the larger maximum
-        const float mine = __builtin_amdgcn_exp2f(nm - neg_m[qt]), theirs = __builtin_amdgcn_exp2f(nm - other);
+        const float mine = weight(nm - neg_m[qt]), theirs = weight(nm - other);
+        neg_m[qt] = nm;
         l_run[qt] = l_run[qt] * mine + part[(qt * (4 * NT + 2) + 1) * 64] * theirs;
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct)
@@ -542,11 +554,13 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     inv[qt] = 1.0f / l;
-    if (grp == 0 && row0 + 16 * qt + r16 < n_q)
+    if (grp == 0 && row0 + 16 * qt + r16 < n_q) {
+      if (!WIDE) ok = ok && fabsf(neg_m[qt]) < FAST_MAX;
 #pragma unroll
       for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
         for (int i = 0; i < 4; ++i) ok = ok && fabsf(acc[ct][qt][i] * inv[qt]) < INFINITY;
+    }
   }
   if constexpr (BF && !FULL32)
     if (__syncthreads_or(!ok)) return false;

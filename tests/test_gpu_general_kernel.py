@@ -114,3 +114,36 @@ def test_infinities_pass_as_in_plain_arithmetic(I, shape, H):
         got[:, 3] = want[:, 3]
         emax, emean = err_stats(got, want)
         assert emax <= tol_max and emean <= tol_mean, (h, emax, emean)
+
+
+# scores far outside the range in which a softmax weight is usually formed: around +-2e10 and 7e11 (a rounded maximum is off by
+# more there than exp2 can express).  Only channel 0 is used, with values that make every
+# score exact in fp32; the weights are then 0 or 1 (shared evenly between keys that tie).
+@pytest.mark.parametrize("exponent,negative", [(12, False), (20, False), (25, False)], ids=["1e8", "2e10", "7e11"])
+@pytest.mark.parametrize("H", [2, 520], ids=["narrow", "wide"])
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_range_of_the_scores(I, shape, H, exponent, negative):
+    block = shape[2]
+    for exact_frac in (0.0, 0.4):
+        wl = _wl(shape, H, (1, 1, 4 * block + 17), (((1, 1, block),),), keep_ratio=1.0, full_frac=0.0, exact_frac=exact_frac, seed=781)
+        n = wl.tokens(0)
+        g = torch.Generator().manual_seed(wl.seed + exponent)
+        Q, K = (torch.zeros((1, H, n, wl.D), dtype=W.torch_dtype(wl.dtype)) for _ in range(2))
+        V = torch.randn((1, H, n, wl.D), generator=g).to(Q.dtype)
+        Q[..., 0] = ((128 + torch.arange(n) % 128) * 2.0 ** exponent).to(Q.dtype)
+        K[..., 0] = (-torch.randint(64, 128, (1, H, n), generator=g) if negative else torch.randint(-127, 128, (1, H, n), generator=g)).to(K.dtype)
+        if not negative:
+            Q[:, :, ::3] *= -1
+        q, k, v = Q.cuda(), K.cuda(), V.cuda()
+        pr = problem_of(wl)
+        ws = I.new_workspace(pr)
+        out, dense = torch.empty_like(q), torch.empty_like(q)
+        I.isa_attention(pr, q, k, v, out, ws)
+        I.isa_dense_attention(pr, q, k, v, dense, ws)
+        torch.cuda.synchronize()
+        for h in sorted({0, H - 1}):
+            Qh, Kh, Vh = f64(Q[0, h]), f64(K[0, h]), f64(V[0, h])
+            want, _ = O.isa_attention(Qh, Kh, Vh, wl.seg_len(0), wl.block, 1.0, 0.0, exact_frac)
+            for name, x, y in (("taylor", out, want), ("dense", dense, O.dense_attention(Qh, Kh, Vh))):
+                emax, emean = err_stats(f64(x[0, h]), y)
+                assert emax <= TOL[wl.dtype][0] and emean <= TOL[wl.dtype][1], (name, exact_frac, h, emax, emean)
