@@ -93,8 +93,9 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 // product is not rounded while the maximum is: all weights of a row share a factor of 2^r with |r| up to half a unit in the
 // last place of the maximum, which cancels in the result as long as it is a small number.  From FAST_MAX on the row is left to the
 // second pass; it and fp32 tensors (WIDE) keep the maximum unscaled and multiply the difference, so that the largest key's
-// exponent is 0 whatever the scores are (one more instruction per weight: clip of 8 heads of 128 channels, 5280 tokens, fp32,
-// 392 -> 394 us; the fast form of bf16 is bound by instruction issue).
+// exponent is 0 whatever the scores are, and start it at -infinity, M_INIT being a score that a row may lie below.  One more
+// instruction per weight and two per half tile: clip of 8 heads of 128 channels, 5280 tokens, fp32, 390 -> 393 us; the fast form
+// of bf16 is bound by instruction issue.
 //
 // NG = 2: two groups of 4 waves work on the same rows, each with stages of its own, and take the tiles of the sequence in turn;
 // the second group hands its running maxima, sums and outputs to the first through LDS at the end.
@@ -240,10 +241,14 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   };
 
   f32x4 acc[NT][QT];                                   // element i: bf16: channel 16 ct + 4 g + i; fp32: see the store
+  constexpr float NONE = WIDE ? INFINITY : -M_INIT;    // minus the maximum of no score
   float neg_m[QT], l_run[QT];                          // minus the running maximum (scaled, log2 domain; WIDE: as the score is); sums per lane
+  // what is added to a score before its weight is formed: while a WIDE row has seen nothing but masked slots, 0, so that their
+  // weights are exp2(-infinity), not of a difference of infinities
+  auto shift = [&](float nm) { return WIDE && nm == INFINITY ? 0.f : nm; };
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
-    neg_m[qt] = -M_INIT;
+    neg_m[qt] = NONE;
     l_run[qt] = 0.f;
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -362,7 +367,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         float m = fmaxf(mx[qt], __shfl_xor(mx[qt], 16, 64));
         m = fmaxf(m, __shfl_xor(m, 32, 64));
         m = fmaxf(m, -neg_m[qt]);
-        const float alpha = weight(-neg_m[qt] - m);
+        const float alpha = weight(shift(-m) - neg_m[qt]);
         neg_m[qt] = -m;
         l_run[qt] *= alpha;
 #pragma unroll
@@ -371,12 +376,14 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     }
     float p[QT][8];                                    // element 4 kt + i
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt)
+    for (int qt = 0; qt < QT; ++qt) {
+      const float sh = shift(neg_m[qt]);
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          p[qt][4 * kt + i] = weight(WIDE ? s[kt][qt][i] + neg_m[qt] : fmaf(s[kt][qt][i], cscale, neg_m[qt]));
+          p[qt][4 * kt + i] = weight(WIDE ? s[kt][qt][i] + sh : fmaf(s[kt][qt][i], cscale, sh));
+    }
     if constexpr (mean) {                              // Eq. 4: a mean key weighs its block's token count
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt)
@@ -533,7 +540,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       for (int qt = 0; qt < QT; ++qt) {
         const float other = part[(qt * (4 * NT + 2)) * 64];
         const float nm = fminf(neg_m[qt], other);      // minus the larger maximum
-        const float mine = weight(nm - neg_m[qt]), theirs = weight(nm - other);
+        const float mine = weight(shift(nm) - neg_m[qt]), theirs = weight(shift(nm) - other);
         neg_m[qt] = nm;
         l_run[qt] = l_run[qt] * mine + part[(qt * (4 * NT + 2) + 1) * 64] * theirs;
 #pragma unroll

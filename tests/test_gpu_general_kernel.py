@@ -117,9 +117,9 @@ def test_infinities_pass_as_in_plain_arithmetic(I, shape, H):
 
 
 # scores far outside the range in which a softmax weight is usually formed: around +-2e10 and 7e11 (a rounded maximum is off by
-# more there than exp2 can express).  Only channel 0 is used, with values that make every
+# more there than exp2 can express), and rows whose scores are all below -1e31.  Only channel 0 is used, with values that make every
 # score exact in fp32; the weights are then 0 or 1 (shared evenly between keys that tie).
-@pytest.mark.parametrize("exponent,negative", [(12, False), (20, False), (25, False)], ids=["1e8", "2e10", "7e11"])
+@pytest.mark.parametrize("exponent,negative", [(12, False), (20, False), (25, False), (90, True)], ids=["1e8", "2e10", "7e11", "below_-1e31"])
 @pytest.mark.parametrize("H", [2, 520], ids=["narrow", "wide"])
 @pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
 def test_range_of_the_scores(I, shape, H, exponent, negative):
