@@ -93,9 +93,10 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 // product is not rounded while the maximum is: all weights of a row share a factor of 2^r with |r| up to half a unit in the
 // last place of the maximum, which cancels in the result as long as it is a small number.  From FAST_MAX on the row is left to the
 // second pass; it and fp32 tensors (WIDE) keep the maximum unscaled and multiply the difference, so that the largest key's
-// exponent is 0 whatever the scores are, and start it at -infinity, M_INIT being a score that a row may lie below.  One more
-// instruction per weight and two per half tile: clip of 8 heads of 128 channels, 5280 tokens, fp32, 390 -> 393 us; the fast form
-// of bf16 is bound by instruction issue.
+// exponent is the same whatever the scores are, and start it at -infinity, M_INIT being a score that a row may lie below.  Their
+// weights carry a factor of 2^-tau, which makes them at most 1: 2^tau times a value near the largest number is none.  One more
+// instruction per weight and two per half tile: clip of 8 heads of 128 channels, 5280 tokens, fp32, 390 -> 390 us, 24 heads of 64
+// channels 405 -> 408; the fast form of bf16 is bound by instruction issue.
 //
 // NG = 2: two groups of 4 waves work on the same rows, each with stages of its own, and take the tiles of the sequence in turn;
 // the second group hands its running maxima, sums and outputs to the first through LDS at the end.
@@ -254,7 +255,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     for (int ct = 0; ct < NT; ++ct) acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   const float cscale = 1.4426950408889634f / sqrtf((float)D);
-  auto weight = [&](float diff) { return __builtin_amdgcn_exp2f(WIDE ? diff * cscale : diff); };      // of a difference in the unit of neg_m
+  auto factor = [&](float diff) { return __builtin_amdgcn_exp2f(WIDE ? diff * cscale : diff); };      // between two maxima, from their difference
 
   // ---- a half tile: 32 keys from row `r0` of the stage; `nk` of them real; wt: weights of a mean tile's 32 slots
   auto half = [&](const unsigned char* kb, const unsigned char* vb, const int r0, const int nk, const auto mean_c, const float* wt)
@@ -367,7 +368,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         float m = fmaxf(mx[qt], __shfl_xor(mx[qt], 16, 64));
         m = fmaxf(m, __shfl_xor(m, 32, 64));
         m = fmaxf(m, -neg_m[qt]);
-        const float alpha = weight(shift(-m) - neg_m[qt]);
+        const float alpha = factor(shift(-m) - neg_m[qt]);
         neg_m[qt] = -m;
         l_run[qt] *= alpha;
 #pragma unroll
@@ -382,7 +383,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          p[qt][4 * kt + i] = weight(WIDE ? s[kt][qt][i] + sh : fmaf(s[kt][qt][i], cscale, sh));
+          p[qt][4 * kt + i] = __builtin_amdgcn_exp2f(WIDE ? fmaf(s[kt][qt][i] + sh, cscale, -RESCALE_TAU) : fmaf(s[kt][qt][i], cscale, sh));
     }
     if constexpr (mean) {                              // Eq. 4: a mean key weighs its block's token count
 #pragma unroll
@@ -540,7 +541,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       for (int qt = 0; qt < QT; ++qt) {
         const float other = part[(qt * (4 * NT + 2)) * 64];
         const float nm = fminf(neg_m[qt], other);      // minus the larger maximum
-        const float mine = weight(shift(nm) - neg_m[qt]), theirs = weight(shift(nm) - other);
+        const float mine = factor(shift(nm) - neg_m[qt]), theirs = factor(shift(nm) - other);
         neg_m[qt] = nm;
         l_run[qt] = l_run[qt] * mine + part[(qt * (4 * NT + 2) + 1) * 64] * theirs;
 #pragma unroll

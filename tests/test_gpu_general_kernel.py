@@ -147,3 +147,23 @@ def test_range_of_the_scores(I, shape, H, exponent, negative):
             for name, x, y in (("taylor", out, want), ("dense", dense, O.dense_attention(Qh, Kh, Vh))):
                 emax, emean = err_stats(f64(x[0, h]), y)
                 assert emax <= TOL[wl.dtype][0] and emean <= TOL[wl.dtype][1], (name, exact_frac, h, emax, emean)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_values_near_the_largest_number(I, shape):
+    """Scores that rise slowly along the keys (by 7.5 powers of two in all, so that a maximum raised only in steps falls behind) beside
+    values of 2^120: the sums of at most 20 such values of weight 1 are numbers, whatever weights the kernel forms."""
+    n, D = 200, shape[1]
+    wl = _wl(shape, 2, (1, 1, n), ((),), seed=791)
+    Q, K = (torch.zeros((1, 2, n, D), dtype=W.torch_dtype(wl.dtype)) for _ in range(2))
+    V = torch.randn((1, 2, n, D), generator=torch.Generator().manual_seed(wl.seed)).clamp(-4, 4).to(Q.dtype)
+    Q[..., 0] = 1.0
+    K[..., 0] = (7.5 * np.log(2.0) * D ** 0.5 * torch.arange(n) / n).to(K.dtype)
+    q, k, v = Q.cuda(), K.cuda(), (V.double() * 2.0 ** 120).to(V.dtype).cuda()
+    out = torch.empty_like(q)
+    pr = problem_of(wl)
+    I.isa_dense_attention(pr, q, k, v, out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    for h in range(2):
+        emax, emean = err_stats(f64(out[0, h]) / 2.0 ** 120, O.dense_attention(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h])))
+        assert emax <= TOL[wl.dtype][0] and emean <= TOL[wl.dtype][1], (h, emax, emean)
