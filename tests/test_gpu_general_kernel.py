@@ -167,3 +167,20 @@ def test_values_near_the_largest_number(I, shape):
     for h in range(2):
         emax, emean = err_stats(f64(out[0, h]) / 2.0 ** 120, O.dense_attention(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h])))
         assert emax <= TOL[wl.dtype][0] and emean <= TOL[wl.dtype][1], (h, emax, emean)
+
+
+@pytest.mark.parametrize("D,bound", [(64, 1.14e-6), (128, 1.06e-6)])
+def test_fp32_scores_no_further_off_than_in_scalar_arithmetic(I, D, bound):
+    """Queries of norm up to 4 sqrt(D): the distance from 64 bits is that of the scores' sums.  The bounds are what a kernel with
+    four partial sums per score, in scalar arithmetic, showed on the same inputs."""
+    H, S = 8, 1000
+    g = torch.Generator().manual_seed(797)
+    q, k, v = (torch.randn((1, H, S, D), generator=g) for _ in range(3))
+    q = q * (0.5 * 8.0 ** torch.rand((1, H, S, 1), generator=g))
+    pr = I.Problem(H=H, D=D, dtype="f32", block=D, seg_len=[[S]], keep_ratio=1.0, full_frac=1.0)
+    out = torch.empty((1, H, S, D), device="cuda")
+    I.isa_dense_attention(pr, q.cuda(), k.cuda(), v.cuda(), out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    want = np.stack([O.dense_attention(f64(q[0, h]), f64(k[0, h]), f64(v[0, h])) for h in range(H)])
+    rel = np.linalg.norm(f64(out[0]) - want) / np.linalg.norm(want)
+    assert rel <= bound, rel
