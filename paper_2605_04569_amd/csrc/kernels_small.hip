@@ -427,8 +427,8 @@ struct SelectSmall {
 };
 
 template <bool SMALL>
-__global__ __launch_bounds__(SEL_THREADS) void k_select(const float* __restrict__ s_ctx, const float* __restrict__ sharp,
-                                                        int* __restrict__ kv_list, int* __restrict__ full_list,
+__global__ __launch_bounds__(SEL_THREADS) void k_select(const float* s_ctx, const float* __restrict__ sharp,      // s_ctx and kv_list: x has them too
+                                                        int* kv_list, int* __restrict__ full_list,
                                                         int* __restrict__ flat_list, Counts cnt, int H, SelectSmall x) {
   extern __shared__ float sm[];
   float* sc = sm;                                   // [T_max]
