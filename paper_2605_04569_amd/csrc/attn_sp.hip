@@ -879,14 +879,17 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
     // every such launch), one per workgroup, with an eighth more workgroups than items and one round of the chip to spare.  The
     // last 64 items run as four key ranges each, so that the launch ends within a quarter of an item of the ideal (whole items to
     // the end: as much lost in the last round as gained, at 40 rounds).  Dense attention at
-    // 480p (40 rounds) 71.1 -> 68.9 ms, 480p at the paper's ratios (20 rounds of the exact branch) 22.7 -> 22.25.
+    // 480p (40 rounds) 71.1 -> 68.9 ms, 480p at the paper's ratios (20 rounds of the exact branch) 22.7 -> 22.25.  Where some batch
+    // item's list is too short to be cut, the items stay whole, from 64 rounds on (dense attention over 480p beside 1000 tokens: equal
+    // shares 69.2 to 70.6 ms on two boxes, from the counter 68.0 to 68.7).
     m.long_ctr = nullptr; m.n_long_all = 0; m.ctr_whole = 0;
     int n_merge = N_XCD * m.n_split;
-    if (ss == 0 && m.n_long >= 8 * cus && min_list >= 16) {
+    const bool cut = min_list >= 16;
+    if (ss == 0 && m.n_long >= (cut ? 8 : 64) * cus) {
       const int all = (int)((long long)pr.p.B * pr.p.H * sf);
       m.long_ctr = ws.taylor_ctr + 1;
-      m.parts = 4;
-      n_merge = SPLIT_MAX_SUB / m.parts;
+      m.parts = cut ? 4 : 1;
+      n_merge = cut ? SPLIT_MAX_SUB / m.parts : 0;
       m.ctr_whole = all - n_merge;
       m.n_long_all = all + n_merge * (m.parts - 1);
       m.n_split = 0;

@@ -106,3 +106,25 @@ def test_counted_items_backward(I):
         for got, want in zip(grads, OB.dense_attention_bwd(*(f64(t[0, h]) for t in (Q, K, V, dO)))):
             d = np.abs(f64(got[0, h]) - want) / np.abs(want).max()
             assert d.max() <= TOL_MAX_REL and d.mean() <= TOL_MEAN_REL, (h, d.max(), d.mean())
+
+
+def test_counted_items_whole(I):
+    """64 rounds of long items beside a batch item too short to be cut: whole items from the counter, those of the short item among them."""
+    import torch
+    from oracle import isa_oracle as O
+    from test_gpu_parity import TOL
+    from util import err_stats, f64
+    H, lens = 256, (128 * 63 + 5, 100)
+    assert 2 * H * 32 // 8 >= 64 * 32                                                   # the premise
+    g = torch.Generator(device="cuda").manual_seed(897)
+    q, k, v = (torch.randn((2, H, lens[0], 128), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    pr = I.Problem(H=H, D=128, dtype="bf16", block=128, seg_len=[[n] for n in lens], keep_ratio=1.0, full_frac=1.0)
+    out = torch.full_like(q, float("nan"))
+    I.isa_dense_attention(pr, q, k, v, out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        assert torch.isfinite(out[b, :, :n]).all() and torch.isnan(out[b, :, n:]).all()
+        for h in (0, 1, 130, H - 1):
+            rows = slice(0, n, 97 if b == 0 else 1)
+            emax, emean = err_stats(f64(out[b, h, :n][rows]), O.dense_attention(f64(q[b, h, :n][rows]), f64(k[b, h, :n]), f64(v[b, h, :n])))
+            assert emax <= TOL["bf16"][0] and emean <= TOL["bf16"][1], (b, h, emax, emean)
