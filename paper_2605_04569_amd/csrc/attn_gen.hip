@@ -23,6 +23,8 @@
 // instruction was slower and not exact) beside 2 matrix instructions; counters of the dense launch: issue port busy
 // 85 % of the cycles, matrix pipe 38 %, no LDS bank conflicts.  Whole call 11.6 -> 0.73 ms against a kernel of one
 // row per four lanes in scalar arithmetic (25 -> 400 TFLOP/s); fp32, 8 heads of 128 channels, 5280 tokens: 1.89 -> 0.39 ms.
+#include <math.h>
+
 #include <type_traits>
 
 #include "attn_mfma.h"
@@ -647,20 +649,35 @@ hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st)
   GenArgs ga;
   ga.a = a;
   int n_long = 0, n_taylor = 0;
+  double set_share = 0.0;                              // of a long item's tokens, those a Taylor item reads for its exact set
   for (int b = 0; b < pr.p.B; ++b) {
     const BatchCounts& c = pr.cnt.b[b];
+    if (!a.dense && a.exact_mask && c.n_flat > 0) set_share = fmax(set_share, (double)c.k_exact / c.T_new);
     const int f = a.dense ? c.T : c.n_full, t = a.dense ? 0 : c.n_flat;
     n_long = f > n_long ? f : n_long;
     n_taylor = t > n_taylor ? t : n_taylor;
   }
   const long long bh = (long long)pr.p.B * pr.p.H;
+  // What a launch has to fill the chip with: its long items, and its Taylor items at what one of them takes of a long one's time (fitted
+  // to the measurements below), or these alone at full count where there is no long one.
+  const bool d64 = pr.p.D == 64;
+  const double chip = (double)N_XCD * cus_per_xcd();
+  auto items = [&](int n, int rows) { return (double)(bh * (pr.p.block >= rows ? n * (pr.p.block / rows) : (n + 1) / 2)); };
+  auto load = [&](int rows) {
+    return n_long > 0 ? items(n_long, rows) + items(n_taylor, rows) * ((d64 ? 1.0 / 32 : 1.0 / 14) + set_share) : items(n_taylor, rows);
+  };
   // bf16: 128 rows per workgroup read every LDS fragment once for two query tiles, but need the chip full of them: measured
   // at 15 600 tokens, keep 0.5, full 0.25, blocks of 64, QT = 2 / 1: D = 64: 24 heads (744 long items of 128 rows) 728 /
   // 833 us, dense over half as many tokens, 8 heads (488) 318 / 343, 12 heads (372) 538 / 480, 2 heads (62) 412 / 315; D = 128:
-  // 24 heads 1288 / 1597, 12 heads (372) 755 / 816, 8 heads (248) 576 / 569, 2 heads 553 / 408.  fp32: a fragment feeds
+  // 24 heads 1288 / 1597, 12 heads (372) 755 / 816, 8 heads (248) 576 / 569, 2 heads 553 / 408.  Fewer long items beside more Taylor
+  // items (long + Taylor of 128 rows): D = 64: 24 heads, full 0.15 (456 + 2496) 539 / 578, full 0.1 (312 + 2640) 523 / 472, 16 heads, full 0.15
+  // (304 + 1656) 507 / 455, 40 heads of 32 768 tokens, full 0.02 (240 + 10 040) 1332 / 1634; D = 128: 16 heads, full 0.1 (208 + 1760) 594 /
+  // 633, 24 heads, full 0.05 (168 + 2784) 673 / 721, full 0.02 (72 + 2880) 677 / 574.  Taylor items alone: D = 64 24, 4, 2 heads (2928, 488, 244)
+  // 186 / 226, 67 / 73, 61 / 58; D = 128 24, 2 heads 351 / 465, 82 / 79.  With exact sets a pair of blocks of 64 reads both blocks' sets, which
+  // Taylor items alone do not make up for at D = 64: 24, 8 heads 435 / 396, 192 / 171 (D = 128: 797 / 814, 302 / 305).  fp32: a fragment feeds
   // four times as many matrix instructions of twice the length, and more waves always won.
-  const long long long128 = bh * (pr.p.block == 128 ? n_long : (n_long + 1) / 2);
-  const bool two = pr.p.dtype == ISA_BF16 && long128 >= (long long)N_XCD * cus_per_xcd() * (pr.p.D == 64 ? 7 : 5) / 4;
+  const bool pair_of_sets = n_long == 0 && set_share > 0.0 && d64 && pr.p.block == 64;
+  const bool two = pr.p.dtype == ISA_BF16 && !pair_of_sets && load(128) >= chip * (d64 ? 7 : 5) / 4;
   const int rows = two ? 128 : 64;
   auto slots = [&](int n) { return pr.p.block >= rows ? n * (pr.p.block / rows) : (n + 1) / 2; };
   ga.slots_long = slots(n_long);
@@ -670,11 +687,14 @@ hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st)
   if (ga.slots_long == 0) ga.slots_long = 1;           // divisors in the kernel; a branch without work gets no workgroups
   if (ga.slots_taylor == 0) ga.slots_taylor = 1;
   const dim3 grid((unsigned)(N_XCD * (ga.per_xcd_long + ga.per_xcd_taylor)));
-  // Two groups per workgroup while the long items leave most SIMDs with one or two waves.  Measured, one / two groups, whole call: D = 64
-  // (two such workgroups fit a compute unit), 2, 4, 6, 8 heads of 15 600 tokens (122, 244, 366, 488 long items) 311 / 238, 317 / 243,
-  // 341 / 315, 347 / 349 us; D = 128 (one fits), 2, 4 heads (122, 244) 404 / 317, 420 / 397, fp32, 12 heads of 5280 tokens (264)
-  // 668 / 733; 5 heads of 990 tokens, D = 64: 44.5 / 41.3.
-  const bool groups = !two && bh * ga.slots_long <= (long long)N_XCD * cus_per_xcd() * (pr.p.D == 64 ? 7 : 4) / 4;
+  // Two groups per workgroup while the launch leaves most SIMDs with one or two waves beside a long item.  Measured, one / two groups,
+  // whole call: D = 64 (two such workgroups fit a compute unit), 2, 4, 6, 8 heads of 15 600 tokens (122, 244, 366, 488 long items of 64 rows) 311 /
+  // 238, 317 / 243, 341 / 315, 347 / 349 us; D = 128 (one fits), 2, 4 heads (122, 244) 404 / 317, 420 / 397, fp32, 12 heads of 5280 tokens
+  // (264) 668 / 733; 5 heads of 990 tokens, D = 64: 44.5 / 41.3.  Fewer long items beside more Taylor items (long + Taylor): D = 64: 16 heads (208 +
+  // 3696, 400 + 3504) 325 / 295, 356 / 381, 24 heads (120 + 5736, 312 + 5544) 337 / 328, 371 / 419; D = 128: 8 heads (104 + 1848, 200 + 1752) 411 /
+  // 356, 416 / 458, 16 heads (80 + 3824) 431 / 501, fp32, 16 heads (224 + 1120) 432 / 393, 24 heads (240 + 1776) 446 / 469.  Taylor items
+  // alone are too short to be shared: 24 heads 226 / 266, D = 128 465 / 595, 8 heads in fp32 60 / 71 (D = 64, 2 heads: 58 / 58).
+  const bool groups = !two && n_long > 0 && items(n_long, 64) <= chip * (d64 ? 7 : 4) / 4 && load(64) <= chip * (d64 ? 1.75 : 1.21);
 #define ISA_GEN(T, D, QT, NG) hipLaunchKernelGGL((k_attn_gen<T, D, QT, NG>), grid, dim3(256 * NG), 0, st, ga)
   if (pr.p.dtype == ISA_BF16) {
     if (pr.p.D == 128) { if (two) ISA_GEN(uint16_t, 128, 2, 1); else if (groups) ISA_GEN(uint16_t, 128, 1, 2); else ISA_GEN(uint16_t, 128, 1, 1); }

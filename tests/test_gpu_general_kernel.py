@@ -48,6 +48,18 @@ def test_wide_workgroups(I, shape, exact_frac):
     check_end_to_end(I, wl, *gen(wl), heads=[0, 7, 150, 299])
 
 
+# no long items at all: 128-row workgroups of Taylor blocks (64-row ones with exact sets at D = 64), the same odd lists
+@pytest.mark.parametrize("exact_frac", [0.0, 0.25])
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] == "bf16"], ids=[i for i in SHAPE_IDS if i[:4] == "bf16"])
+def test_wide_workgroups_of_taylor_blocks(I, shape, exact_frac):
+    dtype, D, block = shape
+    wl = _wl(shape, 300, (1, 1, 5 * block + 40), (((1, 1, 4 * block + 9),), ((1, 1, 2 * block),)), B=2, keep_ratio=0.6, full_frac=0.0,
+             exact_frac=exact_frac, seed=733)
+    c = [I.isa_get_counts(problem_of(wl), b) for b in range(2)]
+    assert c[0]["n_flat"] % 2 == 1 and c[0]["n_full"] == c[1]["n_full"] == 0 and 600 * (c[0]["n_flat"] // 2) >= 448       # the premise
+    check_end_to_end(I, wl, *gen(wl), heads=[0, 7, 150, 299])
+
+
 # 1, 2 and 3 tiles for the two groups of a workgroup to share (fp32: 32 tokens each), token tiles followed by tiles of means
 @pytest.mark.parametrize("tokens", [32, 33, 64, 65, 96])
 @pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
