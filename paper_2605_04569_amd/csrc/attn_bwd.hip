@@ -11,8 +11,8 @@
 // means (kernels at the end of this file), which enters the big launches through their epilogues.
 //
 // One kernel body does these products (dK and dV have a kernel of their own, attn_bwd_kv.hip).  A workgroup (8 waves)
-// keeps 2 x 128 "stationary" rows in registers and streams 64-row tiles of the other side through LDS; per tile it forms T1 = Y1 X1^T (the scores) and, where dS is needed,
-// T2 = Y2 X2^T (dP), turns them into W = P or dS in registers and accumulates acc^T += Yt W^T, where Yt is the
+// keeps 2 x 128 "stationary" rows in registers and streams 64-row tiles of the other side through LDS; per tile it forms
+// T1 = Y1 X1^T (the scores) and, for dS (all but dVc), T2 = Y2 X2^T (dP), turns them into W = P or dS in registers and accumulates acc^T += Yt W^T, where Yt is the
 // transpose of a streamed tile: its fragments are read out of the row-major tile in LDS with ds_read_b64_tr_b16, in the
 // key order of the 16x16x32 accumulators, so no transposed copy of any tensor exists.  The three launches:
 //     dQ, exact branch : stationary (Q, dO) of the full-attention blocks,  streamed K, V of the kept tokens (Yt = K^T)
@@ -70,7 +70,7 @@ struct BwdStream {
                                               // y1's (the mean keys without the subtraction of Kc_0); null otherwise
   const int4* tab;                            // token tiles: [bh][T_max] {token offset, tokens, block id} per list entry; null: mean tiles
   const float2* ybd;                          // per tile of 64 streamed positions: 64 additive exponent terms (-inf: masked), then 64 minus-deltas
-  int kind;                                   // token tiles: list entries = 0 kept blocks, 1 full-attention blocks, 2 Taylor blocks
+  bool flat;                                  // token tiles: the list's entries are the Taylor blocks, otherwise the kept blocks
   int masked;                                 // exact sets (Alg. 2 Part A): 0 none; 1 token tiles of the entries whose bit is set for the
                                               // stationary entry, others skipped; 2 mean tiles, positions whose bit is set are masked;
                                               // 3 (mean rows stationary) entries whose bit is set for the lane's row are masked
@@ -80,7 +80,8 @@ struct BwdArgs {
   // stationary rows: token tensors (strides of `geo`, blocks taken from `stat_list`) or gathered mean rows [bh][Tn_pad][128]
   const uint16_t* x1; const uint16_t* x2;
   const int* stat_list;                       // [bh][T_max] block ids; unused for mean rows
-  const float* bx; const float* dx;           // per stationary row: additive exponent term / delta ([bh][S_max] or [bh][Tn_pad]); null = 0
+  bool stat_flat;                             // they are the Taylor blocks, otherwise the full-attention blocks
+  const float* bx; const float* dx;           // per stationary row: additive exponent term / delta ([bh][S_max] or [bh][Tn_pad]; dx null: 0)
   // EX == 2 only (stationary Taylor queries; the streamed gathered mean keys are stored minus the mean key of block 0):
   // rx [bh][S_max] = q . Kc_0 of every stationary row in raw score units, added to its scores against mean tiles
   const float* rx;
@@ -91,13 +92,12 @@ struct BwdArgs {
   const uint32_t* bits; int mask_words;
   // outputs
   uint16_t* out_bf; float* out_f32;           // token rows (bf16, strides of `geo`) or mean rows (fp32 [bh][Tn_pad][128])
-  const float* add_rows;                      // null, or fp32 rows of 128 of which one, divided by the block's tokens, is added to every row:
-  int add_by_block;                           //   0: [bh][Tn_pad] indexed by the stationary entry; 1: [bh][T_max] indexed by its block id
+  const float* add_rows;                      // token rows: null, or fp32 [bh][T_max][128] by block id: a row's share, divided by the block's
+                                              // tokens, is added
   float oscale;
   const int* blk_start; const int* blk_n;
   Geometry geo; Counts cnt;
   int Tn_pad, S_max;
-  int stat_kind;                              // token rows: 0 full-attention blocks, 1 Taylor blocks, 2 kept blocks
   int items;                                  // work items (pairs of stationary blocks) per (batch, head) in this launch
   // mean rows only: every item runs as `parts` workgroups, each over its share of the streamed entries, and writes its
   // partial sums to out_f32 + part * part_stride (k_bwd_mean_sums adds them up)
@@ -114,12 +114,13 @@ struct BwdArgs {
   int dyn_whole, dyn_total;                   // the first dyn_whole of them are whole items, the others tail_parts parts of an item each
 };
 
-// SM: stationary rows are block means; T2: W = P * (T2 - delta), else W = P; EX: exact-set bits are in play (1: whole
-// tiles are masked or not; 2: also single positions of a tile of gathered means).
-// YD: the streamed rows carry deltas of their own (they are queries) and the stationary rows none; otherwise the other
-// way round.
-template <bool SM, bool T2, int EX, bool YD>
+// SM: stationary rows are block means and the streamed rows are queries, which carry the deltas; otherwise the stationary rows
+// are queries.  T2: W = P * (T2 - delta), else (dVc) W = P.  EX: exact-set bits are in play: 1 (SM) stationary rows masked for a
+// streamed block; 2 (queries) streamed tiles masked or not for a stationary block, and single positions of a tile of gathered means.
+template <bool SM, bool T2, int EX>
 __device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, const int wg, float* const out_f32, const float oscale) {
+  static_assert(SM ? EX == 0 || EX == 1 : T2 && (EX == 0 || EX == 2), "what the three launches use");
+  constexpr bool YD = SM && T2;                              // minus-deltas of the streamed rows start T2
   constexpr int STG = EX == 2 ? STAGE + K_TILE : STAGE;      // EX == 2: a third tile per stage (see BwdStream::y3)
   // Workgroup ids go round-robin over the 8 XCDs: XCD x has its range of the items of all (batch, head)s (xcd_first, head_at) and
   // works through it one head after the other, so that the workgroups that run together on an XCD (and share its L2)
@@ -171,7 +172,7 @@ __device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, 
   const int T_new = a.cnt.b[b].T_new, n_full = a.cnt.b[b].n_full, n_flat = a.cnt.b[b].n_flat;
   const int T_max = a.geo.T_max;
   const long long bh = bhid;
-  const int n_stat = SM ? (T_new + 127) / 128 : (a.stat_kind == 0 ? n_full : a.stat_kind == 1 ? n_flat : T_new);
+  const int n_stat = SM ? (T_new + 127) / 128 : a.stat_flat ? n_flat : n_full;
   if (2 * item >= n_stat) return;
   const long long tbase = (long long)b * a.geo.stride_b + (long long)h * a.geo.stride_h;
 
@@ -201,7 +202,7 @@ __device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, 
     n_x = active ? a.blk_n[b * T_max + blk] : 0;
     x_start = a.blk_start[b * T_max + blk];
     xb1 = a.x1 + tbase + (long long)x_start * a.geo.stride_t;
-    xb2 = T2 ? a.x2 + tbase + (long long)x_start * a.geo.stride_t : nullptr;
+    xb2 = a.x2 + tbase + (long long)x_start * a.geo.stride_t;
     xstride = a.geo.stride_t;
     bx_base = bh * a.S_max + x_start;
   }
@@ -219,7 +220,7 @@ __device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, 
       x1f[qt][ks] = *reinterpret_cast<const bf16x8*>(xb1 + ro + 32 * ks);
       if (T2) x2f[qt][ks] = *reinterpret_cast<const bf16x8*>(xb2 + ro + 32 * ks);
     }
-    bxv[qt] = (a.bx && row_ok[qt]) ? a.bx[bx_base + rowq[qt]] : 0.f;
+    bxv[qt] = row_ok[qt] ? a.bx[bx_base + rowq[qt]] : 0.f;
     dxv[qt] = (a.dx && row_ok[qt]) ? a.dx[bx_base + rowq[qt]] : 0.f;
     if (EX == 2) rxv[qt] = (a.rx && row_ok[qt]) ? a.rx[bx_base + rowq[qt]] : 0.f;
   }
@@ -267,8 +268,8 @@ __device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, 
   // indexing the kernel argument (or a closure) with a run-time phase number would move it to scratch memory.
   struct Cursor { int p, T; };
   const int n_phases = a.n_phases;
-  const int ph_ent0 = a.s[0].kind == 0 ? T_new : a.s[0].kind == 1 ? n_full : n_flat;
-  const int ph_ent1 = a.s[1].kind == 0 ? T_new : a.s[1].kind == 1 ? n_full : n_flat;
+  const int ph_ent0 = a.s[0].flat ? n_flat : T_new;
+  const int ph_ent1 = a.s[1].flat ? n_flat : T_new;
   const int4* const ph_tab0 = a.s[0].tab;
   const int4* const ph_tab1 = a.s[1].tab;
   // this part's share of each phase: tiles [lo, hi), cut between entries (token tiles) or between tiles of means
@@ -558,9 +559,7 @@ __device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, 
   }
   // ---- store: element i of acc[ct][qt] is channel 16 ct + 4 q + i of stationary row 16 qt + r
   const float inv_n = n_x > 0 ? 1.0f / (float)n_x : 0.f;
-  const float* addp = !a.add_rows ? nullptr
-                      : a.add_by_block ? a.add_rows + (bh * T_max + x_blk) * MD + 4 * q
-                                       : a.add_rows + (bh * a.Tn_pad + e_use) * MD + 4 * q;
+  const float* addp = SM || !a.add_rows ? nullptr : a.add_rows + (bh * T_max + x_blk) * MD + 4 * q;
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt) {
     if (!row_ok[qt]) continue;
@@ -592,7 +591,7 @@ __device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, 
 template <int EX>
 __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * (EX == 2 ? STAGE + K_TILE : STAGE) + 2 * SIDE_BYTES / 2];
-  attn_bwd<false, true, EX, false>(a, lds, blockIdx.x, nullptr, a.oscale);
+  attn_bwd<false, true, EX>(a, lds, blockIdx.x, nullptr, a.oscale);
 }
 
 // dKc (the first half of the workgroups) and dVc, stationary gathered means, in one launch: either alone leaves most of the chip
@@ -602,8 +601,8 @@ template <int EX>
 __global__ __launch_bounds__(512, 1) void k_attn_bwd_means(BwdArgs a, float* dvc) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * STAGE + 2 * SIDE_BYTES / 2];
   const int half = gridDim.x / 2;                      // a multiple of the XCDs
-  if ((int)blockIdx.x < half) attn_bwd<true, true, EX, true>(a, lds, blockIdx.x, a.out_f32, a.oscale);
-  else attn_bwd<true, false, EX, false>(a, lds, (int)blockIdx.x - half, dvc, 1.0f);
+  if ((int)blockIdx.x < half) attn_bwd<true, true, EX>(a, lds, blockIdx.x, a.out_f32, a.oscale);
+  else attn_bwd<true, false, EX>(a, lds, (int)blockIdx.x - half, dvc, 1.0f);
 }
 
 // delta[bh][token] = sum_d dO * O (fp32); 16 lanes per token row, 16 bytes per lane and tensor.  O is taken as out + olo:
@@ -1000,7 +999,7 @@ __global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
   const int h = bhid % a.geo.H, b = bhid / a.geo.H;
   const long long bh = bhid;
   const int T_max = a.geo.T_max;
-  const int n_stat = a.stat_kind == 0 ? a.cnt.b[b].n_full : a.stat_kind == 1 ? a.cnt.b[b].n_flat : a.cnt.b[b].T_new;
+  const int n_stat = a.stat_flat ? a.cnt.b[b].n_flat : a.cnt.b[b].n_full;
   const int entry = 2 * item + grp;
   if (entry >= n_stat) return;
   const int blk = block_in_range(a.stat_list[bh * T_max + entry], a.cnt.b[b].T);
@@ -1022,8 +1021,7 @@ __global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
   sum.x *= a.oscale; sum.y *= a.oscale; sum.z *= a.oscale; sum.w *= a.oscale;
   if (a.add_rows) {
     const float inv_n = 1.0f / (float)n_x;
-    const float4 m4 = *reinterpret_cast<const float4*>(a.add_by_block ? a.add_rows + (bh * T_max + blk) * MD + ch
-                                                                      : a.add_rows + (bh * a.Tn_pad + entry) * MD + ch);
+    const float4 m4 = *reinterpret_cast<const float4*>(a.add_rows + (bh * T_max + blk) * MD + ch);
     sum.x = fmaf(m4.x, inv_n, sum.x); sum.y = fmaf(m4.y, inv_n, sum.y);
     sum.z = fmaf(m4.z, inv_n, sum.z); sum.w = fmaf(m4.w, inv_n, sum.w);
   }
@@ -1136,21 +1134,21 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   a.items_xcd = 0; a.tail_items = 0; a.tail_parts = 1; a.tail_scratch = ws.split_o;   // the forward's partial-result area: 256 x 256 x 128 floats
   const float scale = 1.0f / sqrtf((float)MD);
   const uint16_t *Q = (const uint16_t*)q, *K = (const uint16_t*)k, *V = (const uint16_t*)v, *DO = (const uint16_t*)d_out;
-  const BwdStream none = {nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
+  const BwdStream none = {nullptr, nullptr, nullptr, nullptr, nullptr, false, 0};
   hipError_t e;
 
   // ---- dQ: exact branch over the kept tokens; Taylor branch over the tokens of each block's exact
   // set and the means of the other kept blocks
-  const BwdStream kept_tokens = {K, V, nullptr, ws.ktab, ws.ybd_kv, 0, 0};
+  const BwdStream kept_tokens = {K, V, nullptr, ws.ktab, ws.ybd_kv, false, 0};
   const uint16_t* mean_keys = ws.kcn;             // stored minus the mean key of block 0
-  const BwdStream kept_means = {mean_keys, ws.vcn, ex ? ws.kcnb : nullptr, nullptr, ws.ybd_mean, 0, 0};
+  const BwdStream kept_means = {mean_keys, ws.vcn, ex ? ws.kcnb : nullptr, nullptr, ws.ybd_mean, false, 0};
   a.x1 = Q; a.x2 = DO; a.bx = ws.nlse; a.dx = ws.delta; a.rx = nullptr;
   a.out_bf = (uint16_t*)dq; a.out_f32 = nullptr; a.oscale = scale;
-  a.add_rows = resid ? ws.cdq : nullptr; a.add_by_block = 1;       // every query block's share of dQc
-  a.stat_list = full_list; a.stat_kind = 0; a.items = (sf + 1) / 2;
+  a.add_rows = resid ? ws.cdq : nullptr;          // every query block's share of dQc
+  a.stat_list = full_list; a.stat_flat = false; a.items = (sf + 1) / 2;
   a.s[0] = kept_tokens; a.s[1] = none; a.n_phases = 1; a.bits = nullptr;
   if ((e = launch_dq(a, false, B, H, st, min_kept, ws.bwd_ctr + 2, 8 * cus_per_xcd())) != hipSuccess) return e;
-  a.stat_list = flat_list; a.stat_kind = 1; a.items = (sl + 1) / 2;
+  a.stat_list = flat_list; a.stat_flat = true; a.items = (sl + 1) / 2;
   if (ex) {
     a.s[0] = kept_tokens; a.s[0].masked = 1;
     a.s[1] = kept_means; a.s[1].masked = 2;
@@ -1175,8 +1173,8 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
       const double rounds = (double)((wgs + chip - 1) / chip) / p;
       if (rounds < best - 1e-9) { best = rounds; mean_parts = p; }
     }
-    a.x1 = mean_keys; a.x2 = ws.vcn; a.stat_list = nullptr; a.stat_kind = 2; a.bx = ws.bx_mean; a.dx = nullptr; a.rx = nullptr;
-    a.s[0] = {Q, DO, nullptr, ws.ltab, ex ? ws.ybd_flatm : ws.ybd_flat, 2, ex ? 3 : 0};      // scored against gathered means
+    a.x1 = mean_keys; a.x2 = ws.vcn; a.stat_list = nullptr; a.bx = ws.bx_mean; a.dx = nullptr; a.rx = nullptr;
+    a.s[0] = {Q, DO, nullptr, ws.ltab, ex ? ws.ybd_flatm : ws.ybd_flat, true, ex ? 3 : 0};      // scored against gathered means
     a.s[1] = none; a.n_phases = 1; a.bits = ws.mask_t;
     a.out_bf = nullptr; a.out_f32 = ws.dkc; a.add_rows = nullptr; a.items = n_mean_pairs;
     a.parts = mean_parts; a.part_stride = (long long)B * H * pr.Tn_pad * MD;
