@@ -128,3 +128,77 @@ def test_counted_items_whole(I):
             rows = slice(0, n, 97 if b == 0 else 1)
             emax, emean = err_stats(f64(out[b, h, :n][rows]), O.dense_attention(f64(q[b, h, :n][rows]), f64(k[b, h, :n]), f64(v[b, h, :n])))
             assert emax <= TOL["bf16"][0] and emean <= TOL["bf16"][1], (b, h, emax, emean)
+
+
+def test_counted_items_backward_taylor(I):
+    """dQ of Taylor blocks over 1000 kept blocks (16 tiles of means): items from the counter, the last 32 in 8 parts along the means."""
+    import numpy as np
+    import torch
+    from oracle import isa_oracle as O
+    from oracle import isa_oracle_bwd as OB
+    from test_gpu_backward import TOL_MAX_REL, TOL_MEAN_REL
+    from util import f64
+    H, T, S = 5, 1000, 128 * 999 + 77
+    pr = I.Problem(H=H, D=128, dtype="bf16", block=128, seg_len=[[S]], keep_ratio=0.0, full_frac=0.0)
+    c = I.isa_get_counts(pr, 0)
+    assert c["n_flat"] == c["T_new"] == T > 960 and H * (T // 2) // 8 >= 8 * 32                     # the premise
+    g = torch.Generator(device="cuda").manual_seed(898)
+    rand = lambda n: torch.randn((1, H, n, 128), generator=g, device="cuda")
+    blocks = lambda: rand(T).repeat_interleave(128, 2)[:, :, :S]                                # the means differ from block to block
+    q, k, v, d_out = (x.bfloat16() for x in (rand(S), blocks() + 0.3 * rand(S), blocks() + 0.3 * rand(S), rand(S)))
+    ws = I.new_workspace(pr)
+    out = torch.empty_like(q)
+    grads = [torch.full_like(q, float("nan")) for _ in range(3)]
+    I.isa_attention(pr, q, k, v, out, ws)
+    I.isa_attention_backward(pr, q, k, v, out, d_out, *grads, ws)
+    torch.cuda.synchronize()
+    assert all(torch.isfinite(x).all() for x in grads)
+    for h in (0, 3, 4):
+        x = [f64(t[0, h]) for t in (q, k, v, d_out)]
+        plan = O.isa_plan(*x[:3], [S], 128, 0.0, 0.0)
+        some = sorted({0, 1, 500, 934, 935, 936, 937, 980, 997, 998, 999})                     # 936 on: the last 32 pairs of head 4
+        want = OB.isa_attention_bwd(*x, plan, query_blocks=some)[0]
+        for i in some:
+            rows = slice(128 * i, min(S, 128 * i + 128))
+            d = np.abs(f64(grads[0][0, h, rows]) - want[rows]) / np.abs(want).max()
+            assert d.max() <= TOL_MAX_REL and d.mean() <= TOL_MEAN_REL, (h, i, d.max(), d.mean())
+
+
+def test_counted_items_backward_with_exact_sets(I):
+    """dK and dV of 8 rounds or more beside exact sets: the parts of the last 32 items share the exact branch's list and that of the
+    Taylor blocks linked to the item's block."""
+    import numpy as np
+    import torch
+    from oracle import isa_oracle as O
+    from oracle import isa_oracle_bwd as OB
+    from test_gpu_backward import TOL_MAX_REL, TOL_MEAN_REL, _inputs
+    from util import f64, problem_of
+    wl = _wl(200, (1, 1, 128 * 17 + 5), (((1, 1, 500),),), keep_ratio=0.5, full_frac=0.75, exact_frac=0.3, seed=899)
+    pr = problem_of(wl)
+    c = I.isa_get_counts(pr, 0)
+    assert wl.H * c["T_new"] // 8 >= 8 * 32 and c["n_full"] >= 16 and c["n_flat"] >= 5 and c["k_exact"] >= 5       # the premise
+    Q, K, V, dO = _inputs(wl)
+    q, k, v, d_out = (t.cuda() for t in (Q, K, V, dO))
+    ws = I.new_workspace(pr)
+    out = torch.empty_like(q)
+    grads = [torch.full_like(q, float("nan")) for _ in range(3)]
+    I.isa_attention(pr, q, k, v, out, ws)
+    lay = I.isa_workspace_layout(pr)
+    T_max, lists = c["T_max"], (1, wl.H, c["T_max"])
+    kv_g, full_g, flat_g = (I.workspace_array(ws, lay[n], lists, torch.int32).cpu().numpy() for n in ("kv_list", "full_list", "flat_list"))
+    mask_g = I.workspace_array(ws, lay["exact_mask"], lists + ((T_max + 31) // 32,), torch.int32).cpu().numpy().view(np.uint32)
+    I.isa_attention_backward(pr, q, k, v, out, d_out, *grads, ws)
+    torch.cuda.synchronize()
+    assert all(torch.isfinite(x.float()).all() for x in grads)
+    for h in (0, 100, 197, 198, 199):
+        x = [f64(t[0, h]) for t in (Q, K, V, dO)]
+        plan = O.isa_plan(*x[:3], wl.seg_len(0), 128, 0.5, 0.75, 0.3)
+        # the comparison needs the lists and sets of the call: with these inputs fp32 and fp64 scores rank the blocks alike
+        kv = plan["kv_list"].tolist()
+        assert kv == kv_g[0, h, :c["T_new"]].tolist() and plan["full_list"].tolist() == full_g[0, h, :c["n_full"]].tolist()
+        for r, i in enumerate(flat_g[0, h, :c["n_flat"]]):
+            ex = [kv[t] for t in range(c["T_new"]) if (mask_g[0, h, r, t >> 5] >> (t & 31)) & 1]
+            assert ex == list(OB.exact_blocks_of(plan, int(i)))
+        for name, got, want in zip(("dQ", "dK", "dV"), grads, OB.isa_attention_bwd(*x, plan)):
+            d = np.abs(f64(got[0, h]) - want) / np.abs(want).max()
+            assert d.max() <= TOL_MAX_REL and d.mean() <= TOL_MEAN_REL, (h, name, d.max(), d.mean())
