@@ -57,7 +57,7 @@ typedef enum {
   ISA_ERR_DTYPE = -4,       /* dtype is neither ISA_BF16 nor ISA_F32 */
   ISA_ERR_UNSUPPORTED = -5, /* a non-finite gamma; a bf16, D = 128, block = 128 problem whose tokens of one (batch, head)
                                span 4 GiB or more (S_max * stride_t * 2 bytes: the matrix-core kernels use 32-bit byte
-                               offsets; isa_set_mfma(0) selects the portable kernels, which have no such limit); a call
+                               offsets; isa_set_mfma(0) selects the general kernel, which has no such limit); a call
                                that is not available in the stream's state (isa_attention_simple under capture) */
   ISA_ERR_WORKSPACE = -6,   /* workspace NULL, misaligned (256 B) or smaller than required */
   ISA_ERR_HIP = -7          /* a HIP runtime call or kernel launch failed */

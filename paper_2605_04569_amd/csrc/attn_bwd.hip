@@ -27,7 +27,9 @@
 // of the streamed rows when these are (read from the tile's side array as the C operand of the first T2 MFMA), so that
 // a weight costs an fma, an exp2, a multiplication and half a packed conversion.  Matrix and vector instructions issue
 // through one port on this chip and a sub-tile's weights take about as long as its MFMAs, so the weights are issued in
-// slices between the MFMAs of the following sub-tile, with the LDS fragments requested a step ahead.
+// slices between the MFMAs of the following sub-tile, with the LDS fragments requested two steps ahead (one with exact sets).
+// dQ of the exact branch at 480p with the paper's ratios: matrix pipe busy 64 % of the cycles, 2 cycles of bank conflicts per transposed
+// read (1.5e9 of 6.4e9 LDS cycles; another swizzle: see attn_bwd_kv.hip).
 #include "attn_mfma.h"
 
 namespace isa {

@@ -13,8 +13,10 @@
 // Measured at 480p with the paper's ratios (40 heads, 288 kept and 256 full-attention blocks each): 56.0 ms in two launches of 8
 // waves -> 47.2 in this one, 45.1 with the tile set-up, the barrier and the first fragments of the next tile moved into the
 // shadows of matrix instructions.  Matrix pipe busy 52 % of 4000 cycles an iteration at 2.2 GHz; a wave waits 20 % of
-// them for LDS or the barrier and 28 % for the pipe.  Without effect (within 1 %): fragments 5 or 7 steps ahead instead of 3, vector
-// instructions placed one by one behind every matrix instruction, another chunk swizzle.
+// them for LDS or the barrier and 28 % for the pipe.  Every transposed read costs 2 cycles of bank conflicts (the eight rows it takes
+// 32 bytes of at a time meet four places of the swizzle): 3.2e9 of 1.04e10 LDS cycles.  Without effect (within 1 %): fragments 5 or 7
+// steps ahead instead of 3, vector instructions placed one by one behind every matrix instruction, chunk c of row r at
+// c ^ (((r & 7) << 1) | ((r >> 3) & 1)), which frees the transposed reads of conflicts and gives every row read 4 cycles of them.
 //
 // Layouts as in attn_bwd.hip: with r = lane % 16, q = lane / 16, T1 = Q K^T and T2 = dO V^T - delta of a 16-row sub-tile give lane
 // (r, q) streamed rows 4 q + i of key 16 qt + r; the weights P and dS of two sub-tiles are the B operands of dV^T += dO^T P

@@ -15,13 +15,14 @@
 // second product (O^T = V^T P^T), so the weights never leave their registers; V is read transposed out of its row-major
 // tile (ds_read_b64_tr_b16 for bf16; for fp32 a lane's four channels of a row serve four output tiles).  Tiles of 64
 // bf16 (32 fp32) rows go global -> LDS directly, one tile ahead, two stages, 16-byte chunks XOR-swizzled by row.  A stage
-// is 256 D bytes either way, so at least two workgroups share a compute unit and one's softmax runs beside the
-// other's matrix instructions; there is no hand-made interleaving here.
+// is 256 D bytes either way.  Short launches give a workgroup two such groups of 4 waves (NG = 2 below).  Groups that share a
+// compute unit, whose softmax runs beside each other's matrix instructions (there is no hand-made interleaving here): D = 128, 66 KB
+// a group, two (two workgroups, or one of two groups); D = 64, 33 KB, three of QT = 2 (registers) or four of QT = 1.
 //
 // What bounds it (measured, 24 heads of 64 channels, 15 600 tokens in blocks of 64, keep 0.5, full 0.25): instruction issue. A weight
 // costs 9.4 vector instructions (5.5 of them the exact cut into three terms; taking the differences with the bf16 dot
-// instruction was slower and not exact) beside 2 matrix instructions; counters of the dense launch: issue port busy
-// 85 % of the cycles, matrix pipe 38 %, no LDS bank conflicts.  Whole call 11.6 -> 0.73 ms against a kernel of one
+// instruction was slower and not exact) beside 2 matrix instructions; counters of that launch: vector and matrix instructions issuing
+// in 95 % of the cycles, matrix pipe busy 42 %, no LDS bank conflicts.  Whole call 11.6 -> 0.73 ms against a kernel of one
 // row per four lanes in scalar arithmetic (25 -> 400 TFLOP/s); fp32, 8 heads of 128 channels, 5280 tokens: 1.89 -> 0.39 ms.
 #include <math.h>
 

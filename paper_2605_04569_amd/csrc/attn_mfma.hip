@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256) void k_pack_vt(const uint16_t* __restrict__ v,
   const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   if (j == 0 && h == 0 && b == 0) {                               // the all-zero V^T tile the attention kernel pads with
     for (int x = threadIdx.x; x < MD * KT / 8; x += 256) reinterpret_cast<uint4*>(zero_tile)[x] = make_uint4(0, 0, 0, 0);
-    if (threadIdx.x == 0) *long_ctr = 0;                          // the counter a dense launch may take its items from
+    if (threadIdx.x == 0) *long_ctr = 0;                          // the counter a launch of nothing but long items may take them from
   }
   int start, n;
   if (ALL) {

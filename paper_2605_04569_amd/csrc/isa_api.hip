@@ -91,8 +91,8 @@ int validate(const isa_problem* p, Problem* out) {
   pr.S_max = (int)S_max;
   pr.mfma_shape = p->dtype == ISA_BF16 && p->D == 128 && p->block == 128;
   if (pr.mfma_shape && (unsigned long long)S_max * (unsigned long long)p->stride_t * 2ull >= (1ull << 32)) {
-    // Not a silent drop to the portable kernels (slower, and no backward pass): the caller is told, and can
-    // still ask for those kernels explicitly with isa_set_mfma(0).
+    // Not a silent drop to the general kernel (slower, and no backward pass): the caller is told, and can still ask
+    // for that kernel explicitly with isa_set_mfma(0).
     if (g_use_mfma.load()) return ISA_ERR_UNSUPPORTED;
     pr.mfma_shape = false;
   }

@@ -73,7 +73,8 @@ struct Workspace {
   float* biasn;          // [B,H,Tn_pad]: ln(n_j) sqrt(D) per gathered mean key (without exact sets: ln(n_j / block) sqrt(D)), -inf for padding
   int* tflag;            // [B,H,Tn_pad/64]: 1 if a tile of mean keys needs its bias or masks (padding, a short block, exact sets)
   uint16_t* zero_tile;   // 16 KB of zeros, written by the V^T pack kernel
-  int* taylor_ctr;       // the next Taylor group of the attention launch (zeroed by the mean gather, counted up by the launch)
+  int* taylor_ctr;       // two counters of the attention launch: [0] the next Taylor group (zeroed by the mean gather), [1] the next
+                         // long item of a launch of nothing else (zeroed by the V^T pack)
   int* bwd_ctr;          // backward: the next work item of each launch that hands its items out dynamically (8 counters, zeroed by k_bwd_delta)
   int4* ktab;            // [B,H,T_max] the btab rows of the blocks of kv_list, in list order
   float* ocoarse;        // [B,H,T_max,D] pooled attention output (only carved when gamma != 0)
