@@ -86,9 +86,9 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 
 }  // namespace
 
-// One work item: 64 QT rows of one query block (QT = 2, block 64: of two neighbours in the list).  FULL32 evaluates the
-// products of fp32 numbers with fp32 matrix instructions instead of bf16 terms: slower, but infinities go through them
-// as through a multiplication (a term that is zero turns an infinity into NaN).  Returns whether this wave's results are
+// One work item: 64 QT rows of one query block (QT = 2, block 64: of two neighbours in the list).  FULL32 is the second pass over an item:
+// for bf16 tensors it evaluates the products of fp32 numbers with fp32 matrix instructions instead of bf16 terms, slower, but infinities go
+// through them as through a multiplication (a term that is zero turns an infinity into NaN).  Returns whether this wave's results are
 // all finite and its maxima in the range of the fast weights; with FULL32 = false nothing is stored if some wave's are not, and the
 // caller runs the item again.
 //
@@ -96,10 +96,13 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 // product is not rounded while the maximum is: all weights of a row share a factor of 2^r with |r| up to half a unit in the
 // last place of the maximum, which cancels in the result as long as it is a small number.  From FAST_MAX on the row is left to the
 // second pass; it and fp32 tensors (WIDE) keep the maximum unscaled and multiply the difference, so that the largest key's
-// exponent is the same whatever the scores are, and start it at -infinity, M_INIT being a score that a row may lie below.  Their
-// weights carry a factor of 2^-tau, which makes them at most 1: 2^tau times a value near the largest number is none.  One more
-// instruction per weight and two per half tile: clip of 8 heads of 128 channels, 5280 tokens, fp32, 390 -> 390 us, 24 heads of 64
+// exponent is 0 whatever the scores are, and start it at -infinity, M_INIT being a score that a row may lie below.  One more
+// instruction per weight and two per half tile: clip of 8 heads of 128 channels, 5280 tokens, fp32, 390 -> 393 us, 24 heads of 64
 // channels 405 -> 408; the fast form of bf16 is bound by instruction issue.
+//
+// The first pass raises a maximum only when a weight would exceed 2^tau, the second at every larger score: its weights are at most 1, where
+// 2^tau times a value near the largest number is none.  (Raising at once in the first pass cost fp32 1 and 2.5 % on these two; a factor of
+// 2^-tau in its weights cost values near the smallest normal number their last eight bits.)
 //
 // NG = 2: two groups of 4 waves work on the same rows, each with stages of its own, and take the tiles of the sequence in turn;
 // the second group hands its running maxima, sums and outputs to the first through LDS at the end.
@@ -380,7 +383,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 #pragma unroll
       for (int e = 1; e < 7; e += 2) mx[qt] = fmaxf(fmaxf(mx[qt], s[e >> 2][qt][e & 3]), s[(e + 1) >> 2][qt][(e + 1) & 3]);
       mx[qt] = fmaxf(mx[qt], s[1][qt][3]) * (WIDE ? 1.f : cscale);
-      raise |= __ballot((mx[qt] + neg_m[qt]) * (WIDE ? cscale : 1.f) > RESCALE_TAU);
+      raise |= __ballot((mx[qt] + neg_m[qt]) * (WIDE ? cscale : 1.f) > (FULL32 ? 0.f : RESCALE_TAU));
     }
     if (raise != 0ull) {
 #pragma unroll
@@ -403,7 +406,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          p[qt][4 * kt + i] = __builtin_amdgcn_exp2f(WIDE ? fmaf(s[kt][qt][i] + sh, cscale, -RESCALE_TAU) : fmaf(s[kt][qt][i], cscale, sh));
+          p[qt][4 * kt + i] = __builtin_amdgcn_exp2f(WIDE ? (s[kt][qt][i] + sh) * cscale : fmaf(s[kt][qt][i], cscale, sh));
     }
     if constexpr (mean) {                              // Eq. 4: a mean key weighs its block's token count
 #pragma unroll
@@ -590,7 +593,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         for (int i = 0; i < 4; ++i) ok = ok && fabsf(acc[ct][qt][i] * inv[qt]) < INFINITY;
     }
   }
-  if constexpr (BF && !FULL32)
+  if constexpr (!FULL32)
     if (__syncthreads_or(!ok)) return false;
   if (grp != 0) return true;
   // coarse residual (Alg. 1 Stage 5): the block's row of O_coarse, the same for all of its tokens
@@ -639,11 +642,9 @@ __global__ __launch_bounds__(256 * NG, D == 128 ? 2 : QT == 1 ? 4 : 3) void k_at
   auto first_entry = [&](int qt, int n) { return ga.a.geo.block == 64 ? qt * n : n * qt / 2; };
   if (first_entry(QT, slot) >= n_list) return;         // a shorter batch item
   if (attn_gen_item<T, D, QT, false, NG>(ga, lds, bhid, taylor, slot)) return;
-  if constexpr (sizeof(T) == 2) {                      // again, 64 rows at a time
 #pragma unroll 1
-    for (int n = QT * slot; n < QT * (slot + 1); ++n)
-      if (first_entry(1, n) < n_list) attn_gen_item<T, D, 1, true, NG>(ga, lds, bhid, taylor, n);
-  }
+  for (int n = QT * slot; n < QT * (slot + 1); ++n)    // again, 64 rows at a time
+    if (first_entry(1, n) < n_list) attn_gen_item<T, D, 1, true, NG>(ga, lds, bhid, taylor, n);
 }
 
 hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st) {

@@ -181,6 +181,23 @@ def test_values_near_the_largest_number(I, shape):
         assert emax <= TOL[wl.dtype][0] and emean <= TOL[wl.dtype][1], (h, emax, emean)
 
 
+@pytest.mark.parametrize("shape", [x for x in SHAPES if x[0] == "f32"], ids=[i for i in SHAPE_IDS if i[:3] == "f32"])
+def test_values_near_the_smallest_normal_number(I, shape):
+    """Values of 2^-126: the products with weights of at most 1 are multiples of 2^-149, and 300 of them are off by sqrt(300 / 12) such
+    steps, 2^-18 of results of 2^-129.  Weights that carried a factor of 2^-8 would lose eight bits more."""
+    n, D = 300, shape[1]
+    g = torch.Generator().manual_seed(793)
+    q, k, v = (torch.randn((1, 2, n, D), generator=g) for _ in range(3))
+    v = (v.double() * 2.0 ** -126).float()
+    pr = I.Problem(H=2, D=D, dtype="f32", block=shape[2], seg_len=[[n]], keep_ratio=1.0, full_frac=1.0)
+    out = torch.empty((1, 2, n, D), device="cuda")
+    I.isa_dense_attention(pr, q.cuda(), k.cuda(), v.cuda(), out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    want = np.stack([O.dense_attention(f64(q[0, h]), f64(k[0, h]), f64(v[0, h])) for h in range(2)])
+    rel = np.linalg.norm(f64(out[0]) - want) / np.linalg.norm(want)
+    assert rel <= 2.0 ** -18, rel
+
+
 @pytest.mark.parametrize("D,bound", [(64, 1.14e-6), (128, 1.06e-6)])
 def test_fp32_scores_no_further_off_than_in_scalar_arithmetic(I, D, bound):
     """Queries of norm up to 4 sqrt(D): the distance from 64 bits is that of the scores' sums.  The bounds are what a kernel with
