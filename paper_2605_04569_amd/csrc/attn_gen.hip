@@ -95,14 +95,13 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 // A weight is exp2 of the scaled score minus the scaled running maximum.  The fast form of bf16 tensors is one fma, whose
 // product is not rounded while the maximum is: all weights of a row share a factor of 2^r with |r| up to half a unit in the
 // last place of the maximum, which cancels in the result as long as it is a small number.  From FAST_MAX on the row is left to the
-// second pass; it and fp32 tensors (WIDE) keep the maximum unscaled and multiply the difference, so that the largest key's
-// exponent is 0 whatever the scores are, and start it at -infinity, M_INIT being a score that a row may lie below.  One more
-// instruction per weight and two per half tile: clip of 8 heads of 128 channels, 5280 tokens, fp32, 390 -> 393 us, 24 heads of 64
-// channels 405 -> 408; the fast form of bf16 is bound by instruction issue.
+// second pass; it and fp32 tensors (WIDE) subtract the maximum of the scores as they are, so that the largest key's exponent is 0
+// whatever they are, and start it at -infinity, M_INIT being a score that a row may lie below.  fp32 scores come scaled (the queries
+// are multiplied by the scale when they are loaded), the second pass over bf16 rows multiplies the difference.
 //
 // The first pass raises a maximum only when a weight would exceed 2^tau, the second at every larger score: its weights are at most 1, where
-// 2^tau times a value near the largest number is none.  (Raising at once in the first pass cost fp32 1 and 2.5 % on these two; a factor of
-// 2^-tau in its weights cost values near the smallest normal number their last eight bits.)
+// 2^tau times a value near the largest number is none.  (Raising at once in the first pass cost fp32 1 % with 128 channels, 2.5 with
+// 64; a factor of 2^-tau in its weights cost values near the smallest normal number their last eight bits.)
 //
 // NG = 2: two groups of 4 waves work on the same rows, each with stages of its own, and take the tiles of the sequence in turn;
 // the second group hands its running maxima, sums and outputs to the first through LDS at the end.
@@ -156,7 +155,8 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     return bits;
   };
 
-  // Q fragments: bf16 lane (r, g) holds channels 32 ks + 8 g .. + 7 of query 16 qt + r, fp32 channels 16 t + 4 g .. + 3
+  const float cscale = 1.4426950408889634f / sqrtf((float)D);
+  // Q fragments: bf16 lane (r, g) holds channels 32 ks + 8 g .. + 7 of query 16 qt + r, fp32 (scaled) channels 16 t + 4 g .. + 3
   bf16x8 qb[QT][D / 32];
   f32x4 qf[QT][NT];
 #pragma unroll
@@ -168,7 +168,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       for (int ks = 0; ks < D / 32; ++ks) qb[qt][ks] = *reinterpret_cast<const bf16x8*>(qp + 32 * ks + 8 * g);
     } else {
 #pragma unroll
-      for (int t = 0; t < NT; ++t) qf[qt][t] = *reinterpret_cast<const f32x4*>(qp + 16 * t + 4 * g);
+      for (int t = 0; t < NT; ++t) qf[qt][t] = *reinterpret_cast<const f32x4*>(qp + 16 * t + 4 * g) * cscale;
     }
   }
 
@@ -249,7 +249,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 
   f32x4 acc[NT][QT];                                   // element i: bf16: channel 16 ct + 4 g + i; fp32: see the store
   constexpr float NONE = WIDE ? INFINITY : -M_INIT;    // minus the maximum of no score
-  float neg_m[QT], l_run[QT];                          // minus the running maximum (scaled, log2 domain; WIDE: as the score is); sums per lane
+  float neg_m[QT], l_run[QT];                          // minus the running maximum (log2 domain; WIDE bf16: as the score is); sums per lane
   // what is added to a score before its weight is formed: while a WIDE row has seen nothing but masked slots, 0, so that their
   // weights are exp2(-infinity), not of a difference of infinities
   auto shift = [&](float nm) { return WIDE && nm == INFINITY ? 0.f : nm; };
@@ -260,8 +260,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) acc[ct][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  const float cscale = 1.4426950408889634f / sqrtf((float)D);
-  auto factor = [&](float diff) { return __builtin_amdgcn_exp2f(WIDE ? diff * cscale : diff); };      // between two maxima, from their difference
+  auto factor = [&](float diff) { return __builtin_amdgcn_exp2f(WIDE && BF ? diff * cscale : diff); };      // between two maxima, from their difference
 
   // ---- a half tile: 32 keys from row `r0` of the stage; `nk` of them real; wt: weights of a mean tile's 32 slots
   auto half = [&](const unsigned char* kb, const unsigned char* vb, const int r0, const int nk, const auto mean_c, const float* wt)
@@ -284,10 +283,10 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
           k4[t & 1][kt] = *reinterpret_cast<const f32x4*>(kb + ((16 * kt + r16) * CM + ((4 * t + g) ^ r16)) * 16);
       };
       k_load(0);
-      // D = 128: every other group of four channels adds up here, in two chains of half the length.  Error against 64 bits of dense
-      // attention over 1000 tokens with one / two chains 1.10e-6 / 7.5e-7 (four partial sums in scalar arithmetic: 1.06e-6), clip of 8
-      // heads 387 / 388 us.  D = 64 has 8.8e-7 with one chain (scalar: 1.14e-6), and two cost it 2 %.
-      constexpr int CHAINS = D / 64;
+      // every other group of four channels adds up here, in two chains of half the length.  Error against 64 bits of dense attention over
+      // 1000 / 5280 tokens with one chain and with two, 128 channels: 1.15e-6 / 2.31e-6, 7.4e-7 / 1.99e-6 (four partial sums in scalar
+      // arithmetic: 1.08e-6 / 5.87e-6), 64 channels 9.0e-7 / 1.47e-6, 6.3e-7 / 1.26e-6; clip of 8 heads of 128 channels 388 / 389 us, 24
+      // heads of 64 404 / 407
       f32x4 s_odd[2][QT];
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
@@ -303,15 +302,14 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
           for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
             for (int qt = 0; qt < QT; ++qt) {
-              f32x4& to = i & (CHAINS - 1) ? s_odd[kt][qt] : s[kt][qt];
+              f32x4& to = i & 1 ? s_odd[kt][qt] : s[kt][qt];
               to = mfma_f(k4[t & 1][kt][i], qf[qt][t][i], to);
             }
       }
-      if (CHAINS > 1)
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
+      for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-          for (int qt = 0; qt < QT; ++qt) s[kt][qt] += s_odd[kt][qt];
+        for (int qt = 0; qt < QT; ++qt) s[kt][qt] += s_odd[kt][qt];
     } else if constexpr (!mean) {
 #pragma unroll
       for (int ks = 0; ks < D / 32; ++ks)
@@ -383,7 +381,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 #pragma unroll
       for (int e = 1; e < 7; e += 2) mx[qt] = fmaxf(fmaxf(mx[qt], s[e >> 2][qt][e & 3]), s[(e + 1) >> 2][qt][(e + 1) & 3]);
       mx[qt] = fmaxf(mx[qt], s[1][qt][3]) * (WIDE ? 1.f : cscale);
-      raise |= __ballot((mx[qt] + neg_m[qt]) * (WIDE ? cscale : 1.f) > (FULL32 ? 0.f : RESCALE_TAU));
+      raise |= __ballot((mx[qt] + neg_m[qt]) * (WIDE && BF ? cscale : 1.f) > (FULL32 ? 0.f : RESCALE_TAU));
     }
     if (raise != 0ull) {
 #pragma unroll
@@ -406,7 +404,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          p[qt][4 * kt + i] = __builtin_amdgcn_exp2f(WIDE ? (s[kt][qt][i] + sh) * cscale : fmaf(s[kt][qt][i], cscale, sh));
+          p[qt][4 * kt + i] = __builtin_amdgcn_exp2f(WIDE ? (s[kt][qt][i] + sh) * (BF ? cscale : 1.f) : fmaf(s[kt][qt][i], cscale, sh));
     }
     if constexpr (mean) {                              // Eq. 4: a mean key weighs its block's token count
 #pragma unroll
