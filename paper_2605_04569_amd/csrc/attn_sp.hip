@@ -857,6 +857,12 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
     // tokens (7 key blocks), kernel + merge: whole items 31.9 us, ranges of two blocks 25.5, of one 23.5; whole call, 8 heads
     // of 3200 tokens without / with room for the groups 73 / 65 us, 12 heads of 1564 66 / 60; 2 heads of 9360 tokens (ranges of 5
     // blocks) 77 / 79.
+    // After a first full round, Taylor groups fill what the last one leaves idle, and every range costs its start, a partial result and
+    // the merge: ranges of 8 blocks or more there, of 4 where an XCD cuts one or two items.  Whole call, fine ranges / these: 300 heads of
+    // 1000 tokens (lists of 6: not cut) 222 / 203 us, 100 of 2300 (13: not cut) 188 / 164, 48 of 6000 (36: four ranges instead of 8)
+    // 316 / 287, 60 of 2300 (16) 153 / 147, 44 of 3000 (one item, 22; ranges of 8 173) 162 / 159.  Without Taylor groups an item is cut if that
+    // saves the time of 5 blocks: dense, 100 heads of 600 tokens (5 blocks) cut / whole 61.3 / 57.4, 160 of 1000 (8, two ranges) 121 / 116,
+    // 70 of 1000 (8, eight ranges) 69 / 77.
     m.n_split = 0; m.parts = 1;
     m.split_o = ws.split_o; m.split_ml = ws.split_ml;
     const int cus = cus_per_xcd(), rem = m.n_long % cus;
@@ -868,8 +874,10 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
     if (rem > 0 && rem <= cus / 2 && ws.split_o) {
       int parts = cus / rem;
       if (m.n_long < cus && 4 * parts > min_list) parts = (cus - (m.n_taylor_wg < cus / 2 ? m.n_taylor_wg : cus / 2)) / rem;
-      const int most = min_list / 2 > 8 ? min_list / 2 : (min_list < 8 ? min_list : 8);
+      int most = min_list / 2 > 8 ? min_list / 2 : (min_list < 8 ? min_list : 8);
+      if (m.n_long > cus && ss > 0) most = min_list / (rem <= 2 ? 4 : 8);
       if (parts > most) parts = most;
+      if (m.n_long > cus && ss == 0 && min_list * (parts - 1) < 5 * parts) parts = 1;
       while (parts >= 2 && N_XCD * rem * parts > SPLIT_MAX_SUB) --parts;      // the partial-result area holds SPLIT_MAX_SUB sub-items
       if (parts >= 2) { m.n_split = rem; m.parts = parts; }
     }

@@ -202,3 +202,15 @@ def test_counted_items_backward_with_exact_sets(I):
         for name, got, want in zip(("dQ", "dK", "dV"), grads, OB.isa_attention_bwd(*x, plan)):
             d = np.abs(f64(got[0, h]) - want) / np.abs(want).max()
             assert d.max() <= TOL_MAX_REL and d.mean() <= TOL_MEAN_REL, (h, name, d.max(), d.mean())
+
+
+# more than one round of long items and few key blocks: whole items and cut ones, with Taylor groups behind them and without
+@pytest.mark.parametrize("H,src,ctx,full_frac", [(176, 500, 500, 0.6), (100, 2000, 300, 0.3), (44, 2000, 1000, 0.5), (100, 500, 100, 1.0), (70, 500, 500, 1.0)],
+                         ids=["taylor_short", "taylor_13", "taylor_one_item", "long_only_5", "long_only_8"])
+def test_last_round_of_short_lists(I, H, src, ctx, full_frac):
+    from util import problem_of
+    wl = _wl(H, (1, 1, src), (((1, 1, ctx),),), keep_ratio=1.0 if full_frac == 1.0 else 0.5, full_frac=full_frac, seed=905 + H)
+    c = I.isa_get_counts(problem_of(wl), 0)
+    n_long = -(-H * ((c["n_full"] + 1) // 2) // 8)
+    assert n_long > 32 and 0 < n_long % 32 <= 16                                         # the premise
+    check_end_to_end(I, wl, *gen(wl), heads=[0, H // 2, H - 2, H - 1])
