@@ -65,7 +65,9 @@ struct MfmaArgs {
   int* taylor_ctr;                          // k_attn_sp: the next Taylor group to be taken (device memory, 0 when the launch starts)
   int* long_ctr; int n_long_all;            // k_attn_sp: null, or the next long (sub-)item to be taken, numbered over all (batch, head)s, and their number;
   int ctr_whole;                            //   the first ctr_whole are whole items, the others `parts` key ranges of an item each
-  int n_long;                               // k_attn_sp: exact-branch items per XCD (0 if none; an XCD may have one fewer)
+  int n_long;                               // k_attn_sp: exact-branch items per XCD (0 if none; an XCD may have fewer)
+  int ragged;                               // k_attn_sp: 1: batch items differ in their number of exact-branch pairs (see long_item_at), which are
+  int by_length[ISA_MAX_BATCH], own_pairs[ISA_MAX_BATCH];      //   these, of the batch items in the order of their key lists, longest first
   int n_split, parts;                       // k_attn_sp: the last n_split exact-branch items of an XCD run as `parts` sub-items over key ranges
   float* split_o; float* split_ml;          // their partial results: unnormalised outputs [sub-item][2][128][128], {max, sum} [sub-item][2][128][2]
   float* nlse; int S_max;                   // minus the log-sum-exp (log2 domain) of every query row, [bh][S_max]; may be null

@@ -241,6 +241,39 @@ __device__ __forceinline__ void rescale(const float (&alpha)[2], f32x4 (&l_run)[
   }
 }
 
+// The `item`-th of an XCD's long items: its (batch, head) and pair; false past the last.  Batch items alike: the XCD's range of all pairs
+// in the order of xcd_first and head_at.  A ragged batch: an equal range of every batch item's own pairs, longest key lists first, as
+// nothing levels the end of a launch that starts a long item late.  (Through the heads of all batch items as they come, dense attention of
+// 12 heads, items of 3000, 100 and 1620 tokens in this order / the longest last, took 146 / 144 us and takes 96 / 95; 3 heads of 6000 and
+// 1500 tokens 151 -> 98, 19 heads 482 -> 375; every eighth head an XCD's took 135 / 104, 154, 483.)
+__device__ __forceinline__ bool long_item_at(const MfmaArgs& a, int xcd, int item, int& bhid, int& slot) {
+  const int H = a.geo.H, n_bh = a.geo.B * H;
+  if (!a.ragged) {
+    const long long total = (long long)n_bh * a.slots_first;
+    const int at = xcd_first(total, xcd) + item;
+    if (at >= xcd_first(total, xcd + 1)) return false;
+    bhid = head_at(at / a.slots_first, n_bh);
+    slot = at % a.slots_first;
+    return true;
+  }
+  int at = -1, pairs = 1, b = 0;
+#pragma unroll
+  for (int i = 0; i < ISA_MAX_BATCH; ++i) {                     // unrolled: the arguments are loaded together
+    if (i >= a.geo.B || at >= 0) break;
+    const int total = H * a.own_pairs[i], first = total * xcd / N_XCD, last = total * (xcd + 1) / N_XCD;      // at most 8 x 65535 x 2048
+    if (item < last - first) {
+      at = first + item;
+      pairs = a.own_pairs[i];
+      b = a.by_length[i];
+    }
+    item -= last - first;
+  }
+  if (at < 0) return false;
+  bhid = b * H + head_at(at / pairs, H);
+  slot = at % pairs;
+  return true;
+}
+
 // One work item.  `taylor` is a template parameter so that the tile set-up inside the loop carries no selects or
 // branches between the two kinds of key sequence (token tiles of kept blocks / tiles of gathered block means).
 template <bool taylor>
@@ -250,7 +283,7 @@ __device__ __forceinline__ void attn_sp_item(const MfmaArgs& a, uint16_t* lds, c
   uint16_t* ldsQ = lds + NBUF * K_TILE + NBUF * V_TILE;       // 2 x 128 query rows of a Taylor group's next pair
 
   // ---- which work item.  Workgroup ids go round-robin over the 8 XCDs, so XCD x sees ids x, x + 8, ... in
-  // order.  Each XCD has its range of the exact-branch pairs (the long items) of all (batch, head)s (xcd_first, head_at) and
+  // order.  Each XCD has its range of the exact-branch pairs (the long items) of all (batch, head)s (long_item_at) and
   // works through them one head after the other, so
   // that the workgroups that run together on it (and share its L2) read the same head's keys and values.  The Taylor
   // groups (short items) belong to no XCD: the workgroups that come after an XCD's long items take them from one
@@ -272,14 +305,14 @@ __device__ __forceinline__ void attn_sp_item(const MfmaArgs& a, uint16_t* lds, c
   const int split_slot = counted ? taken - a.ctr_whole : xcd * a.n_split + (item - n_whole);
   // A Taylor work item is a group of up to `tgroup` consecutive pairs of one head, handled one after the other (all of
   // them read the same sequence of mean tiles); an exact-branch item is one pair.
-  const int n_bh = a.geo.B * a.geo.H;
-  const long long n_long_items = (long long)n_bh * a.slots_first;
-  const int numbered = counted ? item : xcd_first(n_long_items, xcd) + item;   // counted items are numbered over all (batch, head)s
-  if (!counted && numbered >= xcd_first(n_long_items, xcd + 1)) return;
-  const int hl = numbered / (taylor ? a.groups_second : a.slots_first);
-  int slot = taylor ? (item % a.groups_second) * a.tgroup : numbered % a.slots_first;   // (first) pair index inside its branch
-  if (hl >= n_bh) return;
-  const int bhid = counted ? hl : head_at(hl, n_bh);
+  int bhid, slot;                                               // slot: (first) pair index inside its branch
+  if (counted) {                                                // numbered over all (batch, head)s
+    bhid = item / (taylor ? a.groups_second : a.slots_first);
+    slot = taylor ? (item % a.groups_second) * a.tgroup : item % a.slots_first;
+    if (bhid >= a.geo.B * a.geo.H) return;
+  } else if (!long_item_at(a, xcd, item, bhid, slot)) {
+    return;
+  }
   const int h = bhid % a.geo.H, b = bhid / a.geo.H;
   const BatchCounts c = a.cnt.b[b];
   const int T_max = a.geo.T_max;
@@ -732,7 +765,7 @@ __global__ __launch_bounds__(512, 1) void k_attn_sp(MfmaArgs a) {
 // pair, 8 query rows); 32 threads per row, 4 channels each.
 __global__ __launch_bounds__(256) void k_split_merge(MfmaArgs a) {
   const int rows8 = blockIdx.x & 15, grp = (blockIdx.x >> 4) & 1;
-  const int split_slot = blockIdx.x >> 5, n_bh = a.geo.B * a.geo.H;
+  const int split_slot = blockIdx.x >> 5;
   int slot, bhid;
   if (a.long_ctr) {
     const int item = a.ctr_whole + split_slot;
@@ -740,11 +773,7 @@ __global__ __launch_bounds__(256) void k_split_merge(MfmaArgs a) {
     bhid = item / a.slots_first;
   } else {
     const int r = split_slot % a.n_split, xcd = split_slot / a.n_split;
-    const long long n_items = (long long)n_bh * a.slots_first;
-    const int item = xcd_first(n_items, xcd) + a.n_long - a.n_split + r;
-    if (item >= xcd_first(n_items, xcd + 1)) return;
-    slot = item % a.slots_first;
-    bhid = head_at(item / a.slots_first, n_bh);
+    if (!long_item_at(a, xcd, a.n_long - a.n_split + r, bhid, slot)) return;
   }
   const int h = bhid % a.geo.H, b = bhid / a.geo.H;
   const BatchCounts c = a.cnt.b[b];
@@ -840,6 +869,24 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
     m.slots_first = sf > 0 ? sf : 1;        // divisors in the kernel; a branch with no work gets no workgroups
     m.slots_second = ss > 0 ? ss : 1;
     m.n_long = (int)(((long long)pr.p.B * pr.p.H * sf + N_XCD - 1) / N_XCD);
+    m.ragged = 0;
+    auto list_of = [&](int b) { return a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new; };
+    auto pairs_of = [&](int b) { return ((a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].n_full) + 1) / 2; };
+    for (int b = 0; b < pr.p.B; ++b) {
+      int i = b;                                                // insertion by descending list length, equal ones as they come
+      for (; i > 0 && list_of(m.by_length[i - 1]) < list_of(b); --i) m.by_length[i] = m.by_length[i - 1];
+      m.by_length[i] = b;
+      if (pairs_of(b) != sf) m.ragged = 1;
+    }
+    if (m.ragged) {
+      for (int i = 0; i < pr.p.B; ++i) m.own_pairs[i] = pairs_of(m.by_length[i]);
+      m.n_long = 0;
+      for (int x = 0; x < N_XCD; ++x) {
+        int n = 0;
+        for (int i = 0; i < pr.p.B; ++i) n += xcd_first((long long)pr.p.H * m.own_pairs[i], x + 1) - xcd_first((long long)pr.p.H * m.own_pairs[i], x);
+        m.n_long = n > m.n_long ? n : m.n_long;
+      }
+    }
     // Taylor pairs go in groups of up to TAYLOR_GROUP consecutive pairs of a head per workgroup
     // (fewer when there are not enough pairs for a group per compute unit: then the pairs of a group would only wait for
     // each other)
@@ -852,8 +899,8 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
     m.taylor_ctr = ws.taylor_ctr;
     // An XCD runs one workgroup per compute unit, so its long items go in rounds of `cus`; when the last round is at
     // most half full, its items are cut into as many key ranges as fill it, of two blocks or more, or of one block in up to 8
-    // ranges (a merge reads every range).  Where that round is the only one and the ranges would be as short as the work of a
-    // Taylor group (less than four blocks), the workgroups of the groups need their compute units too.  Measured, 5 heads of 990
+    // ranges (a merge reads every range).  Where that round is the only one and the ranges (of the longest lists) would be as short as the
+    // work of a Taylor group (less than four blocks), the workgroups of the groups need their compute units too.  Measured, 5 heads of 990
     // tokens (7 key blocks), kernel + merge: whole items 31.9 us, ranges of two blocks 25.5, of one 23.5; whole call, 8 heads
     // of 3200 tokens without / with room for the groups 73 / 65 us, 12 heads of 1564 66 / 60; 2 heads of 9360 tokens (ranges of 5
     // blocks) 77 / 79.
@@ -867,13 +914,10 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
     m.split_o = ws.split_o; m.split_ml = ws.split_ml;
     const int cus = cus_per_xcd(), rem = m.n_long % cus;
     int min_list = 1 << 30;
-    for (int b = 0; b < pr.p.B; ++b) {
-      const int nl = a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new;
-      min_list = nl < min_list ? nl : min_list;
-    }
+    for (int b = 0; b < pr.p.B; ++b) min_list = list_of(b) < min_list ? list_of(b) : min_list;
     if (rem > 0 && rem <= cus / 2 && ws.split_o) {
       int parts = cus / rem;
-      if (m.n_long < cus && 4 * parts > min_list) parts = (cus - (m.n_taylor_wg < cus / 2 ? m.n_taylor_wg : cus / 2)) / rem;
+      if (m.n_long < cus && 4 * parts > list_of(m.by_length[0])) parts = (cus - (m.n_taylor_wg < cus / 2 ? m.n_taylor_wg : cus / 2)) / rem;
       int most = min_list / 2 > 8 ? min_list / 2 : (min_list < 8 ? min_list : 8);
       if (m.n_long > cus && ss > 0) most = min_list / (rem <= 2 ? 4 : 8);
       if (parts > most) parts = most;
@@ -893,8 +937,8 @@ hipError_t launch_attn_mfma(const Problem& pr, const Workspace& ws, const AttnAr
     m.long_ctr = nullptr; m.n_long_all = 0; m.ctr_whole = 0;
     int n_merge = N_XCD * m.n_split;
     const bool cut = min_list >= 16;
-    if (ss == 0 && m.n_long >= (cut ? 8 : 64) * cus) {
-      const int all = (int)((long long)pr.p.B * pr.p.H * sf);
+    const int all = (int)((long long)pr.p.B * pr.p.H * sf);                // (numbered over all (batch, head)s alike)
+    if (ss == 0 && (all + N_XCD - 1) / N_XCD >= (cut ? 8 : 64) * cus) {
       m.long_ctr = ws.taylor_ctr + 1;
       m.parts = cut ? 4 : 1;
       n_merge = cut ? SPLIT_MAX_SUB / m.parts : 0;

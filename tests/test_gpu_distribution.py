@@ -214,3 +214,34 @@ def test_last_round_of_short_lists(I, H, src, ctx, full_frac):
     n_long = -(-H * ((c["n_full"] + 1) // 2) // 8)
     assert n_long > 32 and 0 < n_long % 32 <= 16                                         # the premise
     check_end_to_end(I, wl, *gen(wl), heads=[0, H // 2, H - 2, H - 1])
+
+
+# ragged batches: an equal range of every batch item's own pairs per XCD, the longest lists first, whatever the order of the items; heads
+# that 8 does not divide, an item without long items, cut items of both lengths, more than a round
+@pytest.mark.parametrize("lens", [(2000, 100, 1000), (100, 1000, 2000), (600, 900, 900)], ids=["longest_first", "longest_last", "two_alike"])
+@pytest.mark.parametrize("H,full_frac", [(1, 0.4), (3, 0.0), (5, 1.0), (12, 0.3), (30, 0.6)])
+def test_ragged_batches(I, lens, H, full_frac):
+    src = (1, 1, 300)
+    wl = _wl(H, src, tuple(((1, 1, n),) for n in lens), B=3, keep_ratio=0.7, full_frac=full_frac, exact_frac=0.2 if H == 12 else 0.0, seed=930 + H)
+    check_end_to_end(I, wl, *gen(wl), heads=[0, H // 2, H - 1])
+
+
+@pytest.mark.parametrize("lens", [(3000, 100, 1620), (100, 1620, 3000)], ids=["longest_first", "longest_last"])
+@pytest.mark.parametrize("H", [1, 9, 14])
+def test_ragged_dense(I, lens, H):
+    import torch
+    from oracle import isa_oracle as O
+    from test_gpu_parity import TOL
+    from util import err_stats, f64
+    g = torch.Generator(device="cuda").manual_seed(940 + H)
+    q, k, v = (torch.randn((3, H, 3000, 128), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    pr = I.Problem(H=H, D=128, dtype="bf16", block=128, seg_len=[[n] for n in lens], keep_ratio=1.0, full_frac=1.0)
+    out = torch.full_like(q, float("nan"))
+    I.isa_dense_attention(pr, q, k, v, out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        assert torch.isfinite(out[b, :, :n]).all() and torch.isnan(out[b, :, n:]).all()
+        for h in {0, H // 2, H - 1}:
+            rows = slice(0, n, 7)
+            emax, emean = err_stats(f64(out[b, h, :n][rows]), O.dense_attention(f64(q[b, h, :n][rows]), f64(k[b, h, :n]), f64(v[b, h, :n])))
+            assert emax <= TOL["bf16"][0] and emean <= TOL["bf16"][1], (b, h, emax, emean)
