@@ -14,7 +14,7 @@
 // keeps 2 x 128 "stationary" rows in registers and streams 64-row tiles of the other side through LDS; per tile it forms
 // T1 = Y1 X1^T (the scores) and, for dS (all but dVc), T2 = Y2 X2^T (dP), turns them into W = P or dS in registers and accumulates acc^T += Yt W^T, where Yt is the
 // transpose of a streamed tile: its fragments are read out of the row-major tile in LDS with ds_read_b64_tr_b16, in the
-// key order of the 16x16x32 accumulators, so no transposed copy of any tensor exists.  The three launches:
+// key order of the 16x16x32 accumulators, so no transposed copy of any tensor exists.  Three kinds of items, one launch:
 //     dQ, exact branch : stationary (Q, dO) of the full-attention blocks,  streamed K, V of the kept tokens (Yt = K^T)
 //     dQ, Taylor branch: stationary (Q, dO) of the Taylor blocks,          streamed Kc, Vc (block means), after the
 //                        K, V tiles of the blocks' exact sets
@@ -102,11 +102,11 @@ struct BwdArgs {
   int Tn_pad, S_max;
   int items;                                  // work items (pairs of stationary blocks) per (batch, head) in this launch
   // mean rows only: every item runs as `parts` workgroups, each over its share of the streamed entries, and writes its
-  // partial sums to out_f32 + part * part_stride (k_bwd_mean_sums adds them up)
+  // partial sums to out_f32 + part * part_stride (k_bwd_merge adds them up)
   int parts; long long part_stride;
   // token rows: the last tail_items items of every XCD (its last, incomplete round over the compute
   // units) run as tail_parts workgroups each, every one over its share of the streamed entries of each phase; they leave their
-  // unscaled fp32 sums in tail_scratch [XCD][tail item][part][256 rows][128] and k_bwd_tail_merge writes the rows
+  // unscaled fp32 sums in tail_scratch [XCD][tail item][part][256 rows][128] and k_bwd_merge writes the rows
   int items_xcd, tail_items, tail_parts;
   float* tail_scratch;
   // token rows: null, or a counter (0 when the launch starts) from which every workgroup takes the number of its item,
@@ -121,7 +121,7 @@ struct BwdArgs {
 // streamed block; 2 (queries) streamed tiles masked or not for a stationary block, and single positions of a tile of gathered means.
 template <bool SM, bool T2, int EX>
 __device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, const int wg, float* const out_f32, const float oscale) {
-  static_assert(SM ? EX == 0 || EX == 1 : T2 && (EX == 0 || EX == 2), "what the three launches use");
+  static_assert(SM ? EX == 0 || EX == 1 : T2 && (EX == 0 || EX == 2), "what the launch uses");
   constexpr bool YD = SM && T2;                              // minus-deltas of the streamed rows start T2
   constexpr int STG = EX == 2 ? STAGE + K_TILE : STAGE;      // EX == 2: a third tile per stage (see BwdStream::y3)
   // Workgroup ids go round-robin over the 8 XCDs: XCD x has its range of the items of all (batch, head)s (xcd_first, head_at) and
@@ -589,22 +589,25 @@ __device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, 
   }
 }
 
-// dQ: stationary token rows
+// dQ of both branches and the mean-row launch (dKc, then dVc) in one launch: workgroups 0 .. wgs_full - 1 take the exact branch's items (the
+// longest), then come the Taylor branch's, then wgs_means for each of dKc and dVc; all three counts are multiples of the XCDs.
+// None reads what another writes, and each alone leaves compute units idle at its end (all of the time, if it is small).  Measured, three
+// launches / one, a training step of 12 heads of 1564 tokens 211 / 190 us (78 / 33 of them in these launches and their merges), 40 heads of
+// 15 600 tokens with the residual 4460 / 4406, 65 520 tokens at the paper's ratios 99.6 / 99.0 ms.
+struct BwdTokensArgs { BwdArgs full, flat, means; float* dvc; int wgs_full, wgs_flat, wgs_means; };
 template <int EX>
-__global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdArgs a) {
-  __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * (EX == 2 ? STAGE + K_TILE : STAGE) + 2 * SIDE_BYTES / 2];
-  attn_bwd<false, true, EX>(a, lds, blockIdx.x, nullptr, a.oscale);
-}
-
-// dKc (the first half of the workgroups) and dVc, stationary gathered means, in one launch: either alone leaves most of the chip
-// idle (measured, a training step, two launches / one: 12 heads of 1564 tokens with exact sets 233 / 219 us, 40 heads of 15 600
-// tokens with the residual 4490 / 4435)
-template <int EX>
-__global__ __launch_bounds__(512, 1) void k_attn_bwd_means(BwdArgs a, float* dvc) {
-  __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * STAGE + 2 * SIDE_BYTES / 2];
-  const int half = gridDim.x / 2;                      // a multiple of the XCDs
-  if ((int)blockIdx.x < half) attn_bwd<true, true, EX>(a, lds, blockIdx.x, a.out_f32, a.oscale);
-  else attn_bwd<true, false, EX>(a, lds, (int)blockIdx.x - half, dvc, 1.0f);
+__global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdTokensArgs p) {
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * (EX ? STAGE + K_TILE : STAGE) + 2 * SIDE_BYTES / 2];
+  int wg = blockIdx.x;
+  if (wg < p.wgs_full) {
+    attn_bwd<false, true, 0>(p.full, lds, wg, nullptr, p.full.oscale);
+  } else if ((wg -= p.wgs_full) < p.wgs_flat) {
+    attn_bwd<false, true, EX ? 2 : 0>(p.flat, lds, wg, nullptr, p.flat.oscale);
+  } else if ((wg -= p.wgs_flat) < p.wgs_means) {
+    attn_bwd<true, true, EX>(p.means, lds, wg, p.means.out_f32, p.means.oscale);
+  } else {
+    attn_bwd<true, false, EX>(p.means, lds, wg - p.wgs_means, p.dvc, 1.0f);
+  }
 }
 
 // delta[bh][token] = sum_d dO * O (fp32); 16 lanes per token row, 16 bytes per lane and tensor.  O is taken as out + olo:
@@ -964,28 +967,30 @@ static hipError_t launch_bwd_coarse(const Problem& pr, const Workspace& ws, hipS
   return hipGetLastError();
 }
 
-// Gradients of the gathered means, dKc and dVc (blockIdx.z = 2 * batch item + which): the partial sums of the `parts` parts of the
-// launch over the mean rows (0: there was none) plus, with the coarse residual, its gradient of the same mean (coarse, by
-// block id), into part 0.  One workgroup per gathered mean row.
-__global__ __launch_bounds__(128) void k_bwd_mean_sums(float* __restrict__ dkc, float* __restrict__ dvc, int parts, long long part_stride,
-                                                       const float* __restrict__ coarse_k, const float* __restrict__ coarse_v,
-                                                       const int* __restrict__ kv_list, Counts cnt, int H, int Tn_pad) {
-  const int e = blockIdx.x, h = blockIdx.y, b = blockIdx.z >> 1, d = threadIdx.x;
+// Gradients of the gathered means, dKc and dVc: the partial sums of the `parts` parts of the launch over the mean rows (0: there was
+// none) plus, with the coarse residual, its gradient of the same mean (coarse, by block id), into part 0.  Two gathered mean rows per
+// workgroup, 128 threads each; workgroups: {row pair} x H x {2 * batch item + which}.
+struct MeanSums { float *dkc, *dvc; const float *coarse_k, *coarse_v; const int* kv_list; int parts, rows2; long long part_stride; };
+__device__ __forceinline__ void bwd_mean_sums(const MeanSums& m, int wg, const Counts& cnt, int H, int Tn_pad) {
+  const int e = wg % m.rows2 * 2 + (threadIdx.x >> 7), d = threadIdx.x & 127;
+  wg /= m.rows2;
+  const int h = wg % H, b = wg / H >> 1;
+  const bool dv = wg / H & 1;
   if (e >= cnt.b[b].T_new) return;
-  float* const g = blockIdx.z & 1 ? dvc : dkc;
-  const float* const coarse = blockIdx.z & 1 ? coarse_v : coarse_k;
+  float* const g = dv ? m.dvc : m.dkc;
+  const float* const coarse = dv ? m.coarse_v : m.coarse_k;
   const long long bh = (long long)b * H + h, i = (bh * Tn_pad + e) * MD + d;
-  float sum = parts > 0 ? g[i] : 0.f;
-  for (int p = 1; p < parts; ++p) sum += g[p * part_stride + i];
-  if (coarse) sum += coarse[(bh * cnt.T_max + block_in_range(kv_list[bh * cnt.T_max + e], cnt.b[b].T)) * MD + d];
+  float sum = m.parts > 0 ? g[i] : 0.f;
+  for (int p = 1; p < m.parts; ++p) sum += g[p * m.part_stride + i];
+  if (coarse) sum += coarse[(bh * cnt.T_max + block_in_range(m.kv_list[bh * cnt.T_max + e], cnt.b[b].T)) * MD + d];
   g[i] = sum;
 }
 
 // Adds up the parts of the tail items of a token-row launch and writes their rows: what the attention kernel's own store
 // does for whole items.  One workgroup per (XCD, tail item, block of the pair, 8 rows); 32 threads per row, 4 channels each.
-__global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
-  const int rows8 = blockIdx.x & 15, grp = (blockIdx.x >> 4) & 1;
-  const int slot = blockIdx.x >> 5, n_bh = a.geo.B * a.geo.H;
+__device__ __forceinline__ void bwd_tail_merge(const BwdArgs& a, int wg) {
+  const int rows8 = wg & 15, grp = (wg >> 4) & 1;
+  const int slot = wg >> 5, n_bh = a.geo.B * a.geo.H;
   int item, bhid;
   if (a.dyn_ctr) {
     item = (a.dyn_whole + slot) % a.items;
@@ -1036,21 +1041,35 @@ __global__ __launch_bounds__(256) void k_bwd_tail_merge(BwdArgs a) {
   *reinterpret_cast<uint2*>(a.out_bf + tbase + (long long)(x_start + row) * a.geo.stride_t + ch) = o;
 }
 
-// A dQ launch.  split_units: into how many parts the streamed side can be cut (list entries or tiles of means).
-static hipError_t launch_dq(BwdArgs a, bool ex, int B, int H, hipStream_t st, int split_units, int* dyn_ctr, int min_dyn) {
-  if (a.items <= 0) return hipSuccess;
-  const int cus = cus_per_xcd();
+// Both, behind the launch whose parts they add up: the first wgs_full workgroups merge the exact branch's cut items, the next
+// wgs_flat the Taylor branch's, the rest sum the means' gradients.
+struct BwdMergeArgs { BwdArgs full, flat; MeanSums means; int wgs_full, wgs_flat; };
+__global__ __launch_bounds__(256) void k_bwd_merge(BwdMergeArgs p) {
+  const int wg = blockIdx.x;
+  if (wg < p.wgs_full) bwd_tail_merge(p.full, wg);
+  else if (wg < p.wgs_full + p.wgs_flat) bwd_tail_merge(p.flat, wg - p.wgs_full);
+  else bwd_mean_sums(p.means, wg - p.wgs_full - p.wgs_flat, p.full.cnt, p.full.geo.H, p.full.Tn_pad);
+}
+
+// Distribution of the dQ items of one branch: sets the fields of `a` that say which items are cut and returns the number of workgroups
+// (a multiple of the XCDs).  split_units: into how many parts the streamed side can be cut (list entries or tiles of means); one_round: 0,
+// or the parts every item is cut into; n_sub: sub-items that the partial-result area already holds; n_merge: cut items.
+static int plan_dq(BwdArgs& a, int B, int H, int split_units, int* dyn_ctr, int min_dyn, int one_round, int& n_sub, int& n_merge) {
+  n_merge = 0;
+  a.dyn_ctr = nullptr; a.items_xcd = 0; a.tail_items = 0; a.tail_parts = 1; a.dyn_whole = a.dyn_total = 0;
+  if (a.items <= 0) { a.items = 0; return 0; }
+  const int cus = cus_per_xcd(), room = SPLIT_MAX_SUB - n_sub;
+  a.tail_scratch += (long long)n_sub * 256 * MD;
   a.items_xcd = (int)(((long long)a.items * B * H + N_XCD - 1) / N_XCD);
-  a.tail_items = 0; a.tail_parts = 1;
   // items from a counter only where an XCD has min_dyn of them: fewer are cut into parts instead
-  a.dyn_ctr = a.items_xcd < min_dyn ? nullptr : dyn_ctr;
-  if (!a.dyn_ctr && split_units > 1 && a.tail_scratch) {
+  a.dyn_ctr = one_round || a.items_xcd < min_dyn ? nullptr : dyn_ctr;
+  if (!a.dyn_ctr && split_units > 1) {
     // the last round of an XCD's 32 compute units: if at most half of them would have an item, cut those items
-    const int t = a.items_xcd % cus;
-    if (t > 0 && t <= cus / 2) {
-      int parts = cus / t > 8 ? 8 : cus / t;
+    const int t = one_round ? a.items_xcd : a.items_xcd % cus;
+    if (t > 0 && (one_round || t <= cus / 2)) {
+      int parts = one_round ? one_round : cus / t > 8 ? 8 : cus / t;
       if (parts > split_units) parts = split_units;
-      while (parts > 1 && N_XCD * t * parts > SPLIT_MAX_SUB) --parts;       // the partial-result area holds SPLIT_MAX_SUB sub-items
+      while (parts > 1 && N_XCD * t * parts > room) --parts;       // the partial-result area holds SPLIT_MAX_SUB sub-items
       if (parts > 1) { a.tail_items = t; a.tail_parts = parts; }
     }
   }
@@ -1059,23 +1078,19 @@ static hipError_t launch_dq(BwdArgs a, bool ex, int B, int H, hipStream_t st, in
   // likewise: training step 101.35 -> 100.85 ms, at keep 0.5, full 0.2 52.3 -> 51.9.
   a.dyn_whole = a.items * B * H;
   a.dyn_total = a.dyn_whole;
-  int n_merge = N_XCD * a.tail_items;
-  if (a.dyn_ctr && a.items_xcd >= 8 * cus && split_units >= 16 && a.tail_scratch) {
+  n_merge = N_XCD * a.tail_items;
+  if (a.dyn_ctr && a.items_xcd >= 8 * cus && split_units >= 16 && room == SPLIT_MAX_SUB) {
     a.tail_parts = 8;
     n_merge = SPLIT_MAX_SUB / a.tail_parts;
     a.dyn_whole -= n_merge;
     a.dyn_total += n_merge * (a.tail_parts - 1);
   }
+  n_sub += n_merge * a.tail_parts;
   // dynamic items: an eighth more workgroups than items and one round of the chip, so that the faster XCDs do not run out
   // of workgroups before the items run out
   const long long n_dyn = a.dyn_total;
-  const long long dyn_wgs = ((n_dyn + n_dyn / 8) / N_XCD + cus_per_xcd() + 1) * N_XCD;
-  const dim3 grid((unsigned)(a.dyn_ctr ? dyn_wgs : (a.items_xcd - a.tail_items + a.tail_items * a.tail_parts) * 8));
-  if (ex) hipLaunchKernelGGL((k_attn_bwd<2>), grid, dim3(512), 0, st, a);
-  else hipLaunchKernelGGL((k_attn_bwd<0>), grid, dim3(512), 0, st, a);
-  if (n_merge > 0)
-    hipLaunchKernelGGL(k_bwd_tail_merge, dim3((unsigned)(n_merge * 32)), dim3(256), 0, st, a);
-  return hipGetLastError();
+  const long long dyn_wgs = ((n_dyn + n_dyn / 8) / N_XCD + cus + 1) * N_XCD;
+  return (int)(a.dyn_ctr ? dyn_wgs : (a.items_xcd - a.tail_items + a.tail_items * a.tail_parts) * N_XCD);
 }
 
 hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q, const void* k, const void* v,
@@ -1141,6 +1156,8 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
 
   // ---- dQ: exact branch over the kept tokens; Taylor branch over the tokens of each block's exact
   // set and the means of the other kept blocks
+  BwdMergeArgs mg;
+  BwdTokensArgs tk;
   const BwdStream kept_tokens = {K, V, nullptr, ws.ktab, ws.ybd_kv, false, 0};
   const uint16_t* mean_keys = ws.kcn;             // stored minus the mean key of block 0
   const BwdStream kept_means = {mean_keys, ws.vcn, ex ? ws.kcnb : nullptr, nullptr, ws.ybd_mean, false, 0};
@@ -1149,7 +1166,7 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   a.add_rows = resid ? ws.cdq : nullptr;          // every query block's share of dQc
   a.stat_list = full_list; a.stat_flat = false; a.items = (sf + 1) / 2;
   a.s[0] = kept_tokens; a.s[1] = none; a.n_phases = 1; a.bits = nullptr;
-  if ((e = launch_dq(a, false, B, H, st, min_kept, ws.bwd_ctr + 2, 8 * cus_per_xcd())) != hipSuccess) return e;
+  tk.full = a;
   a.stat_list = flat_list; a.stat_flat = true; a.items = (sl + 1) / 2;
   if (ex) {
     a.s[0] = kept_tokens; a.s[0].masked = 1;
@@ -1159,36 +1176,58 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   } else {
     a.s[0] = kept_means; a.n_phases = 1;
   }
-  if ((e = launch_dq(a, ex, B, H, st, (min_kept + KT - 1) / KT, ws.bwd_ctr + 0,
-                                           min_kept > KT ? cus_per_xcd() / 2 + 1 : 0)) != hipSuccess) return e;
-
+  tk.flat = a;
   // ---- dKc, dVc: gradients of the gathered means (streamed Q, dO of every Taylor block, minus its exact set)
-  // dKc: W = dS, read Q transposed; dVc: W = P, dO transposed.  The launch has few items (two per 256 gathered means and head):
-  // each is cut into up to BWD_MEAN_PARTS parts along the streamed entries, as many as make the launch's rounds over the 256
-  // compute units shortest.
-  int mean_parts = 0;
-  if (sl > 0 && sk > 0) {
-    const int n_mean_pairs = ((sk + 127) / 128 + 1) / 2;
+  // dKc: W = dS, read Q transposed; dVc: W = P, dO transposed.
+  const int n_mean_pairs = sl > 0 && sk > 0 ? ((sk + 127) / 128 + 1) / 2 : 0;
+  a.x1 = mean_keys; a.x2 = ws.vcn; a.stat_list = nullptr; a.bx = ws.bx_mean; a.dx = nullptr; a.rx = nullptr;
+  a.s[0] = {Q, DO, nullptr, ws.ltab, ex ? ws.ybd_flatm : ws.ybd_flat, true, ex ? 3 : 0};      // scored against gathered means
+  a.s[1] = none; a.n_phases = 1; a.bits = ws.mask_t;
+  a.out_bf = nullptr; a.out_f32 = ws.dkc; a.add_rows = nullptr; a.items = n_mean_pairs;
+  a.part_stride = (long long)B * H * pr.Tn_pad * MD;
+  a.dyn_ctr = nullptr;
+  tk.means = a; tk.dvc = ws.dvc;
+  // The mean rows have few items (two per 256 gathered means and head): each is cut into up to BWD_MEAN_PARTS parts along the streamed
+  // entries, as many as make their rounds over the compute units shortest.  Where all three kinds of items fit one round, the
+  // exact branch's and the means' parts are those with the shortest longest part (in streamed tiles) that still fit it.
+  const int cus = cus_per_xcd();
+  int mean_parts = 0, one_round = 0;
+  const auto per_xcd = [&](int items) { return (int)(((long long)items * B * H + N_XCD - 1) / N_XCD); };
+  const int e_xcd = per_xcd(tk.full.items), l_xcd = per_xcd(tk.flat.items), m_xcd = per_xcd(n_mean_pairs);
+  if (n_mean_pairs > 0) {
     double best = 1e30;
     for (int p = 1; p <= BWD_MEAN_PARTS; ++p) {
-      const long long chip = (long long)cus_per_xcd() * N_XCD, wgs = 2ll * n_mean_pairs * B * H * p;
+      const long long chip = (long long)cus * N_XCD, wgs = 2ll * n_mean_pairs * B * H * p;
       const double rounds = (double)((wgs + chip - 1) / chip) / p;
       if (rounds < best - 1e-9) { best = rounds; mean_parts = p; }
     }
-    a.x1 = mean_keys; a.x2 = ws.vcn; a.stat_list = nullptr; a.bx = ws.bx_mean; a.dx = nullptr; a.rx = nullptr;
-    a.s[0] = {Q, DO, nullptr, ws.ltab, ex ? ws.ybd_flatm : ws.ybd_flat, true, ex ? 3 : 0};      // scored against gathered means
-    a.s[1] = none; a.n_phases = 1; a.bits = ws.mask_t;
-    a.out_bf = nullptr; a.out_f32 = ws.dkc; a.add_rows = nullptr; a.items = n_mean_pairs;
-    a.parts = mean_parts; a.part_stride = (long long)B * H * pr.Tn_pad * MD;
-    a.dyn_ctr = nullptr;
-    const dim3 grid((unsigned)(2 * (((long long)n_mean_pairs * mean_parts * B * H + N_XCD - 1) / N_XCD * N_XCD)));
-    if (ex) hipLaunchKernelGGL((k_attn_bwd_means<1>), grid, dim3(512), 0, st, a, ws.dvc);
-    else hipLaunchKernelGGL((k_attn_bwd_means<0>), grid, dim3(512), 0, st, a, ws.dvc);
+  }
+  if (e_xcd > 0 && e_xcd + l_xcd + 2 * m_xcd <= cus) {
+    int best = 1 << 30;
+    for (int pe = 1; pe <= 8 && pe <= min_kept; ++pe)
+      for (int pm = n_mean_pairs > 0 ? 1 : 0; pm <= (n_mean_pairs > 0 ? BWD_MEAN_PARTS : 0); ++pm) {
+        if (e_xcd * pe + l_xcd + 2 * per_xcd(n_mean_pairs * pm) > cus) continue;
+        const int longest_e = (sk + pe - 1) / pe, longest_m = pm > 0 ? (sl + pm - 1) / pm : 0, longest = longest_e > longest_m ? longest_e : longest_m;
+        if (longest < best) { best = longest; one_round = pe; mean_parts = pm; }
+      }
+  }
+  tk.means.parts = mean_parts > 0 ? mean_parts : 1;
+  int n_sub = 0, n_merge_full = 0, n_merge_flat = 0;
+  tk.wgs_full = plan_dq(tk.full, B, H, min_kept, ws.bwd_ctr + 2, 8 * cus, one_round, n_sub, n_merge_full);
+  tk.wgs_flat = plan_dq(tk.flat, B, H, (min_kept + KT - 1) / KT, ws.bwd_ctr + 0, min_kept > KT ? cus / 2 + 1 : 0, 0, n_sub, n_merge_flat);
+  tk.wgs_means = n_mean_pairs > 0 ? N_XCD * per_xcd(n_mean_pairs * mean_parts) : 0;
+  const int wgs = tk.wgs_full + tk.wgs_flat + 2 * tk.wgs_means;
+  if (wgs > 0) {
+    if (ex) hipLaunchKernelGGL((k_attn_bwd<1>), dim3((unsigned)wgs), dim3(512), 0, st, tk);
+    else hipLaunchKernelGGL((k_attn_bwd<0>), dim3((unsigned)wgs), dim3(512), 0, st, tk);
     ISA_BWD_CHECK();
   }
-  if (sk > 0 && (mean_parts > 1 || resid)) {
-    hipLaunchKernelGGL(k_bwd_mean_sums, dim3(sk, H, 2 * B), dim3(128), 0, st, ws.dkc, ws.dvc, mean_parts,
-                       (long long)B * H * pr.Tn_pad * MD, resid ? ws.cdk : nullptr, resid ? ws.cdv : nullptr, kv_list, pr.cnt, H, pr.Tn_pad);
+  mg.full = tk.full; mg.flat = tk.flat;
+  mg.wgs_full = n_merge_full * 32; mg.wgs_flat = n_merge_flat * 32;
+  mg.means = {ws.dkc, ws.dvc, resid ? ws.cdk : nullptr, resid ? ws.cdv : nullptr, kv_list, mean_parts, (sk + 1) / 2, tk.means.part_stride};
+  const int wgs_sums = sk > 0 && (mean_parts > 1 || resid) ? mg.means.rows2 * H * 2 * B : 0;
+  if (mg.wgs_full + mg.wgs_flat + wgs_sums > 0) {
+    hipLaunchKernelGGL(k_bwd_merge, dim3((unsigned)(mg.wgs_full + mg.wgs_flat + wgs_sums)), dim3(256), 0, st, mg);
     ISA_BWD_CHECK();
   }
   // ---- dK, dV of the kept tokens: every full-attention block, the Taylor blocks whose exact set holds the block, and

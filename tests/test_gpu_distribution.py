@@ -44,6 +44,18 @@ def test_backward(I, H, exact_frac):
     backward_matches_the_oracle(I, wl)
 
 
+# dQ of both branches and the mean rows in one launch: 48 heads of 3 + 2 blocks are the most that fit one round of the chip (items cut for
+# one round), 49 are the first that do not; one head has room for the most parts
+@pytest.mark.parametrize("exact_frac", [0.0, 0.3])
+@pytest.mark.parametrize("H", [1, 48, 49])
+def test_backward_one_launch(I, H, exact_frac):
+    wl = _wl(H, (1, 6, 64), (((1, 3, 70),),), keep_ratio=0.5, full_frac=0.6, exact_frac=exact_frac, seed=865 + H)
+    c = I.isa_get_counts(I.Problem(H=H, D=128, dtype="bf16", block=128, seg_len=[wl.seg_len(0)], keep_ratio=0.5, full_frac=0.6), 0)
+    assert (c["n_full"], c["n_flat"]) == (3, 2)
+    assert (-(-2 * H // 8) + 3 * -(-H // 8) <= 32) == (H <= 48)      # items of an XCD: two pairs, one pair, one group of means twice
+    backward_matches_the_oracle(I, wl)
+
+
 # one streamed entry only (not to be cut), two, and a ragged batch whose shorter item has fewer entries than parts
 @pytest.mark.parametrize("full_frac", [0.05, 0.25])
 def test_backward_few_streamed_entries(I, full_frac):
