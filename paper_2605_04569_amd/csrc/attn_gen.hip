@@ -15,9 +15,9 @@
 // second product (O^T = V^T P^T), so the weights never leave their registers; V is read transposed out of its row-major
 // tile (ds_read_b64_tr_b16 for bf16; for fp32 a lane's four channels of a row serve four output tiles).  Tiles of 64
 // bf16 (32 fp32) rows go global -> LDS directly, one tile ahead, two stages, 16-byte chunks XOR-swizzled by row.  A stage
-// is 256 D bytes either way.  Short launches give a workgroup two such groups of 4 waves (NG = 2 below).  Groups that share a
-// compute unit, whose softmax runs beside each other's matrix instructions (there is no hand-made interleaving here): D = 128, 66 KB
-// a group, two (two workgroups, or one of two groups); D = 64, 33 KB, three of QT = 2 (registers) or four of QT = 1.
+// is 256 D bytes either way.  A launch with few long items cuts their key lists into parts, a workgroup each, and a second kernel adds
+// them up.  Workgroups that share a compute unit, whose softmax runs beside each other's matrix instructions (there is no hand-made
+// interleaving here): D = 128, 66 KB each, two; D = 64, 33 KB, three of QT = 2 (registers) or four of QT = 1.
 //
 // What bounds it (measured, 24 heads of 64 channels, 15 600 tokens in blocks of 64, keep 0.5, full 0.25): instruction issue. A weight
 // costs 9.4 vector instructions (5.5 of them the exact cut into three terms; taking the differences with the bf16 dot
@@ -38,7 +38,9 @@ namespace {
 
 constexpr float FAST_MAX = 16777216.f;    // 2^24, log2 domain: a maximum below is rounded by half at most
 
-template <int D> constexpr int GROUP_LDS = 512 * D + 2 * 64 * 4;         // two stages of a K and a V tile, weights of mean tiles
+template <int D> constexpr int ITEM_LDS = 512 * D + 2 * 64 * 4;          // two stages of a K and a V tile, weights of mean tiles
+template <int D, int QT> constexpr int RESIDENT = D == 128 ? 2 : QT == 1 ? 4 : 3;     // workgroups of a compute unit: LDS, registers (D = 64, QT = 2)
+constexpr int MAX_PARTS = 8;
 
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4v* lds_s4_ptr;
@@ -47,6 +49,8 @@ struct GenArgs {
   AttnArgs a;
   int slots_long, slots_taylor;     // work items per (batch, head) of the exact branch / of the Taylor branch (largest of the batch)
   int per_xcd_long, per_xcd_taylor; // and per XCD, over all (batch, head)s
+  int parts;                        // 1, or every long item runs as this many workgroups, each over its share of the listed blocks; they leave
+  float* part_o; float2* part_ml;   //   [item][part][row][D] their normalised results and [item][part][row] {maximum, sum} (see store_part)
 };
 
 __device__ __forceinline__ void dma16(const void* src, uint32_t lds_addr) {      // lane i -> LDS bytes lds_addr + 16 i
@@ -103,10 +107,9 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 // 2^tau times a value near the largest number is none.  (Raising at once in the first pass cost fp32 1 % with 128 channels, 2.5 with
 // 64; a factor of 2^-tau in its weights cost values near the smallest normal number their last eight bits.)
 //
-// NG = 2: two groups of 4 waves work on the same rows, each with stages of its own, and take the tiles of the sequence in turn;
-// the second group hands its running maxima, sums and outputs to the first through LDS at the end.
-template <typename T, int D, int QT, bool FULL32, int NG>
-__device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* const lds_all, int bhid, bool taylor, int slot) {
+// PARTS: part >= 0 is the item's part of that number (a template, as whole items have no register to spare for it).  QI: the item's query tiles per wave (the second pass takes its rows 64 at a time).
+template <typename T, int D, int QT, bool FULL32, int QI, bool PARTS>
+__device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* const lds, int bhid, bool taylor, int slot, const int part) {
   constexpr bool BF = sizeof(T) == 2, WIDE = !BF || FULL32;
   constexpr int KTOK = BF ? 64 : 32;                   // tokens per tile; tiles of means hold 32
   constexpr int NT = D / 16;                           // 16-channel tiles
@@ -115,8 +118,6 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   constexpr int ST = (CT < 16 ? CT : 16) - 1, SM = 15; // swizzle: chunk c of row r sits at c ^ (r & S)
   constexpr int NI = D / 32;                           // 1 KB loads per wave, tile and tensor
   constexpr int ROWS = 64 * QT;
-  const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
-  unsigned char* const lds = lds_all + grp * GROUP_LDS<D>;
   const AttnArgs& a = ga.a;
   float* const wts = reinterpret_cast<float*>(lds + 4 * TILE);         // [stage][block of the item][32]: weights of a mean tile's slots
 
@@ -125,12 +126,14 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   const int T_max = a.geo.T_max, block = a.geo.block;
   const long long bh = bhid;
   const int* const kvl = a.dense ? nullptr : a.kv_list + bh * T_max;
-  const int n_kv = a.dense ? c.T : c.T_new;
+  const int n_list_kv = a.dense ? c.T : c.T_new;
+  const int kv_lo = !PARTS || part < 0 ? 0 : (int)((long long)part * n_list_kv / ga.parts);
+  const int n_kv = !PARTS || part < 0 ? n_list_kv : (int)((long long)(part + 1) * n_list_kv / ga.parts);
   const int* const bs = a.blk_start + b * T_max;
   const int* const bn = a.blk_n + b * T_max;
   const long long tbase = (long long)b * a.geo.stride_b + (long long)h * a.geo.stride_h;
 
-  const int tid = NG > 1 ? threadIdx.x & 255 : threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, g = lane >> 4;
 
@@ -174,7 +177,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 
   // ---- the sequence of tiles: the tokens of the listed blocks (Taylor: of the blocks of the exact sets), then, for
   // Taylor blocks, the means of the list.  The lanes hold the table rows of 64 list entries at a time.
-  int c_start = 0, c_n = 0, c_bits = 0, cbase = -64;
+  int c_start = 0, c_n = 0, c_bits = 0, cbase = kv_lo - 64;
   unsigned long long todo = 0ull;
   struct Tile { int start, nk, bits; bool mean, end; };
   Tile at = {0, 0, 3, false, false};                   // the tile that was described last
@@ -504,25 +507,16 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     }
   };
 
-  // ---- the loop: the loads of a group's next tile fly while its current one is multiplied
-  int n_first = 0, n_mine = 0;                         // tiles of the first group / of this one among those described
-  auto next_mine = [&]() -> Tile {
-    Tile mine = at;
-#pragma unroll
-    for (int u = 0; u < NG; ++u) {
-      if (!at.end) next_tile();
-      if (u == 0) n_first += at.end ? 0 : 1;
-      if (u == grp) mine = at;
-    }
-    return mine;
-  };
-  Tile cur = next_mine();
+  // ---- the loop: the loads of the next tile fly while the current one is multiplied
+  next_tile();
+  Tile cur = at;
   if (!cur.end) issue(cur, 0);
   int stage = 0;
   auto tiles = [&](const auto mean_c) __attribute__((always_inline)) {
     constexpr bool mean = decltype(mean_c)::value;
     for (; !cur.end && cur.mean == mean; stage ^= 1) {
-      const Tile nxt = next_mine();                    // its table reads wait together with the tile loads
+      next_tile();                                     // its table reads wait together with the tile loads
+      const Tile nxt = at;
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();                                 // the tile is complete; everybody has left the one before, whose stage is filled next
       if (!nxt.end) issue(nxt, stage ^ 1);
@@ -532,47 +526,12 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         for (int r0 = 0; r0 < cur.nk; r0 += 32) half(kb, kb + TILE, r0, cur.nk - r0, mean_c, wts + stage * 64 + own * 32);
       }
       cur = nxt;
-      ++n_mine;
     }
   };
   // two loops: the kinds of tile share no code path through which the accumulators would have to be moved
   tiles(std::false_type{});
   tiles(std::true_type{});
-  if (NG > 1 && n_mine < n_first) __syncthreads();     // the first group has had one tile, and one barrier, more
   __syncthreads();                                     // nobody reads LDS any more: the caller may start another pass
-
-  // ---- the second group's part (the merge step of the online softmax)
-  if constexpr (NG > 1) {
-    constexpr int W = QT * (4 * NT + 2);               // floats of a lane
-    float* const part = reinterpret_cast<float*>(lds_all + GROUP_LDS<D>) + wave * W * 64 + lane;
-    if (grp == 1) {
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) {
-        part[(qt * (4 * NT + 2)) * 64] = neg_m[qt];
-        part[(qt * (4 * NT + 2) + 1) * 64] = l_run[qt];
-#pragma unroll
-        for (int ct = 0; ct < NT; ++ct)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) part[(qt * (4 * NT + 2) + 2 + 4 * ct + i) * 64] = acc[ct][qt][i];
-      }
-    }
-    __syncthreads();
-    if (grp == 0) {
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) {
-        const float other = part[(qt * (4 * NT + 2)) * 64];
-        const float nm = fminf(neg_m[qt], other);      // minus the larger maximum
-        const float mine = factor(shift(nm) - neg_m[qt]), theirs = factor(shift(nm) - other);
-        neg_m[qt] = nm;
-        l_run[qt] = l_run[qt] * mine + part[(qt * (4 * NT + 2) + 1) * 64] * theirs;
-#pragma unroll
-        for (int ct = 0; ct < NT; ++ct)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) acc[ct][qt][i] = acc[ct][qt][i] * mine + part[(qt * (4 * NT + 2) + 2 + 4 * ct + i) * 64] * theirs;
-      }
-    }
-    __syncthreads();                                   // read before the caller's next pass fills the stages again
-  }
 
   // ---- normalise, check, store
   float inv[QT];
@@ -583,7 +542,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     inv[qt] = 1.0f / l;
-    if (grp == 0 && row0 + 16 * qt + r16 < n_q) {
+    if (row0 + 16 * qt + r16 < n_q) {
       if (!WIDE) ok = ok && fabsf(neg_m[qt]) < FAST_MAX;
 #pragma unroll
       for (int ct = 0; ct < NT; ++ct)
@@ -593,7 +552,30 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   }
   if constexpr (!FULL32)
     if (__syncthreads_or(!ok)) return false;
-  if (grp != 0) return true;
+  if (PARTS && part >= 0) {
+    // the item's number worked out again, not kept through the loop
+    int wg = blockIdx.x;
+    asm volatile("" : "+s"(wg));
+    const int x = wg & 7, idx = xcd_first((long long)a.geo.B * a.geo.H * ga.slots_long, x) + (wg >> 3) % ga.per_xcd_long;
+    const long long part_row = ((long long)idx * ga.parts + (wg >> 3) / ga.per_xcd_long) * (64 * QI) + (FULL32 ? 64 * (slot % QI) : 0);
+    // normalised; the maximum in the units it was subtracted in: a minus in the sum's
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {                  // sign bit: of the score as it is (WIDE, bf16), else in the log2 domain
+      float l = l_run[qt];
+      l += __shfl_xor(l, 16, 64);
+      l += __shfl_xor(l, 32, 64);
+      const long long row = part_row + wave * 16 * QT + 16 * qt + r16;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        f32x4 r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = (BF ? acc[n][qt][i] : acc[4 * (n >> 2) + i][qt][n & 3]) * inv[qt];
+        *reinterpret_cast<f32x4*>(ga.part_o + row * D + (BF ? 16 * n + 4 * g : 64 * (n >> 2) + 16 * g + 4 * (n & 3))) = r;
+      }
+      if (g == 0) ga.part_ml[row] = make_float2(-neg_m[qt], WIDE && BF ? -l : l);
+    }
+    return true;
+  }
   // coarse residual (Alg. 1 Stage 5): the block's row of O_coarse, the same for all of its tokens
   const float* const oc = (a.ocoarse && !a.dense) ? a.ocoarse + (bh * T_max + qi) * D : nullptr;
 #pragma unroll
@@ -621,17 +603,18 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 }
 
 // D = 128: 66 KB of LDS a group, two groups per compute unit; D = 64: registers for three workgroups (QT = 2) or four groups
-template <typename T, int D, int QT, int NG>
-__global__ __launch_bounds__(256 * NG, D == 128 ? 2 : QT == 1 ? 4 : 3) void k_attn_gen(GenArgs ga) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[NG * GROUP_LDS<D>];
+template <typename T, int D, int QT, bool PARTS>
+__global__ __launch_bounds__(256, (RESIDENT<D, QT>)) void k_attn_gen(GenArgs ga) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[ITEM_LDS<D>];
   // Workgroup ids go round-robin over the 8 XCDs; each has its range of the items of all (batch, head)s, the long ones
   // (exact branch) first.
   const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const bool taylor = j >= ga.per_xcd_long;
+  const int n_long = ga.per_xcd_long * (PARTS ? ga.parts : 1);      // all items' first parts, then their second ones: what runs together reads the same keys
+  const bool taylor = j >= n_long;
   const int n_bh = ga.a.geo.B * ga.a.geo.H;
   const int slots = taylor ? ga.slots_taylor : ga.slots_long;
   const long long total = (long long)n_bh * slots;
-  const int idx = xcd_first(total, xcd) + (taylor ? j - ga.per_xcd_long : j);
+  const int idx = xcd_first(total, xcd) + (taylor ? j - n_long : PARTS ? j % ga.per_xcd_long : j);
   if (idx >= xcd_first(total, xcd + 1)) return;
   const int bhid = head_at(idx / slots, n_bh), slot = idx % slots;
   const BatchCounts c = ga.a.cnt.b[bhid / ga.a.geo.H];
@@ -639,13 +622,74 @@ __global__ __launch_bounds__(256 * NG, D == 128 ? 2 : QT == 1 ? 4 : 3) void k_at
   // QT-tile slot n of a list: rows 64 QT n .. of a 128-row block's sequence of rows, or block n / blocks 2 n, 2 n + 1 of 64 rows
   auto first_entry = [&](int qt, int n) { return ga.a.geo.block == 64 ? qt * n : n * qt / 2; };
   if (first_entry(QT, slot) >= n_list) return;         // a shorter batch item
-  if (attn_gen_item<T, D, QT, false, NG>(ga, lds, bhid, taylor, slot)) return;
+  const int part = !PARTS || taylor ? -1 : j / ga.per_xcd_long;
+  if (attn_gen_item<T, D, QT, false, QT, PARTS>(ga, lds, bhid, taylor, slot, part)) return;
 #pragma unroll 1
   for (int n = QT * slot; n < QT * (slot + 1); ++n)    // again, 64 rows at a time
-    if (first_entry(1, n) < n_list) attn_gen_item<T, D, 1, true, NG>(ga, lds, bhid, taylor, n);
+    if (first_entry(1, n) < n_list) attn_gen_item<T, D, 1, true, QT, PARTS>(ga, lds, bhid, taylor, n, part);
 }
 
-hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st) {
+// Adds up the parts of the long items: out = sum_p o_p l_p 2^(m_p - m) / sum_p l_p 2^(m_p - m) with m = max_p m_p (the merge step
+// of the online softmax).  The parts' results are normalised, so that no sum of them leaves the range; a part that has seen nothing but
+// masked keys (l_p = 0) has none.  Maxima of the two passes over bf16 rows meet in double precision: a difference of theirs must not carry
+// the rounding of a large score.  One workgroup per item and 1024 / D rows, 4 channels a thread.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void k_gen_merge(GenArgs ga, int rows) {
+  constexpr int RW = 1024 / D;                         // rows of a workgroup
+  const AttnArgs& a = ga.a;
+  const int per_item = rows / RW, idx = blockIdx.x / per_item;
+  const int row = blockIdx.x % per_item * RW + threadIdx.x / (D / 4), ch = threadIdx.x % (D / 4) * 4;
+  const int n_bh = a.geo.B * a.geo.H, slots = ga.slots_long;
+  const int bhid = head_at(idx / slots, n_bh), slot = idx % slots, b = bhid / a.geo.H, h = bhid % a.geo.H;
+  const BatchCounts c = a.cnt.b[b];
+  const bool pair = rows == 128 && a.geo.block == 64;
+  const int subs = pair ? 1 : a.geo.block / rows;
+  const int entry = pair ? 2 * slot + row / 64 : slot / subs;
+  if (entry >= (a.dense ? c.T : c.n_full)) return;
+  const int qi = a.dense ? entry : block_in_range(a.full_list[(long long)bhid * a.geo.T_max + entry], c.T);
+  const int in_block = pair ? row % 64 : slot % subs * rows + row;
+  if (in_block >= a.blk_n[b * a.geo.T_max + qi]) return;
+  const long long first = (long long)idx * ga.parts * rows + row;
+  const double cs = 1.4426950408889634 / sqrt((double)D);
+  auto log2_max = [&](const float2 ml) { return sizeof(T) == 2 && (__float_as_uint(ml.y) >> 31) ? (double)ml.x * cs : (double)ml.x; };
+  // all parts' loads in flight at once (a part past the last repeats it, with weight 0)
+  float2 ml[MAX_PARTS];
+  float4 o[MAX_PARTS];
+#pragma unroll
+  for (int p = 0; p < MAX_PARTS; ++p) {
+    const long long at = first + (long long)min(p, ga.parts - 1) * rows;
+    ml[p] = ga.part_ml[at];
+    o[p] = *reinterpret_cast<const float4*>(ga.part_o + at * D + ch);
+  }
+  double m = -INFINITY;
+#pragma unroll
+  for (int p = 0; p < MAX_PARTS; ++p)
+    if (ml[p].y != 0.f) m = fmax(m, log2_max(ml[p]));  // (a NaN sum makes the result NaN below)
+  float w[MAX_PARTS], l = 0.f;
+#pragma unroll
+  for (int p = 0; p < MAX_PARTS; ++p) {
+    w[p] = p < ga.parts && ml[p].y != 0.f ? fabsf(ml[p].y) * __builtin_amdgcn_exp2f((float)(log2_max(ml[p]) - m)) : 0.f;
+    l += w[p];
+  }
+  const float inv = 1.0f / l;
+  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int p = 0; p < MAX_PARTS; ++p) {
+    if (p >= ga.parts || ml[p].y == 0.f) continue;
+    const float x = w[p] * inv;
+    sum.x = fmaf(x, o[p].x, sum.x); sum.y = fmaf(x, o[p].y, sum.y); sum.z = fmaf(x, o[p].z, sum.z); sum.w = fmaf(x, o[p].w, sum.w);
+  }
+  if (l == 0.f) sum = make_float4(NAN, NAN, NAN, NAN);                   // no key at all that is not masked
+  if (a.ocoarse && !a.dense) {
+    const float4 oc = *reinterpret_cast<const float4*>(a.ocoarse + ((long long)bhid * a.geo.T_max + qi) * D + ch);
+    sum.x = fmaf(a.gamma, oc.x, sum.x); sum.y = fmaf(a.gamma, oc.y, sum.y); sum.z = fmaf(a.gamma, oc.z, sum.z); sum.w = fmaf(a.gamma, oc.w, sum.w);
+  }
+  T* op = (T*)a.out + (long long)b * a.geo.stride_b + (long long)h * a.geo.stride_h + (long long)(a.blk_start[b * a.geo.T_max + qi] + in_block) * a.geo.stride_t + ch;
+  if constexpr (sizeof(T) == 2) *reinterpret_cast<uint2*>(op) = make_uint2(f2bf(sum.x) | ((uint32_t)f2bf(sum.y) << 16), f2bf(sum.z) | ((uint32_t)f2bf(sum.w) << 16));
+  else *reinterpret_cast<float4*>(op) = sum;
+}
+
+hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArgs& a, hipStream_t st) {
   GenArgs ga;
   ga.a = a;
   int n_long = 0, n_taylor = 0;
@@ -658,26 +702,50 @@ hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st)
     n_taylor = t > n_taylor ? t : n_taylor;
   }
   const long long bh = (long long)pr.p.B * pr.p.H;
-  // What a launch has to fill the chip with: its long items, and its Taylor items at what one of them takes of a long one's time (fitted
-  // to the measurements below), or these alone at full count where there is no long one.
-  const bool d64 = pr.p.D == 64;
+  const bool d64 = pr.p.D == 64, bf = pr.p.dtype == ISA_BF16;
   const double chip = (double)N_XCD * cus_per_xcd();
-  auto items = [&](int n, int rows) { return (double)(bh * (pr.p.block >= rows ? n * (pr.p.block / rows) : (n + 1) / 2)); };
-  auto load = [&](int rows) {
-    return n_long > 0 ? items(n_long, rows) + items(n_taylor, rows) * ((d64 ? 1.0 / 32 : 1.0 / 14) + set_share) : items(n_taylor, rows);
-  };
-  // bf16: 128 rows per workgroup read every LDS fragment once for two query tiles, but need the chip full of them: measured
-  // at 15 600 tokens, keep 0.5, full 0.25, blocks of 64, QT = 2 / 1: D = 64: 24 heads (744 long items of 128 rows) 728 /
-  // 833 us, dense over half as many tokens, 8 heads (488) 318 / 343, 12 heads (372) 538 / 480, 2 heads (62) 412 / 315; D = 128:
-  // 24 heads 1288 / 1597, 12 heads (372) 755 / 816, 8 heads (248) 576 / 569, 2 heads 553 / 408.  Fewer long items beside more Taylor
-  // items (long + Taylor of 128 rows): D = 64: 24 heads, full 0.15 (456 + 2496) 539 / 578, full 0.1 (312 + 2640) 523 / 472, 16 heads, full 0.15
-  // (304 + 1656) 507 / 455, 40 heads of 32 768 tokens, full 0.02 (240 + 10 040) 1332 / 1634; D = 128: 16 heads, full 0.1 (208 + 1760) 594 /
-  // 633, 24 heads, full 0.05 (168 + 2784) 673 / 721, full 0.02 (72 + 2880) 677 / 574.  Taylor items alone: D = 64 24, 4, 2 heads (2928, 488, 244)
-  // 186 / 226, 67 / 73, 61 / 58; D = 128 24, 2 heads 351 / 465, 82 / 79.  With exact sets a pair of blocks of 64 reads both blocks' sets, which
-  // Taylor items alone do not make up for at D = 64: 24, 8 heads 435 / 396, 192 / 171 (D = 128: 797 / 814, 302 / 305).  fp32: a fragment feeds
-  // four times as many matrix instructions of twice the length, and more waves always won.
-  const bool pair_of_sets = n_long == 0 && set_share > 0.0 && d64 && pr.p.block == 64;
-  const bool two = pr.p.dtype == ISA_BF16 && !pair_of_sets && load(128) >= chip * (d64 ? 7 : 5) / 4;
+  auto items = [&](int n, int rows) { return bh * (pr.p.block >= rows ? n * (pr.p.block / rows) : (n + 1) / 2); };
+  // Rows per workgroup (128 read every LDS fragment once for two query tiles; bf16 only: an fp32 fragment feeds four times as many matrix
+  // instructions of twice the length, and more waves always won) and parts per long item, chosen together by a model of the
+  // launch's time: with k workgroups per compute unit a block of 64 tokens takes each of them pace[k - 1], in us as measured (k
+  // beyond what fits a compute unit: further rounds), and a workgroup spends `start` tokens' time on its start and its share of the merge.  A
+  // Taylor item takes 1/32 (D = 64) or 1/14 (D = 128) of a long one's time, plus its exact set's share.
+  // Measured, whole calls, us, keep 0.5, full 0.25, whole items of 128 rows / of 64 / as chosen (64 rows in two groups of waves that
+  // shared a workgroup's tiles, which this replaces): bf16, 15 600 tokens, blocks of 64: D = 64, 1 head 380 / 298 / 95, 2 heads
+  // 393 / 308 / 120 (238), 4 400 / 317 / 178 (243), 8 409 / 343 / 295, 12 499 / 461 / 394, 16 524 / 574 / 524, 24 712 / 819 / 712; D = 128: 2 heads
+  // 536 / 401 / 176 (317), 4 546 / 419 / 279 (397), 8 567 / 561 / 470, 16 840 / 1058 / 840; fp32, 5280 tokens: D = 128, 4 heads 388 / 185 (381), 8 397 /
+  // 300 (389), 12 662 / 475, 16 664 / 537, D = 64, 3 heads 274 / 95, 8 282 / 169 (243), 24 417 / 397 (403).
+  struct Form { int rows, resident; double pace[4], start; };
+  static const Form forms[2][2][2] = {                 // [bf16][D = 64][64 / 128 rows]
+      {{{64, 2, {5.55, 9.9}, 80}, {}}, {{64, 4, {3.6, 5.5, 7.9, 10.5}, 64}, {}}},
+      {{{64, 2, {1.85, 2.74}, 384}, {128, 2, {2.65, 4.35}, 384}}, {{64, 4, {1.36, 1.54, 2.15, 2.8}, 384}, {128, 3, {1.82, 2.33, 3.4}, 384}}}};
+  bool two = false;
+  ga.parts = 1;
+  if (n_long == 0) {
+    // Taylor items alone, 128 rows / 64: D = 64, 24, 4, 2 heads (2928, 488, 244 items of 128 rows) 186 / 226, 67 / 73, 61 / 58; D = 128, 24, 2 heads
+    // 351 / 465, 82 / 79.  With exact sets a pair of blocks of 64 reads both blocks' sets, which Taylor items do not make up for at D = 64:
+    // 24, 8 heads 435 / 396, 192 / 171 (D = 128: 797 / 814, 302 / 305).
+    two = bf && !(set_share > 0.0 && d64 && pr.p.block == 64) && items(n_taylor, 128) >= chip * (d64 ? 7 : 5) / 4;
+  } else {
+    int shortest = 1 << 30;
+    for (int b = 0; b < pr.p.B; ++b) shortest = min(shortest, a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new);
+    const double tokens = (double)shortest * pr.p.block;
+    const double merge = 5.0 * 64;                     // its launch
+    double best = INFINITY;
+    for (int f = 0; f < (bf ? 2 : 1); ++f) {
+      const Form& form = forms[bf][d64][f];
+      const long long n = items(n_long, form.rows);
+      const double taylor = (double)items(n_taylor, form.rows) * ((d64 ? 1.0 / 32 : 1.0 / 14) + set_share) / chip * form.pace[form.resident - 1] / form.resident * tokens;
+      for (int p = 1; p <= MAX_PARTS && p <= shortest; ++p) {
+        if (p > 1 && (!ws.split_o || n * p * form.rows * pr.p.D > SPLIT_MAX_SUB * 256ll * 128)) break;
+        const int k = (int)ceil((double)(n * p) / chip), rounds = (k - 1) / form.resident;
+        const double pace = rounds * form.pace[form.resident - 1] + form.pace[(k - 1) % form.resident];
+        const double cost = pace * (tokens / p + form.start) + taylor + (p > 1 ? merge : 0.0);
+        if (cost < best) { best = cost; two = f == 1; ga.parts = p; }
+      }
+    }
+  }
+  ga.part_o = ws.split_o; ga.part_ml = (float2*)ws.split_ml;
   const int rows = two ? 128 : 64;
   auto slots = [&](int n) { return pr.p.block >= rows ? n * (pr.p.block / rows) : (n + 1) / 2; };
   ga.slots_long = slots(n_long);
@@ -686,22 +754,25 @@ hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st)
   ga.per_xcd_taylor = (int)((bh * ga.slots_taylor + N_XCD - 1) / N_XCD);
   if (ga.slots_long == 0) ga.slots_long = 1;           // divisors in the kernel; a branch without work gets no workgroups
   if (ga.slots_taylor == 0) ga.slots_taylor = 1;
-  const dim3 grid((unsigned)(N_XCD * (ga.per_xcd_long + ga.per_xcd_taylor)));
-  // Two groups per workgroup while the launch leaves most SIMDs with one or two waves beside a long item.  Measured, one / two groups,
-  // whole call: D = 64 (two such workgroups fit a compute unit), 2, 4, 6, 8 heads of 15 600 tokens (122, 244, 366, 488 long items of 64 rows) 311 /
-  // 238, 317 / 243, 341 / 315, 347 / 349 us; D = 128 (one fits), 2, 4 heads (122, 244) 404 / 317, 420 / 397, fp32, 12 heads of 5280 tokens
-  // (264) 668 / 733; 5 heads of 990 tokens, D = 64: 44.5 / 41.3.  Fewer long items beside more Taylor items (long + Taylor): D = 64: 16 heads (208 +
-  // 3696, 400 + 3504) 325 / 295, 356 / 381, 24 heads (120 + 5736, 312 + 5544) 337 / 328, 371 / 419; D = 128: 8 heads (104 + 1848, 200 + 1752) 411 /
-  // 356, 416 / 458, 16 heads (80 + 3824) 431 / 501, fp32, 16 heads (224 + 1120) 432 / 393, 24 heads (240 + 1776) 446 / 469.  Taylor items
-  // alone are too short to be shared: 24 heads 226 / 266, D = 128 465 / 595, 8 heads in fp32 60 / 71 (D = 64, 2 heads: 58 / 58).
-  const bool groups = !two && n_long > 0 && items(n_long, 64) <= chip * (d64 ? 7 : 4) / 4 && load(64) <= chip * (d64 ? 1.75 : 1.21);
-#define ISA_GEN(T, D, QT, NG) hipLaunchKernelGGL((k_attn_gen<T, D, QT, NG>), grid, dim3(256 * NG), 0, st, ga)
-  if (pr.p.dtype == ISA_BF16) {
-    if (pr.p.D == 128) { if (two) ISA_GEN(uint16_t, 128, 2, 1); else if (groups) ISA_GEN(uint16_t, 128, 1, 2); else ISA_GEN(uint16_t, 128, 1, 1); }
-    else { if (two) ISA_GEN(uint16_t, 64, 2, 1); else if (groups) ISA_GEN(uint16_t, 64, 1, 2); else ISA_GEN(uint16_t, 64, 1, 1); }
-  } else {
-    if (pr.p.D == 128) { if (groups) ISA_GEN(float, 128, 1, 2); else ISA_GEN(float, 128, 1, 1); }
-    else { if (groups) ISA_GEN(float, 64, 1, 2); else ISA_GEN(float, 64, 1, 1); }
+  const dim3 grid((unsigned)(N_XCD * (ga.per_xcd_long * ga.parts + ga.per_xcd_taylor)));
+#define ISA_GEN(T, D, QT)                                                                                  \
+  do {                                                                                                     \
+    if (ga.parts > 1) hipLaunchKernelGGL((k_attn_gen<T, D, QT, true>), grid, dim3(256), 0, st, ga);         \
+    else hipLaunchKernelGGL((k_attn_gen<T, D, QT, false>), grid, dim3(256), 0, st, ga);                     \
+  } while (0)
+  if (bf && d64) { if (two) ISA_GEN(uint16_t, 64, 2); else ISA_GEN(uint16_t, 64, 1); }
+  else if (bf) { if (two) ISA_GEN(uint16_t, 128, 2); else ISA_GEN(uint16_t, 128, 1); }
+  else if (d64) ISA_GEN(float, 64, 1);
+  else ISA_GEN(float, 128, 1);
+  if (ga.parts > 1) {
+    const dim3 merge((unsigned)(bh * ga.slots_long * (rows * pr.p.D / 1024)));
+    if (bf) {
+      if (d64) hipLaunchKernelGGL((k_gen_merge<uint16_t, 64>), merge, dim3(256), 0, st, ga, rows);
+      else hipLaunchKernelGGL((k_gen_merge<uint16_t, 128>), merge, dim3(256), 0, st, ga, rows);
+    } else {
+      if (d64) hipLaunchKernelGGL((k_gen_merge<float, 64>), merge, dim3(256), 0, st, ga, rows);
+      else hipLaunchKernelGGL((k_gen_merge<float, 128>), merge, dim3(256), 0, st, ga, rows);
+    }
   }
 #undef ISA_GEN
   return hipGetLastError();

@@ -189,7 +189,11 @@ void carve(const Problem& pr, void* base, Workspace* ws, bool forward_only) {
     ws->zero_tile = nullptr;
     ws->taylor_ctr = nullptr;
     ws->ktab = nullptr;
-    ws->split_o = ws->split_ml = nullptr;
+  }
+  ws->least = off;
+  if (!pr.mfma_shape) {
+    ws->split_o = (float*)take((size_t)SPLIT_MAX_SUB * 256 * 128 * 4);
+    ws->split_ml = (float*)take((size_t)SPLIT_MAX_SUB * 256 * (128 / D) * 2 * 4);
   }
   ws->bytes = off;
 }
@@ -197,7 +201,8 @@ void carve(const Problem& pr, void* base, Workspace* ws, bool forward_only) {
 static int check_ws(const Problem& pr, void* workspace, size_t bytes, Workspace* ws) {
   if (!workspace || ((uintptr_t)workspace & 255)) return ISA_ERR_WORKSPACE;
   carve(pr, workspace, ws);
-  if (bytes < ws->bytes) return ISA_ERR_WORKSPACE;
+  if (bytes < ws->least) return ISA_ERR_WORKSPACE;
+  if (bytes < ws->bytes) ws->split_o = ws->split_ml = nullptr;
   return ISA_OK;
 }
 
@@ -255,7 +260,7 @@ static int run_attend(const Problem& pr, const Workspace& ws, const AttnArgs& a,
                       hipStream_t st, bool means_ready = false) {
   const bool mfma = pr.mfma_shape && g_use_mfma.load();
   if (!mfma) {
-    ISA_STAGE(launch_attn_gen(pr, a, st));
+    ISA_STAGE(launch_attn_gen(pr, ws, a, st));
     return ISA_OK;
   }
   if (!vt_ready) ISA_STAGE(launch_pack_vt(pr, ws, v, st));
@@ -449,10 +454,11 @@ int isa_attention_static(const isa_problem* p, const void* q, const void* k, con
   if (!all_aligned16(q, k, v, out)) return ISA_ERR_SHAPE;
   Workspace ws;
   carve(pr, nullptr, &ws, true);                       // the forward pass only: nothing is kept for a backward call
-  if (ws.bytes > (size_t)ISA_STATIC_SCRATCH_BYTES) return ISA_ERR_WORKSPACE;
+  if (ws.least > (size_t)ISA_STATIC_SCRATCH_BYTES) return ISA_ERR_WORKSPACE;
   void* base = nullptr;
   if ((rc = static_scratch(&base)) != ISA_OK) return rc;
   carve(pr, base, &ws, true);
+  if (ws.bytes > (size_t)ISA_STATIC_SCRATCH_BYTES) ws.split_o = ws.split_ml = nullptr;
   // every array of the carve-up is written by a kernel of this call before any kernel reads it, so what the previous
   // call left in the scratch does not matter and nothing has to be cleared
   return run_attention(pr, ws, q, k, v, out, (hipStream_t)hip_stream);

@@ -78,8 +78,9 @@ struct Workspace {
   int* bwd_ctr;          // backward: the next work item of each launch that hands its items out dynamically (8 counters, zeroed by k_bwd_delta)
   int4* ktab;            // [B,H,T_max] the btab rows of the blocks of kv_list, in list order
   float* ocoarse;        // [B,H,T_max,D] pooled attention output (only carved when gamma != 0)
-  float* split_o;        // partial outputs of work items split along the key sequence (at most 256 sub-items)
-  float* split_ml;       // their running maxima and sums
+  // partial outputs of work items split along the key sequence, 256 x 256 rows, and their running maxima and sums.  Null if the general kernel's
+  // caller has no room for them: its items then stay whole
+  float* split_o; float* split_ml;
   // backward pass (MFMA path): what the forward leaves for it, and its own scratch
   float* nlse;           // [B,H,S_max] minus the log-sum-exp of every query row, log2 domain (written by the forward)
   uint16_t* olo;         // [B,H,S_max,D] bf16: what the rounding of the output to bf16 cut off (written by the forward)
@@ -99,6 +100,7 @@ struct Workspace {
   float* doc; float* cdq; float* cdk; float* cdv;   // [B,H,T_max,D] coarse residual: gamma * block sums of dO, gradients of the means (only when gamma != 0)
   float4* cstats;        // [B,H,T_max] {max, sum, rowsum(dS * S)} of every row of the pooled map (only when gamma != 0)
   size_t bytes;          // total size
+  size_t least;          // without split_o and split_ml, where these may be missing (general kernel)
 };
 
 struct Problem {          // validated problem + everything derived from it
@@ -163,7 +165,7 @@ hipError_t launch_coarse(const Problem& pr, const Workspace& ws, const float* qc
 bool select_is_small(const Problem& pr);
 hipError_t launch_select(const Problem& pr, const Workspace& ws, const float* s_ctx, const float* sharp, const float* z,
                          int* kv_list, int* full_list, int* flat_list, uint32_t* exact_mask, hipStream_t st, bool small = false);
-hipError_t launch_attn_gen(const Problem& pr, const AttnArgs& a, hipStream_t st);
+hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArgs& a, hipStream_t st);
 
 // MFMA path (bf16, D = 128, block = 128)
 hipError_t launch_pack_vt(const Problem& pr, const Workspace& ws, const void* v, hipStream_t st);

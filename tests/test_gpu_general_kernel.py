@@ -60,7 +60,7 @@ def test_wide_workgroups_of_taylor_blocks(I, shape, exact_frac):
     check_end_to_end(I, wl, *gen(wl), heads=[0, 7, 150, 299])
 
 
-# 1, 2 and 3 tiles for the two groups of a workgroup to share (fp32: 32 tokens each), token tiles followed by tiles of means
+# 1, 2 and 3 tiles (fp32: 32 tokens each), token tiles followed by tiles of means
 @pytest.mark.parametrize("tokens", [32, 33, 64, 65, 96])
 @pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
 def test_few_tiles_for_two_groups(I, shape, tokens):
@@ -68,12 +68,68 @@ def test_few_tiles_for_two_groups(I, shape, tokens):
     check_end_to_end(I, wl, *gen(wl))
 
 
-# a long list with fewer than 256 long items (two groups) and with more (one group): the same answers
+# a long list with few long items (in parts) and with many: the same answers
 @pytest.mark.parametrize("H", [2, 60])
 @pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
 def test_one_and_two_groups(I, shape, H):
     wl = _wl(shape, H, (1, 1, 1500), (((1, 1, 900),),), keep_ratio=0.5, full_frac=0.5, exact_frac=0.2, gamma=0.5, seed=745 + H)
     check_end_to_end(I, wl, *gen(wl), heads=[0, H // 2, H - 1])
+
+
+# few heads: long items in 2 to 8 parts over key lists of 2 blocks (one each), of 9 (unequal parts) and of 40; odd lists of blocks, a shorter
+# batch item, the residual added where the parts are
+@pytest.mark.parametrize("blocks", [2, 9, 40])
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_items_in_parts(I, shape, blocks):
+    block = shape[2]
+    wl = _wl(shape, 3, (1, 1, block * (blocks - 1) + 9), (((1, 1, 3 * block),), ((1, 1, block + 1),)), B=2, keep_ratio=0.0, full_frac=0.4,
+             exact_frac=0.2 if blocks == 9 else 0.0, gamma=0.5, seed=752 + blocks)
+    assert I.isa_get_counts(problem_of(wl), 0)["T_new"] == blocks
+    check_end_to_end(I, wl, *gen(wl))
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_no_room_for_parts(I, shape):
+    """A workspace that holds everything but the partial results (a slice of one that does) is accepted: the items stay whole."""
+    wl = _wl(shape, 2, (1, 1, 1000), (((1, 1, 500),),), keep_ratio=0.5, full_frac=0.5, seed=757)
+    Q, K, V, q, k, v = gen(wl)
+    pr = problem_of(wl)
+    ws = I.new_workspace(pr)
+    least = I.isa_workspace_bytes(pr) - 4 * 256 * 256 * (128 + 2 * 128 // shape[1])
+    outs = [torch.empty_like(q) for _ in range(2)]
+    for out, w in zip(outs, (ws, ws[:least])):
+        I.isa_dense_attention(pr, q, k, v, out, w)
+    with pytest.raises(I.IsaError):
+        I.isa_dense_attention(pr, q, k, v, outs[0], ws[:least - 256])
+    torch.cuda.synchronize()
+    want = np.stack([O.dense_attention(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h])) for h in range(2)])
+    for out in outs:
+        emax, emean = err_stats(f64(out[0]), want)
+        assert emax <= TOL[wl.dtype][0] and emean <= TOL[wl.dtype][1], (emax, emean)
+
+
+@pytest.mark.parametrize("exponent", [12, 25])
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_parts_of_both_passes(I, shape, exponent):
+    """Scores of up to 1e8 and 7e11 against the keys of one block and of 0 elsewhere: the part that holds the block goes through the second
+    pass, the others do not, and their maxima meet in the sum.  Channel 0 only, every score exact in fp32: weights of 0 and 1."""
+    block, n = shape[2], 12 * shape[2] + 5
+    wl = _wl(shape, 2, (1, 1, n), ((),), seed=759)
+    g = torch.Generator().manual_seed(wl.seed + exponent)
+    Q, K = (torch.zeros((1, 2, n, wl.D), dtype=W.torch_dtype(wl.dtype)) for _ in range(2))
+    V = torch.randn((1, 2, n, wl.D), generator=g).to(Q.dtype)
+    Q[..., 0] = ((128 + torch.arange(n) % 128) * 2.0 ** exponent).to(Q.dtype)
+    Q[:, :, ::3] *= -1
+    Q[:, :, ::7] = 0                                    # these rows see all keys alike
+    at = slice(5 * block + 3, 6 * block)
+    K[:, :, at, 0] = torch.randint(-127, 128, (1, 2, block - 3), generator=g).to(K.dtype)
+    out = torch.empty_like(Q, device="cuda")
+    pr = problem_of(wl)
+    I.isa_dense_attention(pr, Q.cuda(), K.cuda(), V.cuda(), out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    for h in range(2):
+        emax, emean = err_stats(f64(out[0, h]), O.dense_attention(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h])))
+        assert emax <= TOL[wl.dtype][0] and emean <= TOL[wl.dtype][1], (h, emax, emean)
 
 
 @pytest.mark.parametrize("H", [1, 3, 5, 9, 20])
