@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256) void k_gather_means(GatherArgs a, int* __restr
   __shared__ GatherLds sm;
   // the attention launch that follows hands out its Taylor groups by counting this up from zero
   if (threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) *taylor_ctr = 0;
-  gather_tile(a, sm, threadIdx.x, blockIdx.x, blockIdx.y, blockIdx.z, true);
+  gather_tile(a, sm, a.kv_list + ((long long)blockIdx.z * a.H + blockIdx.y) * a.cnt.T_max, threadIdx.x, blockIdx.x, blockIdx.y, blockIdx.z, true);
 }
 
 GatherArgs gather_args(const Problem& pr, const Workspace& ws, const float* kc, const float* vc, const int* kv_list) {

@@ -19,9 +19,9 @@ struct GatherLds { uint16_t vtile[KT][MD + 2]; int ids[KT]; };
 // Mean keys (without exact sets: minus the mean key of block 0) / values gathered in kv_list order, rounded to bf16, in the
 // layouts the attention kernel reads:
 // kcn[bh][t][d], vcn[bh][t][d]; vcnt[bh][t/64][d][pos] with the list position t%64 = key_of_pos16(pos); biasn[bh][t] = ln(n_j) sqrt(D), -inf past T_new.
-// Called by 256 threads (tid 0..255, the first 64 of them one wave); every thread of the workgroup calls it together (it has two
+// `list`: the (batch, head)'s kept blocks.  Called by 256 threads (tid 0..255, the first 64 of them one wave); every thread of the workgroup calls it together (it has two
 // barriers), those whose tile does not exist with on = false.
-__device__ __forceinline__ void gather_tile(const GatherArgs& a, GatherLds& sm, const int tid, const int tile, const int h,
+__device__ __forceinline__ void gather_tile(const GatherArgs& a, GatherLds& sm, const int* list, const int tid, const int tile, const int h,
                                             const int b, const bool on) {
   uint16_t (&vtile)[KT][MD + 2] = sm.vtile;
   int (&ids)[KT] = sm.ids;
@@ -35,7 +35,7 @@ __device__ __forceinline__ void gather_tile(const GatherArgs& a, GatherLds& sm, 
   const int t0 = tile * KT;
   if (on && tid < KT) {               // one wave
     const int t = t0 + tid;
-    const int j = t < T_new ? block_in_range(a.kv_list[bh * T_max + t], cnt.b[b].T) : -1;
+    const int j = t < T_new ? block_in_range(list[t], cnt.b[b].T) : -1;
     ids[tid] = j;
     int4 row = make_int4(0, 0, 0, 0);
     if (j >= 0) {

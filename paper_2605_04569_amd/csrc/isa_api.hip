@@ -401,9 +401,13 @@ static int run_attention(const Problem& pr, const Workspace& ws, const void* q, 
     ISA_STAGE(launch_layout(pr, ws, st));
     ISA_STAGE(launch_block_means(pr, ws, q, k, v, ws.qc, ws.kc, ws.vc, st));
   }
-  const bool small = pack_first && select_is_small(pr);
-  ISA_STAGE(launch_coarse(pr, ws, ws.qc, ws.kc, ws.s_ctx, ws.sharp, ws.z, ws.vc, ws.ocoarse, st, !small));
-  ISA_STAGE(launch_select(pr, ws, ws.s_ctx, ws.sharp, ws.z, ws.kv_list, ws.full_list, ws.flat_list, ws.exact_mask, st, small));
+  const bool plan = plan_is_small(pr), small = pack_first && (plan || select_is_small(pr));
+  if (plan) {
+    ISA_STAGE(launch_plan(pr, ws, pack_first, st));
+  } else {
+    ISA_STAGE(launch_coarse(pr, ws, ws.qc, ws.kc, ws.s_ctx, ws.sharp, ws.z, ws.vc, ws.ocoarse, st, !small));
+    ISA_STAGE(launch_select(pr, ws, ws.s_ctx, ws.sharp, ws.z, ws.kv_list, ws.full_list, ws.flat_list, ws.exact_mask, st, small));
+  }
   AttnArgs a = attn_args(pr, ws, q, k, v, out, ws.kc, ws.vc, ws.kv_list, ws.full_list, ws.flat_list, ws.exact_mask, ws.ocoarse, 0);
   return run_attend(pr, ws, a, v, pack_first, st, small);
 }

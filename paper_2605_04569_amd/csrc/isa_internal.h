@@ -165,6 +165,10 @@ hipError_t launch_coarse(const Problem& pr, const Workspace& ws, const float* qc
 bool select_is_small(const Problem& pr);
 hipError_t launch_select(const Problem& pr, const Workspace& ws, const float* s_ctx, const float* sharp, const float* z,
                          int* kv_list, int* full_list, int* flat_list, uint32_t* exact_mask, hipStream_t st, bool small = false);
+// pooled scores, selection, exact sets and (gather: MFMA path) the mean gather of a problem for which plan_is_small holds, on the workspace's
+// own arrays, in one launch
+bool plan_is_small(const Problem& pr);
+hipError_t launch_plan(const Problem& pr, const Workspace& ws, bool gather, hipStream_t st);
 hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArgs& a, hipStream_t st);
 
 // MFMA path (bf16, D = 128, block = 128)

@@ -468,7 +468,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const float* s_ctx, cons
       __threadfence_block();                         // the list as the other threads of this workgroup have just written it
       __syncthreads();
       const int tile = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
-      gather_tile(x.g, tiles[tile], threadIdx.x & 255, tile, h, b, tile < x.g.Tn_pad / KT);
+      gather_tile(x.g, tiles[tile], kv_list + off, threadIdx.x & 255, tile, h, b, tile < x.g.Tn_pad / KT);
     }
   } else {                     // query blocks by sharpness
     for (int i = threadIdx.x; i < c.T; i += SEL_THREADS) sc[i] = sharp[off + i];
@@ -495,21 +495,13 @@ bool select_is_small(const Problem& pr) {
 // compares, where counting every entry's rank against all others takes T_new of them.  40 heads of 256 Taylor blocks, 288 kept
 // blocks: 133 -> 26 us.  A NaN beats nothing and nothing beats it: it is marked whenever k_exact > 0 and takes nobody's place.
 template <int NV>
-__global__ __launch_bounds__(256) void k_exact_sets(const float* __restrict__ z, const int* __restrict__ kv_list,
-                                                    const int* __restrict__ flat_list, uint32_t* __restrict__ mask,
-                                                    Counts cnt, int H) {
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, h = blockIdx.y, b = blockIdx.z;
-  const BatchCounts c = cnt.b[b];
-  if (r >= c.n_flat) return;                         // uniform over the wave; nothing below synchronises waves
-  const long long bh = (long long)b * H + h;
-  const int i = block_in_range(flat_list[bh * cnt.T_max + r], c.T);
-  const float* zr = z + (bh * cnt.T_max + i) * cnt.T_max;
+__device__ __forceinline__ void exact_set(const float* zr, const int* kv, uint32_t* mrow, const BatchCounts& c, int mask_words, int lane) {
   uint32_t key[NV];                                  // 0: past the list, or NaN (every number's key is larger)
   unsigned long long nan[NV];
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
     const int t = lane + 64 * u;
-    const int j = t < c.T_new ? block_in_range(kv_list[bh * cnt.T_max + t], c.T) : -1;
+    const int j = t < c.T_new ? block_in_range(kv[t], c.T) : -1;
     const float x = j >= 0 ? zr[j] + 0.0f : 0.f;     // -0 and 0 tie
     const uint32_t bits = __float_as_uint(x);
     const bool is_nan = x != x;
@@ -527,18 +519,162 @@ __global__ __launch_bounds__(256) void k_exact_sets(const float* __restrict__ z,
     if (count(kth | bit) >= c.k_exact) kth |= bit;
   // all larger keys, and the first of the equal ones
   int equal = c.k_exact - (kth == 0xffffffffu ? 0 : count(kth + 1u));
-  uint32_t* mrow = mask + (bh * cnt.T_max + r) * cnt.mask_words;
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
-    if (2 * u >= cnt.mask_words) break;
+    if (2 * u >= mask_words) break;
     const unsigned long long eq = __ballot(kth != 0u && key[u] == kth);
     const int before = __popcll(eq & ((1ull << lane) - 1ull));
     unsigned long long set = __ballot(key[u] > kth || (kth != 0u && key[u] == kth && before < equal));
     equal -= __popcll(eq);
     if (c.k_exact > 0) set |= nan[u];
     if (lane == 0) mrow[2 * u] = (uint32_t)set;
-    if (lane == 1 && 2 * u + 1 < cnt.mask_words) mrow[2 * u + 1] = (uint32_t)(set >> 32);
+    if (lane == 1 && 2 * u + 1 < mask_words) mrow[2 * u + 1] = (uint32_t)(set >> 32);
   }
+}
+template <int NV>
+__global__ __launch_bounds__(256) void k_exact_sets(const float* __restrict__ z, const int* __restrict__ kv_list,
+                                                    const int* __restrict__ flat_list, uint32_t* __restrict__ mask,
+                                                    Counts cnt, int H) {
+  const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, h = blockIdx.y, b = blockIdx.z;
+  const BatchCounts c = cnt.b[b];
+  if (r >= c.n_flat) return;                         // uniform over the wave; nothing below synchronises waves
+  const long long row0 = ((long long)b * H + h) * cnt.T_max;
+  const int i = block_in_range(flat_list[row0 + r], c.T);
+  exact_set<NV>(z + (row0 + i) * cnt.T_max, kv_list + row0, mask + (row0 + r) * cnt.mask_words, c, cnt.mask_words, lane);
+}
+
+// Everything between the block means and the attention launch for a (batch, head) of at most 64 blocks, in one workgroup of 16 waves: the
+// pooled map with its softmax, column means and sharpness (as k_coarse and k_colmean, in the same order of additions), both
+// selections (a wave each: a lane per block, ranks by comparing with every other lane, lists by the bits of a ballot), then the gathered means (GATHER:
+// the pipelined kernels) beside the exact sets.  All latency at these sizes: 5 heads of 9 blocks k_coarse 6.7 + k_select 10.8 us and the
+// launch between them -> 9.9; whole call 44.8 -> 39.2 us, 8 heads of 42 blocks in fp32 306 -> 304.
+constexpr int PLAN_BLOCKS = 64;
+struct PlanArgs {
+  const float *qc, *kc;
+  float *s_ctx, *sharp;
+  int *kv_list, *full_list, *flat_list;
+  uint32_t* exact_mask;                              // null: no exact sets
+  int* taylor_ctr;
+  GatherArgs g;
+  Counts cnt;
+  int H;
+};
+
+template <int D, bool GATHER>
+__global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
+  constexpr int ZS = PLAN_BLOCKS + 4, NT = D / 16;
+  __shared__ __attribute__((aligned(16))) float zs[PLAN_BLOCKS * ZS];          // logits
+  __shared__ float ps[PLAN_BLOCKS * ZS];                                       // softmax weights of the source rows' context columns
+  __shared__ double sums[4][PLAN_BLOCKS];
+  __shared__ float sh[PLAN_BLOCKS];
+  __shared__ int kvs[PLAN_BLOCKS], flat[PLAN_BLOCKS];
+  __shared__ GatherLds tile;
+  const int h = blockIdx.x, b = blockIdx.y, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const BatchCounts c = a.cnt.b[b];
+  const int T = c.T, T_src = c.T_src;
+  const long long row0 = ((long long)b * a.H + h) * a.cnt.T_max;
+  if (GATHER && threadIdx.x == 0 && h == 0 && b == 0) *a.taylor_ctr = 0;       // see k_gather_means
+  {                                                  // a 16 x 16 tile of the map per wave; operands as in k_coarse
+    const int it = wave >> 2, jt = wave & 3, l16 = lane & 15, g = lane >> 4;
+    if (it * 16 < T && jt * 16 < T) {
+      const float* qrow = a.qc + (row0 + min(it * 16 + l16, T - 1)) * D + 4 * g;
+      const float* krow = a.kc + (row0 + min(jt * 16 + l16, T - 1)) * D + 4 * g;
+      float4 bq[NT], ak[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        bq[t] = *reinterpret_cast<const float4*>(qrow + 16 * t);
+        ak[t] = *reinterpret_cast<const float4*>(krow + 16 * t);
+      }
+      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ak[t].x, bq[t].x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ak[t].y, bq[t].y, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ak[t].z, bq[t].z, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ak[t].w, bq[t].w, acc, 0, 0, 0);
+      }
+      const float scale = 1.0f / sqrtf((float)D);
+      *reinterpret_cast<float4*>(zs + (it * 16 + l16) * ZS + jt * 16 + 4 * g) = make_float4(acc[0] * scale, acc[1] * scale, acc[2] * scale, acc[3] * scale);
+    }
+  }
+  __syncthreads();
+  for (int i = wave; i < T; i += 16) {               // a row of at most 64 columns per wave
+    const float zv = lane < T ? zs[i * ZS + lane] : -INFINITY;
+    const float m = wave_max(zv);
+    const float e = lane < T ? expf(zv - m) : 0.f;
+    const double ed = (double)e, src = lane < T_src ? ed : 0.0;
+    const double l = wave_sum(ed), l_src = wave_sum(src), q_src = wave_sum(src * src);
+    const double mu = l_src / l / (double)T_src;
+    const double var = q_src / (l * l) / (double)T_src - mu * mu;
+    if (lane == 0) {
+      sh[i] = (float)fmax(var, 0.0);
+      a.sharp[row0 + i] = sh[i];
+    }
+    if (i < T_src && lane >= T_src && lane < T) ps[i * ZS + lane - T_src] = e * (float)(1.0 / l);
+  }
+  __syncthreads();
+  if (wave < 4) {                                    // Eq. 1, a quarter of the source rows per wave (see k_colmean)
+    const int per = (T_src + 3) / 4, i_lo = wave * per, i_hi = min(T_src, i_lo + per);
+    double acc = 0.0;
+    if (lane < c.T_ctx)
+      for (int i = i_lo; i < i_hi; ++i) acc += (double)ps[i * ZS + lane];
+    sums[wave][lane] = acc;
+  }
+  __syncthreads();
+  if (wave < 2) {                                    // wave 0: context blocks by saliency; wave 1: query blocks by sharpness
+    const int n = wave == 0 ? c.T_ctx : T, k = wave == 0 ? c.k_keep : c.n_full;
+    float s = 0.f;
+    if (lane < n) {
+      if (wave == 0) {
+        s = (float)((((sums[0][lane] + sums[1][lane]) + sums[2][lane]) + sums[3][lane]) / (double)T_src);
+        a.s_ctx[row0 + lane] = s;
+      } else {
+        s = sh[lane];
+      }
+    }
+    int rank = 0;
+    for (int x = 0; x < n; ++x) rank += beats(__shfl(s, x, 64), x, s, lane) ? 1 : 0;
+    const unsigned long long yes = __ballot(lane < n && rank < k), below = (1ull << lane) - 1ull;
+    const int at_yes = __popcll(yes & below), at_no = lane - at_yes;
+    const bool chosen = (yes >> lane) & 1ull;
+    if (wave == 0) {
+      if (lane < T_src) kvs[lane] = lane;
+      if (chosen) kvs[T_src + at_yes] = T_src + lane;
+      // (the same wave reads what it has just written)
+      __builtin_amdgcn_wave_barrier();
+      if (lane < a.cnt.T_max) a.kv_list[row0 + lane] = lane < T_src + __popcll(yes) ? kvs[lane] : -1;      // (NaN scores: more than k of them)
+    } else if (lane < a.cnt.T_max) {
+      const int n_yes = __popcll(yes);
+      flat[lane] = -1;
+      if (lane >= n_yes) a.full_list[row0 + lane] = -1;
+      if (lane >= T - n_yes) a.flat_list[row0 + lane] = -1;
+      if (lane < T) {
+        (chosen ? a.full_list : a.flat_list)[row0 + (chosen ? at_yes : at_no)] = lane;
+        if (!chosen) flat[at_no] = lane;
+      }
+    }
+  }
+  __syncthreads();
+  if (a.exact_mask && wave >= 4)
+    for (int r = wave - 4; r < c.n_flat; r += 12) exact_set<1>(zs + block_in_range(flat[r], T) * ZS, kvs, a.exact_mask + (row0 + r) * a.cnt.mask_words, c, a.cnt.mask_words, lane);
+  if (GATHER) gather_tile(a.g, tile, kvs, threadIdx.x & 255, 0, h, b, wave < 4);
+}
+
+bool plan_is_small(const Problem& pr) { return pr.cnt.T_max <= PLAN_BLOCKS && pr.p.gamma == 0.0; }
+
+hipError_t launch_plan(const Problem& pr, const Workspace& ws, bool gather, hipStream_t st) {
+  PlanArgs a = {ws.qc, ws.kc, ws.s_ctx, ws.sharp, ws.kv_list, ws.full_list, ws.flat_list, pr.p.exact_frac > 0.0 ? ws.exact_mask : nullptr,
+                ws.taylor_ctr, {}, pr.cnt, pr.p.H};
+  const dim3 grid(pr.p.H, pr.p.B);
+  if (gather) {
+    a.g = gather_args(pr, ws, ws.kc, ws.vc, ws.kv_list);
+    hipLaunchKernelGGL((k_plan<128, true>), grid, dim3(1024), 0, st, a);
+  } else if (pr.p.D == 128) {
+    hipLaunchKernelGGL((k_plan<128, false>), grid, dim3(1024), 0, st, a);
+  } else {
+    hipLaunchKernelGGL((k_plan<64, false>), grid, dim3(1024), 0, st, a);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_select(const Problem& pr, const Workspace& ws, const float* s_ctx, const float* sharp, const float* z,

@@ -60,3 +60,51 @@ def test_select_edges(I, T_src, T_ctx, keep, exact):
             bits[:len(kv)] = _chosen(z[0, h, i, kv], c["k_exact"])
             want = np.packbits(bits, bitorder="little").view(np.uint32)
             assert (mask_g[0, h, r] == want).all(), (h, r, i)
+
+
+# at most 64 blocks: pooled scores, lists, exact sets and gathered means in one launch, 65: in separate ones; against the staged entry points
+# (the general kernels) on the call's own block means, bit by bit.  Repeated blocks tie; one block of infinite keys and a ragged batch item.
+@pytest.mark.parametrize("shape", [("bf16", 128, 128), ("bf16", 64, 64), ("f32", 128, 128)], ids=["bf16_d128_b128", "bf16_d64_b64", "f32_d128_b128"])
+@pytest.mark.parametrize("T_src,T_ctx,keep,full,exact", [
+    (1, 0, 1.0, 1.0, 0.0), (1, 1, 1.0, 0.5, 1.0), (15, 1, 1.0, 0.0, 0.5), (9, 8, 0.5, 0.3, 0.3), (1, 62, 0.5, 0.2, 0.1), (33, 31, 0.75, 0.25, 0.0625),
+    (62, 2, 0.5, 0.4, 0.2), (33, 32, 0.5, 0.3, 0.1)])
+def test_one_launch_plan(I, shape, T_src, T_ctx, keep, full, exact):
+    dtype, D, block = shape
+    H, T = 3, T_src + T_ctx
+    short = max(1, T_src // 2) * block - block // 3
+    pr = I.Problem(H=H, D=D, dtype=dtype, block=block, seg_len=[[T_src * block - 5, T_ctx * block], [short]], keep_ratio=keep, full_frac=full, exact_frac=exact)
+    c = [I.isa_get_counts(pr, b) for b in range(2)]
+    assert c[0]["T"] == T
+    S = T * block - 5
+    g = torch.Generator(device="cuda").manual_seed(T)
+    q, k, v = (torch.randn((2, H, S, D), generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32) for _ in range(3))
+    if T_src > 4:                                       # blocks 1 and 3 alike (their scores tie), and infinite keys in one head's block 2
+        for x in (q, k):
+            x[:, :, 3 * block:4 * block] = x[:, :, block:2 * block]
+        k[0, 1, 2 * block:3 * block, 0] = float("inf")
+    ws = I.new_workspace(pr)
+    I.isa_attention(pr, q, k, v, torch.empty_like(q), ws)
+    torch.cuda.synchronize()
+    lay = I.isa_workspace_layout(pr)
+    at = lambda name, dt, *more: I.workspace_array(ws, lay[name], (2, H, T) + more, dt).clone()
+    qc, kc = at("qc", torch.float32, D), at("kc", torch.float32, D)
+    words = (T + 31) // 32
+    names = ["s_ctx", "sharp", "kv_list", "full_list", "flat_list"]
+    got = {n: at(n, torch.float32 if i < 2 else torch.int32) for i, n in enumerate(names)}
+    if exact > 0:
+        got["exact_mask"] = at("exact_mask", torch.int32, words)
+    ws2 = I.new_workspace(pr)
+    s_ctx, sharp = (torch.zeros((2, H, T), device="cuda") for _ in range(2))
+    z = torch.zeros((2, H, T, T), device="cuda")
+    lists = [torch.zeros((2, H, T), device="cuda", dtype=torch.int32) for _ in range(3)]
+    mask = torch.zeros((2, H, T, words), device="cuda", dtype=torch.int32)
+    I.isa_coarse_scores(pr, qc, kc, s_ctx, sharp, z, ws2)
+    I.isa_select(pr, s_ctx, sharp, z, *lists, mask, ws2)
+    torch.cuda.synchronize()
+    want = dict(zip(names, [s_ctx, sharp, *lists]), exact_mask=mask)
+    rows = {"s_ctx": "T_ctx", "sharp": "T", "exact_mask": "n_flat"}
+    for n, x in got.items():
+        for b in range(2):
+            m = c[b][rows[n]] if n in rows else T
+            a, w = x[b, :, :m], want[n][b, :, :m]
+            assert torch.equal(torch.nan_to_num(a, nan=-7.0) if a.is_floating_point() else a, torch.nan_to_num(w, nan=-7.0) if w.is_floating_point() else w), (n, b)
