@@ -590,7 +590,7 @@ __device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, 
 }
 
 // dQ of both branches and the mean-row launch (dKc, then dVc) in one launch: workgroups 0 .. wgs_full - 1 take the exact branch's items (the
-// longest), then come the Taylor branch's, then wgs_means for each of dKc and dVc; all three counts are multiples of the XCDs.
+// longest), then come wgs_means for each of dKc and dVc, then the Taylor branch's; all three counts are multiples of the XCDs.
 // None reads what another writes, and each alone leaves compute units idle at its end (all of the time, if it is small).  Measured, three
 // launches / one, a training step of 12 heads of 1564 tokens 211 / 190 us (78 / 33 of them in these launches and their merges), 40 heads of
 // 15 600 tokens with the residual 4460 / 4406, 65 520 tokens at the paper's ratios 99.6 / 99.0 ms.
@@ -601,12 +601,12 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdTokensArgs p) {
   int wg = blockIdx.x;
   if (wg < p.wgs_full) {
     attn_bwd<false, true, 0>(p.full, lds, wg, nullptr, p.full.oscale);
-  } else if ((wg -= p.wgs_full) < p.wgs_flat) {
-    attn_bwd<false, true, EX ? 2 : 0>(p.flat, lds, wg, nullptr, p.flat.oscale);
-  } else if ((wg -= p.wgs_flat) < p.wgs_means) {
+  } else if ((wg -= p.wgs_full) < p.wgs_means) {
     attn_bwd<true, true, EX>(p.means, lds, wg, p.means.out_f32, p.means.oscale);
+  } else if ((wg -= p.wgs_means) < p.wgs_means) {
+    attn_bwd<true, false, EX>(p.means, lds, wg, p.dvc, 1.0f);
   } else {
-    attn_bwd<true, false, EX>(p.means, lds, wg - p.wgs_means, p.dvc, 1.0f);
+    attn_bwd<false, true, EX ? 2 : 0>(p.flat, lds, wg - p.wgs_means, nullptr, p.flat.oscale);
   }
 }
 
@@ -1214,7 +1214,9 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   tk.means.parts = mean_parts > 0 ? mean_parts : 1;
   int n_sub = 0, n_merge_full = 0, n_merge_flat = 0;
   tk.wgs_full = plan_dq(tk.full, B, H, min_kept, ws.bwd_ctr + 2, 8 * cus, one_round, n_sub, n_merge_full);
-  tk.wgs_flat = plan_dq(tk.flat, B, H, (min_kept + KT - 1) / KT, ws.bwd_ctr + 0, min_kept > KT ? cus / 2 + 1 : 0, 0, n_sub, n_merge_flat);
+  // (the surplus workgroups of a counted launch would keep the rest of a single round waiting)
+  const int flat_units = one_round ? 1 : (min_kept + KT - 1) / KT, flat_dyn = one_round ? 1 << 30 : min_kept > KT ? cus / 2 + 1 : 0;
+  tk.wgs_flat = plan_dq(tk.flat, B, H, flat_units, ws.bwd_ctr + 0, flat_dyn, 0, n_sub, n_merge_flat);
   tk.wgs_means = n_mean_pairs > 0 ? N_XCD * per_xcd(n_mean_pairs * mean_parts) : 0;
   const int wgs = tk.wgs_full + tk.wgs_flat + 2 * tk.wgs_means;
   if (wgs > 0) {
