@@ -610,78 +610,108 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdTokensArgs p) {
   }
 }
 
-// delta[bh][token] = sum_d dO * O (fp32); 16 lanes per token row, 16 bytes per lane and tensor.  O is taken as out + olo:
-// the bf16 output plus what its rounding cut off, which the forward kernels keep for this purpose.  With the bf16 output
-// alone, delta carries that rounding (2^-9 |dO||O|) into dS = P (dP - delta), which for a query that attends almost
-// one-hot is a difference of nearly equal numbers.
-__global__ __launch_bounds__(256) void k_bwd_delta(const uint16_t* __restrict__ o, const uint16_t* __restrict__ olo,
-                                                   const uint16_t* __restrict__ d_o, float* __restrict__ delta, int* __restrict__ ctr,
-                                                   Geometry g, Counts cnt, int S_max) {
-  const int h = blockIdx.y, b = blockIdx.z;
-  // the item counters of the launches that follow start at zero (ordinary stores: the call can be captured in a graph)
-  if (blockIdx.x == 0 && h == 0 && b == 0 && threadIdx.x < 8) ctr[threadIdx.x] = 0;
-  const int t = blockIdx.x * 16 + (threadIdx.x >> 4), c16 = threadIdx.x & 15;
-  const bool ok = t < cnt.b[b].S;
-  float s = 0.f;
-  if (ok) {
-    const long long off = (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)t * g.stride_t + 8 * c16;
-    const uint4 uo = *reinterpret_cast<const uint4*>(o + off), ud = *reinterpret_cast<const uint4*>(d_o + off);
-    uint4 ul = make_uint4(0u, 0u, 0u, 0u);
-    if (olo) ul = *reinterpret_cast<const uint4*>(olo + (((long long)b * g.H + h) * S_max + t) * MD + 8 * c16);
-    const uint32_t wo[4] = {uo.x, uo.y, uo.z, uo.w}, wd[4] = {ud.x, ud.y, ud.z, ud.w}, wl[4] = {ul.x, ul.y, ul.z, ul.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      s += (__uint_as_float(wo[i] << 16) + __uint_as_float(wl[i] << 16)) * __uint_as_float(wd[i] << 16) +
-           (__uint_as_float(wo[i] & 0xffff0000u) + __uint_as_float(wl[i] & 0xffff0000u)) * __uint_as_float(wd[i] & 0xffff0000u);
-  }
-#pragma unroll
-  for (int m = 8; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
-  if (ok && c16 == 0) delta[((long long)b * g.H + h) * S_max + t] = s;
-}
+// What the launches need before they start, in one launch of 256 threads a workgroup, blockIdx.z = task * B + batch item.  Tasks: the lists of
+// the kept, the full-attention and the Taylor blocks (bwd_rows), the fill (bwd_fill), with exact sets the transposed bits (bwd_tmask): none
+// reads what another writes.  Delta belongs to the blocks' rows and is worked out where their terms are: as a launch of its own it
+// was one more wait and another 4 us of the host's time (a training step of 12 heads of 1564 tokens 183 / 177 us, two runs where the host
+// bounds it; 65 520 tokens at the paper's ratios equal).
+struct PrepArgs {
+  int B, H, Tn_pad, S_max;
+  const int* list[3]; int4* tab[3]; float2* ybd[3];          // kept, full-attention, Taylor blocks
+  const float* rq; float2* ybd_flatm;                        // exact sets: the Taylor rows' terms a second time (null: none)
+  const int4* btab; const float* nlse; float rq_scale;
+  const uint16_t *o, *olo, *d_o;                             // o null: delta is there already (k_bwd_delta_residual)
+  float* delta; int* ctr;
+  float2* ybd_mean; float* bx_mean;
+  uint16_t* dk; uint16_t* dv; const float* rows_k; const float* rows_v;
+  const uint32_t* mask; uint32_t* mask_t;
+  Geometry geo; Counts cnt;
+};
 
 // Per list entry: the table row of its block and the {exponent term, minus delta} pair of each of its 128 row positions
-// (masked positions: -inf, 0), stored per tile of 64 positions as 64 terms followed by 64 minus-deltas.  kind 0: kept blocks as streamed keys (term 0), plus the per-mean arrays of the Taylor
-// branch (log2 n_j per gathered mean, -inf for the padding); kinds 1, 2: full-attention / Taylor blocks as streamed
-// queries (term = minus the row's log-sum-exp in the log2 domain, delta of the row); with `rq` (Taylor blocks under exact
-// sets, for scores against the gathered means, which are stored minus Kc_0) the row's q . Kc_0, scaled to the log2
-// domain, is added to the term.
-struct RowLists {
-  const int* list[4]; int kind[4]; const float* rq[4]; int4* tab[4]; float2* ybd[4];
-};
-__device__ __forceinline__ void bwd_rows(const RowLists& ls, int which, int b, const int4* __restrict__ btab, const float* __restrict__ nlse,
-                                         float rq_scale, const float* __restrict__ delta, float2* __restrict__ ybd_mean,
-                                         float* __restrict__ bx_mean, const Counts& cnt, int H, int Tn_pad, int S_max) {
-  const int e = blockIdx.x, h = blockIdx.y, r = threadIdx.x;
-  const int* const list = ls.list[which];
-  const int kind = ls.kind[which];
-  const float* const rq = ls.rq[which];
-  int4* const tab = ls.tab[which];
-  float2* const ybd = ls.ybd[which];
+// (masked positions: -inf, 0), stored per tile of 64 positions as 64 terms followed by 64 minus-deltas.  kind 0: kept blocks as streamed
+// keys (term 0), plus the per-mean arrays of the Taylor branch (log2 n_j per gathered mean, -inf for the padding); kinds 1, 2:
+// full-attention / Taylor blocks as streamed queries (term = minus the row's log-sum-exp in the log2 domain, delta of the row); for scores
+// against the gathered means under exact sets, which are stored minus Kc_0, the Taylor rows a second time with their q . Kc_0, scaled
+// to the log2 domain, added to the term.
+// delta = sum_d dO * O (fp32); 16 lanes per token row, 16 bytes per lane and tensor.  O is taken as out + olo: the bf16 output plus
+// what its rounding cut off, which the forward kernels keep for this purpose.  With the bf16 output alone, delta carries that rounding
+// (2^-9 |dO||O|) into dS = P (dP - delta), which for a query that attends almost one-hot is a difference of nearly equal numbers.
+__device__ __forceinline__ void bwd_rows(const PrepArgs& p, int kind, int b) {
+  __shared__ float dl[128];
+  const int e = blockIdx.x, h = blockIdx.y;
+  const Counts& cnt = p.cnt;
+  const int* const list = p.list[kind];
   const int T_max = cnt.T_max;
-  const long long bh = (long long)b * H + h;
+  const long long bh = (long long)b * p.H + h;
   const int n_list = kind == 0 ? cnt.b[b].T_new : kind == 1 ? cnt.b[b].n_full : cnt.b[b].n_flat;
-  if (kind == 0 && e < Tn_pad && r == 0) {
+  if (kind == 0 && e < p.Tn_pad && threadIdx.x == 0) {
     float l2 = -INFINITY;
-    if (e < n_list) l2 = log2f((float)btab[b * T_max + block_in_range(list[bh * T_max + e], cnt.b[b].T)].y);
-    const long long m = bh * Tn_pad + e;                      // planar per 64 positions: 64 terms, then 64 deltas
-    float* ym = reinterpret_cast<float*>(ybd_mean);
+    if (e < n_list) l2 = log2f((float)p.btab[b * T_max + block_in_range(list[bh * T_max + e], cnt.b[b].T)].y);
+    const long long m = bh * p.Tn_pad + e;                    // planar per 64 positions: 64 terms, then 64 deltas
+    float* ym = reinterpret_cast<float*>(p.ybd_mean);
     ym[(m >> 6) * 128 + (m & 63)] = l2;
     ym[(m >> 6) * 128 + 64 + (m & 63)] = 0.f;
-    bx_mean[bh * Tn_pad + e] = e < n_list ? l2 : 0.f;
+    p.bx_mean[bh * p.Tn_pad + e] = e < n_list ? l2 : 0.f;
   }
   if (e >= n_list || e >= T_max) return;
-  const int4 ent = btab[b * T_max + block_in_range(list[bh * T_max + e], cnt.b[b].T)];
-  if (r == 0) tab[bh * T_max + e] = ent;
-  float2 v = make_float2(-INFINITY, 0.f);
-  if (r < ent.y) {
-    if (kind == 0) v = make_float2(0.f, 0.f);
-    else v = make_float2(nlse[bh * S_max + ent.x + r] + (rq ? rq_scale * rq[bh * S_max + ent.x + r] : 0.f),
-                         -delta[bh * S_max + ent.x + r]);
+  const int4 ent = p.btab[b * T_max + block_in_range(list[bh * T_max + e], cnt.b[b].T)];
+  if (threadIdx.x == 0) p.tab[kind][bh * T_max + e] = ent;
+  if (kind > 0 && p.o) {
+    const int c16 = threadIdx.x & 15, rg = threadIdx.x >> 4;
+    const long long base = (long long)b * p.geo.stride_b + (long long)h * p.geo.stride_h + (long long)ent.x * p.geo.stride_t + 8 * c16;
+    uint4 uo[8], ud[8], ul[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = rg + 16 * i;
+      uo[i] = ud[i] = ul[i] = make_uint4(0u, 0u, 0u, 0u);
+      if (r < ent.y) {
+        uo[i] = *reinterpret_cast<const uint4*>(p.o + base + (long long)r * p.geo.stride_t);
+        ud[i] = *reinterpret_cast<const uint4*>(p.d_o + base + (long long)r * p.geo.stride_t);
+        if (p.olo) ul[i] = *reinterpret_cast<const uint4*>(p.olo + (bh * p.S_max + ent.x + r) * MD + 8 * c16);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = rg + 16 * i;
+      const uint32_t wo[4] = {uo[i].x, uo[i].y, uo[i].z, uo[i].w}, wd[4] = {ud[i].x, ud[i].y, ud[i].z, ud[i].w},
+                     wl[4] = {ul[i].x, ul[i].y, ul[i].z, ul[i].w};
+      float s = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        s += (__uint_as_float(wo[k] << 16) + __uint_as_float(wl[k] << 16)) * __uint_as_float(wd[k] << 16) +
+             (__uint_as_float(wo[k] & 0xffff0000u) + __uint_as_float(wl[k] & 0xffff0000u)) * __uint_as_float(wd[k] & 0xffff0000u);
+#pragma unroll
+      for (int m = 8; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
+      if (c16 == 0) {
+        dl[r] = s;
+        if (r < ent.y) p.delta[bh * p.S_max + ent.x + r] = s;
+      }
+    }
+    __syncthreads();
   }
-  const long long pos = (bh * T_max + e) * 128 + r;
-  float* yf = reinterpret_cast<float*>(ybd);
-  yf[(pos >> 6) * 128 + (pos & 63)] = v.x;
-  yf[(pos >> 6) * 128 + 64 + (pos & 63)] = v.y;
+  const int r = threadIdx.x;
+  if (r >= 128) return;
+  float2 v = make_float2(-INFINITY, 0.f);
+  float vm = -INFINITY;
+  if (r < ent.y) {
+    if (kind == 0) {
+      v.x = 0.f;
+    } else {
+      const long long row = bh * p.S_max + ent.x + r;
+      v = make_float2(p.nlse[row], -(p.o ? dl[r] : p.delta[row]));
+      if (kind == 2 && p.rq) vm = v.x + p.rq_scale * p.rq[row];
+    }
+  }
+  const long long pos = (bh * T_max + e) * 128 + r, at = (pos >> 6) * 128 + (pos & 63);
+  float* yf = reinterpret_cast<float*>(p.ybd[kind]);
+  yf[at] = v.x;
+  yf[at + 64] = v.y;
+  if (kind == 2 && p.rq) {
+    yf = reinterpret_cast<float*>(p.ybd_flatm);
+    yf[at] = vm;
+    yf[at + 64] = v.y;
+  }
 }
 
 // Rows of dK and dV that no later launch writes (keys and values of blocks that were not kept): zero, or, with the
@@ -695,7 +725,7 @@ __device__ __forceinline__ void bwd_fill(uint16_t* __restrict__ dk, uint16_t* __
   if (blk >= T) return;
   const long long bh = (long long)b * g.H + h;
   int kept = 0;
-  for (int t = threadIdx.x; t < T_new; t += 128) kept |= block_in_range(kv_list[bh * cnt.T_max + t], T) == blk ? 1 : 0;
+  for (int t = threadIdx.x; t < T_new; t += 256) kept |= block_in_range(kv_list[bh * cnt.T_max + t], T) == blk ? 1 : 0;
   if (__syncthreads_or(kept)) return;
   const int4 ent = btab[b * cnt.T_max + blk];
   const int c16 = threadIdx.x & 15;
@@ -712,7 +742,7 @@ __device__ __forceinline__ void bwd_fill(uint16_t* __restrict__ dk, uint16_t* __
       val = make_uint4(w[0], w[1], w[2], w[3]);
     }
     uint16_t* x = (t ? dv : dk) + (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)ent.x * g.stride_t + 8 * c16;
-    for (int r = threadIdx.x >> 4; r < ent.y; r += 8) *reinterpret_cast<uint4*>(x + (long long)r * g.stride_t) = val;
+    for (int r = threadIdx.x >> 4; r < ent.y; r += 16) *reinterpret_cast<uint4*>(x + (long long)r * g.stride_t) = val;
   }
 }
 
@@ -732,21 +762,12 @@ __device__ __forceinline__ void bwd_tmask(const uint32_t* __restrict__ mask, uin
   mask_t[(bh * T_max + t) * mw + w] = out;
 }
 
-// The three in one launch, blockIdx.z = task * B + batch item, task: the n_lists lists of `ls`, then the fill, then (mask != null)
-// the transposed bits: none reads what another writes, and one after the other each waits for a nearly idle chip
-// (measured, a training step of 12 heads of 1564 tokens, three launches / one: 218 / 212 us).
-struct PrepArgs {
-  RowLists ls; int n_lists, B, H, Tn_pad, S_max;
-  const int4* btab; const float* nlse; const float* delta; float rq_scale;
-  float2* ybd_mean; float* bx_mean;
-  uint16_t* dk; uint16_t* dv; const float* rows_k; const float* rows_v; const int* kv_list;
-  const uint32_t* mask; uint32_t* mask_t;
-  Geometry geo; Counts cnt;
-};
-__global__ __launch_bounds__(128) void k_bwd_prepare(PrepArgs p) {
+__global__ __launch_bounds__(256) void k_bwd_prepare(PrepArgs p) {
   const int task = blockIdx.z / p.B, b = blockIdx.z % p.B;
-  if (task < p.n_lists) bwd_rows(p.ls, task, b, p.btab, p.nlse, p.rq_scale, p.delta, p.ybd_mean, p.bx_mean, p.cnt, p.H, p.Tn_pad, p.S_max);
-  else if (task == p.n_lists) bwd_fill(p.dk, p.dv, b, p.rows_k, p.rows_v, p.kv_list, p.btab, p.geo, p.cnt);
+  // the item counters of the launches that follow start at zero (ordinary stores: the call can be captured in a graph)
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x < 8) p.ctr[threadIdx.x] = 0;
+  if (task < 3) bwd_rows(p, task, b);
+  else if (task == 3) bwd_fill(p.dk, p.dv, b, p.rows_k, p.rows_v, p.list[0], p.btab, p.geo, p.cnt);
   else bwd_tmask(p.mask, p.mask_t, b, p.cnt, p.H);
 }
 
@@ -754,17 +775,16 @@ __global__ __launch_bounds__(128) void k_bwd_prepare(PrepArgs p) {
 // Its gradient: dOc[i] = gamma * (sum of dO over block i); dVc = S^T dOc; dS = dOc Vc^T; dZ = S * (dS - rowsum(dS * S));
 // dQc = dZ Kc / sqrt D; dKc = dZ^T Qc / sqrt D; each mean's gradient is spread evenly over its block's tokens.
 
-// One workgroup per (block, head), in place of k_bwd_delta: delta without the residual's share (the attention branches' delta
+// One workgroup per (block, head): delta without the residual's share (the attention branches' delta
 // is rowsum(dO * (out - gamma * O_coarse[block]))), and doc[block] = gamma * column sums of the block's dO rows, from one
 // read of dO.  HBM-bound: 40 heads of 15 600 tokens 97 + 60 us in two kernels -> 114.
 __global__ __launch_bounds__(256) void k_bwd_delta_residual(const uint16_t* __restrict__ o, const uint16_t* __restrict__ olo,
                                                             const uint16_t* __restrict__ d_o, const float* __restrict__ ocoarse,
                                                             float gamma, float* __restrict__ delta, float* __restrict__ doc,
-                                                            int* __restrict__ ctr, const int4* __restrict__ btab, Geometry g,
+                                                            const int4* __restrict__ btab, Geometry g,
                                                             Counts cnt, int S_max) {
   __shared__ float red[16][MD];
   const int blk = blockIdx.x, h = blockIdx.y, b = blockIdx.z, c16 = threadIdx.x & 15, rg = threadIdx.x >> 4;
-  if (blk == 0 && h == 0 && b == 0 && threadIdx.x < 8) ctr[threadIdx.x] = 0;      // as in k_bwd_delta
   if (blk >= cnt.b[b].T) return;
   const int4 ent = btab[b * cnt.T_max + blk];
   const long long bh = (long long)b * g.H + h;
@@ -1121,26 +1141,19 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
     // delta without the residual's share; gradient of the coarse residual with respect to the block means (all blocks, by
     // block id)
     hipLaunchKernelGGL(k_bwd_delta_residual, dim3(T_max, H, B), dim3(256), 0, st, (const uint16_t*)out, ws.olo, (const uint16_t*)d_out,
-                       ws.ocoarse, gamma, ws.delta, ws.doc, ws.bwd_ctr, ws.btab, pr.geo, pr.cnt, S_max);
+                       ws.ocoarse, gamma, ws.delta, ws.doc, ws.btab, pr.geo, pr.cnt, S_max);
     ISA_BWD_CHECK();
     const bool wide = T_max <= 1088;
     hipError_t ec = wide ? launch_bwd_coarse<16, false>(pr, ws, st) : launch_bwd_coarse<4, false>(pr, ws, st);
     if (ec == hipSuccess) ec = wide ? launch_bwd_coarse<16, true>(pr, ws, st) : launch_bwd_coarse<4, true>(pr, ws, st);
     if (ec != hipSuccess) return ec;
-  } else {
-    hipLaunchKernelGGL(k_bwd_delta, dim3((S_max + 15) / 16, H, B), dim3(256), 0, st, (const uint16_t*)out,
-                       ws.olo, (const uint16_t*)d_out, ws.delta, ws.bwd_ctr, pr.geo, pr.cnt, S_max);
-    ISA_BWD_CHECK();
   }
   const int gx = T_max > pr.Tn_pad ? T_max : pr.Tn_pad;
-  const float cs = 1.4426950408889634f / sqrtf((float)MD);      // raw score -> log2 domain
-  RowLists ls = {{kv_list, full_list, flat_list, flat_list}, {0, 1, 2, 2}, {nullptr, nullptr, nullptr, ws.rq},
-                 {ws.ktab, ws.ftab, ws.ltab, ws.ltab}, {ws.ybd_kv, ws.ybd_full, ws.ybd_flat, ws.ybd_flatm}};
-  // with exact sets the Taylor rows a second time, with q . Kc_0 in their exponent terms, for the launches that score them
-  // against gathered means
-  const PrepArgs pa = {ls, ex ? 4 : 3, B, H, pr.Tn_pad, S_max, ws.btab, ws.nlse, ws.delta, cs, ws.ybd_mean, ws.bx_mean, (uint16_t*)dk,
-                       (uint16_t*)dv, resid ? ws.cdk : nullptr, resid ? ws.cdv : nullptr, kv_list, exact_mask, ws.mask_t, pr.geo, pr.cnt};
-  hipLaunchKernelGGL(k_bwd_prepare, dim3(gx, H, B * (ex ? 6 : 4)), dim3(128), 0, st, pa);
+  PrepArgs pa = {B, H, pr.Tn_pad, S_max, {kv_list, full_list, flat_list}, {ws.ktab, ws.ftab, ws.ltab}, {ws.ybd_kv, ws.ybd_full, ws.ybd_flat},
+                 ex ? ws.rq : nullptr, ws.ybd_flatm, ws.btab, ws.nlse, 1.4426950408889634f / sqrtf((float)MD) /* raw score -> log2 domain */,
+                 resid ? nullptr : (const uint16_t*)out, ws.olo, (const uint16_t*)d_out, ws.delta, ws.bwd_ctr, ws.ybd_mean, ws.bx_mean,
+                 (uint16_t*)dk, (uint16_t*)dv, resid ? ws.cdk : nullptr, resid ? ws.cdv : nullptr, exact_mask, ws.mask_t, pr.geo, pr.cnt};
+  hipLaunchKernelGGL(k_bwd_prepare, dim3(gx, H, B * (ex ? 5 : 4)), dim3(256), 0, st, pa);
   ISA_BWD_CHECK();
 
   BwdArgs a;

@@ -75,7 +75,7 @@ struct Workspace {
   uint16_t* zero_tile;   // 16 KB of zeros, written by the V^T pack kernel
   int* taylor_ctr;       // two counters of the attention launch: [0] the next Taylor group (zeroed by the mean gather), [1] the next
                          // long item of a launch of nothing else (zeroed by the V^T pack)
-  int* bwd_ctr;          // backward: the next work item of each launch that hands its items out dynamically (8 counters, zeroed by k_bwd_delta)
+  int* bwd_ctr;          // backward: the next work item of each launch that hands its items out dynamically (8 counters, zeroed by k_bwd_prepare)
   int4* ktab;            // [B,H,T_max] the btab rows of the blocks of kv_list, in list order
   float* ocoarse;        // [B,H,T_max,D] pooled attention output (only carved when gamma != 0)
   // partial outputs of work items split along the key sequence, 256 x 256 rows, and their running maxima and sums.  Null if the general kernel's
