@@ -57,7 +57,7 @@ struct MfmaArgs {
   Counts cnt;
   int dense;
   int Tn_pad;
-  int slots;                                // work slots per (batch, head) = T_max
+  int slots;                                // work slots per (batch, head): the most Taylor blocks of one
   int total;                                // B * H * slots
   int slots_first, slots_second;            // k_attn_sp: exact / Taylor pair slots per (batch, head), each at least 1
   int tgroup, groups_second;                // k_attn_sp: Taylor pairs per group; such groups per (batch, head), at least 1
@@ -77,6 +77,7 @@ struct MfmaArgs {
   int taylor_here;                          // k_attn_sp: 1 = also process the Taylor slots (no exact sets), 0 = exact branch only
 };
 
-hipError_t launch_attn_mfma4(const Problem& pr, MfmaArgs m, hipStream_t st);
+// Taylor blocks with exact sets, and the merge of the n_merge cut items of the k_attn_sp launch before it
+hipError_t launch_attn_mfma4(const Problem& pr, MfmaArgs m, int n_merge, hipStream_t st);
 
 }  // namespace isa

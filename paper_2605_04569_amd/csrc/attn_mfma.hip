@@ -20,6 +20,7 @@
 // block means gathered in kv_list order, its "values" the gathered mean values, and the token count n_j
 // enters as an additive ln(n_j) on the scaled logit, which is the same as weighting exp() by n_j.
 #include "gather.h"
+#include "split_merge.h"
 
 namespace isa {
 
@@ -278,7 +279,11 @@ __device__ __forceinline__ uint4 halves_of_two_groups(uint2 a, uint2 b) {
   return make_uint4(x[0], y[0], x[1], y[1]);
 }
 
-__global__ __launch_bounds__(256, 2) void k_attn_mfma(MfmaArgs a) {
+// Workgroups from n_wgs on merge the cut items of the launch before (four times the rows of a workgroup of k_split_merge: only two
+// workgroups of this kernel fit a compute unit).  Measured, two launches / one: 12 heads of 1564 tokens 8.5 + 14.3 / 18.0 us, the call at the
+// paper's ratios over 65 520 tokens 21.64 / 21.53 ms (of which the workgroups that used to be launched for exact-branch blocks are a part).
+constexpr int MERGE_ROWS = 4;
+__global__ __launch_bounds__(256, 2) void k_attn_mfma(MfmaArgs a, int n_wgs) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * K_TILE + 2 * V_TILE + 2 * 512];
   uint16_t* ldsK = lds;                     // [2][K_TILE]
   uint16_t* ldsV = lds + 2 * K_TILE;        // [2][V_TILE]
@@ -286,24 +291,25 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(MfmaArgs a) {
 
   // ---- which work item: consecutive logical ids go to the same XCD, so that the workgroups that run
   // together on one XCD (and share its L2) read the same head's keys and values
-  const int nwg = gridDim.x;
-  const int per_xcd = nwg >> 3;             // grid is a multiple of 8
+  if ((int)blockIdx.x >= n_wgs) {
+    split_merge<MERGE_ROWS>(a, (int)blockIdx.x - n_wgs);
+    return;
+  }
+  const int per_xcd = n_wgs >> 3;           // a multiple of 8
   const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (logical >= a.total) return;
   const int slot = logical % a.slots;
   const int bhid = logical / a.slots;
   const int h = bhid % a.geo.H, b = bhid / a.geo.H;
   const BatchCounts c = a.cnt.b[b];
-  if (slot >= c.T) return;
+  if (slot >= c.n_flat) return;
   const int T_max = a.geo.T_max;
   const long long bh = bhid;
 
-  // only the Taylor slots of the (batch, head): its exact-branch blocks are handled by the 8-wave kernel
-  if (slot < c.n_full) return;
   const int n_list = c.T_new;
-  const int qi = block_in_range(a.flat_list[bh * T_max + slot - c.n_full], c.T);
+  const int qi = block_in_range(a.flat_list[bh * T_max + slot], c.T);
   const uint32_t* mrow = (a.exact_mask && c.k_exact > 0)
-                             ? a.exact_mask + (bh * T_max + (slot - c.n_full)) * a.cnt.mask_words : nullptr;
+                             ? a.exact_mask + (bh * T_max + slot) * a.cnt.mask_words : nullptr;
   const int* bn = a.blk_n + b * T_max;
   const int* bs = a.blk_start + b * T_max;
   const int n_q = bn[qi];
@@ -551,12 +557,14 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(MfmaArgs a) {
   }
 }
 
-// The 4-wave kernel on the Taylor slots only (used when Taylor blocks carry exact sets).
-hipError_t launch_attn_mfma4(const Problem& pr, MfmaArgs m, hipStream_t st) {
-  m.slots = pr.cnt.T_max;
-  m.total = pr.p.B * pr.p.H * pr.cnt.T_max;
-  const int grid = (m.total + 7) / 8 * 8;
-  hipLaunchKernelGGL(k_attn_mfma, dim3(grid), dim3(256), 0, st, m);
+// The 4-wave kernel: the Taylor blocks that carry exact sets.
+hipError_t launch_attn_mfma4(const Problem& pr, MfmaArgs m, int n_merge, hipStream_t st) {
+  m.slots = 0;
+  for (int b = 0; b < pr.p.B; ++b) m.slots = pr.cnt.b[b].n_flat > m.slots ? pr.cnt.b[b].n_flat : m.slots;
+  m.total = pr.p.B * pr.p.H * m.slots;
+  const int n_wgs = (m.total + 7) / 8 * 8, grid = n_wgs + n_merge * (32 / MERGE_ROWS);
+  if (grid == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_attn_mfma, dim3(grid), dim3(256), 0, st, m, n_wgs);
   return hipGetLastError();
 }
 
