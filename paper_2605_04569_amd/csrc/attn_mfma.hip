@@ -31,7 +31,7 @@ namespace isa {
 // 16x16x32 kernel (position p holds key key_of_pos16(p)).
 //
 // ALL: the first kernel of the whole call.  The same workgroup also takes the block means of its block of V, Q and K
-// (fp32, Alg. 1 Stage 1), and finds its block's place from the segment lengths instead of reading it from the block
+// (fp32, Alg. 1 Stage 1).  Either form finds its block's place from the segment lengths instead of reading it from the block
 // table, which the workgroups of head 0 write for the kernels that follow.  One launch instead of three, and a thread
 // has its 16-byte loads of all three tensors in flight at once.  HBM-bound at the rate of a copy: 5.1 TB/s for
 // 117 000 tokens of 40 heads (940 us as before); short calls gain: 40 heads of 15 600 tokens 157 -> 126 us, 5 heads of 990
@@ -51,16 +51,11 @@ __global__ __launch_bounds__(256) void k_pack_vt(const uint16_t* __restrict__ v,
     if (threadIdx.x == 0) *long_ctr = 0;                          // the counter a launch of nothing but long items may take them from
   }
   int start, n;
-  if (ALL) {
-    block_place(seg, 128, b, j, start, n);
-    if (h == 0 && threadIdx.x == 0) {
-      blk_start[b * g.T_max + j] = start;
-      blk_n[b * g.T_max + j] = n;
-      btab[b * g.T_max + j] = make_int4(start, n, j, 0);
-    }
-  } else {
-    start = blk_start[b * g.T_max + j];
-    n = blk_n[b * g.T_max + j];
+  block_place(seg, 128, b, j, start, n);
+  if (h == 0 && threadIdx.x == 0) {
+    blk_start[b * g.T_max + j] = start;
+    blk_n[b * g.T_max + j] = n;
+    btab[b * g.T_max + j] = make_int4(start, n, j, 0);
   }
   if (n == 0) return;
   const int c = threadIdx.x & 15, rg = threadIdx.x >> 4;          // 16-byte chunk c of rows rg, rg + 16, ..

@@ -256,14 +256,16 @@ static AttnArgs attn_args(const Problem& pr, const Workspace& ws, const void* q,
   return a;
 }
 
-static int run_attend(const Problem& pr, const Workspace& ws, const AttnArgs& a, const void* v, bool vt_ready,
+// ready: the block table and, for the pipelined kernels, the packed V^T copy are there already.
+static int run_attend(const Problem& pr, const Workspace& ws, const AttnArgs& a, const void* v, bool ready,
                       hipStream_t st, bool means_ready = false) {
   const bool mfma = pr.mfma_shape && g_use_mfma.load();
   if (!mfma) {
+    if (!ready) ISA_STAGE(launch_layout(pr, ws, st));
     ISA_STAGE(launch_attn_gen(pr, ws, a, st));
     return ISA_OK;
   }
-  if (!vt_ready) ISA_STAGE(launch_pack_vt(pr, ws, v, st));
+  if (!ready) ISA_STAGE(launch_pack_vt(pr, ws, v, st));
   if (!a.dense && !means_ready) ISA_STAGE(launch_gather_means(pr, ws, a.kc, a.vc, a.kv_list, st));
   ISA_STAGE(launch_attn_mfma(pr, ws, a, st));
   return ISA_OK;
@@ -324,7 +326,6 @@ int isa_block_means(const isa_problem* p, const void* q, const void* k, const vo
   Workspace ws;
   if ((rc = check_ws(pr, workspace, workspace_bytes, &ws)) != ISA_OK) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
-  ISA_STAGE(launch_layout(pr, ws, st));
   ISA_STAGE(launch_block_means(pr, ws, q, k, v, qc, kc, vc, st));
   return ISA_OK;
 }
@@ -384,7 +385,6 @@ int isa_attend(const isa_problem* p, const void* q, const void* k, const void* v
   Workspace ws;
   if ((rc = check_ws(pr, workspace, workspace_bytes, &ws)) != ISA_OK) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
-  ISA_STAGE(launch_layout(pr, ws, st));
   AttnArgs a = attn_args(pr, ws, q, k, v, out, kc, vc, kv_list, full_list, flat_list,
                          p->exact_frac > 0.0 ? exact_mask : nullptr, o_coarse, 0);
   return run_attend(pr, ws, a, v, false, st);
@@ -398,7 +398,6 @@ static int run_attention(const Problem& pr, const Workspace& ws, const void* q, 
   if (pack_first) {
     ISA_STAGE(launch_front(pr, ws, q, k, v, st));
   } else {
-    ISA_STAGE(launch_layout(pr, ws, st));
     ISA_STAGE(launch_block_means(pr, ws, q, k, v, ws.qc, ws.kc, ws.vc, st));
   }
   const bool plan = plan_is_small(pr), small = pack_first && (plan || select_is_small(pr));
@@ -409,7 +408,7 @@ static int run_attention(const Problem& pr, const Workspace& ws, const void* q, 
     ISA_STAGE(launch_select(pr, ws, ws.s_ctx, ws.sharp, ws.z, ws.kv_list, ws.full_list, ws.flat_list, ws.exact_mask, st, small));
   }
   AttnArgs a = attn_args(pr, ws, q, k, v, out, ws.kc, ws.vc, ws.kv_list, ws.full_list, ws.flat_list, ws.exact_mask, ws.ocoarse, 0);
-  return run_attend(pr, ws, a, v, pack_first, st, small);
+  return run_attend(pr, ws, a, v, true, st, small);
 }
 
 int isa_attention(const isa_problem* p, const void* q, const void* k, const void* v, void* out, void* workspace,
@@ -478,7 +477,6 @@ int isa_dense_attention(const isa_problem* p, const void* q, const void* k, cons
   Workspace ws;
   if ((rc = check_ws(pr, workspace, workspace_bytes, &ws)) != ISA_OK) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
-  ISA_STAGE(launch_layout(pr, ws, st));
   AttnArgs a = attn_args(pr, ws, q, k, v, out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 1);
   return run_attend(pr, ws, a, v, false, st);
 }
@@ -508,7 +506,6 @@ int isa_attention_backward(const isa_problem* p, const void* q, const void* k, c
   // from the workspace) the block table, the block means, the gathered mean keys and O_coarse are still there as well;
   // the staged forward takes its means and O_coarse from the caller, so after it they are computed again here.
   if (n_lists != 0) {
-    ISA_STAGE(launch_layout(pr, ws, st));
     ISA_STAGE(launch_block_means(pr, ws, q, k, v, ws.qc, ws.kc, ws.vc, st));
     ISA_STAGE(launch_gather_means(pr, ws, ws.kc, ws.vc, kv_list, st));
     if (p->gamma != 0.0)                            // O_coarse of Alg. 1 Stage 1

@@ -155,6 +155,7 @@ struct AttnArgs {
 };
 
 hipError_t launch_layout(const Problem& pr, const Workspace& ws, hipStream_t st);
+// (writes the block table as well)
 hipError_t launch_block_means(const Problem& pr, const Workspace& ws, const void* q, const void* k, const void* v,
                               float* qc, float* kc, float* vc, hipStream_t st);
 hipError_t launch_coarse(const Problem& pr, const Workspace& ws, const float* qc, const float* kc,
@@ -172,6 +173,7 @@ hipError_t launch_plan(const Problem& pr, const Workspace& ws, bool gather, hipS
 hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArgs& a, hipStream_t st);
 
 // MFMA path (bf16, D = 128, block = 128)
+// the packed V^T copy and the block table
 hipError_t launch_pack_vt(const Problem& pr, const Workspace& ws, const void* v, hipStream_t st);
 // the block table, the block means of q, k, v (into the workspace) and the packed V^T copy, in one launch
 hipError_t launch_front(const Problem& pr, const Workspace& ws, const void* q, const void* k, const void* v, hipStream_t st);

@@ -11,37 +11,40 @@ namespace isa {
 // ------------------------------------------------------------------------------------------
 // helpers
 // ------------------------------------------------------------------------------------------
-__device__ inline float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
+// Reductions over the 64 lanes of a wave, every lane gets the result: partners 32, 16, 8, 4, 2, 1 lanes away in turn.  The halves and the rows
+// of 16 lanes meet through the two swap instructions, the lanes of a row by rotating it (by 8, 4, 2, 1: by then the lanes 8, 4, 2
+// further on hold the same value, so the rotated lane stands for the exchanged one).  All on the vector unit: through the LDS (ds_bpermute), 16
+// waves' reductions of 64-bit numbers were what k_plan spent its time on (whole calls, 5 heads of 9 blocks 38.9 -> 38.1 us, 10 heads of
+// 62 blocks 92.8 -> 90.2).
+template <int O> __device__ __forceinline__ void partners(uint32_t x, uint32_t& a, uint32_t& b) {
+  if constexpr (O == 32) {
+    const auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    a = s[0]; b = s[1];
+  } else if constexpr (O == 16) {
+    const auto s = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    a = s[0]; b = s[1];
+  } else {
+    a = x;
+    b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + O, 0xf, 0xf, true);           // row_ror
+  }
 }
-__device__ inline double wave_sum(double x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
+template <int O> __device__ __forceinline__ float lanes_max(float x) {
+  uint32_t a, b;
+  partners<O>(__float_as_uint(x), a, b);
+  return fmaxf(__uint_as_float(a), __uint_as_float(b));
 }
-__device__ inline float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
+template <int O> __device__ __forceinline__ double lanes_add(double x) {
+  uint32_t a0, b0, a1, b1;
+  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+  partners<O>((uint32_t)u, a0, b0);
+  partners<O>((uint32_t)(u >> 32), a1, b1);
+  return __longlong_as_double((long long)(((unsigned long long)a1 << 32) | a0)) + __longlong_as_double((long long)(((unsigned long long)b1 << 32) | b0));
 }
-
-// Block-wide reductions for 256 threads (4 waves); every thread gets the result.
-template <typename T>
-__device__ inline T block_sum(T x, T* red /* >= 4 elements of LDS */) {
-  x = wave_sum(x);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-  __syncthreads();
-  return ((red[0] + red[1]) + red[2]) + red[3];
+__device__ __forceinline__ double wave_sum(double x) {
+  return lanes_add<1>(lanes_add<2>(lanes_add<4>(lanes_add<8>(lanes_add<16>(lanes_add<32>(x))))));
 }
-__device__ inline float block_max(float x, float* red) {
-  x = wave_max(x);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-  __syncthreads();
-  return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+__device__ __forceinline__ float wave_max(float x) {
+  return lanes_max<1>(lanes_max<2>(lanes_max<4>(lanes_max<8>(lanes_max<16>(lanes_max<32>(x))))));
 }
 
 __device__ inline float bf16_bits_to_float(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
@@ -66,7 +69,8 @@ hipError_t launch_layout(const Problem& pr, const Workspace& ws, hipStream_t st)
 }
 
 // ------------------------------------------------------------------------------------------
-// Block means.  One workgroup per (block, head, batch); q, k and v in turn.
+// Block means, and the block table (the workgroups of head 0 write it: a launch less than with k_layout in front).  One workgroup per
+// (block, head, batch); q, k and v in turn.
 // A thread owns VEC consecutive channels (one 16-byte load) of every RP-th row.
 // ------------------------------------------------------------------------------------------
 template <typename T> struct Vec16;
@@ -94,16 +98,21 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void k_block_means(const T* __restrict__ q, const T* __restrict__ k,
                                                      const T* __restrict__ v, float* __restrict__ qc,
                                                      float* __restrict__ kc, float* __restrict__ vc,
-                                                     const int* __restrict__ blk_start, const int* __restrict__ blk_n,
-                                                     Geometry g) {
+                                                     int* __restrict__ blk_start, int* __restrict__ blk_n,
+                                                     int4* __restrict__ btab, SegDesc seg, Geometry g) {
   constexpr int VEC = Vec16<T>::N;
   constexpr int CH = D / VEC;          // 16-byte chunks per row
   constexpr int RP = 256 / CH;         // rows covered per pass
   __shared__ float red[RP][D];
   const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int n = blk_n[b * g.T_max + j];
+  int start, n;
+  block_place(seg, g.block, b, j, start, n);
+  if (h == 0 && threadIdx.x == 0) {
+    blk_start[b * g.T_max + j] = start;
+    blk_n[b * g.T_max + j] = n;
+    btab[b * g.T_max + j] = make_int4(start, n, j, 0);
+  }
   if (n == 0) return;
-  const int start = blk_start[b * g.T_max + j];
   const int c = threadIdx.x % CH, rg = threadIdx.x / CH;
   const long long base = (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)start * g.stride_t + c * VEC;
   const long long obase = (((long long)b * g.H + h) * g.T_max + j) * D;
@@ -137,7 +146,7 @@ hipError_t launch_block_means(const Problem& pr, const Workspace& ws, const void
   const dim3 grid(pr.cnt.T_max, pr.p.H, pr.p.B), blk(256);
 #define ISA_MEANS(T, D)                                                                                        \
   hipLaunchKernelGGL((k_block_means<T, D>), grid, blk, 0, st, (const T*)q, (const T*)k, (const T*)v, qc, kc, vc, \
-                     ws.blk_start, ws.blk_n, pr.geo)
+                     ws.blk_start, ws.blk_n, ws.btab, pr.seg, pr.geo)
   if (pr.p.dtype == ISA_BF16) {
     if (pr.p.D == 128) ISA_MEANS(uint16_t, 128); else ISA_MEANS(uint16_t, 64);
   } else {
@@ -547,7 +556,7 @@ __global__ __launch_bounds__(256) void k_exact_sets(const float* __restrict__ z,
 // pooled map with its softmax, column means and sharpness (as k_coarse and k_colmean, in the same order of additions), both
 // selections (a wave each: a lane per block, ranks by comparing with every other lane, lists by the bits of a ballot), then the gathered means (GATHER:
 // the pipelined kernels) beside the exact sets.  All latency at these sizes: 5 heads of 9 blocks k_coarse 6.7 + k_select 10.8 us and the
-// launch between them -> 9.9; whole call 44.8 -> 39.2 us, 8 heads of 42 blocks in fp32 306 -> 304.
+// launch between them -> 9.9; whole call 44.8 -> 38.1 us.
 constexpr int PLAN_BLOCKS = 64;
 struct PlanArgs {
   const float *qc, *kc;
@@ -598,26 +607,49 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
     }
   }
   __syncthreads();
-  for (int i = wave; i < T; i += 16) {               // a row of at most 64 columns per wave
-    const float zv = lane < T ? zs[i * ZS + lane] : -INFINITY;
-    const float m = wave_max(zv);
-    const float e = lane < T ? expf(zv - m) : 0.f;
-    const double ed = (double)e, src = lane < T_src ? ed : 0.0;
-    const double l = wave_sum(ed), l_src = wave_sum(src), q_src = wave_sum(src * src);
-    const double mu = l_src / l / (double)T_src;
-    const double var = q_src / (l * l) / (double)T_src - mu * mu;
-    if (lane == 0) {
-      sh[i] = (float)fmax(var, 0.0);
-      a.sharp[row0 + i] = sh[i];
+  // a row of at most 64 columns per wave, two rows' reductions side by side
+  for (int i0 = wave; i0 < T; i0 += 32) {
+    float e[2];
+    double l[2], l_src[2], q_src[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const float zv = lane < T ? zs[min(i0 + 16 * u, T - 1) * ZS + lane] : -INFINITY;
+      e[u] = zv - wave_max(zv);
     }
-    if (i < T_src && lane >= T_src && lane < T) ps[i * ZS + lane - T_src] = e * (float)(1.0 / l);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      e[u] = lane < T ? expf(e[u]) : 0.f;
+      l[u] = (double)e[u];
+      l_src[u] = lane < T_src ? l[u] : 0.0;
+      q_src[u] = l_src[u] * l_src[u];
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      l[u] = wave_sum(l[u]);
+      l_src[u] = wave_sum(l_src[u]);
+      q_src[u] = wave_sum(q_src[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int i = i0 + 16 * u;
+      if (i >= T) break;
+      const double mu = l_src[u] / l[u] / (double)T_src;
+      const double var = q_src[u] / (l[u] * l[u]) / (double)T_src - mu * mu;
+      if (lane == 0) {
+        sh[i] = (float)fmax(var, 0.0);
+        a.sharp[row0 + i] = sh[i];
+      }
+      if (i < T_src && lane >= T_src && lane < T) ps[i * ZS + lane - T_src] = e[u] * (float)(1.0 / l[u]);
+    }
   }
   __syncthreads();
   if (wave < 4) {                                    // Eq. 1, a quarter of the source rows per wave (see k_colmean)
     const int per = (T_src + 3) / 4, i_lo = wave * per, i_hi = min(T_src, i_lo + per);
     double acc = 0.0;
-    if (lane < c.T_ctx)
+    if (lane < c.T_ctx) {
+#pragma unroll 8
       for (int i = i_lo; i < i_hi; ++i) acc += (double)ps[i * ZS + lane];
+    }
     sums[wave][lane] = acc;
   }
   __syncthreads();
@@ -633,7 +665,8 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
       }
     }
     int rank = 0;
-    for (int x = 0; x < n; ++x) rank += beats(__shfl(s, x, 64), x, s, lane) ? 1 : 0;
+#pragma unroll 8
+    for (int x = 0; x < n; ++x) rank += beats(__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(s), x)), x, s, lane) ? 1 : 0;
     const unsigned long long yes = __ballot(lane < n && rank < k), below = (1ull << lane) - 1ull;
     const int at_yes = __popcll(yes & below), at_no = lane - at_yes;
     const bool chosen = (yes >> lane) & 1ull;
@@ -660,7 +693,10 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
   if (GATHER) gather_tile(a.g, tile, kvs, threadIdx.x & 255, 0, h, b, wave < 4);
 }
 
-bool plan_is_small(const Problem& pr) { return pr.cnt.T_max <= PLAN_BLOCKS && pr.p.gamma == 0.0; }
+// One workgroup has all rows of a head to itself, which stops paying off towards 64 blocks unless the exact sets' launch is saved as well.  Whole
+// calls, separate launches / one: 10 heads of 33, 48, 62 blocks 66.2 / 61.8, 76.0 / 74.7, 88.5 / 90.2 us, with exact sets 33, 62 blocks 91.7 /
+// 77.6, 133.6 / 131.3.
+bool plan_is_small(const Problem& pr) { return pr.cnt.T_max <= (pr.p.exact_frac > 0.0 ? PLAN_BLOCKS : 48) && pr.p.gamma == 0.0; }
 
 hipError_t launch_plan(const Problem& pr, const Workspace& ws, bool gather, hipStream_t st) {
   PlanArgs a = {ws.qc, ws.kc, ws.s_ctx, ws.sharp, ws.kv_list, ws.full_list, ws.flat_list, pr.p.exact_frac > 0.0 ? ws.exact_mask : nullptr,
