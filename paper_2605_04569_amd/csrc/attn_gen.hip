@@ -709,7 +709,11 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
   // instructions of twice the length, and more waves always won) and parts per long item, chosen together by a model of the
   // launch's time: with k workgroups per compute unit a block of 64 tokens takes each of them pace[k - 1], in us as measured (k
   // beyond what fits a compute unit: further rounds), and a workgroup spends `start` tokens' time on its start and its share of the merge.  A
-  // Taylor item takes 1/32 (D = 64) or 1/14 (D = 128) of a long one's time, plus its exact set's share.
+  // Taylor item counts for 1/32 of a long one of the same rows, plus its exact set's share.  The time is that of the long items' rounds or
+  // that of all items with the chip full, whichever is longer: Taylor items fill what the long ones leave idle, and where there are many of
+  // them parts gain nothing (20 heads of 128 channels, 3 x 1176 tokens, whole items of 128 rows / in two parts / of 64 rows: with exact sets
+  // 170 / 194 / 179 us, without 168 / 144 / 157).  A bf16 part has at least 256 tokens (5 heads, 2 x 495 tokens, D = 128, 1, 2, 4, 6, 8 parts: 51,
+  // 44, 42, 44, 47 us), an fp32 one may be a single block (1 head, 300 tokens: 54 whole, 44 in parts).
   // Measured, whole calls, us, keep 0.5, full 0.25, whole items of 128 rows / of 64 / as chosen (64 rows in two groups of waves that
   // shared a workgroup's tiles, which this replaces): bf16, 15 600 tokens, blocks of 64: D = 64, 1 head 380 / 298 / 95, 2 heads
   // 393 / 308 / 120 (238), 4 400 / 317 / 178 (243), 8 409 / 343 / 295, 12 499 / 461 / 394, 16 524 / 574 / 524, 24 712 / 819 / 712; D = 128: 2 heads
@@ -718,7 +722,7 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
   struct Form { int rows, resident; double pace[4], start; };
   static const Form forms[2][2][2] = {                 // [bf16][D = 64][64 / 128 rows]
       {{{64, 2, {5.55, 9.9}, 80}, {}}, {{64, 4, {3.6, 5.5, 7.9, 10.5}, 64}, {}}},
-      {{{64, 2, {1.85, 2.74}, 384}, {128, 2, {2.65, 4.35}, 384}}, {{64, 4, {1.36, 1.54, 2.15, 2.8}, 384}, {128, 3, {1.82, 2.33, 3.4}, 384}}}};
+      {{{64, 2, {1.85, 2.74}, 320}, {128, 2, {2.65, 4.35}, 320}}, {{64, 4, {1.36, 1.54, 2.15, 2.8}, 320}, {128, 3, {1.82, 2.33, 3.4}, 320}}}};
   bool two = false;
   ga.parts = 1;
   if (n_long == 0) {
@@ -735,12 +739,16 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
     for (int f = 0; f < (bf ? 2 : 1); ++f) {
       const Form& form = forms[bf][d64][f];
       const long long n = items(n_long, form.rows);
-      const double taylor = (double)items(n_taylor, form.rows) * ((d64 ? 1.0 / 32 : 1.0 / 14) + set_share) / chip * form.pace[form.resident - 1] / form.resident * tokens;
+      // per workgroup with the chip full; a pair of blocks of 64 reads both blocks' exact sets
+      const double full = form.pace[form.resident - 1] / form.resident / chip;
+      const double share = 1.0 / 32 + set_share * (form.rows > pr.p.block ? 2 : 1);
+      const double taylor = (double)items(n_taylor, form.rows) * share * tokens * full;
       for (int p = 1; p <= MAX_PARTS && p <= shortest; ++p) {
-        if (p > 1 && (!ws.split_o || n * p * form.rows * pr.p.D > SPLIT_MAX_SUB * 256ll * 128)) break;
+        if (p > 1 && (!ws.split_o || (bf && tokens < 256.0 * p) || n * p * form.rows * pr.p.D > SPLIT_MAX_SUB * 256ll * 128)) break;
         const int k = (int)ceil((double)(n * p) / chip), rounds = (k - 1) / form.resident;
         const double pace = rounds * form.pace[form.resident - 1] + form.pace[(k - 1) % form.resident];
-        const double cost = pace * (tokens / p + form.start) + taylor + (p > 1 ? merge : 0.0);
+        const double each = tokens / p + form.start;
+        const double cost = fmax(pace * each, (double)(n * p) * each * full + taylor) + (p > 1 ? merge : 0.0);
         if (cost < best) { best = cost; two = f == 1; ga.parts = p; }
       }
     }

@@ -76,7 +76,7 @@ def test_one_and_two_groups(I, shape, H):
     check_end_to_end(I, wl, *gen(wl), heads=[0, H // 2, H - 1])
 
 
-# few heads: long items in 2 to 8 parts over key lists of 2 blocks (one each), of 9 (unequal parts) and of 40; odd lists of blocks, a shorter
+# few heads: long items in 2 to 8 parts over key lists of 2 blocks (fp32: one each; bf16: whole), of 9 (unequal parts) and of 40; odd lists of blocks, a shorter
 # batch item, the residual added where the parts are
 @pytest.mark.parametrize("blocks", [2, 9, 40])
 @pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
