@@ -21,11 +21,11 @@ def _zero_past_the_end(x, problem):
 
 class _IsaAttentionFunction(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, q, k, v, problem, workspace):
+    def forward(ctx, q, k, v, problem, cp, workspace):
         out = _zero_past_the_end(torch.empty_like(q), problem)
-        B.isa_attention(problem, q, k, v, out, workspace)
+        B._attention(cp, q, k, v, out, workspace)
         ctx.save_for_backward(q, k, v, out)
-        ctx.problem, ctx.workspace = problem, workspace
+        ctx.problem, ctx.cp, ctx.strides, ctx.workspace = problem, cp, q.stride(), workspace
         return out
 
     @staticmethod
@@ -36,8 +36,11 @@ class _IsaAttentionFunction(torch.autograd.Function):
             g.copy_(d_out)
             d_out = g
         dq, dk, dv = (_zero_past_the_end(torch.empty_like(q), ctx.problem) for _ in range(3))
-        B.isa_attention_backward(ctx.problem, q, k, v, out, d_out, dq, dk, dv, ctx.workspace)
-        return dq, dk, dv, None, None
+        cp = ctx.cp
+        if q.stride() != ctx.strides:            # saved tensors may come back in another layout
+            cp = ctx.problem.c_struct(q)[0]
+        B._attention_backward(cp, q, k, v, out, d_out, dq, dk, dv, ctx.workspace)
+        return dq, dk, dv, None, None, None
 
 
 class InContextSparseAttention(torch.nn.Module):
@@ -61,11 +64,12 @@ class InContextSparseAttention(torch.nn.Module):
             "the differentiable path covers bf16, D = 128, block = 128"
         assert q.shape[0] == len(self.seg_len)
         pr = B.Problem(H=q.shape[1], D=q.shape[3], dtype="bf16", block=self.block, seg_len=self.seg_len, **self.ratios)
-        need = B.isa_workspace_bytes(pr)
+        cp, _ = pr.c_struct(q)                   # one for the size and both passes
+        need = B._workspace_bytes(cp)
         if self._workspace is None or self._workspace.numel() < need or self._workspace.device != q.device:
             self._workspace = torch.empty(max(256, need), dtype=torch.uint8, device=q.device)
         if k.stride() != q.stride():
             k = k.contiguous() if q.is_contiguous() else torch.empty_like(q).copy_(k)
         if v.stride() != q.stride():
             v = v.contiguous() if q.is_contiguous() else torch.empty_like(q).copy_(v)
-        return _IsaAttentionFunction.apply(q, k, v, pr, self._workspace)
+        return _IsaAttentionFunction.apply(q, k, v, pr, cp, self._workspace)

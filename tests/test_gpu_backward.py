@@ -429,3 +429,21 @@ def test_autograd_module_matches_the_oracle(I, layout):
     I.isa_attention(pr, q.detach(), k.detach(), v.detach(), want, I.new_workspace(pr))
     assert torch.equal(out.detach(), want)
     _compare(wl, Q, K, V, dO, plans, q.grad, k.grad, v.grad)
+
+
+def test_saved_tensors_in_another_layout(I):
+    """Hooks that give the backward pass contiguous copies of token-major tensors: the same gradients, bit for bit."""
+    wl = SMALL.with_(exact_frac=0.25, gamma=0.5)
+    Q, K, V, dO = _inputs(wl)
+    grads = []
+    for pack in (lambda t: t, lambda t: t.contiguous()):
+        q, k, v = (t.cuda().transpose(1, 2).contiguous().transpose(1, 2).requires_grad_(True) for t in (Q, K, V))
+        attn = I.InContextSparseAttention([wl.seg_len(b) for b in range(wl.B)], keep_ratio=wl.keep_ratio, full_frac=wl.full_frac,
+                                          exact_frac=wl.exact_frac, gamma=wl.gamma)
+        with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t):
+            out = attn(q, k, v)
+        out.backward(dO.cuda())
+        grads.append((q.grad, k.grad, v.grad))
+    torch.cuda.synchronize()
+    for a, b in zip(*grads):
+        assert torch.equal(a, b)
