@@ -208,7 +208,8 @@ int isa_attend(const isa_problem* p, const void* q, const void* k, const void* v
  * q, k, v, out: as given to / written by the forward call; d_out: gradient of the loss with respect to `out`;
  * dq, dk, dv: receive the gradients.  All seven are device bf16 tensors with the layout and strides of the problem;
  * every row of dq, dk and dv is written (with gamma == 0, keys and values of context blocks that were not kept get
- * zeros).
+ * zeros).  No gradient is written before `out` has been read for the last time, so one of dq, dk and dv may be the buffer of `out`;
+ * they must share no memory with the other inputs or with each other.
  * kv_list, full_list, flat_list, exact_mask: the device lists (and, when exact_frac > 0, the exact-set bits, as written
  * by isa_select) the forward call ran with, or all NULL for those that isa_attention left in the workspace.
  * The workspace must be the one the forward call used, untouched since: it holds the log-sum-exp of every query row and

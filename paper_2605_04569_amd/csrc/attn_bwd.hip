@@ -611,8 +611,8 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdTokensArgs p) {
 }
 
 // What the launches need before they start, in one launch of 256 threads a workgroup, blockIdx.z = task * B + batch item.  Tasks: the lists of
-// the kept, the full-attention and the Taylor blocks (bwd_rows), the fill (bwd_fill), with exact sets the transposed bits (bwd_tmask): none
-// reads what another writes.  Delta belongs to the blocks' rows and is worked out where their terms are: as a launch of its own it
+// the kept, the full-attention and the Taylor blocks (bwd_rows), with exact sets the transposed bits (bwd_tmask): none reads what another
+// writes, and none writes a gradient: `out` is read here for the last time, and its buffer may be that of one of them.  Delta belongs to the blocks' rows and is worked out where their terms are: as a launch of its own it
 // was one more wait and another 4 us of the host's time (a training step of 12 heads of 1564 tokens 183 / 177 us, two runs where the host
 // bounds it; 65 520 tokens at the paper's ratios equal).
 struct PrepArgs {
@@ -623,7 +623,6 @@ struct PrepArgs {
   const uint16_t *o, *olo, *d_o;                             // o null: delta is there already (k_bwd_delta_residual)
   float* delta; int* ctr;
   float2* ybd_mean; float* bx_mean;
-  uint16_t* dk; uint16_t* dv; const float* rows_k; const float* rows_v;
   const uint32_t* mask; uint32_t* mask_t;
   Geometry geo; Counts cnt;
 };
@@ -717,22 +716,21 @@ __device__ __forceinline__ void bwd_rows(const PrepArgs& p, int kind, int b) {
 // Rows of dK and dV that no later launch writes (keys and values of blocks that were not kept): zero, or, with the
 // coarse residual, the block's share `rows[block] / n` of the gradient of its mean.  The launches over the kept blocks write
 // theirs, so those are left alone (480p at the paper's ratios, half the blocks kept: 220 us for all rows of both -> 79).
-__device__ __forceinline__ void bwd_fill(uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int b,
-                                         const float* __restrict__ rows_k, const float* __restrict__ rows_v,
-                                         const int* __restrict__ kv_list, const int4* __restrict__ btab, const Geometry& g, const Counts& cnt) {
-  const int blk = blockIdx.x, h = blockIdx.y;
+struct Fill { uint16_t *dk, *dv; const float *rows_k, *rows_v; const int* kv_list; const int4* btab; };
+__device__ __forceinline__ void bwd_fill(const Fill& f, int wg, const Geometry& g, const Counts& cnt) {
+  const int blk = wg % cnt.T_max, h = wg / cnt.T_max % g.H, b = wg / cnt.T_max / g.H;
   const int T = cnt.b[b].T, T_new = cnt.b[b].T_new;
   if (blk >= T) return;
   const long long bh = (long long)b * g.H + h;
   int kept = 0;
-  for (int t = threadIdx.x; t < T_new; t += 256) kept |= block_in_range(kv_list[bh * cnt.T_max + t], T) == blk ? 1 : 0;
+  for (int t = threadIdx.x; t < T_new; t += 256) kept |= block_in_range(f.kv_list[bh * cnt.T_max + t], T) == blk ? 1 : 0;
   if (__syncthreads_or(kept)) return;
-  const int4 ent = btab[b * cnt.T_max + blk];
+  const int4 ent = f.btab[b * cnt.T_max + blk];
   const int c16 = threadIdx.x & 15;
   const float inv = 1.0f / (float)ent.y;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    const float* rows = t ? rows_v : rows_k;
+    const float* rows = t ? f.rows_v : f.rows_k;
     uint4 val = make_uint4(0, 0, 0, 0);
     if (rows) {
       const float* rp = rows + (bh * cnt.T_max + blk) * MD + 8 * c16;
@@ -741,7 +739,7 @@ __device__ __forceinline__ void bwd_fill(uint16_t* __restrict__ dk, uint16_t* __
       for (int i = 0; i < 4; ++i) w[i] = f2bf(rp[2 * i] * inv) | ((uint32_t)f2bf(rp[2 * i + 1] * inv) << 16);
       val = make_uint4(w[0], w[1], w[2], w[3]);
     }
-    uint16_t* x = (t ? dv : dk) + (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)ent.x * g.stride_t + 8 * c16;
+    uint16_t* x = (t ? f.dv : f.dk) + (long long)b * g.stride_b + (long long)h * g.stride_h + (long long)ent.x * g.stride_t + 8 * c16;
     for (int r = threadIdx.x >> 4; r < ent.y; r += 16) *reinterpret_cast<uint4*>(x + (long long)r * g.stride_t) = val;
   }
 }
@@ -767,7 +765,6 @@ __global__ __launch_bounds__(256) void k_bwd_prepare(PrepArgs p) {
   // the item counters of the launches that follow start at zero (ordinary stores: the call can be captured in a graph)
   if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x < 8) p.ctr[threadIdx.x] = 0;
   if (task < 3) bwd_rows(p, task, b);
-  else if (task == 3) bwd_fill(p.dk, p.dv, b, p.rows_k, p.rows_v, p.list[0], p.btab, p.geo, p.cnt);
   else bwd_tmask(p.mask, p.mask_t, b, p.cnt, p.H);
 }
 
@@ -1061,14 +1058,16 @@ __device__ __forceinline__ void bwd_tail_merge(const BwdArgs& a, int wg) {
   *reinterpret_cast<uint2*>(a.out_bf + tbase + (long long)(x_start + row) * a.geo.stride_t + ch) = o;
 }
 
-// Both, behind the launch whose parts they add up: the first wgs_full workgroups merge the exact branch's cut items, the next
-// wgs_flat the Taylor branch's, the rest sum the means' gradients.
-struct BwdMergeArgs { BwdArgs full, flat; MeanSums means; int wgs_full, wgs_flat; };
+// Both, behind the launch whose parts they add up, and the fill: the first wgs_full workgroups merge the exact branch's cut items, the next
+// wgs_flat the Taylor branch's, wgs_sums sum the means' gradients, the rest (a block of a head each) fill the rows of blocks that were not
+// kept.
+struct BwdMergeArgs { BwdArgs full, flat; MeanSums means; Fill fill; int wgs_full, wgs_flat, wgs_sums; };
 __global__ __launch_bounds__(256) void k_bwd_merge(BwdMergeArgs p) {
-  const int wg = blockIdx.x;
+  int wg = blockIdx.x;
   if (wg < p.wgs_full) bwd_tail_merge(p.full, wg);
-  else if (wg < p.wgs_full + p.wgs_flat) bwd_tail_merge(p.flat, wg - p.wgs_full);
-  else bwd_mean_sums(p.means, wg - p.wgs_full - p.wgs_flat, p.full.cnt, p.full.geo.H, p.full.Tn_pad);
+  else if ((wg -= p.wgs_full) < p.wgs_flat) bwd_tail_merge(p.flat, wg);
+  else if ((wg -= p.wgs_flat) < p.wgs_sums) bwd_mean_sums(p.means, wg, p.full.cnt, p.full.geo.H, p.full.Tn_pad);
+  else bwd_fill(p.fill, wg - p.wgs_sums, p.full.geo, p.full.cnt);
 }
 
 // Distribution of the dQ items of one branch: sets the fields of `a` that say which items are cut and returns the number of workgroups
@@ -1136,7 +1135,7 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
     hipError_t e__ = hipGetLastError();           \
     if (e__ != hipSuccess) return e__;            \
   } while (0)
-  // delta, zero fill, per-list tables and row terms
+  // delta, per-list tables and row terms
   if (resid) {
     // delta without the residual's share; gradient of the coarse residual with respect to the block means (all blocks, by
     // block id)
@@ -1152,8 +1151,8 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   PrepArgs pa = {B, H, pr.Tn_pad, S_max, {kv_list, full_list, flat_list}, {ws.ktab, ws.ftab, ws.ltab}, {ws.ybd_kv, ws.ybd_full, ws.ybd_flat},
                  ex ? ws.rq : nullptr, ws.ybd_flatm, ws.btab, ws.nlse, 1.4426950408889634f / sqrtf((float)MD) /* raw score -> log2 domain */,
                  resid ? nullptr : (const uint16_t*)out, ws.olo, (const uint16_t*)d_out, ws.delta, ws.bwd_ctr, ws.ybd_mean, ws.bx_mean,
-                 (uint16_t*)dk, (uint16_t*)dv, resid ? ws.cdk : nullptr, resid ? ws.cdv : nullptr, exact_mask, ws.mask_t, pr.geo, pr.cnt};
-  hipLaunchKernelGGL(k_bwd_prepare, dim3(gx, H, B * (ex ? 5 : 4)), dim3(256), 0, st, pa);
+                 exact_mask, ws.mask_t, pr.geo, pr.cnt};
+  hipLaunchKernelGGL(k_bwd_prepare, dim3(gx, H, B * (ex ? 4 : 3)), dim3(256), 0, st, pa);
   ISA_BWD_CHECK();
 
   BwdArgs a;
@@ -1240,9 +1239,13 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   mg.full = tk.full; mg.flat = tk.flat;
   mg.wgs_full = n_merge_full * 32; mg.wgs_flat = n_merge_flat * 32;
   mg.means = {ws.dkc, ws.dvc, resid ? ws.cdk : nullptr, resid ? ws.cdv : nullptr, kv_list, mean_parts, (sk + 1) / 2, tk.means.part_stride};
-  const int wgs_sums = sk > 0 && (mean_parts > 1 || resid) ? mg.means.rows2 * H * 2 * B : 0;
-  if (mg.wgs_full + mg.wgs_flat + wgs_sums > 0) {
-    hipLaunchKernelGGL(k_bwd_merge, dim3((unsigned)(mg.wgs_full + mg.wgs_flat + wgs_sums)), dim3(256), 0, st, mg);
+  mg.wgs_sums = sk > 0 && (mean_parts > 1 || resid) ? mg.means.rows2 * H * 2 * B : 0;
+  mg.fill = {(uint16_t*)dk, (uint16_t*)dv, resid ? ws.cdk : nullptr, resid ? ws.cdv : nullptr, kv_list, ws.btab};
+  bool all_kept = true;
+  for (int b = 0; b < B; ++b) all_kept = all_kept && pr.cnt.b[b].T_new == pr.cnt.b[b].T;
+  const int wgs_fill = all_kept ? 0 : T_max * H * B, wgs_merge = mg.wgs_full + mg.wgs_flat + mg.wgs_sums + wgs_fill;
+  if (wgs_merge > 0) {
+    hipLaunchKernelGGL(k_bwd_merge, dim3((unsigned)wgs_merge), dim3(256), 0, st, mg);
     ISA_BWD_CHECK();
   }
   // ---- dK, dV of the kept tokens: every full-attention block, the Taylor blocks whose exact set holds the block, and

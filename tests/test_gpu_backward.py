@@ -447,3 +447,24 @@ def test_saved_tensors_in_another_layout(I):
     torch.cuda.synchronize()
     for a, b in zip(*grads):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("taken", ["dq", "dk", "dv"])
+@pytest.mark.parametrize("exact_frac,gamma", [(0.0, 0.0), (0.2, 0.0), (0.0, 0.5)])
+def test_a_gradient_in_the_buffer_of_the_output(I, taken, exact_frac, gamma):
+    """The rows of blocks that were not kept (here three quarters of the context) are written while nobody reads `out` any more, so a caller
+    can give its buffer to one of the gradients: the same bits as in buffers of their own."""
+    wl = SMALL.with_(H=24, src_grid=(1, 10, 33), ctx_grids=(((12, 10, 33),),), keep_ratio=0.25, exact_frac=exact_frac, gamma=gamma, seed=83)
+    Q, K, V, dO = _inputs(wl)
+    q, k, v, d_out = Q.cuda(), K.cuda(), V.cuda(), dO.cuda()
+    pr = problem_of(wl)
+    ws = I.new_workspace(pr)
+    out = torch.empty_like(q)
+    want = {n: torch.empty_like(q) for n in ("dq", "dk", "dv")}
+    I.isa_attention(pr, q, k, v, out, ws)
+    I.isa_attention_backward(pr, q, k, v, out, d_out, *want.values(), ws)
+    got = {n: out if n == taken else torch.empty_like(q) for n in want}
+    I.isa_attention_backward(pr, q, k, v, out, d_out, *got.values(), ws)
+    torch.cuda.synchronize()
+    for n in want:
+        assert torch.equal(got[n], want[n]), n
