@@ -610,7 +610,9 @@ __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdTokensArgs p) {
   }
 }
 
-// What the launches need before they start, in one launch of 256 threads a workgroup, blockIdx.z = task * B + batch item.  Tasks: the lists of
+// What the launches need before they start, in one launch of 256 threads a workgroup, blockIdx = {block or list entry, head, task * B + batch
+// item}: the arrays over the padded means are a thread's work each.  (As a workgroup's each they had 128 workgroups and more per head start
+// beside the one of a single block: training steps of 100 heads of 128 tokens 103 / 68 us, 8 x 40 heads of 500 + 100 tokens 666 / 437.)  Tasks: the lists of
 // the kept, the full-attention and the Taylor blocks (bwd_rows), with exact sets the transposed bits (bwd_tmask): none reads what another
 // writes, and none writes a gradient: `out` is read here for the last time, and its buffer may be that of one of them.  Delta belongs to the blocks' rows and is worked out where their terms are: as a launch of its own it
 // was one more wait and another 4 us of the host's time (a training step of 12 heads of 1564 tokens 183 / 177 us, two runs where the host
@@ -644,16 +646,17 @@ __device__ __forceinline__ void bwd_rows(const PrepArgs& p, int kind, int b) {
   const int T_max = cnt.T_max;
   const long long bh = (long long)b * p.H + h;
   const int n_list = kind == 0 ? cnt.b[b].T_new : kind == 1 ? cnt.b[b].n_full : cnt.b[b].n_flat;
-  if (kind == 0 && e < p.Tn_pad && threadIdx.x == 0) {
-    float l2 = -INFINITY;
-    if (e < n_list) l2 = log2f((float)p.btab[b * T_max + block_in_range(list[bh * T_max + e], cnt.b[b].T)].y);
-    const long long m = bh * p.Tn_pad + e;                    // planar per 64 positions: 64 terms, then 64 deltas
-    float* ym = reinterpret_cast<float*>(p.ybd_mean);
-    ym[(m >> 6) * 128 + (m & 63)] = l2;
-    ym[(m >> 6) * 128 + 64 + (m & 63)] = 0.f;
-    p.bx_mean[bh * p.Tn_pad + e] = e < n_list ? l2 : 0.f;
-  }
-  if (e >= n_list || e >= T_max) return;
+  if (kind == 0)
+    for (int t = e * 256 + threadIdx.x; t < p.Tn_pad; t += T_max * 256) {
+      float l2 = -INFINITY;
+      if (t < n_list) l2 = log2f((float)p.btab[b * T_max + block_in_range(list[bh * T_max + t], cnt.b[b].T)].y);
+      const long long m = bh * p.Tn_pad + t;                  // planar per 64 positions: 64 terms, then 64 deltas
+      float* ym = reinterpret_cast<float*>(p.ybd_mean);
+      ym[(m >> 6) * 128 + (m & 63)] = l2;
+      ym[(m >> 6) * 128 + 64 + (m & 63)] = 0.f;
+      p.bx_mean[m] = t < n_list ? l2 : 0.f;
+    }
+  if (e >= n_list) return;
   const int4 ent = p.btab[b * T_max + block_in_range(list[bh * T_max + e], cnt.b[b].T)];
   if (threadIdx.x == 0) p.tab[kind][bh * T_max + e] = ent;
   if (kind > 0 && p.o) {
@@ -1147,12 +1150,11 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
     if (ec == hipSuccess) ec = wide ? launch_bwd_coarse<16, true>(pr, ws, st) : launch_bwd_coarse<4, true>(pr, ws, st);
     if (ec != hipSuccess) return ec;
   }
-  const int gx = T_max > pr.Tn_pad ? T_max : pr.Tn_pad;
   PrepArgs pa = {B, H, pr.Tn_pad, S_max, {kv_list, full_list, flat_list}, {ws.ktab, ws.ftab, ws.ltab}, {ws.ybd_kv, ws.ybd_full, ws.ybd_flat},
                  ex ? ws.rq : nullptr, ws.ybd_flatm, ws.btab, ws.nlse, 1.4426950408889634f / sqrtf((float)MD) /* raw score -> log2 domain */,
                  resid ? nullptr : (const uint16_t*)out, ws.olo, (const uint16_t*)d_out, ws.delta, ws.bwd_ctr, ws.ybd_mean, ws.bx_mean,
                  exact_mask, ws.mask_t, pr.geo, pr.cnt};
-  hipLaunchKernelGGL(k_bwd_prepare, dim3(gx, H, B * (ex ? 4 : 3)), dim3(256), 0, st, pa);
+  hipLaunchKernelGGL(k_bwd_prepare, dim3(T_max, H, B * (ex ? 4 : 3)), dim3(256), 0, st, pa);
   ISA_BWD_CHECK();
 
   BwdArgs a;
