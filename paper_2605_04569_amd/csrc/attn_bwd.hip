@@ -1203,7 +1203,10 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
   tk.means = a; tk.dvc = ws.dvc;
   // The mean rows have few items (two per 256 gathered means and head): each is cut into up to BWD_MEAN_PARTS parts along the streamed
   // entries, as many as make their rounds over the compute units shortest.  Where all three kinds of items fit one round, the
-  // exact branch's and the means' parts are those with the shortest longest part (in streamed tiles) that still fit it.
+  // exact branch's and the means' parts are those with which the launch ends first by a model of it, in streamed blocks (a start counts for
+  // one): the longest part, or all of them shared evenly and, past a round, the last of the short Taylor items behind them.
+  // (Parts only as far as they fit the round left an exact branch's item almost whole where the Taylor items filled the rest: training steps of
+  // 8 heads of 6000 tokens 355 / 272 us, of 6100 394 / 299, 3 heads of 15 600 with the residual 805 / 688, 40 heads of 1024 139 / 125.)
   const int cus = cus_per_xcd();
   int mean_parts = 0, one_round = 0;
   const auto per_xcd = [&](int items) { return (int)(((long long)items * B * H + N_XCD - 1) / N_XCD); };
@@ -1217,12 +1220,17 @@ hipError_t launch_attn_bwd(const Problem& pr, const Workspace& ws, const void* q
     }
   }
   if (e_xcd > 0 && e_xcd + l_xcd + 2 * m_xcd <= cus) {
-    int best = 1 << 30;
-    for (int pe = 1; pe <= 8 && pe <= min_kept; ++pe)
+    int k_exact = 0;
+    for (int b = 0; b < B; ++b) k_exact = ex && pr.cnt.b[b].k_exact > k_exact ? pr.cnt.b[b].k_exact : k_exact;
+    const double taylor = 1.0 + 0.5 * ((sk + KT - 1) / KT) + 2.0 * k_exact;
+    double best = INFINITY;
+    for (int pe = 1; pe <= 8 && pe <= min_kept && (pe == 1 || N_XCD * e_xcd * pe <= SPLIT_MAX_SUB); ++pe)
       for (int pm = n_mean_pairs > 0 ? 1 : 0; pm <= (n_mean_pairs > 0 ? BWD_MEAN_PARTS : 0); ++pm) {
-        if (e_xcd * pe + l_xcd + 2 * per_xcd(n_mean_pairs * pm) > cus) continue;
-        const int longest_e = (sk + pe - 1) / pe, longest_m = pm > 0 ? (sl + pm - 1) / pm : 0, longest = longest_e > longest_m ? longest_e : longest_m;
-        if (longest < best) { best = longest; one_round = pe; mean_parts = pm; }
+        const int n_e = e_xcd * pe, n_m = 2 * per_xcd(n_mean_pairs * pm);
+        const double exact = 1.0 + (sk + pe - 1) / pe, mean = pm > 0 ? 1.0 + (sl + pm - 1) / pm : 0.0;
+        const double even = (n_e * exact + n_m * mean + l_xcd * taylor) / cus + (n_e + n_m + l_xcd > cus ? taylor : 0.0);
+        const double cost = fmax(fmax(exact, mean), fmax(l_xcd > 0 ? taylor : 0.0, even));
+        if (cost < best - 0.01) { best = cost; one_round = pe; mean_parts = pm; }
       }
   }
   tk.means.parts = mean_parts > 0 ? mean_parts : 1;

@@ -56,6 +56,16 @@ def test_backward_one_launch(I, H, exact_frac):
     backward_matches_the_oracle(I, wl)
 
 
+# the three kinds of items fit one round as they are, their parts do not (6 pairs of an XCD in up to 5 parts each, 15 Taylor pairs, 3 groups of
+# means twice in up to 4)
+@pytest.mark.parametrize("exact_frac", [0.0, 0.2])
+def test_backward_parts_past_a_round(I, exact_frac):
+    wl = _wl(24, (1, 9, 100), (((1, 5, 127),),), keep_ratio=0.5, full_frac=0.3, exact_frac=exact_frac, seed=868)
+    c = I.isa_get_counts(I.Problem(H=24, D=128, dtype="bf16", block=128, seg_len=[wl.seg_len(0)], keep_ratio=0.5, full_frac=0.3), 0)
+    assert (c["n_full"], c["n_flat"], c["T_new"]) == (4, 9, 10)
+    backward_matches_the_oracle(I, wl)
+
+
 # one streamed entry only (not to be cut), two, and a ragged batch whose shorter item has fewer entries than parts
 @pytest.mark.parametrize("full_frac", [0.05, 0.25])
 def test_backward_few_streamed_entries(I, full_frac):
