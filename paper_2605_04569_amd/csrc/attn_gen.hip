@@ -45,12 +45,27 @@ constexpr int MAX_PARTS = 8;
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4v* lds_s4_ptr;
 
+// Eight small numbers, one per batch item, in a word (what a launch hands over is copied for every call)
+static_assert(ISA_MAX_BATCH <= 8, "four bits a batch item");
+__host__ __device__ __forceinline__ int nibble(uint32_t x, int b) { return (x >> (4 * b)) & 15; }
+
+// Work items of `rows` rows of n blocks: two blocks of 64 rows make one of 128, a block of 128 two of 64.
+__host__ __device__ __forceinline__ int slots_of(int block, int n, int rows) { return block >= rows ? n * (block / rows) : (n + 1) / 2; }
+
 struct GenArgs {
   AttnArgs a;
-  int slots_long, slots_taylor;     // work items per (batch, head) of the exact branch / of the Taylor branch (largest of the batch)
+  int slots_long, slots_taylor;     // work items per (batch, head) of the exact branch / of the Taylor branch (batch items alike)
   int per_xcd_long, per_xcd_taylor; // and per XCD, over all (batch, head)s
-  int parts;                        // 1, or every long item runs as this many workgroups, each over its share of the listed blocks; they leave
-  float* part_o; float2* part_ml;   //   [item][part][row][D] their normalised results and [item][part][row] {maximum, sum} (see store_part)
+  // Batch items that differ: an XCD has an equal range of every one's own items, longest key lists first (by_length), as in the heads' order of
+  // all of them, with the most items of any, an XCD could get nothing but short ones.  With parts by each one's own list (both, whole
+  // calls; before: as many parts as the shortest list can have, or none): bf16, D = 128, blocks of 64, 8 heads of 6000 and 1500 tokens
+  // 298 / 144 us, of 5000 and 100 253 / 113, D = 64, 2 heads of 15 600 and 64 297 / 114; fp32, dense, D = 128, 2 heads of 6000 and 1500 737 / 524.
+  int ragged; uint32_t by_length;
+  // A long item of batch item b runs as own_parts(b) workgroups (at most `parts`), each over its share of the listed blocks; if that is more
+  // than one, they leave [first_part[b] + item of b * own_parts(b) + part][row][D] their normalised results and {maximum, sum} of the row
+  int parts; uint32_t own_parts;
+  int first_part[ISA_MAX_BATCH];
+  float* part_o; float2* part_ml;
 };
 
 __device__ __forceinline__ void dma16(const void* src, uint32_t lds_addr) {      // lane i -> LDS bytes lds_addr + 16 i
@@ -107,9 +122,9 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 // 2^tau times a value near the largest number is none.  (Raising at once in the first pass cost fp32 1 % with 128 channels, 2.5 with
 // 64; a factor of 2^-tau in its weights cost values near the smallest normal number their last eight bits.)
 //
-// PARTS: part >= 0 is the item's part of that number (a template, as whole items have no register to spare for it).  QI: the item's query tiles per wave (the second pass takes its rows 64 at a time).
+// PARTS: part >= 0 is the item's part of that number, first_part the place of its first one's results (a template, as whole items have no register to spare for it).  QI: the item's query tiles per wave (the second pass takes its rows 64 at a time).
 template <typename T, int D, int QT, bool FULL32, int QI, bool PARTS>
-__device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* const lds, int bhid, bool taylor, int slot, const int part) {
+__device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* const lds, int bhid, bool taylor, int slot, const int part, const int first_part) {
   constexpr bool BF = sizeof(T) == 2, WIDE = !BF || FULL32;
   constexpr int KTOK = BF ? 64 : 32;                   // tokens per tile; tiles of means hold 32
   constexpr int NT = D / 16;                           // 16-channel tiles
@@ -127,8 +142,8 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   const long long bh = bhid;
   const int* const kvl = a.dense ? nullptr : a.kv_list + bh * T_max;
   const int n_list_kv = a.dense ? c.T : c.T_new;
-  const int kv_lo = !PARTS || part < 0 ? 0 : (int)((long long)part * n_list_kv / ga.parts);
-  const int n_kv = !PARTS || part < 0 ? n_list_kv : (int)((long long)(part + 1) * n_list_kv / ga.parts);
+  const int kv_lo = !PARTS || part < 0 ? 0 : part * n_list_kv / nibble(ga.own_parts, b);
+  const int n_kv = !PARTS || part < 0 ? n_list_kv : (part + 1) * n_list_kv / nibble(ga.own_parts, b);
   const int* const bs = a.blk_start + b * T_max;
   const int* const bn = a.blk_n + b * T_max;
   const long long tbase = (long long)b * a.geo.stride_b + (long long)h * a.geo.stride_h;
@@ -553,11 +568,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   if constexpr (!FULL32)
     if (__syncthreads_or(!ok)) return false;
   if (PARTS && part >= 0) {
-    // the item's number worked out again, not kept through the loop
-    int wg = blockIdx.x;
-    asm volatile("" : "+s"(wg));
-    const int x = wg & 7, idx = xcd_first((long long)a.geo.B * a.geo.H * ga.slots_long, x) + (wg >> 3) % ga.per_xcd_long;
-    const long long part_row = ((long long)idx * ga.parts + (wg >> 3) / ga.per_xcd_long) * (64 * QI) + (FULL32 ? 64 * (slot % QI) : 0);
+    const long long part_row = (long long)(first_part + part) * (64 * QI) + (FULL32 ? 64 * (slot % QI) : 0);
     // normalised; the maximum in the units it was subtracted in: a minus in the sum's
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {                  // sign bit: of the score as it is (WIDE, bf16), else in the log2 domain
@@ -607,26 +618,53 @@ template <typename T, int D, int QT, bool PARTS>
 __global__ __launch_bounds__(256, (RESIDENT<D, QT>)) void k_attn_gen(GenArgs ga) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[ITEM_LDS<D>];
   // Workgroup ids go round-robin over the 8 XCDs; each has its range of the items of all (batch, head)s, the long ones
-  // (exact branch) first.
-  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int n_long = ga.per_xcd_long * (PARTS ? ga.parts : 1);      // all items' first parts, then their second ones: what runs together reads the same keys
-  const bool taylor = j >= n_long;
-  const int n_bh = ga.a.geo.B * ga.a.geo.H;
-  const int slots = taylor ? ga.slots_taylor : ga.slots_long;
-  const long long total = (long long)n_bh * slots;
-  const int idx = xcd_first(total, xcd) + (taylor ? j - n_long : PARTS ? j % ga.per_xcd_long : j);
-  if (idx >= xcd_first(total, xcd + 1)) return;
-  const int bhid = head_at(idx / slots, n_bh), slot = idx % slots;
-  const BatchCounts c = ga.a.cnt.b[bhid / ga.a.geo.H];
+  // (exact branch) first: all items' first parts, then their second ones (what runs together reads the same keys).
+  const int xcd = blockIdx.x & 7, n_bh = ga.a.geo.B * ga.a.geo.H;
+  int j = blockIdx.x >> 3, bhid = -1, slot = 0, part = -1, first_part = 0;
+  bool taylor = false;
+  if (!ga.ragged) {
+    const int n_long = ga.per_xcd_long * (PARTS ? ga.parts : 1);
+    taylor = j >= n_long;
+    if (taylor) j -= n_long;
+    else if (PARTS) { part = j / ga.per_xcd_long; j %= ga.per_xcd_long; }
+    const int slots = taylor ? ga.slots_taylor : ga.slots_long;
+    const long long total = (long long)n_bh * slots;
+    const int idx = xcd_first(total, xcd) + j;
+    if (idx >= xcd_first(total, xcd + 1)) return;
+    bhid = head_at(idx / slots, n_bh);
+    slot = idx % slots;
+  } else {
+    for (int i = 0; i < 2 * ga.a.geo.B; ++i) {
+      const int b = nibble(ga.by_length, i % ga.a.geo.B), slots = slots_of(ga.a.geo.block, ga.a.dense ? i < ga.a.geo.B ? ga.a.cnt.b[b].T : 0 : i < ga.a.geo.B ? ga.a.cnt.b[b].n_full : ga.a.cnt.b[b].n_flat, 64 * QT);
+      const int parts = PARTS && i < ga.a.geo.B ? nibble(ga.own_parts, b) : 1;
+      const long long total = (long long)ga.a.geo.H * slots;
+      const int first = xcd_first(total, xcd), n = xcd_first(total, xcd + 1) - first;
+      if (j < n * parts) {
+        taylor = i >= ga.a.geo.B;
+        part = parts > 1 ? j / n : -1;
+        bhid = b * ga.a.geo.H + head_at((first + j % n) / slots, ga.a.geo.H);
+        slot = (first + j % n) % slots;
+        break;
+      }
+      j -= n * parts;
+    }
+    if (bhid < 0) return;
+  }
+  bhid = __builtin_amdgcn_readfirstlane(bhid);
+  slot = __builtin_amdgcn_readfirstlane(slot);
+  part = PARTS ? __builtin_amdgcn_readfirstlane(part) : -1;
+  taylor = __builtin_amdgcn_readfirstlane(taylor ? 1 : 0) != 0;
+  const int b = bhid / ga.a.geo.H;
+  const BatchCounts c = ga.a.cnt.b[b];
   const int n_list = ga.a.dense ? c.T : taylor ? c.n_flat : c.n_full;
+  if (PARTS && part >= 0)
+    first_part = ga.first_part[b] + (bhid % ga.a.geo.H * slots_of(ga.a.geo.block, n_list, 64 * QT) + slot) * nibble(ga.own_parts, b);
   // QT-tile slot n of a list: rows 64 QT n .. of a 128-row block's sequence of rows, or block n / blocks 2 n, 2 n + 1 of 64 rows
   auto first_entry = [&](int qt, int n) { return ga.a.geo.block == 64 ? qt * n : n * qt / 2; };
-  if (first_entry(QT, slot) >= n_list) return;         // a shorter batch item
-  const int part = !PARTS || taylor ? -1 : j / ga.per_xcd_long;
-  if (attn_gen_item<T, D, QT, false, QT, PARTS>(ga, lds, bhid, taylor, slot, part)) return;
+  if (attn_gen_item<T, D, QT, false, QT, PARTS>(ga, lds, bhid, taylor, slot, part, first_part)) return;
 #pragma unroll 1
   for (int n = QT * slot; n < QT * (slot + 1); ++n)    // again, 64 rows at a time
-    if (first_entry(1, n) < n_list) attn_gen_item<T, D, 1, true, QT, PARTS>(ga, lds, bhid, taylor, n, part);
+    if (first_entry(1, n) < n_list) attn_gen_item<T, D, 1, true, QT, PARTS>(ga, lds, bhid, taylor, n, part, first_part);
 }
 
 // Adds up the parts of the long items: out = sum_p o_p l_p 2^(m_p - m) / sum_p l_p 2^(m_p - m) with m = max_p m_p (the merge step
@@ -642,14 +680,16 @@ __global__ __launch_bounds__(256) void k_gen_merge(GenArgs ga, int rows) {
   const int n_bh = a.geo.B * a.geo.H, slots = ga.slots_long;
   const int bhid = head_at(idx / slots, n_bh), slot = idx % slots, b = bhid / a.geo.H, h = bhid % a.geo.H;
   const BatchCounts c = a.cnt.b[b];
+  const int parts = nibble(ga.own_parts, b), n_list = a.dense ? c.T : c.n_full;
+  if (parts == 1) return;
   const bool pair = rows == 128 && a.geo.block == 64;
   const int subs = pair ? 1 : a.geo.block / rows;
   const int entry = pair ? 2 * slot + row / 64 : slot / subs;
-  if (entry >= (a.dense ? c.T : c.n_full)) return;
+  if (entry >= n_list) return;
   const int qi = a.dense ? entry : block_in_range(a.full_list[(long long)bhid * a.geo.T_max + entry], c.T);
   const int in_block = pair ? row % 64 : slot % subs * rows + row;
   if (in_block >= a.blk_n[b * a.geo.T_max + qi]) return;
-  const long long first = (long long)idx * ga.parts * rows + row;
+  const long long first = (long long)(ga.first_part[b] + (h * slots_of(a.geo.block, n_list, rows) + slot) * parts) * rows + row;
   const double cs = 1.4426950408889634 / sqrt((double)D);
   auto log2_max = [&](const float2 ml) { return sizeof(T) == 2 && (__float_as_uint(ml.y) >> 31) ? (double)ml.x * cs : (double)ml.x; };
   // all parts' loads in flight at once (a part past the last repeats it, with weight 0)
@@ -657,7 +697,7 @@ __global__ __launch_bounds__(256) void k_gen_merge(GenArgs ga, int rows) {
   float4 o[MAX_PARTS];
 #pragma unroll
   for (int p = 0; p < MAX_PARTS; ++p) {
-    const long long at = first + (long long)min(p, ga.parts - 1) * rows;
+    const long long at = first + (long long)min(p, parts - 1) * rows;
     ml[p] = ga.part_ml[at];
     o[p] = *reinterpret_cast<const float4*>(ga.part_o + at * D + ch);
   }
@@ -668,14 +708,14 @@ __global__ __launch_bounds__(256) void k_gen_merge(GenArgs ga, int rows) {
   float w[MAX_PARTS], l = 0.f;
 #pragma unroll
   for (int p = 0; p < MAX_PARTS; ++p) {
-    w[p] = p < ga.parts && ml[p].y != 0.f ? fabsf(ml[p].y) * __builtin_amdgcn_exp2f((float)(log2_max(ml[p]) - m)) : 0.f;
+    w[p] = p < parts && ml[p].y != 0.f ? fabsf(ml[p].y) * __builtin_amdgcn_exp2f((float)(log2_max(ml[p]) - m)) : 0.f;
     l += w[p];
   }
   const float inv = 1.0f / l;
   float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
   for (int p = 0; p < MAX_PARTS; ++p) {
-    if (p >= ga.parts || ml[p].y == 0.f) continue;
+    if (p >= parts || ml[p].y == 0.f) continue;
     const float x = w[p] * inv;
     sum.x = fmaf(x, o[p].x, sum.x); sum.y = fmaf(x, o[p].y, sum.y); sum.z = fmaf(x, o[p].z, sum.z); sum.w = fmaf(x, o[p].w, sum.w);
   }
@@ -689,8 +729,28 @@ __global__ __launch_bounds__(256) void k_gen_merge(GenArgs ga, int rows) {
   else *reinterpret_cast<float4*>(op) = sum;
 }
 
+// The long items cut: those of the batch item with the longest key list into p parts, the others into parts of about the same length (of
+// at least a block, bf16: 256 tokens).  cut.slots (long items of a (batch, head)) is there; false if p parts are too many or the partial
+// results have no room.
+struct Cut { int slots[ISA_MAX_BATCH], parts[ISA_MAX_BATCH], first[ISA_MAX_BATCH]; };
+static bool cut_long_items(const Problem& pr, bool dense, int rows, int p, Cut& cut) {
+  int longest = 1;
+  for (int b = 0; b < pr.p.B; ++b)
+    if (cut.slots[b] > 0) longest = max(longest, dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new);
+  const int least = pr.p.dtype == ISA_BF16 ? 256 / pr.p.block : 1;          // blocks of a part
+  if (p > 1 && longest < p * least) return false;
+  long long n = 0;
+  for (int b = 0; b < pr.p.B; ++b) {
+    const int list = dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new;             // at most 4096
+    cut.parts[b] = list == longest ? p : max(1, min(min(list / least, p), (2 * list * p + longest) / (2 * longest)));
+    cut.first[b] = (int)n;
+    if (cut.parts[b] > 1) n += (long long)pr.p.H * cut.slots[b] * cut.parts[b];
+  }
+  return n * rows * pr.p.D <= SPLIT_MAX_SUB * 256ll * 128;
+}
+
 hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArgs& a, hipStream_t st) {
-  GenArgs ga;
+  GenArgs ga = {};
   ga.a = a;
   int n_long = 0, n_taylor = 0;
   double set_share = 0.0;                              // of a long item's tokens, those a Taylor item reads for its exact set
@@ -724,6 +784,7 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
       {{{64, 2, {5.55, 9.9}, 80}, {}}, {{64, 4, {3.6, 5.5, 7.9, 10.5}, 64}, {}}},
       {{{64, 2, {1.85, 2.74}, 320}, {128, 2, {2.65, 4.35}, 320}}, {{64, 4, {1.36, 1.54, 2.15, 2.8}, 320}, {128, 3, {1.82, 2.33, 3.4}, 320}}}};
   bool two = false;
+  Cut chosen = {};
   ga.parts = 1;
   if (n_long == 0) {
     // Taylor items alone, 128 rows / 64: D = 64, 24, 4, 2 heads (2928, 488, 244 items of 128 rows) 186 / 226, 67 / 73, 61 / 58; D = 128, 24, 2 heads
@@ -731,38 +792,66 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
     // 24, 8 heads 435 / 396, 192 / 171 (D = 128: 797 / 814, 302 / 305).
     two = bf && !(set_share > 0.0 && d64 && pr.p.block == 64) && items(n_taylor, 128) >= chip * (d64 ? 7 : 5) / 4;
   } else {
-    int shortest = 1 << 30;
-    for (int b = 0; b < pr.p.B; ++b) shortest = min(shortest, a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new);
-    const double tokens = (double)shortest * pr.p.block;
-    const double merge = 5.0 * 64;                     // its launch
     double best = INFINITY;
     for (int f = 0; f < (bf ? 2 : 1); ++f) {
       const Form& form = forms[bf][d64][f];
-      const long long n = items(n_long, form.rows);
       // per workgroup with the chip full; a pair of blocks of 64 reads both blocks' exact sets
       const double full = form.pace[form.resident - 1] / form.resident / chip;
-      const double share = 1.0 / 32 + set_share * (form.rows > pr.p.block ? 2 : 1);
-      const double taylor = (double)items(n_taylor, form.rows) * share * tokens * full;
-      for (int p = 1; p <= MAX_PARTS && p <= shortest; ++p) {
-        if (p > 1 && (!ws.split_o || (bf && tokens < 256.0 * p) || n * p * form.rows * pr.p.D > SPLIT_MAX_SUB * 256ll * 128)) break;
-        const int k = (int)ceil((double)(n * p) / chip), rounds = (k - 1) / form.resident;
+      Cut cut;
+      double taylor = 0.0;                             // the Taylor items, in tokens (as all below)
+      for (int b = 0; b < pr.p.B; ++b) {
+        const BatchCounts& c = pr.cnt.b[b];
+        cut.slots[b] = slots_of(pr.p.block, a.dense ? c.T : c.n_full, form.rows);
+        if (a.dense) continue;
+        const double set = a.exact_mask && c.n_flat > 0 ? (double)c.k_exact / c.T_new : 0.0;
+        taylor += (double)pr.p.H * slots_of(pr.p.block, c.n_flat, form.rows) * (1.0 / 32 + set * (form.rows > pr.p.block ? 2 : 1)) * c.T_new * pr.p.block;
+      }
+      for (int p = 1; p <= MAX_PARTS && (p == 1 || ws.split_o) && cut_long_items(pr, a.dense, form.rows, p, cut); ++p) {
+        double work = 0.0, each = 0.0;                 // all long items; the longest part
+        for (int b = 0; b < pr.p.B; ++b) {
+          if (cut.slots[b] == 0) continue;
+          const double tokens = (double)(a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new) * pr.p.block, own = tokens / cut.parts[b] + form.start;
+          work += (double)pr.p.H * cut.slots[b] * cut.parts[b] * own;
+          each = fmax(each, own);
+        }
+        const int k = (int)ceil(work / (each * chip) - 1e-9), rounds = (k - 1) / form.resident;      // as many as if all were as long as the longest
         const double pace = rounds * form.pace[form.resident - 1] + form.pace[(k - 1) % form.resident];
-        const double each = tokens / p + form.start;
-        const double cost = fmax(pace * each, (double)(n * p) * each * full + taylor) + (p > 1 ? merge : 0.0);
-        if (cost < best) { best = cost; two = f == 1; ga.parts = p; }
+        const double cost = fmax(pace * each, (work + taylor) * full) + (p > 1 ? 5.0 * 64 : 0.0);       // (the merge's launch)
+        if (cost < best) { best = cost; two = f == 1; ga.parts = p; chosen = cut; }
       }
     }
   }
   ga.part_o = ws.split_o; ga.part_ml = (float2*)ws.split_ml;
   const int rows = two ? 128 : 64;
-  auto slots = [&](int n) { return pr.p.block >= rows ? n * (pr.p.block / rows) : (n + 1) / 2; };
-  ga.slots_long = slots(n_long);
-  ga.slots_taylor = slots(n_taylor);
+  ga.slots_long = slots_of(pr.p.block, n_long, rows);
+  ga.slots_taylor = slots_of(pr.p.block, n_taylor, rows);
   ga.per_xcd_long = (int)((bh * ga.slots_long + N_XCD - 1) / N_XCD);
   ga.per_xcd_taylor = (int)((bh * ga.slots_taylor + N_XCD - 1) / N_XCD);
+  int wgs = ga.per_xcd_long * ga.parts + ga.per_xcd_taylor;               // of an XCD
+  for (int b = 0; b < pr.p.B; ++b) {
+    const BatchCounts &c = pr.cnt.b[b], &d = pr.cnt.b[0];
+    ga.ragged |= a.dense ? c.T != d.T : c.T_new != d.T_new || c.n_full != d.n_full || c.n_flat != d.n_flat;
+  }
+  for (int b = 0; b < pr.p.B; ++b) {
+    ga.first_part[b] = chosen.first[b];
+    ga.own_parts |= (uint32_t)(ga.parts > 1 ? chosen.parts[b] : 1) << (4 * b);
+  }
+  if (ga.ragged) {
+    wgs = 0;
+    int order[ISA_MAX_BATCH];                          // longest key lists first, ties in order
+    for (int b = 0; b < pr.p.B; ++b) {
+      const BatchCounts& c = pr.cnt.b[b];
+      int at = b;
+      for (; at > 0 && (a.dense ? pr.cnt.b[order[at - 1]].T < c.T : pr.cnt.b[order[at - 1]].T_new < c.T_new); --at) order[at] = order[at - 1];
+      order[at] = b;
+      wgs += (int)(((long long)pr.p.H * slots_of(pr.p.block, a.dense ? c.T : c.n_full, rows) + N_XCD - 1) / N_XCD) * nibble(ga.own_parts, b) +
+             (int)(((long long)pr.p.H * (a.dense ? 0 : slots_of(pr.p.block, c.n_flat, rows)) + N_XCD - 1) / N_XCD);
+    }
+    for (int i = 0; i < pr.p.B; ++i) ga.by_length |= (uint32_t)order[i] << (4 * i);
+  }
   if (ga.slots_long == 0) ga.slots_long = 1;           // divisors in the kernel; a branch without work gets no workgroups
   if (ga.slots_taylor == 0) ga.slots_taylor = 1;
-  const dim3 grid((unsigned)(N_XCD * (ga.per_xcd_long * ga.parts + ga.per_xcd_taylor)));
+  const dim3 grid((unsigned)(N_XCD * wgs));
 #define ISA_GEN(T, D, QT)                                                                                  \
   do {                                                                                                     \
     if (ga.parts > 1) hipLaunchKernelGGL((k_attn_gen<T, D, QT, true>), grid, dim3(256), 0, st, ga);         \
@@ -773,7 +862,7 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
   else if (d64) ISA_GEN(float, 64, 1);
   else ISA_GEN(float, 128, 1);
   if (ga.parts > 1) {
-    const dim3 merge((unsigned)(bh * ga.slots_long * (rows * pr.p.D / 1024)));
+    const dim3 merge((unsigned)(bh * ga.slots_long * (rows * pr.p.D / 1024)));      // (slots_long: the most of a batch item)
     if (bf) {
       if (d64) hipLaunchKernelGGL((k_gen_merge<uint16_t, 64>), merge, dim3(256), 0, st, ga, rows);
       else hipLaunchKernelGGL((k_gen_merge<uint16_t, 128>), merge, dim3(256), 0, st, ga, rows);

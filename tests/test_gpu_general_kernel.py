@@ -88,6 +88,47 @@ def test_items_in_parts(I, shape, blocks):
     check_end_to_end(I, wl, *gen(wl))
 
 
+def _align(n):
+    return (n + 255) // 256 * 256
+
+
+def _bytes_without_parts(I, pr):
+    """The workspace up to the end of its last array before the partial results: exact_mask, o_coarse or flat_list."""
+    lay, T = I.isa_workspace_layout(pr), I.isa_get_counts(pr, 0)["T_max"]
+    rows = pr.B * pr.H * T
+    if pr.exact_frac > 0:
+        return lay["exact_mask"] + _align(rows * ((T + 31) // 32) * 4)
+    if pr.gamma != 0:
+        return lay["o_coarse"] + _align(rows * pr.D * 4)
+    return lay["flat_list"] + _align(rows * 4)
+
+
+def _is_cut(I, pr, q, k, v):
+    """Whether isa_attention runs long items in parts: without room for partial results they stay whole, and some sum then ends otherwise."""
+    ws, outs = I.new_workspace(pr), [torch.zeros_like(q) for _ in range(2)]
+    I.isa_attention(pr, q, k, v, outs[0], ws)
+    I.isa_attention(pr, q, k, v, outs[1], ws[:_bytes_without_parts(I, pr)])
+    torch.cuda.synchronize()
+    return not torch.equal(*outs)
+
+
+# batch items with key lists of different length, the longest neither first nor last: parts of about one length, so that the longest list has
+# the most and the shortest one part, whose item is stored whole; 8 batch items; a launch of whole items over the same XCDs' shares
+@pytest.mark.parametrize("H,blocks,cut", [(3, (3, 30, 1, 12), True), (1, (9, 0, 4, 30, 2, 30, 17, 1), True), (70, (3, 12, 1), False)],
+                         ids=["4_items", "8_items", "whole"])
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_ragged_batches(I, shape, H, blocks, cut):
+    block = shape[2]
+    ctx = tuple(((1, 1, n * block + 7),) if n else () for n in blocks)
+    wl = _wl(shape, H, (1, 1, 2 * block + 9), ctx, B=len(blocks), keep_ratio=0.8, full_frac=0.4, exact_frac=0.1 if H == 3 else 0.0,
+             gamma=0.5 if H == 3 else 0.0, seed=763)
+    assert len({I.isa_get_counts(problem_of(wl), b)["T_new"] for b in range(wl.B)}) > 2
+    inputs = gen(wl)
+    check_end_to_end(I, wl, *inputs, heads=sorted({0, H // 2, H - 1}))
+    if cut:
+        assert _is_cut(I, problem_of(wl), *inputs[3:])
+
+
 @pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
 def test_no_room_for_parts(I, shape):
     """A workspace that holds everything but the partial results (a slice of one that does) is accepted: the items stay whole."""
