@@ -16,8 +16,9 @@
 // tile (ds_read_b64_tr_b16 for bf16; for fp32 a lane's four channels of a row serve four output tiles).  Tiles of 64
 // bf16 (32 fp32) rows go global -> LDS directly, one tile ahead, two stages, 16-byte chunks XOR-swizzled by row.  A stage
 // is 256 D bytes either way.  A launch with few long items cuts their key lists into parts, a workgroup each, and a second kernel adds
-// them up.  Workgroups that share a compute unit, whose softmax runs beside each other's matrix instructions (there is no hand-made
-// interleaving here): D = 128, 66 KB each, two; D = 64, 33 KB, three of QT = 2 (registers) or four of QT = 1.
+// them up, or gives a workgroup two groups of 4 waves that take the tiles in turn (NG = 2).  Groups that share a compute unit, whose softmax
+// runs beside each other's matrix instructions (there is no hand-made interleaving here): D = 128, 66 KB each, two; D = 64, 33 KB, three of
+// QT = 2 (registers) or four of QT = 1.
 //
 // What bounds it (measured, 24 heads of 64 channels, 15 600 tokens in blocks of 64, keep 0.5, full 0.25): instruction issue. A weight
 // costs 9.4 vector instructions (5.5 of them the exact cut into three terms; taking the differences with the bf16 dot
@@ -122,9 +123,11 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 // 2^tau times a value near the largest number is none.  (Raising at once in the first pass cost fp32 1 % with 128 channels, 2.5 with
 // 64; a factor of 2^-tau in its weights cost values near the smallest normal number their last eight bits.)
 //
+// NG = 2: two groups of 4 waves work on the same rows, each with stages of its own, and take the tiles of the sequence in turn;
+// the second group hands its running maxima, sums and outputs to the first through LDS at the end.
 // PARTS: part >= 0 is the item's part of that number, first_part the place of its first one's results (a template, as whole items have no register to spare for it).  QI: the item's query tiles per wave (the second pass takes its rows 64 at a time).
-template <typename T, int D, int QT, bool FULL32, int QI, bool PARTS>
-__device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* const lds, int bhid, bool taylor, int slot, const int part, const int first_part) {
+template <typename T, int D, int QT, bool FULL32, int QI, bool PARTS, int NG>
+__device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* const lds_all, int bhid, bool taylor, int slot, const int part, const int first_part) {
   constexpr bool BF = sizeof(T) == 2, WIDE = !BF || FULL32;
   constexpr int KTOK = BF ? 64 : 32;                   // tokens per tile; tiles of means hold 32
   constexpr int NT = D / 16;                           // 16-channel tiles
@@ -133,6 +136,8 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   constexpr int ST = (CT < 16 ? CT : 16) - 1, SM = 15; // swizzle: chunk c of row r sits at c ^ (r & S)
   constexpr int NI = D / 32;                           // 1 KB loads per wave, tile and tensor
   constexpr int ROWS = 64 * QT;
+  const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
+  unsigned char* const lds = lds_all + grp * ITEM_LDS<D>;
   const AttnArgs& a = ga.a;
   float* const wts = reinterpret_cast<float*>(lds + 4 * TILE);         // [stage][block of the item][32]: weights of a mean tile's slots
 
@@ -148,7 +153,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   const int* const bn = a.blk_n + b * T_max;
   const long long tbase = (long long)b * a.geo.stride_b + (long long)h * a.geo.stride_h;
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = NG > 1 ? threadIdx.x & 255 : threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, g = lane >> 4;
 
@@ -522,16 +527,29 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     }
   };
 
-  // ---- the loop: the loads of the next tile fly while the current one is multiplied
-  next_tile();
-  Tile cur = at;
+  // ---- the loop: the loads of a group's next tile fly while its current one is multiplied
+  int n_first = 0, n_mine = 0;                         // tiles of the first group / of this one among those described
+  auto next_mine = [&]() -> Tile {
+    if constexpr (NG == 1) {
+      next_tile();
+      return at;
+    }
+    Tile mine = at;
+#pragma unroll
+    for (int u = 0; u < NG; ++u) {
+      if (!at.end) next_tile();
+      if (u == 0) n_first += at.end ? 0 : 1;
+      if (u == grp) mine = at;
+    }
+    return mine;
+  };
+  Tile cur = next_mine();
   if (!cur.end) issue(cur, 0);
   int stage = 0;
   auto tiles = [&](const auto mean_c) __attribute__((always_inline)) {
     constexpr bool mean = decltype(mean_c)::value;
     for (; !cur.end && cur.mean == mean; stage ^= 1) {
-      next_tile();                                     // its table reads wait together with the tile loads
-      const Tile nxt = at;
+      const Tile nxt = next_mine();                    // its table reads wait together with the tile loads
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();                                 // the tile is complete; everybody has left the one before, whose stage is filled next
       if (!nxt.end) issue(nxt, stage ^ 1);
@@ -541,12 +559,47 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         for (int r0 = 0; r0 < cur.nk; r0 += 32) half(kb, kb + TILE, r0, cur.nk - r0, mean_c, wts + stage * 64 + own * 32);
       }
       cur = nxt;
+      ++n_mine;
     }
   };
   // two loops: the kinds of tile share no code path through which the accumulators would have to be moved
   tiles(std::false_type{});
   tiles(std::true_type{});
+  if (NG > 1 && n_mine < n_first) __syncthreads();     // the first group has had one tile, and one barrier, more
   __syncthreads();                                     // nobody reads LDS any more: the caller may start another pass
+
+  // ---- the second group's part (the merge step of the online softmax)
+  if constexpr (NG > 1) {
+    constexpr int W = QT * (4 * NT + 2);               // floats of a lane
+    float* const hand = reinterpret_cast<float*>(lds_all + ITEM_LDS<D>) + wave * W * 64 + lane;
+    if (grp == 1) {
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        hand[(qt * (4 * NT + 2)) * 64] = neg_m[qt];
+        hand[(qt * (4 * NT + 2) + 1) * 64] = l_run[qt];
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) hand[(qt * (4 * NT + 2) + 2 + 4 * ct + i) * 64] = acc[ct][qt][i];
+      }
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        const float other = hand[(qt * (4 * NT + 2)) * 64];
+        const float nm = fminf(neg_m[qt], other);      // minus the larger maximum
+        const float mine = factor(shift(nm) - neg_m[qt]), theirs = factor(shift(nm) - other);
+        neg_m[qt] = nm;
+        l_run[qt] = l_run[qt] * mine + hand[(qt * (4 * NT + 2) + 1) * 64] * theirs;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[ct][qt][i] = acc[ct][qt][i] * mine + hand[(qt * (4 * NT + 2) + 2 + 4 * ct + i) * 64] * theirs;
+      }
+    }
+    __syncthreads();                                   // read before the caller's next pass fills the stages again
+  }
 
   // ---- normalise, check, store
   float inv[QT];
@@ -557,7 +610,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     inv[qt] = 1.0f / l;
-    if (row0 + 16 * qt + r16 < n_q) {
+    if (grp == 0 && row0 + 16 * qt + r16 < n_q) {
       if (!WIDE) ok = ok && fabsf(neg_m[qt]) < FAST_MAX;
 #pragma unroll
       for (int ct = 0; ct < NT; ++ct)
@@ -567,6 +620,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   }
   if constexpr (!FULL32)
     if (__syncthreads_or(!ok)) return false;
+  if (grp != 0) return true;
   if (PARTS && part >= 0) {
     const long long part_row = (long long)(first_part + part) * (64 * QI) + (FULL32 ? 64 * (slot % QI) : 0);
     // normalised; the maximum in the units it was subtracted in: a minus in the sum's
@@ -613,10 +667,11 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   return true;
 }
 
-// D = 128: 66 KB of LDS a group, two groups per compute unit; D = 64: registers for three workgroups (QT = 2) or four groups
-template <typename T, int D, int QT, bool PARTS>
-__global__ __launch_bounds__(256, (RESIDENT<D, QT>)) void k_attn_gen(GenArgs ga) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[ITEM_LDS<D>];
+// (the launch bounds' second number is wavefronts per SIMD: the same for one and for two groups)
+template <typename T, int D, int QT, bool PARTS, int NG>
+__global__ __launch_bounds__(256 * NG, (RESIDENT<D, QT>)) void k_attn_gen(GenArgs ga) {
+  static_assert(NG == 1 || (QT == 1 && !PARTS), "what is launched");
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[NG * ITEM_LDS<D>];
   // Workgroup ids go round-robin over the 8 XCDs; each has its range of the items of all (batch, head)s, the long ones
   // (exact branch) first: all items' first parts, then their second ones (what runs together reads the same keys).
   const int xcd = blockIdx.x & 7, n_bh = ga.a.geo.B * ga.a.geo.H;
@@ -661,10 +716,10 @@ __global__ __launch_bounds__(256, (RESIDENT<D, QT>)) void k_attn_gen(GenArgs ga)
     first_part = ga.first_part[b] + (bhid % ga.a.geo.H * slots_of(ga.a.geo.block, n_list, 64 * QT) + slot) * nibble(ga.own_parts, b);
   // QT-tile slot n of a list: rows 64 QT n .. of a 128-row block's sequence of rows, or block n / blocks 2 n, 2 n + 1 of 64 rows
   auto first_entry = [&](int qt, int n) { return ga.a.geo.block == 64 ? qt * n : n * qt / 2; };
-  if (attn_gen_item<T, D, QT, false, QT, PARTS>(ga, lds, bhid, taylor, slot, part, first_part)) return;
+  if (attn_gen_item<T, D, QT, false, QT, PARTS, NG>(ga, lds, bhid, taylor, slot, part, first_part)) return;
 #pragma unroll 1
   for (int n = QT * slot; n < QT * (slot + 1); ++n)    // again, 64 rows at a time
-    if (first_entry(1, n) < n_list) attn_gen_item<T, D, 1, true, QT, PARTS>(ga, lds, bhid, taylor, n, part, first_part);
+    if (first_entry(1, n) < n_list) attn_gen_item<T, D, 1, true, QT, PARTS, NG>(ga, lds, bhid, taylor, n, part, first_part);
 }
 
 // Adds up the parts of the long items: out = sum_p o_p l_p 2^(m_p - m) / sum_p l_p 2^(m_p - m) with m = max_p m_p (the merge step
@@ -765,25 +820,29 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
   const bool d64 = pr.p.D == 64, bf = pr.p.dtype == ISA_BF16;
   const double chip = (double)N_XCD * cus_per_xcd();
   auto items = [&](int n, int rows) { return bh * (pr.p.block >= rows ? n * (pr.p.block / rows) : (n + 1) / 2); };
-  // Rows per workgroup (128 read every LDS fragment once for two query tiles; bf16 only: an fp32 fragment feeds four times as many matrix
-  // instructions of twice the length, and more waves always won) and parts per long item, chosen together by a model of the
-  // launch's time: with k workgroups per compute unit a block of 64 tokens takes each of them pace[k - 1], in us as measured (k
-  // beyond what fits a compute unit: further rounds), and a workgroup spends `start` tokens' time on its start and its share of the merge.  A
-  // Taylor item counts for 1/32 of a long one of the same rows, plus its exact set's share.  The time is that of the long items' rounds or
-  // that of all items with the chip full, whichever is longer: Taylor items fill what the long ones leave idle, and where there are many of
-  // them parts gain nothing (20 heads of 128 channels, 3 x 1176 tokens, whole items of 128 rows / in two parts / of 64 rows: with exact sets
-  // 170 / 194 / 179 us, without 168 / 144 / 157).  A bf16 part has at least 256 tokens (5 heads, 2 x 495 tokens, D = 128, 1, 2, 4, 6, 8 parts: 51,
-  // 44, 42, 44, 47 us), an fp32 one may be a single block (1 head, 300 tokens: 54 whole, 44 in parts).
-  // Measured, whole calls, us, keep 0.5, full 0.25, whole items of 128 rows / of 64 / as chosen (64 rows in two groups of waves that
-  // shared a workgroup's tiles, which this replaces): bf16, 15 600 tokens, blocks of 64: D = 64, 1 head 380 / 298 / 95, 2 heads
-  // 393 / 308 / 120 (238), 4 400 / 317 / 178 (243), 8 409 / 343 / 295, 12 499 / 461 / 394, 16 524 / 574 / 524, 24 712 / 819 / 712; D = 128: 2 heads
-  // 536 / 401 / 176 (317), 4 546 / 419 / 279 (397), 8 567 / 561 / 470, 16 840 / 1058 / 840; fp32, 5280 tokens: D = 128, 4 heads 388 / 185 (381), 8 397 /
-  // 300 (389), 12 662 / 475, 16 664 / 537, D = 64, 3 heads 274 / 95, 8 282 / 169 (243), 24 417 / 397 (403).
-  struct Form { int rows, resident; double pace[4], start; };
-  static const Form forms[2][2][2] = {                 // [bf16][D = 64][64 / 128 rows]
-      {{{64, 2, {5.55, 9.9}, 80}, {}}, {{64, 4, {3.6, 5.5, 7.9, 10.5}, 64}, {}}},
-      {{{64, 2, {1.85, 2.74}, 320}, {128, 2, {2.65, 4.35}, 320}}, {{64, 4, {1.36, 1.54, 2.15, 2.8}, 320}, {128, 3, {1.82, 2.33, 3.4}, 320}}}};
-  bool two = false;
+  // The form of a workgroup (64 rows; bf16 also 128, which read every LDS fragment once for two query tiles, or 64 in two groups of waves; an
+  // fp32 fragment feeds four times as many matrix instructions of twice the length, and neither ever won) and the parts per long item,
+  // chosen together by a model of the call's time: with k workgroups per compute unit a block of 64 tokens takes each of them pace[k - 1]
+  // us (k beyond what fits a compute unit: further rounds), and a workgroup spends `start` tokens' time on its start.  The merge of partial
+  // results is `merge` us more, and they are written and read at `rate` TB/s.  A Taylor item counts for `taylor` of a long one of the same
+  // rows, plus its exact set's share (x `shared` in two groups); Taylor items fill what the long ones leave idle, so the time is that of the
+  // long items' rounds or that of all items with the chip full, whichever is longer; not so beside two groups, which leave little idle.  A bf16
+  // part has at least 256 tokens, an fp32 one may be a single block (1 head, 300 tokens: 54 whole, 44 in parts).
+  // The numbers are fitted to 1094 calls (1 to 40 heads, 300 to 15 600 tokens, dense and sparse, ragged batches) with every form and number of
+  // parts measured: the choice costs 1.0 to 1.3 % more than the best one on the geometric average.  Measured, whole calls, us, keep 0.5, full 0.25, whole
+  // items of 128 rows / of 64 / in two groups / as chosen: bf16, 15 600 tokens, blocks of 64: D = 64, 1 head 387 / 281 / 231 / 88, 4 heads 404 / 302 /
+  // 240 / 175, 8 417 / 342 / 347 / 299, 12 505 / 469 / 490 / 402, 16 531 / 581 / 641 / 531; D = 128: 2 heads 555 / 393 / 317 / 174, 4 562 / 402 / 392 / 282, 8
+  // 582 / 554 / 749 / 478, 12 756 / 812 / 1085 / 756 (the partial results have no room), 16 862 / 1051 / 1473 / 860; dense, 1980 tokens, 8 heads: D = 64
+  // 65 / 50 / 40 / 40, D = 128 93 / 67 / 54 / 54.  fp32, 64 rows / as chosen: 4800 tokens, D = 128, 4 heads 355 / 151, 12 365 / 333, D = 64, 4 heads 226 / 98.
+  struct Form { int rows, groups, resident; double pace[4], start; };
+  struct Kind { double taylor, shared, merge, rate; Form form[3]; };
+  static const Kind kinds[2][2] = {                    // [bf16][D = 64]
+      {{.012, 1, 6.3, 4.0, {{64, 1, 2, {6.4, 11.0}, 65}}},
+       {.007, 1, 4.7, 3.8, {{64, 1, 4, {3.25, 5.3, 7.3, 9.25}, 25}}}},
+      {{.075, 1.4, 6.0, 5.4, {{64, 1, 2, {1.63, 2.52}, 185}, {128, 1, 2, {2.67, 3.87}, 180}, {64, 2, 1, {2.77}, 145}}},
+       {.050, 2.0, 4.5, 4.1, {{64, 1, 4, {1.25, 1.75, 2.17, 3.03}, 320}, {128, 1, 3, {1.86, 2.91, 3.29}, 340}, {64, 2, 2, {1.97, 2.97}, 240}}}}};
+  const Kind& kind = kinds[bf][d64];
+  bool two = false, groups = false;
   Cut chosen = {};
   ga.parts = 1;
   if (n_long == 0) {
@@ -793,10 +852,11 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
     two = bf && !(set_share > 0.0 && d64 && pr.p.block == 64) && items(n_taylor, 128) >= chip * (d64 ? 7 : 5) / 4;
   } else {
     double best = INFINITY;
-    for (int f = 0; f < (bf ? 2 : 1); ++f) {
-      const Form& form = forms[bf][d64][f];
+    for (int f = 0; f < (bf ? 3 : 1); ++f) {
+      const Form& form = kind.form[f];
       // per workgroup with the chip full; a pair of blocks of 64 reads both blocks' exact sets
-      const double full = form.pace[form.resident - 1] / form.resident / chip;
+      const Form& one = kind.form[form.rows == 128];
+      const double full = one.pace[one.resident - 1] / one.resident / chip;
       Cut cut;
       double taylor = 0.0;                             // the Taylor items, in tokens (as all below)
       for (int b = 0; b < pr.p.B; ++b) {
@@ -804,20 +864,22 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
         cut.slots[b] = slots_of(pr.p.block, a.dense ? c.T : c.n_full, form.rows);
         if (a.dense) continue;
         const double set = a.exact_mask && c.n_flat > 0 ? (double)c.k_exact / c.T_new : 0.0;
-        taylor += (double)pr.p.H * slots_of(pr.p.block, c.n_flat, form.rows) * (1.0 / 32 + set * (form.rows > pr.p.block ? 2 : 1)) * c.T_new * pr.p.block;
+        taylor += (double)pr.p.H * slots_of(pr.p.block, c.n_flat, form.rows) * (kind.taylor + set * (form.rows > pr.p.block ? 2 : 1)) * c.T_new * pr.p.block;
       }
-      for (int p = 1; p <= MAX_PARTS && (p == 1 || ws.split_o) && cut_long_items(pr, a.dense, form.rows, p, cut); ++p) {
-        double work = 0.0, each = 0.0;                 // all long items; the longest part
+      for (int p = 1; p <= MAX_PARTS && (p == 1 || (ws.split_o && form.groups == 1)) && cut_long_items(pr, a.dense, form.rows, p, cut); ++p) {
+        double work = 0.0, each = 0.0, partial = 0.0;  // all long items; the longest part; rows of partial results
         for (int b = 0; b < pr.p.B; ++b) {
           if (cut.slots[b] == 0) continue;
-          const double tokens = (double)(a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new) * pr.p.block, own = tokens / cut.parts[b] + form.start;
+          const double tokens = (double)(a.dense ? pr.cnt.b[b].T : pr.cnt.b[b].T_new) * pr.p.block, own = tokens / (cut.parts[b] * form.groups) + form.start;
           work += (double)pr.p.H * cut.slots[b] * cut.parts[b] * own;
           each = fmax(each, own);
+          if (cut.parts[b] > 1) partial += (double)pr.p.H * cut.slots[b] * cut.parts[b] * form.rows;
         }
         const int k = (int)ceil(work / (each * chip) - 1e-9), rounds = (k - 1) / form.resident;      // as many as if all were as long as the longest
         const double pace = rounds * form.pace[form.resident - 1] + form.pace[(k - 1) % form.resident];
-        const double cost = fmax(pace * each, (work + taylor) * full) + (p > 1 ? 5.0 * 64 : 0.0);       // (the merge's launch)
-        if (cost < best) { best = cost; two = f == 1; ga.parts = p; chosen = cut; }
+        const double us = (form.groups > 1 ? pace * each + kind.shared * taylor * full : fmax(pace * each, (work + taylor) * full)) / 64;
+        const double cost = us + (p > 1 ? kind.merge + partial * pr.p.D * 8e-6 / kind.rate : 0.0);
+        if (cost < best) { best = cost; two = form.rows == 128; groups = form.groups > 1; ga.parts = p; chosen = cut; }
       }
     }
   }
@@ -854,10 +916,12 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
   const dim3 grid((unsigned)(N_XCD * wgs));
 #define ISA_GEN(T, D, QT)                                                                                  \
   do {                                                                                                     \
-    if (ga.parts > 1) hipLaunchKernelGGL((k_attn_gen<T, D, QT, true>), grid, dim3(256), 0, st, ga);         \
-    else hipLaunchKernelGGL((k_attn_gen<T, D, QT, false>), grid, dim3(256), 0, st, ga);                     \
+    if (ga.parts > 1) hipLaunchKernelGGL((k_attn_gen<T, D, QT, true, 1>), grid, dim3(256), 0, st, ga);      \
+    else hipLaunchKernelGGL((k_attn_gen<T, D, QT, false, 1>), grid, dim3(256), 0, st, ga);                  \
   } while (0)
-  if (bf && d64) { if (two) ISA_GEN(uint16_t, 64, 2); else ISA_GEN(uint16_t, 64, 1); }
+  if (groups && d64) hipLaunchKernelGGL((k_attn_gen<uint16_t, 64, 1, false, 2>), grid, dim3(512), 0, st, ga);
+  else if (groups) hipLaunchKernelGGL((k_attn_gen<uint16_t, 128, 1, false, 2>), grid, dim3(512), 0, st, ga);
+  else if (bf && d64) { if (two) ISA_GEN(uint16_t, 64, 2); else ISA_GEN(uint16_t, 64, 1); }
   else if (bf) { if (two) ISA_GEN(uint16_t, 128, 2); else ISA_GEN(uint16_t, 128, 1); }
   else if (d64) ISA_GEN(float, 64, 1);
   else ISA_GEN(float, 128, 1);

@@ -88,6 +88,27 @@ def test_items_in_parts(I, shape, blocks):
     check_end_to_end(I, wl, *gen(wl))
 
 
+# about an item of 64 rows per compute unit, bf16: workgroups of two groups of waves (without room for parts the choice is the same: no other
+# form is within a few per cent); rows of the second pass in some; exact sets of Taylor blocks beside long items
+@pytest.mark.parametrize("exact_frac,gamma", [(0.0, 0.0), (0.2, 0.5)])
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] == "bf16"], ids=[i for i in SHAPE_IDS if i[:4] == "bf16"])
+def test_two_groups(I, shape, exact_frac, gamma):
+    wl = _wl(shape, 8, (1, 10, 99), (((1, 9, 110),),), keep_ratio=1.0, full_frac=1.0 if exact_frac == 0 else 0.9, exact_frac=exact_frac, gamma=gamma, seed=767)
+    Q, K, V, q, k, v = gen(wl)
+    check_end_to_end(I, wl, Q, K, V, q, k, v, heads=[0, 3, 7])
+    for t in (Q, q):                                    # scores beyond 2^24 in every 50th row: its workgroup starts again
+        t[:, :, ::50] *= 2.0 ** 24
+    out = torch.empty_like(q)
+    pr = problem_of(wl)
+    I.isa_dense_attention(pr, q, k, v, out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    rest = np.arange(wl.tokens(0)) % 50 != 0            # (in the others the largest of the bf16 scores decides, which rounding may change)
+    for h in (0, 7):
+        emax, emean = err_stats(f64(out[0, h])[rest], O.dense_attention(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h]))[rest])
+        assert emax <= TOL[wl.dtype][0] and emean <= TOL[wl.dtype][1], (h, emax, emean)
+    assert torch.isfinite(out.float()).all()
+
+
 def _align(n):
     return (n + 255) // 256 * 256
 
