@@ -745,7 +745,7 @@ __global__ __launch_bounds__(256) void k_gen_merge(GenArgs ga, int rows) {
   const int in_block = pair ? row % 64 : slot % subs * rows + row;
   if (in_block >= a.blk_n[b * a.geo.T_max + qi]) return;
   const long long first = (long long)(ga.first_part[b] + (h * slots_of(a.geo.block, n_list, rows) + slot) * parts) * rows + row;
-  const double cs = 1.4426950408889634 / sqrt((double)D);
+  const double cs = 1.4426950408889634f / sqrtf((float)D);       // the factor of the passes, rounded as there: another is 1e-8 of a large score off
   auto log2_max = [&](const float2 ml) { return sizeof(T) == 2 && (__float_as_uint(ml.y) >> 31) ? (double)ml.x * cs : (double)ml.x; };
   // all parts' loads in flight at once (a part past the last repeats it, with weight 0)
   float2 ml[MAX_PARTS];

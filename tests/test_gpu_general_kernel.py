@@ -194,6 +194,37 @@ def test_parts_of_both_passes(I, shape, exponent):
         assert emax <= TOL[wl.dtype][0] and emean <= TOL[wl.dtype][1], (h, emax, emean)
 
 
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] == "bf16"], ids=[i for i in SHAPE_IDS if i[:4] == "bf16"])
+def test_maxima_of_both_passes_on_one_scale(I, shape):
+    """All scores of a row are 2^26 and a little (exact in fp32, 2^23 in the log2 domain): the keys of one block share the weight evenly with all others, and
+    other rows of the workgroup send the part that holds the block through the second pass, whose maximum has another unit.  Values 1 and -1:
+    with the two units off by 1e-8 from each other the result is off by a few per cent."""
+    block, D = shape[2], shape[1]
+    n = 24 * block
+    wl = _wl(shape, 2, (1, 1, n), ((),), seed=765)
+    g = torch.Generator().manual_seed(wl.seed)
+    Q, K, V = (torch.zeros((1, 2, n, D), dtype=torch.bfloat16) for _ in range(3))
+    at = slice(5 * block, 6 * block)
+    K[..., 0] = 2.0 ** 13
+    K[..., 1] = (8 * torch.randint(0, 4, (1, 2, n), generator=g)).bfloat16()
+    K[:, :, at, 1] += 8 * round(np.log(23.0) * D ** 0.5 / 8)
+    K[:, :, at, 2] = 2.0 ** 14
+    Q[..., 0], Q[..., 1] = 2.0 ** 13, 1.0
+    Q[:, :, 7::16] = 0
+    Q[:, :, 7::16, 2] = 2.0 ** 14                       # 2^28 against the block, 0 against the others
+    V[...], V[:, :, at] = -1.0, 1.0
+    q, k, v = Q.cuda(), K.cuda(), V.cuda()
+    pr = problem_of(wl)
+    out = torch.empty_like(q)
+    I.isa_dense_attention(pr, q, k, v, out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    for h in range(2):
+        want = O.dense_attention(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h]))
+        assert np.abs(want[0]).max() < 0.5              # the premise: neither side has all the weight
+        emax, _ = err_stats(f64(out[0, h]), want)       # the rounding of the result, 2^-9, and as much for the weights
+        assert emax <= 2.0 ** -8, (h, emax)
+
+
 @pytest.mark.parametrize("H", [1, 3, 5, 9, 20])
 def test_head_counts_over_the_xcds(I, H):
     wl = _wl(("bf16", 64, 64), H, (2, 10, 33), (((1, 10, 33),),), keep_ratio=0.5, full_frac=0.4, seed=750 + H)
