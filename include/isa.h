@@ -59,7 +59,7 @@ typedef enum {
                                span 4 GiB or more (S_max * stride_t * 2 bytes: the matrix-core kernels use 32-bit byte
                                offsets; isa_set_mfma(0) selects the general kernel, which has no such limit); a call
                                that is not available in the stream's state (isa_attention_simple under capture) */
-  ISA_ERR_WORKSPACE = -6,   /* workspace NULL, misaligned (256 B) or smaller than required */
+  ISA_ERR_WORKSPACE = -6,   /* workspace NULL, misaligned (256 B) or smaller than required (see isa_workspace_bytes) */
   ISA_ERR_HIP = -7          /* a HIP runtime call or kernel launch failed */
 } isa_status;
 
@@ -98,7 +98,11 @@ typedef struct isa_counts {
 int isa_get_counts(const isa_problem* p, int b, isa_counts* out);
 
 /* Host only.  Bytes of device workspace any entry point below needs for `p` (0 if `p` is invalid).
- * The workspace must be 256-byte aligned.  Its contents are scratch: undefined before and after. */
+ * The workspace must be 256-byte aligned.  Its contents are scratch: undefined before and after.
+ * For the general kernel (fp32, D = 64 or block = 64) the size ends with room for partial results: up to 35 MB, as much as the problem's
+ * long key lists can use when they are cut into parts that run beside each other.  A buffer without that room (one that holds the arrays
+ * before it) is accepted: the lists are then not cut, which takes longer where there are few of them, and as sums are added in another
+ * order the results differ in their last bits from those with a buffer of the full size. */
 size_t isa_workspace_bytes(const isa_problem* p);
 
 /* Where isa_attention leaves its intermediate results inside the workspace: byte offsets from the workspace pointer.
@@ -144,11 +148,12 @@ int isa_attention_simple(const void* q, const void* k, const void* v, int H, int
 
 /* isa_attention for callers that cannot allocate device memory or hand over a workspace: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and the same result as
- * isa_attention, but the scratch memory is a fixed array of ISA_STATIC_SCRATCH_BYTES inside the library's own device
+ * isa_attention (with a workspace of the full size), but the scratch memory is a fixed array inside the library's own device
  * image (every GPU the library runs on holds one copy until the process ends); the call allocates and frees nothing.
  * Limits: the forward-only workspace of `p` (the arrays isa_attention needs, without those it would leave for
- * isa_attention_backward) must fit that array, else ISA_ERR_WORKSPACE and nothing is launched; at D = 128 in bf16 that is
- * about 330 000 head-tokens (H * S), e.g. 40 heads of 8 000 tokens.  No backward call can follow it.  The array is shared
+ * isa_attention_backward) must fit ISA_STATIC_SCRATCH_BYTES, else ISA_ERR_WORKSPACE and nothing is launched; at D = 128 in bf16
+ * that is about 330 000 head-tokens (H * S), e.g. 40 heads of 8 000 tokens (the general kernel's partial results do not count:
+ * the array has another 35 MB for them).  No backward call can follow it.  The array is shared
  * by every call on the same GPU and keeps the previous call's contents (no call relies on them): two calls that overlap on
  * one GPU (different streams, different threads) race; calls on one stream are ordered.  The first call on a device
  * looks the array's address up (hipGetSymbolAddress), so make it before a stream capture begins. */

@@ -801,7 +801,18 @@ static bool cut_long_items(const Problem& pr, bool dense, int rows, int p, Cut& 
     cut.first[b] = (int)n;
     if (cut.parts[b] > 1) n += (long long)pr.p.H * cut.slots[b] * cut.parts[b];
   }
-  return n * rows * pr.p.D <= SPLIT_MAX_SUB * 256ll * 128;
+  return n * rows * pr.p.D <= GEN_PARTIAL_ELEMENTS;
+}
+
+// Dense attention has the longest lists and the most long items; a workgroup of 128 rows holds one block of 64 at worst.
+long long gen_partial_rows(const Problem& pr) {
+  const int least = pr.p.dtype == ISA_BF16 ? 256 / pr.p.block : 1;
+  long long rows = 0;
+  for (int b = 0; b < pr.p.B; ++b) {
+    const int T = pr.cnt.b[b].T, parts = min(MAX_PARTS, T / least);
+    if (parts > 1) rows += (long long)pr.p.H * slots_of(pr.p.block, T, 128) * max(128, pr.p.block) * parts;
+  }
+  return min(rows, GEN_PARTIAL_ELEMENTS / pr.p.D);
 }
 
 hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArgs& a, hipStream_t st) {

@@ -192,8 +192,9 @@ void carve(const Problem& pr, void* base, Workspace* ws, bool forward_only) {
   }
   ws->least = off;
   if (!pr.mfma_shape) {
-    ws->split_o = (float*)take((size_t)SPLIT_MAX_SUB * 256 * 128 * 4);
-    ws->split_ml = (float*)take((size_t)SPLIT_MAX_SUB * 256 * (128 / D) * 2 * 4);
+    const size_t rows = (size_t)gen_partial_rows(pr);
+    ws->split_o = rows ? (float*)take(rows * D * 4) : nullptr;
+    ws->split_ml = rows ? (float*)take(rows * 2 * 4) : nullptr;
   }
   ws->bytes = off;
 }
@@ -202,7 +203,7 @@ static int check_ws(const Problem& pr, void* workspace, size_t bytes, Workspace*
   if (!workspace || ((uintptr_t)workspace & 255)) return ISA_ERR_WORKSPACE;
   carve(pr, workspace, ws);
   if (bytes < ws->least) return ISA_ERR_WORKSPACE;
-  if (bytes < ws->bytes) ws->split_o = ws->split_ml = nullptr;
+  if (bytes < ws->bytes) ws->split_o = ws->split_ml = nullptr;      // long items stay whole (see isa_workspace_bytes)
   return ISA_OK;
 }
 
@@ -427,7 +428,10 @@ int isa_attention(const isa_problem* p, const void* q, const void* k, const void
 // Its scratch is this file-scope device array: every GPU the library's code object is loaded on holds one copy, at its own
 // address, until the process ends.  In host code the array's name is only a handle for hipGetSymbolAddress; the device
 // address obtained from it (once per device, kept in g_static_ptr) is what kernels and carve() are given.
-static __device__ __align__(256) unsigned char scratch[ISA_STATIC_SCRATCH_BYTES];
+// The general kernel's partial results have room beside ISA_STATIC_SCRATCH_BYTES, so that the items run in the same parts as in isa_attention
+// whatever the other arrays take.
+constexpr size_t STATIC_BYTES = (size_t)ISA_STATIC_SCRATCH_BYTES + GEN_PARTIAL_BYTES;
+static __device__ __align__(256) unsigned char scratch[STATIC_BYTES];
 constexpr int STATIC_MAX_DEVICES = 64;
 static void* g_static_ptr[STATIC_MAX_DEVICES];          // device address of `scratch` on each device; null = not asked yet
 static std::mutex g_static_mu;
@@ -442,7 +446,7 @@ static int static_scratch(void** ptr) {
     size_t bytes = 0;
     ISA_TRY(hipGetSymbolAddress(&d, HIP_SYMBOL(scratch)));      // of the current device's copy
     ISA_TRY(hipGetSymbolSize(&bytes, HIP_SYMBOL(scratch)));
-    if (!d || bytes < (size_t)ISA_STATIC_SCRATCH_BYTES || ((uintptr_t)d & 255)) return ISA_ERR_WORKSPACE;
+    if (!d || bytes < STATIC_BYTES || ((uintptr_t)d & 255)) return ISA_ERR_WORKSPACE;
     g_static_ptr[dev] = d;
   }
   *ptr = g_static_ptr[dev];
@@ -461,7 +465,6 @@ int isa_attention_static(const isa_problem* p, const void* q, const void* k, con
   void* base = nullptr;
   if ((rc = static_scratch(&base)) != ISA_OK) return rc;
   carve(pr, base, &ws, true);
-  if (ws.bytes > (size_t)ISA_STATIC_SCRATCH_BYTES) ws.split_o = ws.split_ml = nullptr;
   // every array of the carve-up is written by a kernel of this call before any kernel reads it, so what the previous
   // call left in the scratch does not matter and nothing has to be cleared
   return run_attention(pr, ws, q, k, v, out, (hipStream_t)hip_stream);

@@ -50,6 +50,8 @@ struct Geometry {
 // Workspace carve-up (device pointers into the caller's workspace).
 constexpr int BWD_MEAN_PARTS = 4;    // backward: parts a mean-row work item may be cut into (partial sums in dkc / dvc)
 constexpr int SPLIT_MAX_SUB = 256;   // sub-items of split work items per launch: at most one per compute unit
+constexpr long long GEN_PARTIAL_ELEMENTS = SPLIT_MAX_SUB * 256ll * 128;       // general kernel: most elements of partial results, rows x channels
+constexpr size_t GEN_PARTIAL_BYTES = GEN_PARTIAL_ELEMENTS * 4 + GEN_PARTIAL_ELEMENTS / 64 * 8 + 512;      // with a {maximum, sum} of each row of 64
 
 struct Workspace {
   int* blk_start;        // [B][T_max] token offset of each block inside its batch item
@@ -78,8 +80,8 @@ struct Workspace {
   int* bwd_ctr;          // backward: the next work item of each launch that hands its items out dynamically (8 counters, zeroed by k_bwd_prepare)
   int4* ktab;            // [B,H,T_max] the btab rows of the blocks of kv_list, in list order
   float* ocoarse;        // [B,H,T_max,D] pooled attention output (only carved when gamma != 0)
-  // partial outputs of work items split along the key sequence, 256 x 256 rows, and their running maxima and sums.  Null if the general kernel's
-  // caller has no room for them: its items then stay whole
+  // partial outputs of work items split along the key sequence, 256 x 256 rows (general kernel: gen_partial_rows), and their running maxima and
+  // sums.  Null if the general kernel's caller has no room for them: its items then stay whole
   float* split_o; float* split_ml;
   // backward pass (MFMA path): what the forward leaves for it, and its own scratch
   float* nlse;           // [B,H,S_max] minus the log-sum-exp of every query row, log2 domain (written by the forward)
@@ -170,6 +172,8 @@ hipError_t launch_select(const Problem& pr, const Workspace& ws, const float* s_
 // own arrays, in one launch
 bool plan_is_small(const Problem& pr);
 hipError_t launch_plan(const Problem& pr, const Workspace& ws, bool gather, hipStream_t st);
+// the most rows of partial results that a call of the general kernel leaves for this problem
+long long gen_partial_rows(const Problem& pr);
 hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArgs& a, hipStream_t st);
 
 // MFMA path (bf16, D = 128, block = 128)

@@ -157,13 +157,14 @@ def test_no_room_for_parts(I, shape):
     Q, K, V, q, k, v = gen(wl)
     pr = problem_of(wl)
     ws = I.new_workspace(pr)
-    least = I.isa_workspace_bytes(pr) - 4 * 256 * 256 * (128 + 2 * 128 // shape[1])
+    least = _bytes_without_parts(I, pr)
     outs = [torch.empty_like(q) for _ in range(2)]
     for out, w in zip(outs, (ws, ws[:least])):
         I.isa_dense_attention(pr, q, k, v, out, w)
     with pytest.raises(I.IsaError):
         I.isa_dense_attention(pr, q, k, v, outs[0], ws[:least - 256])
     torch.cuda.synchronize()
+    assert not torch.equal(*outs)                       # the first call did cut them: its sums end otherwise
     want = np.stack([O.dense_attention(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h])) for h in range(2)])
     for out in outs:
         emax, emean = err_stats(f64(out[0]), want)

@@ -110,6 +110,20 @@ def test_token_span_of_4_gib_is_refused_not_rerouted():
     assert status(base_problem(H=40, D=128, block=128, dtype="bf16", seg_len=[[32760, 32760]]), strides=(65520 * 15360, 128, 15360)) == 0
 
 
+@pytest.mark.parametrize("dtype,D,block", [("f32", 64, 64), ("f32", 128, 128), ("bf16", 64, 128), ("bf16", 128, 64)])
+def test_room_for_partial_results(dtype, D, block):
+    """What the workspace of a general-kernel shape has behind its last array: nothing for key lists that are never cut (one block, bf16 below 512
+    tokens), as much as 8 parts of the few rows of a short problem need, 35 MB at most."""
+    def room(n, H=1):
+        pr = base_problem(dtype=dtype, D=D, block=block, H=H, seg_len=[[n]])
+        return I.isa_workspace_bytes(pr) - (I.isa_workspace_layout(pr)["flat_list"] + (H * -(-n // block) * 4 + 255) // 256 * 256)
+
+    assert room(block) == 0 and (dtype == "f32" or room(511 - 511 % block) == 0)
+    for n in (512, 1000, 2049):
+        assert 0 < room(n) <= 8 * (n + 2 * block) * (D * 4 + 8) + 512, n
+    assert room(2049) < room(200000, H=2) <= 35_000_000
+
+
 def test_workspace_layout_is_consistent():
     """isa_workspace_layout: every array lies inside the workspace, 256-byte aligned, no two overlap; optional arrays
     are reported absent exactly when the problem does not have them."""

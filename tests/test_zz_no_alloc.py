@@ -82,6 +82,25 @@ def test_static_scratch_call_replays_from_a_hip_graph():
         torch.cuda.synchronize()
 
 
+def test_static_scratch_has_room_for_partial_results():
+    """The general kernel's arrays up to the partial results take 113 MB here, all but 15 of the limit: the items run in parts all the same, as in
+    isa_attention (which gives other bits where they stay whole)."""
+    import paper_2605_04569_amd as I
+    pr = I.Problem(H=2, D=128, dtype="bf16", block=64, seg_len=[[104000, 104000]], keep_ratio=0.5, full_frac=0.01, exact_frac=0.001)
+    lay, T = I.isa_workspace_layout(pr), I.isa_get_counts(pr)["T_max"]
+    least = lay["exact_mask"] + 2 * T * ((T + 31) // 32) * 4
+    assert 100 << 20 < least < 128 << 20
+    g = torch.Generator(device="cuda").manual_seed(303)
+    q, k, v = (torch.randn((1, 2, 208000, 128), generator=g, device="cuda").bfloat16() for _ in range(3))
+    ws, outs = I.new_workspace(pr), [torch.empty_like(q) for _ in range(3)]
+    I.isa_attention(pr, q, k, v, outs[0], ws)
+    I.isa_attention_static(pr, q, k, v, outs[1])
+    I.isa_attention(pr, q, k, v, outs[2], ws[:(least + 255) // 256 * 256])
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])
+    assert not torch.equal(outs[0], outs[2])
+
+
 def test_static_scratch_rejects_what_does_not_fit():
     """cfg2's forward-only workspace (0.7 GB) is beyond the array: a clear error, nothing launched."""
     import paper_2605_04569_amd as I
