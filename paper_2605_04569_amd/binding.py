@@ -153,9 +153,13 @@ def _ptr(t):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
+# the handle without a Stream object around it: 0.4 us instead of 2.8, and a short training step is bound by what the host does.  Not a public
+# function of torch: without it, the handle of the public object
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream():
-    # the handle without a Stream object around it: 0.4 us instead of 2.8, and a short training step is bound by what the host does
-    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    return C.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
 def _check(rc, where):

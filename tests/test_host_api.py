@@ -219,3 +219,19 @@ def test_counts_agree_with_oracle(seg, block, keep, full, exact):
         assert (c["n_full"], c["n_flat"]) == O.group_counts(full, T)
         assert c["k_exact"] == O.exact_count(exact, c["T_new"])
     assert I.isa_workspace_bytes(pr) > 0
+
+
+def test_stream_handle_without_the_private_function(monkeypatch):
+    """A torch without _cuda_getCurrentRawStream: the handle comes from the public stream object."""
+    import importlib.util
+    import sys
+    import types
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: types.SimpleNamespace(cuda_stream=1234))
+    spec = importlib.util.spec_from_file_location("binding_of_another_torch", I.binding.__file__)
+    binding = importlib.util.module_from_spec(spec)
+    monkeypatch.setitem(sys.modules, spec.name, binding)                   # dataclasses look their module up
+    spec.loader.exec_module(binding)
+    assert binding._stream().value == 1234
