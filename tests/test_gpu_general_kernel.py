@@ -27,6 +27,30 @@ def _wl(shape, H, src, ctx, **kw):
     return W.CONFIGS["cfg1"].with_(name="general", H=H, D=D, dtype=dtype, block=block, src_grid=src, ctx_grids=ctx, **kw)
 
 
+def _align(n):
+    return (n + 255) // 256 * 256
+
+
+def _bytes_without_parts(I, pr):
+    """The workspace up to the end of its last array before the partial results: exact_mask, o_coarse or flat_list."""
+    lay, T = I.isa_workspace_layout(pr), I.isa_get_counts(pr, 0)["T_max"]
+    rows = pr.B * pr.H * T
+    if pr.exact_frac > 0:
+        return lay["exact_mask"] + _align(rows * ((T + 31) // 32) * 4)
+    if pr.gamma != 0:
+        return lay["o_coarse"] + _align(rows * pr.D * 4)
+    return lay["flat_list"] + _align(rows * 4)
+
+
+def _is_cut(I, pr, q, k, v):
+    """Whether isa_attention runs long items in parts: without room for partial results they stay whole, and some sum then ends otherwise."""
+    ws, outs = I.new_workspace(pr), [torch.zeros_like(q) for _ in range(2)]
+    I.isa_attention(pr, q, k, v, outs[0], ws)
+    I.isa_attention(pr, q, k, v, outs[1], ws[:_bytes_without_parts(I, pr)])
+    torch.cuda.synchronize()
+    return not torch.equal(*outs)
+
+
 # tails of 1, 31, 32, 33, 63, 64 and 65 tokens: a tile's half, both halves, one past
 @pytest.mark.parametrize("tail", [1, 31, 32, 33, 63, 64, 65])
 @pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
@@ -63,7 +87,7 @@ def test_wide_workgroups_of_taylor_blocks(I, shape, exact_frac):
 # 1, 2 and 3 tiles (fp32: 32 tokens each), token tiles followed by tiles of means
 @pytest.mark.parametrize("tokens", [32, 33, 64, 65, 96])
 @pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
-def test_few_tiles_for_two_groups(I, shape, tokens):
+def test_few_tiles(I, shape, tokens):
     wl = _wl(shape, 2, (1, 1, tokens), (((1, 1, 40),),), keep_ratio=1.0, full_frac=0.5, exact_frac=0.5, seed=740 + tokens)
     check_end_to_end(I, wl, *gen(wl))
 
@@ -71,13 +95,13 @@ def test_few_tiles_for_two_groups(I, shape, tokens):
 # a long list with few long items (in parts) and with many: the same answers
 @pytest.mark.parametrize("H", [2, 60])
 @pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
-def test_one_and_two_groups(I, shape, H):
+def test_few_and_many_long_items(I, shape, H):
     wl = _wl(shape, H, (1, 1, 1500), (((1, 1, 900),),), keep_ratio=0.5, full_frac=0.5, exact_frac=0.2, gamma=0.5, seed=745 + H)
     check_end_to_end(I, wl, *gen(wl), heads=[0, H // 2, H - 1])
 
 
-# few heads: long items in 2 to 8 parts over key lists of 2 blocks (fp32: one each; bf16: whole), of 9 (unequal parts) and of 40; odd lists of blocks, a shorter
-# batch item, the residual added where the parts are
+# few heads: long items in parts over key lists of 2 blocks (of 128 in fp32: one each), of 9 (unequal parts) and of 40; odd lists of blocks, a
+# batch item with fewer of them, the residual added where the parts are
 @pytest.mark.parametrize("blocks", [2, 9, 40])
 @pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
 def test_items_in_parts(I, shape, blocks):
@@ -85,17 +109,30 @@ def test_items_in_parts(I, shape, blocks):
     wl = _wl(shape, 3, (1, 1, block * (blocks - 1) + 9), (((1, 1, 3 * block),), ((1, 1, block + 1),)), B=2, keep_ratio=0.0, full_frac=0.4,
              exact_frac=0.2 if blocks == 9 else 0.0, gamma=0.5, seed=752 + blocks)
     assert I.isa_get_counts(problem_of(wl), 0)["T_new"] == blocks
-    check_end_to_end(I, wl, *gen(wl))
+    inputs = gen(wl)
+    check_end_to_end(I, wl, *inputs)
+    whole = shape[0] == "bf16" and blocks == 2 or (shape, blocks) in ((SHAPES[0], 9), (SHAPES[3], 2))       # lists too short for parts to pay
+    assert _is_cut(I, problem_of(wl), *inputs[3:]) == (not whole)
 
 
-# about an item of 64 rows per compute unit, bf16: workgroups of two groups of waves (without room for parts the choice is the same: no other
-# form is within a few per cent); rows of the second pass in some; exact sets of Taylor blocks beside long items
+# about an item of 64 rows per compute unit, bf16: workgroups of two groups of waves; rows of the second pass in some; exact sets of Taylor
+# blocks beside long items
 @pytest.mark.parametrize("exact_frac,gamma", [(0.0, 0.0), (0.2, 0.5)])
 @pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] == "bf16"], ids=[i for i in SHAPE_IDS if i[:4] == "bf16"])
 def test_two_groups(I, shape, exact_frac, gamma):
     wl = _wl(shape, 8, (1, 10, 99), (((1, 9, 110),),), keep_ratio=1.0, full_frac=1.0 if exact_frac == 0 else 0.9, exact_frac=exact_frac, gamma=gamma, seed=767)
     Q, K, V, q, k, v = gen(wl)
     check_end_to_end(I, wl, Q, K, V, q, k, v, heads=[0, 3, 7])
+    if exact_frac == 0:
+        # the premise: whole items, whose sums do not end as with one group of waves (enough heads to fill the chip with those)
+        assert not _is_cut(I, problem_of(wl), q, k, v)
+        many = [t[:, :1].expand(1, 70, -1, -1).contiguous() for t in (q, k, v)]
+        outs = [torch.empty_like(q), torch.empty_like(many[0])]
+        for x, out in zip(((q, k, v), many), outs):
+            pr = problem_of(wl, H=x[0].shape[1])
+            I.isa_attention(pr, *x, out, I.new_workspace(pr))
+        torch.cuda.synchronize()
+        assert not torch.equal(outs[0][:, 0], outs[1][:, 0]) and torch.equal(outs[1][:, 0], outs[1][:, 69])
     for t in (Q, q):                                    # scores beyond 2^24 in every 50th row: its workgroup starts again
         t[:, :, ::50] *= 2.0 ** 24
     out = torch.empty_like(q)
@@ -107,30 +144,6 @@ def test_two_groups(I, shape, exact_frac, gamma):
         emax, emean = err_stats(f64(out[0, h])[rest], O.dense_attention(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h]))[rest])
         assert emax <= TOL[wl.dtype][0] and emean <= TOL[wl.dtype][1], (h, emax, emean)
     assert torch.isfinite(out.float()).all()
-
-
-def _align(n):
-    return (n + 255) // 256 * 256
-
-
-def _bytes_without_parts(I, pr):
-    """The workspace up to the end of its last array before the partial results: exact_mask, o_coarse or flat_list."""
-    lay, T = I.isa_workspace_layout(pr), I.isa_get_counts(pr, 0)["T_max"]
-    rows = pr.B * pr.H * T
-    if pr.exact_frac > 0:
-        return lay["exact_mask"] + _align(rows * ((T + 31) // 32) * 4)
-    if pr.gamma != 0:
-        return lay["o_coarse"] + _align(rows * pr.D * 4)
-    return lay["flat_list"] + _align(rows * 4)
-
-
-def _is_cut(I, pr, q, k, v):
-    """Whether isa_attention runs long items in parts: without room for partial results they stay whole, and some sum then ends otherwise."""
-    ws, outs = I.new_workspace(pr), [torch.zeros_like(q) for _ in range(2)]
-    I.isa_attention(pr, q, k, v, outs[0], ws)
-    I.isa_attention(pr, q, k, v, outs[1], ws[:_bytes_without_parts(I, pr)])
-    torch.cuda.synchronize()
-    return not torch.equal(*outs)
 
 
 # batch items with key lists of different length, the longest neither first nor last: parts of about one length, so that the longest list has
@@ -181,6 +194,7 @@ def test_parts_of_both_passes(I, shape, exponent):
     g = torch.Generator().manual_seed(wl.seed + exponent)
     Q, K = (torch.zeros((1, 2, n, wl.D), dtype=W.torch_dtype(wl.dtype)) for _ in range(2))
     V = torch.randn((1, 2, n, wl.D), generator=g).to(Q.dtype)
+    assert _is_cut(I, problem_of(wl, keep_ratio=1.0, full_frac=1.0), *(V.cuda(),) * 3)
     Q[..., 0] = ((128 + torch.arange(n) % 128) * 2.0 ** exponent).to(Q.dtype)
     Q[:, :, ::3] *= -1
     Q[:, :, ::7] = 0                                    # these rows see all keys alike

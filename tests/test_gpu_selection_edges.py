@@ -83,11 +83,12 @@ def test_one_launch_plan(I, shape, T_src, T_ctx, keep, full, exact):
             x[:, :, 3 * block:4 * block] = x[:, :, block:2 * block]
         k[0, 1, 2 * block:3 * block, 0] = float("inf")
     ws = I.new_workspace(pr)
-    I.isa_attention(pr, q, k, v, torch.empty_like(q), ws)
+    out = torch.zeros_like(q)
+    I.isa_attention(pr, q, k, v, out, ws)
     torch.cuda.synchronize()
     lay = I.isa_workspace_layout(pr)
     at = lambda name, dt, *more: I.workspace_array(ws, lay[name], (2, H, T) + more, dt).clone()
-    qc, kc = at("qc", torch.float32, D), at("kc", torch.float32, D)
+    qc, kc, vc = (at(n, torch.float32, D) for n in ("qc", "kc", "vc"))
     words = (T + 31) // 32
     names = ["s_ctx", "sharp", "kv_list", "full_list", "flat_list"]
     got = {n: at(n, torch.float32 if i < 2 else torch.int32) for i, n in enumerate(names)}
@@ -108,3 +109,8 @@ def test_one_launch_plan(I, shape, T_src, T_ctx, keep, full, exact):
             m = c[b][rows[n]] if n in rows else T
             a, w = x[b, :, :m], want[n][b, :, :m]
             assert torch.equal(torch.nan_to_num(a, nan=-7.0) if a.is_floating_point() else a, torch.nan_to_num(w, nan=-7.0) if w.is_floating_point() else w), (n, b)
+    # the gathered means are seen in what the attention makes of them (with exact sets or not, whole Taylor rows of NaN among them)
+    out2 = torch.zeros_like(q)
+    I.isa_attend(pr, q, k, v, kc, vc, *lists, mask if exact > 0 else None, out2, ws2)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.nan_to_num(out.float(), nan=-7.0), torch.nan_to_num(out2.float(), nan=-7.0))
