@@ -891,6 +891,7 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
         const double us = (form.groups > 1 ? pace * each + kind.shared * taylor * full : fmax(pace * each, (work + taylor) * full)) / 64;
         const double cost = us + (p > 1 ? kind.merge + partial * pr.p.D * 8e-6 / kind.rate : 0.0);
         if (cost < best) { best = cost; two = form.rows == 128; groups = form.groups > 1; ga.parts = p; chosen = cut; }
+        if (p == 1 && best <= (work + taylor) * full / 64 + kind.merge) break;       // no number of parts can be quicker: they add starts and a merge
       }
     }
   }
