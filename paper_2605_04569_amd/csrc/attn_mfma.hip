@@ -274,11 +274,15 @@ __device__ __forceinline__ uint4 halves_of_two_groups(uint2 a, uint2 b) {
   return make_uint4(x[0], y[0], x[1], y[1]);
 }
 
-// Workgroups from n_wgs on merge the cut items of the launch before (four times the rows of a workgroup of k_split_merge: only two
-// workgroups of this kernel fit a compute unit).  Measured, two launches / one: 12 heads of 1564 tokens 8.5 + 14.3 / 18.0 us, the call at the
-// paper's ratios over 65 520 tokens 21.64 / 21.53 ms (of which the workgroups that used to be launched for exact-branch blocks are a part).
+// merge.wgs workgroups from merge.first on merge the cut items of the launch before, each 8 rows, or 4 x 8 of them beyond one and a half
+// rounds of workgroups (only two of this kernel fit a compute unit; but one head of 60 blocks has 8 items in 32 ranges each, whose rows' waits
+// one after the other took 20 us: whole call 105 / 75; 3 heads of 72 blocks 91 / 80).  They come first, unless they fill a place of every compute unit: behind
+// the attention items their waits were the end of the launch (40 heads of 56 blocks 415 / 402 us; 8 heads of 60 blocks, 512 of
+// them, 134 last / 138 first).  Measured, two launches / one: 12 heads of 1564 tokens 8.5 + 14.3 / 18.0 us, the call at the paper's ratios over
+// 65 520 tokens 21.64 / 21.53 ms (of which the workgroups that used to be launched for exact-branch blocks are a part).
 constexpr int MERGE_ROWS = 4;
-__global__ __launch_bounds__(256, 2) void k_attn_mfma(MfmaArgs a, int n_wgs) {
+struct MergeWgs { int first, wgs, rows; };
+__global__ __launch_bounds__(256, 2) void k_attn_mfma(MfmaArgs a, MergeWgs merge) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[2 * K_TILE + 2 * V_TILE + 2 * 512];
   uint16_t* ldsK = lds;                     // [2][K_TILE]
   uint16_t* ldsV = lds + 2 * K_TILE;        // [2][V_TILE]
@@ -286,12 +290,15 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma(MfmaArgs a, int n_wgs) {
 
   // ---- which work item: consecutive logical ids go to the same XCD, so that the workgroups that run
   // together on one XCD (and share its L2) read the same head's keys and values
-  if ((int)blockIdx.x >= n_wgs) {
-    split_merge<MERGE_ROWS>(a, (int)blockIdx.x - n_wgs);
+  int wg = (int)blockIdx.x - merge.first;
+  if (wg >= 0 && wg < merge.wgs) {
+    if (merge.rows == 1) split_merge<1>(a, wg);
+    else split_merge<MERGE_ROWS>(a, wg);
     return;
   }
-  const int per_xcd = n_wgs >> 3;           // a multiple of 8
-  const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  wg = (int)blockIdx.x - (merge.first == 0 ? merge.wgs : 0);
+  const int per_xcd = ((int)gridDim.x - merge.wgs) >> 3;       // both counts are multiples of 8
+  const int logical = (wg & 7) * per_xcd + (wg >> 3);
   if (logical >= a.total) return;
   const int slot = logical % a.slots;
   const int bhid = logical / a.slots;
@@ -557,9 +564,14 @@ hipError_t launch_attn_mfma4(const Problem& pr, MfmaArgs m, int n_merge, hipStre
   m.slots = 0;
   for (int b = 0; b < pr.p.B; ++b) m.slots = pr.cnt.b[b].n_flat > m.slots ? pr.cnt.b[b].n_flat : m.slots;
   m.total = pr.p.B * pr.p.H * m.slots;
-  const int n_wgs = (m.total + 7) / 8 * 8, grid = n_wgs + n_merge * (32 / MERGE_ROWS);
-  if (grid == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_attn_mfma, dim3(grid), dim3(256), 0, st, m, n_wgs);
+  const int n_wgs = (m.total + 7) / 8 * 8;
+  const int chip = N_XCD * cus_per_xcd();
+  MergeWgs merge;
+  merge.rows = n_wgs + n_merge * 32 <= 3 * chip ? 1 : MERGE_ROWS;
+  merge.wgs = n_merge * (32 / merge.rows);
+  merge.first = merge.wgs <= chip ? 0 : n_wgs;
+  if (n_wgs + merge.wgs == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_attn_mfma, dim3(n_wgs + merge.wgs), dim3(256), 0, st, m, merge);
   return hipGetLastError();
 }
 
