@@ -695,8 +695,9 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a) {
 
 // One workgroup has all rows of a head to itself, which stops paying off towards 64 blocks unless the exact sets' launch is saved as well.  Whole
 // calls, separate launches / one: 10 heads of 33, 48, 62 blocks 66.2 / 61.8, 76.0 / 74.7, 88.5 / 90.2 us, with exact sets 33, 62 blocks 91.7 /
-// 77.6, 133.6 / 131.3.
-bool plan_is_small(const Problem& pr) { return pr.cnt.T_max <= (pr.p.exact_frac > 0.0 ? PLAN_BLOCKS : 48) && pr.p.gamma == 0.0; }
+// 77.6, 133.6 / 131.3.  Sources without context have the most rows to add up: 1, 3, 8 heads of 48 blocks 57.5 / 59.7, 63.5 / 65.6, 92.8 / 94.6, of 44
+// 57.5 / 58.1, 62.8 / 63.2, 89.6 / 90.3 (half of them context: 59.1 / 58.0, 63.5 / 61.3, 85.6 / 83.3).
+bool plan_is_small(const Problem& pr) { return pr.cnt.T_max <= (pr.p.exact_frac > 0.0 ? PLAN_BLOCKS : 44) && pr.p.gamma == 0.0; }
 
 hipError_t launch_plan(const Problem& pr, const Workspace& ws, bool gather, hipStream_t st) {
   PlanArgs a = {ws.qc, ws.kc, ws.s_ctx, ws.sharp, ws.kv_list, ws.full_list, ws.flat_list, pr.p.exact_frac > 0.0 ? ws.exact_mask : nullptr,
