@@ -592,8 +592,8 @@ __device__ __forceinline__ void attn_bwd(const BwdArgs& a, uint16_t* const lds, 
 // dQ of both branches and the mean-row launch (dKc, then dVc) in one launch: workgroups 0 .. wgs_full - 1 take the exact branch's items (the
 // longest), then come wgs_means for each of dKc and dVc, then the Taylor branch's; all three counts are multiples of the XCDs.
 // None reads what another writes, and each alone leaves compute units idle at its end (all of the time, if it is small).  Measured, three
-// launches / one, a training step of 12 heads of 1564 tokens 211 / 190 us (78 / 33 of them in these launches and their merges), 40 heads of
-// 15 600 tokens with the residual 4460 / 4406, 65 520 tokens at the paper's ratios 99.6 / 99.0 ms.
+// launches / one, a training step of 12 heads of 1564 tokens 211 / 190 us (78 / 33 of them in these launches and their merges); steps of 15 600
+// and 65 520 tokens gain less than 1 %, no more than runs and boxes differ.
 struct BwdTokensArgs { BwdArgs full, flat, means; float* dvc; int wgs_full, wgs_flat, wgs_means; };
 template <int EX>
 __global__ __launch_bounds__(512, 1) void k_attn_bwd(BwdTokensArgs p) {

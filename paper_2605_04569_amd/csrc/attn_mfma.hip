@@ -276,10 +276,9 @@ __device__ __forceinline__ uint4 halves_of_two_groups(uint2 a, uint2 b) {
 
 // merge.wgs workgroups from merge.first on merge the cut items of the launch before, each 8 rows, or 4 x 8 of them beyond one and a half
 // rounds of workgroups (only two of this kernel fit a compute unit; but one head of 60 blocks has 8 items in 32 ranges each, whose rows' waits
-// one after the other took 20 us: whole call 105 / 75; 3 heads of 72 blocks 91 / 80).  They come first, unless they fill a place of every compute unit: behind
-// the attention items their waits were the end of the launch (40 heads of 56 blocks 415 / 402 us; 8 heads of 60 blocks, 512 of
-// them, 134 last / 138 first).  Measured, two launches / one: 12 heads of 1564 tokens 8.5 + 14.3 / 18.0 us, the call at the paper's ratios over
-// 65 520 tokens 21.64 / 21.53 ms (of which the workgroups that used to be launched for exact-branch blocks are a part).
+// one after the other took 20 us: whole call 105 / 75; 3 heads of 72 blocks 91 / 80).  They come first, unless they fill a place of every
+// compute unit: behind the attention items their waits were the end of the launch (40 heads of 56 blocks 415 / 402 us; 8 heads of 60
+// blocks, 512 of them, 134 last / 138 first).  Measured, two launches / one: 12 heads of 1564 tokens 8.5 + 14.3 / 18.0 us; long calls alike.
 constexpr int MERGE_ROWS = 4;
 struct MergeWgs { int first, wgs, rows; };
 __global__ __launch_bounds__(256, 2) void k_attn_mfma(MfmaArgs a, MergeWgs merge) {
