@@ -51,7 +51,7 @@ static_assert(ISA_MAX_BATCH <= 8, "four bits a batch item");
 __host__ __device__ __forceinline__ int nibble(uint32_t x, int b) { return (x >> (4 * b)) & 15; }
 
 // Work items of `rows` rows of n blocks: two blocks of 64 rows make one of 128, a block of 128 two of 64.
-__host__ __device__ __forceinline__ int slots_of(int block, int n, int rows) { return block >= rows ? n * (block / rows) : (n + 1) / 2; }
+__host__ __device__ __forceinline__ int slots_of(int block, int n, int rows) { return block > rows ? 2 * n : block == rows ? n : (n + 1) / 2; }
 
 struct GenArgs {
   AttnArgs a;
@@ -61,7 +61,7 @@ struct GenArgs {
   // all of them, with the most items of any, an XCD could get nothing but short ones.  With parts by each one's own list (both, whole
   // calls; before: as many parts as the shortest list can have, or none): bf16, D = 128, blocks of 64, 8 heads of 6000 and 1500 tokens
   // 298 / 144 us, of 5000 and 100 253 / 113, D = 64, 2 heads of 15 600 and 64 297 / 114; fp32, dense, D = 128, 2 heads of 6000 and 1500 737 / 524.
-  int ragged; uint32_t by_length;
+  int ragged; uint32_t by_length, long_items[ISA_MAX_BATCH], taylor_items[ISA_MAX_BATCH];       // items in that order, at most 65535 x 8192
   // A long item of batch item b runs as own_parts(b) workgroups (at most `parts`), each over its share of the listed blocks; if that is more
   // than one, they leave [first_part[b] + item of b * own_parts(b) + part][row][D] their normalised results and {maximum, sum} of the row
   int parts; uint32_t own_parts;
@@ -689,21 +689,27 @@ __global__ __launch_bounds__(256 * NG, (RESIDENT<D, QT>)) void k_attn_gen(GenArg
     bhid = head_at(idx / slots, n_bh);
     slot = idx % slots;
   } else {
-    for (int i = 0; i < 2 * ga.a.geo.B; ++i) {
-      const int b = nibble(ga.by_length, i % ga.a.geo.B), slots = slots_of(ga.a.geo.block, ga.a.dense ? i < ga.a.geo.B ? ga.a.cnt.b[b].T : 0 : i < ga.a.geo.B ? ga.a.cnt.b[b].n_full : ga.a.cnt.b[b].n_flat, 64 * QT);
-      const int parts = PARTS && i < ga.a.geo.B ? nibble(ga.own_parts, b) : 1;
-      const long long total = (long long)ga.a.geo.H * slots;
-      const int first = xcd_first(total, xcd), n = xcd_first(total, xcd + 1) - first;
-      if (j < n * parts) {
-        taylor = i >= ga.a.geo.B;
-        part = parts > 1 ? j / n : -1;
-        bhid = b * ga.a.geo.H + head_at((first + j % n) / slots, ga.a.geo.H);
-        slot = (first + j % n) % slots;
-        break;
-      }
-      j -= n * parts;
+    uint32_t first = 0, n = 0;
+    int found = -1, parts = 1;
+#pragma unroll
+    for (int i = 0; i < 2 * ISA_MAX_BATCH; ++i) {      // unrolled: the arguments are loaded together
+      const int k = i % ISA_MAX_BATCH;
+      const uint32_t total = i < ISA_MAX_BATCH ? ga.long_items[k] : ga.taylor_items[k];
+      if (found >= 0) continue;
+      first = total * xcd >> 3;                        // x 8 is below 2^32
+      n = (total * (xcd + 1) >> 3) - first;
+      parts = PARTS && i < ISA_MAX_BATCH ? nibble(ga.own_parts, nibble(ga.by_length, k)) : 1;
+      if (j < (int)n * parts) found = i;
+      else j -= (int)n * parts;
     }
-    if (bhid < 0) return;
+    if (found < 0) return;
+    taylor = found >= ISA_MAX_BATCH;
+    const int b = nibble(ga.by_length, found % ISA_MAX_BATCH);
+    const int slots = slots_of(ga.a.geo.block, ga.a.dense ? ga.a.cnt.b[b].T : taylor ? ga.a.cnt.b[b].n_flat : ga.a.cnt.b[b].n_full, 64 * QT);
+    part = parts > 1 ? j / (int)n : -1;
+    const int item = (int)first + j % (int)n;
+    bhid = b * ga.a.geo.H + head_at(item / slots, ga.a.geo.H);
+    slot = item % slots;
   }
   bhid = __builtin_amdgcn_readfirstlane(bhid);
   slot = __builtin_amdgcn_readfirstlane(slot);
@@ -918,10 +924,14 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
       int at = b;
       for (; at > 0 && (a.dense ? pr.cnt.b[order[at - 1]].T < c.T : pr.cnt.b[order[at - 1]].T_new < c.T_new); --at) order[at] = order[at - 1];
       order[at] = b;
-      wgs += (int)(((long long)pr.p.H * slots_of(pr.p.block, a.dense ? c.T : c.n_full, rows) + N_XCD - 1) / N_XCD) * nibble(ga.own_parts, b) +
-             (int)(((long long)pr.p.H * (a.dense ? 0 : slots_of(pr.p.block, c.n_flat, rows)) + N_XCD - 1) / N_XCD);
     }
-    for (int i = 0; i < pr.p.B; ++i) ga.by_length |= (uint32_t)order[i] << (4 * i);
+    for (int i = 0; i < pr.p.B; ++i) {
+      const BatchCounts& c = pr.cnt.b[order[i]];
+      ga.by_length |= (uint32_t)order[i] << (4 * i);
+      ga.long_items[i] = (uint32_t)pr.p.H * slots_of(pr.p.block, a.dense ? c.T : c.n_full, rows);
+      ga.taylor_items[i] = a.dense ? 0u : (uint32_t)pr.p.H * slots_of(pr.p.block, c.n_flat, rows);
+      wgs += (int)((ga.long_items[i] + N_XCD - 1) / N_XCD) * nibble(ga.own_parts, order[i]) + (int)((ga.taylor_items[i] + N_XCD - 1) / N_XCD);
+    }
   }
   if (ga.slots_long == 0) ga.slots_long = 1;           // divisors in the kernel; a branch without work gets no workgroups
   if (ga.slots_taylor == 0) ga.slots_taylor = 1;
