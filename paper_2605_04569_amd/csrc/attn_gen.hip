@@ -3,7 +3,11 @@
 // Part A), block-wise 0-th order Taylor attention with and without exact sets (Sec. 3, Eq. 3-4; Alg. 2 Parts A+B), dense.
 //
 // Precision: everything that a plain fp32 evaluation holds in fp32 keeps its 24 bits here.
-//   fp32 tensors: both products with v_mfma_f32_16x16x4_f32.
+//   fp32 tensors: queries, keys, values, means and weights are cut into three bf16 terms of 8 bits each whose sum is the number, and a
+//     product is the sum of six products of terms (v_mfma_f32_16x16x32_bf16; middle x low and low x low, below 2^-22 of it, are left
+//     out).  An item with a number whose terms have lost bits (below about 2^-110) is run again with v_mfma_f32_16x16x4_f32.  Error against 64
+//     bits on fp32 matrix instructions / in terms, 2-norm: 8 heads of 5280 tokens 5.8e-7 / 3.7e-7, dense 2.5e-6 / 2.1e-6, 24 heads of 15 600
+//     4.7e-6 / 4.1e-6, D = 64 4.6e-6 / 4.0e-6 (an instruction adds 32 products where one on fp32 adds 4).
 //   bf16 tensors: scores of tokens with v_mfma_f32_16x16x32_bf16 (products of bf16 numbers are exact in fp32); the softmax
 //     weights and the fp32 block means are cut into three bf16 terms whose sum is the fp32 number (8 bits each), and
 //     the product is the sum of the terms' products: 3 matrix instructions for weights x tokens, 3 for queries x means, 8
@@ -13,9 +17,10 @@
 // that 128 a workgroup would leave compute units idle).  With r = lane % 16, g = lane / 16 the scores are computed
 // transposed (S^T = K Q^T): lane (r, g) holds keys 16 kt + 4 g + i of query 16 qt + r, which is the operand layout of the
 // second product (O^T = V^T P^T), so the weights never leave their registers; V is read transposed out of its row-major
-// tile (ds_read_b64_tr_b16 for bf16; for fp32 a lane's four channels of a row serve four output tiles).  Tiles of 64
+// tile (ds_read_b64_tr_b16; on fp32 matrix instructions a lane's four channels of a row serve four output tiles).  Tiles of 64
 // bf16 (32 fp32) rows go global -> LDS directly, one tile ahead, two stages, 16-byte chunks XOR-swizzled by row.  A stage
-// is 256 D bytes either way.  A launch with few long items cuts their key lists into parts, a workgroup each, and a second kernel adds
+// is 256 D bytes either way.  An fp32 tile is taken apart once per workgroup, from its one raw place into the place of the terms, which
+// keys and values share (a wave takes apart what it has fetched itself); the raw place is filled again at once.  A launch with few long items cuts their key lists into parts, a workgroup each, and a second kernel adds
 // them up, or gives a workgroup two groups of 4 waves that take the tiles in turn (NG = 2).  Groups that share a compute unit, whose softmax
 // runs beside each other's matrix instructions (there is no hand-made interleaving here): D = 128, 66 KB each, two; D = 64, 33 KB, three of
 // QT = 2 (registers) or four of QT = 1.
@@ -24,7 +29,11 @@
 // costs 9.4 vector instructions (5.5 of them the exact cut into three terms; taking the differences with the bf16 dot
 // instruction was slower and not exact) beside 2 matrix instructions; counters of that launch: vector and matrix instructions issuing
 // in 95 % of the cycles, matrix pipe busy 42 %, no LDS bank conflicts.  Whole call 11.6 -> 0.73 ms against a kernel of one
-// row per four lanes in scalar arithmetic (25 -> 400 TFLOP/s); fp32, 8 heads of 128 channels, 5280 tokens: 1.89 -> 0.39 ms.
+// row per four lanes in scalar arithmetic (25 -> 400 TFLOP/s).
+//
+// fp32 is bound by bf16 matrix instructions: six in place of eight fp32 ones that take twice as long each: 24 heads of 128 channels,
+// 15 600 tokens, 5.6 -> 3.2 ms a call (1.1 PFLOP/s of bf16 products), 64 channels in blocks of 64 2.97 -> 1.53 ms; 8 heads of 5280 tokens
+// 301 -> 190 us.  With 16 rows a wave the LDS reads take as long as the products, with 32 half of that.
 #include <math.h>
 
 #include <type_traits>
@@ -34,6 +43,8 @@
 namespace isa {
 
 #define ISA_GEN_FENCE() __builtin_amdgcn_sched_barrier(0)
+// a barrier of the workgroup that leaves global loads in flight
+#define ISA_GEN_BARRIER() asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
 
 namespace {
 
@@ -60,7 +71,7 @@ struct GenArgs {
   // Batch items that differ: an XCD has an equal range of every one's own items, longest key lists first (by_length), as in the heads' order of
   // all of them, with the most items of any, an XCD could get nothing but short ones.  With parts by each one's own list (both, whole
   // calls; before: as many parts as the shortest list can have, or none): bf16, D = 128, blocks of 64, 8 heads of 6000 and 1500 tokens
-  // 298 / 144 us, of 5000 and 100 253 / 113, D = 64, 2 heads of 15 600 and 64 297 / 114; fp32, dense, D = 128, 2 heads of 6000 and 1500 737 / 524.
+  // 298 / 144 us, of 5000 and 100 253 / 113, D = 64, 2 heads of 15 600 and 64 297 / 114.
   int ragged; uint32_t by_length, long_items[ISA_MAX_BATCH], taylor_items[ISA_MAX_BATCH];       // items in that order, at most 65535 x 8192
   // A long item of batch item b runs as own_parts(b) workgroups (at most `parts`), each over its share of the listed blocks; if that is more
   // than one, they leave [first_part[b] + item of b * own_parts(b) + part][row][D] their normalised results and {maximum, sum} of the row
@@ -84,9 +95,11 @@ __device__ __forceinline__ f32x4 mfma_f(float a, float b, f32x4 c) {
 __device__ __forceinline__ float bits_f(uint32_t u) { return __uint_as_float(u); }
 
 // Eight fp32 numbers as three bf16 fragments that add up to them: every term is the leading 8 bits of what the terms before it
-// left over (cut off, not rounded, so the differences are exact and the third term ends at bit 24).
-__device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
-  uint32_t w[3][4];
+// left over (cut off, not rounded, so the differences are exact and the third term ends at bit 24).  Returns a word whose low half is 0
+// unless a number is so small that its third term has lost bits.
+__device__ __forceinline__ uint32_t split3(const float (&x)[8], bf16x8 (&t)[3]) {
+#pragma clang fp contract(off)                         // of the numbers as they are, not of a product they come from
+  uint32_t w[3][4], rest = 0;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     float a = x[2 * e], b = x[2 * e + 1];
@@ -97,19 +110,22 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
       if (k < 2) {
         a -= bits_f(ua & 0xffff0000u);
         b -= bits_f(ub & 0xffff0000u);
+      } else {
+        rest |= ua | ub;
       }
     }
   }
 #pragma unroll
   for (int k = 0; k < 3; ++k) t[k] = __builtin_bit_cast(bf16x8, make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]));
+  return rest;
 }
 
 }  // namespace
 
 // One work item: 64 QT rows of one query block (QT = 2, block 64: of two neighbours in the list).  FULL32 is the second pass over an item:
-// for bf16 tensors it evaluates the products of fp32 numbers with fp32 matrix instructions instead of bf16 terms, slower, but infinities go
+// it evaluates the products of fp32 numbers with fp32 matrix instructions instead of bf16 terms, slower, but infinities go
 // through them as through a multiplication (a term that is zero turns an infinity into NaN).  Returns whether this wave's results are
-// all finite and its maxima in the range of the fast weights; with FULL32 = false nothing is stored if some wave's are not, and the
+// all finite, its maxima in the range of the fast weights and its terms complete; with FULL32 = false nothing is stored if some wave's are not, and the
 // caller runs the item again.
 //
 // A weight is exp2 of the scaled score minus the scaled running maximum.  The fast form of bf16 tensors is one fma, whose
@@ -120,8 +136,8 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 // are multiplied by the scale when they are loaded), the second pass over bf16 rows multiplies the difference.
 //
 // The first pass raises a maximum only when a weight would exceed 2^tau, the second at every larger score: its weights are at most 1, where
-// 2^tau times a value near the largest number is none.  (Raising at once in the first pass cost fp32 1 % with 128 channels, 2.5 with
-// 64; a factor of 2^-tau in its weights cost values near the smallest normal number their last eight bits.)
+// 2^tau times a value near the largest number is none.  (A factor of 2^-tau in the first pass's weights cost values near the
+// smallest normal number their last eight bits.)
 //
 // NG = 2: two groups of 4 waves work on the same rows, each with stages of its own, and take the tiles of the sequence in turn;
 // the second group hands its running maxima, sums and outputs to the first through LDS at the end.
@@ -129,11 +145,13 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8 (&t)[3]) {
 template <typename T, int D, int QT, bool FULL32, int QI, bool PARTS, int NG>
 __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* const lds_all, int bhid, bool taylor, int slot, const int part, const int first_part) {
   constexpr bool BF = sizeof(T) == 2, WIDE = !BF || FULL32;
+  constexpr bool FM = !BF && FULL32, TERMS = !BF && !FULL32;           // fp32 tensors: on fp32 matrix instructions / in bf16 terms
   constexpr int KTOK = BF ? 64 : 32;                   // tokens per tile; tiles of means hold 32
   constexpr int NT = D / 16;                           // 16-channel tiles
   constexpr int TILE = 128 * D;                        // bytes of a K (or V) tile, token or mean
   constexpr int CT = D * (int)sizeof(T) / 16, CM = D / 4;      // 16-byte chunks per row of token / mean tiles
   constexpr int ST = (CT < 16 ? CT : 16) - 1, SM = 15; // swizzle: chunk c of row r sits at c ^ (r & S)
+  constexpr int CP = D / 8, SP = CP - 1, PLANE = 64 * D;       // 16-byte chunks per row, swizzle and bytes of a tile's terms of one kind
   constexpr int NI = D / 32;                           // 1 KB loads per wave, tile and tensor
   constexpr int ROWS = 64 * QT;
   const int grp = NG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
@@ -179,9 +197,11 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   };
 
   const float cscale = 1.4426950408889634f / sqrtf((float)D);
-  // Q fragments: bf16 lane (r, g) holds channels 32 ks + 8 g .. + 7 of query 16 qt + r, fp32 (scaled) channels 16 t + 4 g .. + 3
+  // Q fragments: bf16 lane (r, g) holds channels 32 ks + 8 g .. + 7 of query 16 qt + r, fp32 (scaled) channels 16 t + 4 g .. + 3 or, in terms, as bf16
   bf16x8 qb[QT][D / 32];
   f32x4 qf[QT][NT];
+  bf16x8 q3[QT][D / 32][3];                            // TERMS: of the scaled queries, channels as in qb
+  uint32_t cut_off = 0;                                // TERMS: bits that some number's terms have lost
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     const int row = row0 + 16 * qt + r16;
@@ -189,6 +209,18 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     if constexpr (BF) {
 #pragma unroll
       for (int ks = 0; ks < D / 32; ++ks) qb[qt][ks] = *reinterpret_cast<const bf16x8*>(qp + 32 * ks + 8 * g);
+    } else if constexpr (TERMS) {
+#pragma unroll
+      for (int ks = 0; ks < D / 32; ++ks) {
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const f32x4 y = *reinterpret_cast<const f32x4*>(qp + 32 * ks + 8 * g + 4 * u) * cscale;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x[4 * u + i] = y[i];
+        }
+        cut_off |= split3(x, q3[qt][ks]);
+      }
     } else {
 #pragma unroll
       for (int t = 0; t < NT; ++t) qf[qt][t] = *reinterpret_cast<const f32x4*>(qp + 16 * t + 4 * g) * cscale;
@@ -238,6 +270,32 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     at.bits = 3;
     if (at.nk <= 0) at.end = true;
   };
+  // TERMS: one tensor (v or k) of tile t to its place.  16-byte piece u of eight-channel chunk p at (u * 4 D + p) * 16: a lane takes
+  // the same chunks apart again that it has fetched
+  auto issue_terms = [&](const Tile& t, const auto mean_c, const bool value) {
+    constexpr bool mean = decltype(mean_c)::value;
+    int li = lane;
+    asm volatile("" : "+v"(li));
+#pragma unroll
+    for (int i = 0; i < D / 64; ++i) {
+      const int p = wave * D + i * 64 + li, row = min(p / CP, t.nk - 1), ch = p % CP * 8;
+      const float* src;
+      if constexpr (!mean) src = (const float*)(value ? a.v : a.k) + tbase + (long long)(t.start + row) * a.geo.stride_t + ch;
+      else src = (value ? a.vc : a.kc) + (bh * T_max + block_in_range(kvl[t.start + row], c.T)) * D + ch;
+      const uint32_t dst = lds_addr(lds) + (value ? TILE : 0) + (wave * D + i * 64) * 16;
+      dma16(src, dst);
+      dma16(src + 4, dst + TILE / 2);
+    }
+  };
+  // the weights of a mean tile's slots: slot tid % 32 as block tid / 32 of the item sees it: n_j, or 0
+  auto mean_weights = [&](const Tile& t, int stage) {
+    if (tid < 64) {
+      const int s = t.start + (tid & 31);
+      float w = 0.f;
+      if ((tid & 31) < t.nk && !(sets && ((set_bits(s) >> (tid >> 5)) & 1))) w = (float)bn[block_in_range(kvl[s], c.T)];
+      wts[stage * 64 + tid] = w;
+    }
+  };
   auto issue = [&](const Tile& t, int stage) {
     unsigned char* const kdst = lds + stage * 2 * TILE;
     int li = lane;
@@ -261,16 +319,11 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         dma16(a.kc + off, dst);
         dma16(a.vc + off, dst + TILE);
       }
-      if (tid < 64) {                                  // slot tid % 32 as block tid / 32 of the item sees it: n_j, or 0
-        const int s = t.start + (tid & 31);
-        float w = 0.f;
-        if ((tid & 31) < t.nk && !(sets && ((set_bits(s) >> (tid >> 5)) & 1))) w = (float)bn[block_in_range(kvl[s], c.T)];
-        wts[stage * 64 + tid] = w;
-      }
+      mean_weights(t, stage);
     }
   };
 
-  f32x4 acc[NT][QT];                                   // element i: bf16: channel 16 ct + 4 g + i; fp32: see the store
+  f32x4 acc[NT][QT];                                   // element i: channel 16 ct + 4 g + i; on fp32 matrix instructions: see the store
   constexpr float NONE = WIDE ? INFINITY : -M_INIT;    // minus the maximum of no score
   float neg_m[QT], l_run[QT];                          // minus the running maximum (log2 domain; WIDE bf16: as the score is); sums per lane
   // what is added to a score before its weight is formed: while a WIDE row has seen nothing but masked slots, 0, so that their
@@ -285,20 +338,52 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   }
   auto factor = [&](float diff) { return __builtin_amdgcn_exp2f(WIDE && BF ? diff * cscale : diff); };      // between two maxima, from their difference
 
-  // ---- a half tile: 32 keys from row `r0` of the stage; `nk` of them real; wt: weights of a mean tile's 32 slots
-  auto half = [&](const unsigned char* kb, const unsigned char* vb, const int r0, const int nk, const auto mean_c, const float* wt)
+  // ---- a half tile: 32 keys from row `r0` of the stage; `nk` of them real; wt: weights of a mean tile's 32 slots.  TERMS: kb and vb are the
+  // same place, filled with the terms of the keys and, while `between` runs, with those of the values
+  auto half = [&](const unsigned char* kb, const unsigned char* vb, const int r0, const int nk, const auto mean_c, const float* wt, const auto between)
       __attribute__((always_inline)) {
     constexpr bool mean = decltype(mean_c)::value;
     // the lane's coordinates for the reads of mean tiles: opaque, so that their many LDS addresses are worked out where they
     // are used instead of being kept in registers through the loop
     int rm = r16, gm = g;
-    if (BF) asm volatile("" : "+v"(rm), "+v"(gm));
+    if (BF || TERMS) asm volatile("" : "+v"(rm), "+v"(gm));
     f32x4 s[2][QT];
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) s[kt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (!BF) {
+    if constexpr (TERMS) {
+      f32x4 small[2][QT];                              // all products but high x high
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) small[kt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < D / 32; ++ks) {
+        ISA_GEN_FENCE();
+        bf16x8 k3[2][3];
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+          for (int u = 0; u < 3; ++u)
+            k3[kt][u] = *reinterpret_cast<const bf16x8*>(kb + u * PLANE + ((16 * kt + rm) * CP + ((4 * ks + gm) ^ (rm & SP))) * 16);
+#pragma unroll
+        for (int u = 2; u >= 0; --u)                   // the smallest first; terms below 2^-22 of a product are left out
+#pragma unroll
+          for (int w = 2 - u; w >= 0; --w)
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+              for (int qt = 0; qt < QT; ++qt) {
+                f32x4& to = u + w > 0 ? small[kt][qt] : s[kt][qt];
+                to = mfma_bf(k3[kt][u], q3[qt][ks][w], to);
+              }
+      }
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) s[kt][qt] += small[kt][qt];
+    } else if constexpr (FM) {
       f32x4 k4[2][2];                                  // [t % 2][kt]: the fragments of a step are read a step ahead
       auto k_load = [&](int t) {
 #pragma unroll
@@ -308,8 +393,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       k_load(0);
       // every other group of four channels adds up here, in two chains of half the length.  Error against 64 bits of dense attention over
       // 1000 / 5280 tokens with one chain and with two, 128 channels: 1.15e-6 / 2.31e-6, 7.4e-7 / 1.99e-6 (four partial sums in scalar
-      // arithmetic: 1.08e-6 / 5.87e-6), 64 channels 9.0e-7 / 1.47e-6, 6.3e-7 / 1.26e-6; clip of 8 heads of 128 channels 388 / 389 us, 24
-      // heads of 64 404 / 407
+      // arithmetic: 1.08e-6 / 5.87e-6), 64 channels 9.0e-7 / 1.47e-6, 6.3e-7 / 1.26e-6
       f32x4 s_odd[2][QT];
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
@@ -440,7 +524,41 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 #pragma unroll
       for (int e = 0; e < 8; ++e) l_run[qt] += p[qt][e];
     // O^T += V^T P^T
-    if constexpr (!BF) {
+    if constexpr (TERMS) {
+      bf16x8 p3[QT][3];
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        split3(p[qt], p3[qt]);
+        asm volatile("" : "+v"(p3[qt][0]), "+v"(p3[qt][1]), "+v"(p3[qt][2]), "+v"(l_run[qt]));      // before the barriers, not where they are used
+      }
+      ISA_GEN_FENCE();
+      between();
+      asm volatile("" : "+v"(rm), "+v"(gm));
+      const int tr_row = 4 * gm + (rm >> 2);
+      constexpr int GR = 2;                            // (one at a time 4 % slower, four alike)
+#pragma unroll
+      for (int c0 = 0; c0 < NT; c0 += GR) {
+        ISA_GEN_FENCE();
+        bf16x8 v3[GR][3];
+#pragma unroll
+        for (int n = 0; n < GR; ++n)
+#pragma unroll
+          for (int u = 0; u < 3; ++u) {
+            const unsigned char* src = vb + u * PLANE + (tr_row * CP + ((2 * (c0 + n) + ((rm & 3) >> 1)) ^ (tr_row & SP))) * 16 + (rm & 1) * 8;
+            const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src));
+            const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src + 16 * CP * 16));
+            v3[n][u] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+          }
+#pragma unroll
+        for (int u = 2; u >= 0; --u)
+#pragma unroll
+          for (int w = 2 - u; w >= 0; --w)
+#pragma unroll
+            for (int n = 0; n < GR; ++n)
+#pragma unroll
+              for (int qt = 0; qt < QT; ++qt) acc[c0 + n][qt] = mfma_bf(v3[n][u], p3[qt][w], acc[c0 + n][qt]);
+      }
+    } else if constexpr (FM) {
       f32x4 v4[2][NT / 4];                             // tiles 4 u + e: output row m is channel 64 u + 4 m + e
       auto v_load = [&](int n) {                       // key slot 16 kt + 4 g + i, n = 4 kt + i
         const int row = 4 * (n & 4) + 4 * g + (n & 3);
@@ -544,10 +662,71 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     return mine;
   };
   Tile cur = next_mine();
-  if (!cur.end) issue(cur, 0);
   int stage = 0;
+  if (!TERMS && !cur.end) issue(cur, 0);
+  // TERMS: this wave's share of a tile of keys or values, which it has fetched itself, taken apart into the common place
+  auto take_apart = [&](const bool value) {
+    const unsigned char* const src = lds + (value ? TILE : 0);
+    int li = lane;
+    asm volatile("" : "+v"(li));
+#pragma unroll
+    for (int i = 0; i < D / 64; ++i) {
+      ISA_GEN_FENCE();
+      const int p = wave * D + i * 64 + li, row = p / CP;
+      float x[8];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const f32x4 y = *reinterpret_cast<const f32x4*>(src + u * (TILE / 2) + p * 16);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[4 * u + e] = y[e];
+      }
+      bf16x8 t[3];
+      cut_off |= split3(x, t);
+      asm volatile("" : "+v"(cut_off));                // here, not where it is read
+#pragma unroll
+      for (int u = 0; u < 3; ++u) *reinterpret_cast<bf16x8*>(lds + 2 * TILE + u * PLANE + (row * CP + ((p % CP) ^ (row & SP))) * 16) = t[u];
+    }
+  };
   auto tiles = [&](const auto mean_c) __attribute__((always_inline)) {
     constexpr bool mean = decltype(mean_c)::value;
+    if constexpr (TERMS) {
+      // The keys' raw tile, then the values', become terms in one place; each raw place is filled again as soon as its wave has read it
+      // (with the same tile where there is no next one: with branches around the loads, and tiles of both kinds in one loop, the compiler
+      // keeps the accumulators twice and spills 80 registers).  Loads end in order: when no more than one tensor's are in flight,
+      // those of the tensor before it are there.
+      if (cur.end || cur.mean != mean) return;
+      if (mean) mean_weights(cur, stage);
+      issue_terms(cur, mean_c, false);
+      issue_terms(cur, mean_c, true);
+      for (bool more = true; more; stage ^= 1) {
+        const Tile nxt = next_mine();
+        more = !nxt.end && nxt.mean == mean;
+        const Tile load = more ? nxt : cur;
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NI) : "memory");
+        ISA_GEN_BARRIER();                             // everybody has left the values of the tile before
+        take_apart(false);
+        if (mean) mean_weights(load, stage ^ 1);
+        issue_terms(load, mean_c, false);
+        ISA_GEN_BARRIER();
+        __builtin_amdgcn_s_setprio(1);
+        auto values = [&]() __attribute__((always_inline)) {
+          asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NI) : "memory");
+          ISA_GEN_BARRIER();                           // everybody has left the keys
+          __builtin_amdgcn_s_setprio(0);
+          take_apart(true);
+          issue_terms(load, mean_c, true);
+          ISA_GEN_BARRIER();
+          __builtin_amdgcn_s_setprio(1);
+        };
+        // a tile of the other block's exact set has no keys for this wave
+        half(lds + 2 * TILE, lds + 2 * TILE, 0, (cur.bits >> own) & 1 ? cur.nk : 0, mean_c, wts + stage * 64 + own * 32, values);
+        __builtin_amdgcn_s_setprio(0);
+        cur = nxt;
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      ISA_GEN_BARRIER();                               // everybody has left the weights of the last tile
+      return;
+    }
     for (; !cur.end && cur.mean == mean; stage ^= 1) {
       const Tile nxt = next_mine();                    // its table reads wait together with the tile loads
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -556,7 +735,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       const unsigned char* kb = lds + stage * 2 * TILE;
       if ((cur.bits >> own) & 1) {                     // wave-uniform
 #pragma unroll 1
-        for (int r0 = 0; r0 < cur.nk; r0 += 32) half(kb, kb + TILE, r0, cur.nk - r0, mean_c, wts + stage * 64 + own * 32);
+        for (int r0 = 0; r0 < cur.nk; r0 += 32) half(kb, kb + TILE, r0, cur.nk - r0, mean_c, wts + stage * 64 + own * 32, [] {});
       }
       cur = nxt;
       ++n_mine;
@@ -603,7 +782,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 
   // ---- normalise, check, store
   float inv[QT];
-  bool ok = true;
+  bool ok = !TERMS || (cut_off & 0xffffu) == 0;
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     float l = l_run[qt];
@@ -634,8 +813,8 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       for (int n = 0; n < NT; ++n) {
         f32x4 r;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = (BF ? acc[n][qt][i] : acc[4 * (n >> 2) + i][qt][n & 3]) * inv[qt];
-        *reinterpret_cast<f32x4*>(ga.part_o + row * D + (BF ? 16 * n + 4 * g : 64 * (n >> 2) + 16 * g + 4 * (n & 3))) = r;
+        for (int i = 0; i < 4; ++i) r[i] = (FM ? acc[4 * (n >> 2) + i][qt][n & 3] : acc[n][qt][i]) * inv[qt];
+        *reinterpret_cast<f32x4*>(ga.part_o + row * D + (FM ? 64 * (n >> 2) + 16 * g + 4 * (n & 3) : 16 * n + 4 * g)) = r;
       }
       if (g == 0) ga.part_ml[row] = make_float2(-neg_m[qt], WIDE && BF ? -l : l);
     }
@@ -651,10 +830,10 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 #pragma unroll
     for (int n = 0; n < NT; ++n) {                     // four consecutive channels at a time
       float r[4];
-      const int ch = BF ? 16 * n + 4 * g : 64 * (n >> 2) + 16 * g + 4 * (n & 3);
+      const int ch = FM ? 64 * (n >> 2) + 16 * g + 4 * (n & 3) : 16 * n + 4 * g;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        r[i] = (BF ? acc[n][qt][i] : acc[4 * (n >> 2) + i][qt][n & 3]) * inv[qt];
+        r[i] = (FM ? acc[4 * (n >> 2) + i][qt][n & 3] : acc[n][qt][i]) * inv[qt];
         if (oc) r[i] = fmaf(a.gamma, oc[ch + i], r[i]);
       }
       if constexpr (BF) {
@@ -837,25 +1016,24 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
   const bool d64 = pr.p.D == 64, bf = pr.p.dtype == ISA_BF16;
   const double chip = (double)N_XCD * cus_per_xcd();
   auto items = [&](int n, int rows) { return bh * (pr.p.block >= rows ? n * (pr.p.block / rows) : (n + 1) / 2); };
-  // The form of a workgroup (64 rows; bf16 also 128, which read every LDS fragment once for two query tiles, or 64 in two groups of waves; an
-  // fp32 fragment feeds four times as many matrix instructions of twice the length, and neither ever won) and the parts per long item,
+  // The form of a workgroup (64 rows; 128, which read every LDS fragment once for two query tiles; bf16 also 64 in two groups of waves) and the parts per long item,
   // chosen together by a model of the call's time: with k workgroups per compute unit a block of 64 tokens takes each of them pace[k - 1]
   // us (k beyond what fits a compute unit: further rounds), and a workgroup spends `start` tokens' time on its start.  The merge of partial
   // results is `merge` us more, and they are written and read at `rate` TB/s.  A Taylor item counts for `taylor` of a long one of the same
   // rows, plus its exact set's share (x `shared` in two groups); Taylor items fill what the long ones leave idle, so the time is that of the
   // long items' rounds or that of all items with the chip full, whichever is longer; not so beside two groups, which leave little idle.  A bf16
-  // part has at least 256 tokens, an fp32 one may be a single block (1 head, 300 tokens: 54 whole, 44 in parts).
-  // The numbers are fitted to 1094 calls (1 to 40 heads, 300 to 15 600 tokens, dense and sparse, ragged batches) with every form and number of
-  // parts measured: the choice costs 1.0 to 1.3 % more than the best one on the geometric average.  Measured, whole calls, us, keep 0.5, full 0.25, whole
+  // part has at least 256 tokens, an fp32 one may be a single block (D = 128, 1 head, 300 tokens: 46 whole, 35 in parts).
+  // The numbers are fitted to 1094 calls (1 to 40 heads, 300 to 15 600 tokens, dense and sparse, ragged batches; fp32 to 522) with every form and number of
+  // parts measured: the choice costs 0.7 to 1.3 % more than the best one on the geometric average.  Measured, whole calls, us, keep 0.5, full 0.25, whole
   // items of 128 rows / of 64 / in two groups / as chosen: bf16, 15 600 tokens, blocks of 64: D = 64, 1 head 387 / 281 / 231 / 88, 4 heads 404 / 302 /
   // 240 / 175, 8 417 / 342 / 347 / 299, 12 505 / 469 / 490 / 402, 16 531 / 581 / 641 / 531; D = 128: 2 heads 555 / 393 / 317 / 174, 4 562 / 402 / 392 / 282, 8
   // 582 / 554 / 749 / 478, 12 756 / 812 / 1085 / 756 (the partial results have no room), 16 862 / 1051 / 1473 / 860; dense, 1980 tokens, 8 heads: D = 64
-  // 65 / 50 / 40 / 40, D = 128 93 / 67 / 54 / 54.  fp32, 64 rows / as chosen: 4800 tokens, D = 128, 4 heads 355 / 151, 12 365 / 333, D = 64, 4 heads 226 / 98.
+  // 65 / 50 / 40 / 40, D = 128 93 / 67 / 54 / 54.  fp32, 64 rows / 128 / as chosen: 4800 tokens, D = 128, 4 heads 341 / 434 / 109, 12 351 / 448 / 192, D = 64, 4 heads 213 / 269 / 75.
   struct Form { int rows, groups, resident; double pace[4], start; };
   struct Kind { double taylor, shared, merge, rate; Form form[3]; };
   static const Kind kinds[2][2] = {                    // [bf16][D = 64]
-      {{.012, 1, 6.3, 4.0, {{64, 1, 2, {6.4, 11.0}, 65}}},
-       {.007, 1, 4.7, 3.8, {{64, 1, 4, {3.25, 5.3, 7.3, 9.25}, 25}}}},
+      {{.0086, 1, 6.3, 4.7, {{64, 1, 2, {4.1, 4.8}, 40}, {128, 1, 2, {5.13, 6.52}, 30}}},
+       {.013, 1, 3.7, 4.3, {{64, 1, 4, {2.15, 2.6, 3.04, 4.75}, 16}, {128, 1, 3, {3.15, 3.27, 5.25}, 14.5}}}},
       {{.075, 1.4, 6.0, 5.4, {{64, 1, 2, {1.63, 2.52}, 185}, {128, 1, 2, {2.67, 3.87}, 180}, {64, 2, 1, {2.77}, 145}}},
        {.050, 2.0, 4.5, 4.1, {{64, 1, 4, {1.25, 1.75, 2.17, 3.03}, 320}, {128, 1, 3, {1.86, 2.91, 3.29}, 340}, {64, 2, 2, {1.97, 2.97}, 240}}}}};
   const Kind& kind = kinds[bf][d64];
@@ -866,10 +1044,12 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
     // Taylor items alone, 128 rows / 64: D = 64, 24, 4, 2 heads (2928, 488, 244 items of 128 rows) 186 / 226, 67 / 73, 61 / 58; D = 128, 24, 2 heads
     // 351 / 465, 82 / 79.  With exact sets a pair of blocks of 64 reads both blocks' sets, which Taylor items do not make up for at D = 64:
     // 24, 8 heads 435 / 396, 192 / 171 (D = 128: 797 / 814, 302 / 305).
-    two = bf && !(set_share > 0.0 && d64 && pr.p.block == 64) && items(n_taylor, 128) >= chip * (d64 ? 7 : 5) / 4;
+    // fp32: D = 128, 24 heads (2928) 430 / 524, 8 (976) 151 / 184, 24 (288) 39 / 41, 2 (244) 63 / 61; D = 64 (2928) 202 / 221, (912) 60.3 / 60.4, (304)
+    // 39.4 / 38.8; pairs with exact sets (every wave multiplies both blocks' tiles) D = 128 2424 / 1946, D = 64 1207 / 885.
+    two = !(set_share > 0.0 && (d64 || !bf) && pr.p.block == 64) && items(n_taylor, 128) >= chip * (bf ? (d64 ? 1.75 : 1.25) : d64 ? 3.5 : 1.0);
   } else {
     double best = INFINITY;
-    for (int f = 0; f < (bf ? 3 : 1); ++f) {
+    for (int f = 0; f < (bf ? 3 : 2); ++f) {
       const Form& form = kind.form[f];
       // per workgroup with the chip full; a pair of blocks of 64 reads both blocks' exact sets
       const Form& one = kind.form[form.rows == 128];
@@ -945,7 +1125,8 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
   else if (groups) hipLaunchKernelGGL((k_attn_gen<uint16_t, 128, 1, false, 2>), grid, dim3(512), 0, st, ga);
   else if (bf && d64) { if (two) ISA_GEN(uint16_t, 64, 2); else ISA_GEN(uint16_t, 64, 1); }
   else if (bf) { if (two) ISA_GEN(uint16_t, 128, 2); else ISA_GEN(uint16_t, 128, 1); }
-  else if (d64) ISA_GEN(float, 64, 1);
+  else if (d64) { if (two) ISA_GEN(float, 64, 2); else ISA_GEN(float, 64, 1); }
+  else if (two) ISA_GEN(float, 128, 2);
   else ISA_GEN(float, 128, 1);
   if (ga.parts > 1) {
     const dim3 merge((unsigned)(bh * ga.slots_long * (rows * pr.p.D / 1024)));      // (slots_long: the most of a batch item)

@@ -377,3 +377,60 @@ def test_fp32_scores_no_further_off_than_in_scalar_arithmetic(I, D, bound):
     want = np.stack([O.dense_attention(f64(q[0, h]), f64(k[0, h]), f64(v[0, h])) for h in range(H)])
     rel = np.linalg.norm(f64(out[0]) - want) / np.linalg.norm(want)
     assert rel <= bound, rel
+
+
+F32 = [x for x in SHAPES if x[0] == "f32"]
+F32_IDS = [i for i in SHAPE_IDS if i[:3] == "f32"]
+
+
+# fp32, enough heads for 128-row workgroups: odd lists of blocks (a pair with one), short blocks, exact sets of both blocks of a pair, a ragged
+# batch; with full_frac 0 Taylor blocks alone
+@pytest.mark.parametrize("full_frac,exact_frac", [(0.6, 0.0), (0.6, 0.25), (0.0, 0.0), (0.0, 0.25)])
+@pytest.mark.parametrize("shape", F32, ids=F32_IDS)
+def test_fp32_wide_workgroups(I, shape, full_frac, exact_frac):
+    block = shape[2]
+    wl = _wl(shape, 300, (1, 1, 5 * block + 40), (((1, 1, 4 * block + 9),), ((1, 1, 2 * block),)), B=2, keep_ratio=0.6, full_frac=full_frac,
+             exact_frac=exact_frac, seed=801)
+    check_end_to_end(I, wl, *gen(wl), heads=[0, 7, 150, 299])
+
+
+@pytest.mark.parametrize("full_frac", [1.0, 0.0], ids=["exact", "taylor"])
+@pytest.mark.parametrize("small", ["q", "k", "v"])
+@pytest.mark.parametrize("H", [2, 300], ids=["narrow", "wide"])
+@pytest.mark.parametrize("shape", F32, ids=F32_IDS)
+def test_fp32_numbers_whose_terms_lose_bits(I, shape, H, small, full_frac):
+    """One tensor of about 2^-114 (queries and keys beside the other at 2^114): the third bf16 term of such a number would end below 2^-133, the
+    smallest bf16 number, so it has lost bits and the item has to be run without terms.  Bound: as for numbers of about 1."""
+    wl = _wl(shape, H, (1, 10, 33), (((1, 5, 33),),), keep_ratio=1.0, full_frac=full_frac, seed=807)
+    g = torch.Generator().manual_seed(wl.seed)
+    x = {n: torch.randn((1, H, wl.tokens(0), wl.D), generator=g) for n in "qkv"}
+    scale = {"q": {"q": -114, "k": 114}, "k": {"q": 114, "k": -114}, "v": {"v": -114}}[small]
+    for n, e in scale.items():
+        x[n] = torch.ldexp(x[n], torch.tensor(e))
+    pr = problem_of(wl)
+    q, k, v = (x[n].cuda() for n in "qkv")
+    out = torch.empty_like(q)
+    I.isa_attention(pr, q, k, v, out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    for h in sorted({0, H - 1}):
+        got, want = f64(out[0, h]), O.isa_attention(f64(x["q"][0, h]), f64(x["k"][0, h]), f64(x["v"][0, h]), wl.seg_len(0), wl.block, 1.0, full_frac)[0]
+        rel = np.linalg.norm(got - want) / np.linalg.norm(want)
+        assert rel <= 30 * 2.0 ** -24, (h, rel)
+
+
+@pytest.mark.parametrize("shape", F32, ids=F32_IDS)
+def test_fp32_infinities_in_wide_workgroups(I, shape):
+    """An infinite value in the last token of a short block makes its channel infinite and leaves the others as they are without it."""
+    wl = _wl(shape, 300, (1, 1, 4 * shape[2] + 17), ((),), seed=811)
+    g = torch.Generator().manual_seed(wl.seed)
+    q, k, v = (torch.randn((1, 300, wl.tokens(0), wl.D), generator=g).cuda() for _ in range(3))
+    pr = problem_of(wl)
+    ws, outs = I.new_workspace(pr), [torch.empty_like(q) for _ in range(2)]
+    for out in outs:
+        I.isa_dense_attention(pr, q, k, v, out, ws)
+        v[:, :, -1, 3] = float("inf")
+    torch.cuda.synchronize()
+    assert torch.isposinf(outs[1][..., 3]).all()
+    others = [c for c in range(wl.D) if c != 3]
+    diff = (outs[1][..., others] - outs[0][..., others]).norm() / outs[0][..., others].norm()
+    assert diff <= 30 * 2.0 ** -24, diff
