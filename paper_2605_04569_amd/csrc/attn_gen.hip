@@ -25,11 +25,13 @@
 // runs beside each other's matrix instructions (there is no hand-made interleaving here): D = 128, 66 KB each, two; D = 64, 33 KB, three of
 // QT = 2 (registers) or four of QT = 1.
 //
-// What bounds it (measured, 24 heads of 64 channels, 15 600 tokens in blocks of 64, keep 0.5, full 0.25): instruction issue. A weight
-// costs 9.4 vector instructions (5.5 of them the exact cut into three terms; taking the differences with the bf16 dot
-// instruction was slower and not exact) beside 2 matrix instructions; counters of that launch: vector and matrix instructions issuing
-// in 95 % of the cycles, matrix pipe busy 42 %, no LDS bank conflicts.  Whole call 11.6 -> 0.73 ms against a kernel of one
-// row per four lanes in scalar arithmetic (25 -> 400 TFLOP/s).
+// What bounds it (measured, 24 heads of 64 channels, 15 600 tokens in blocks of 64, keep 0.5, full 0.25): the vector issue port, which a matrix
+// instruction holds too. The exact cut of a weight into three terms takes 1.5 vector instructions and half a matrix instruction: the
+// differences are taken by matrix instructions (with 5.5 vector instructions 2 % slower; the bf16 dot instruction is slower still
+// and not exact).  A full tile is fetched from scalar addresses, its keys are weighed 64 at a time, and a loop has tiles of one kind only, so
+// that the accumulators stay where they are: 131 -> 80 vector instructions per 16 matrix ones, and 40 to 60 registers less.  Counters of that
+// launch: vector instructions issuing in 94 -> 70 % of the cycles, matrix pipe busy 42 -> 62 %, no LDS bank conflicts.  Whole call 740 -> 651 us;
+// 128 channels 1271 -> 1133, dense attention of 8 such heads 1153 -> 977.  A kernel of one row per four lanes in scalar arithmetic took 11.6 ms.
 //
 // fp32 is bound by bf16 matrix instructions: six in place of eight fp32 ones that take twice as long each: 24 heads of 128 channels,
 // 15 600 tokens, 5.6 -> 3.2 ms a call (1.1 PFLOP/s of bf16 products), 64 channels in blocks of 64 2.97 -> 1.53 ms; 8 heads of 5280 tokens
@@ -83,6 +85,9 @@ struct GenArgs {
 __device__ __forceinline__ void dma16(const void* src, uint32_t lds_addr) {      // lane i -> LDS bytes lds_addr + 16 i
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_addr), "v"(src) : "memory", "m0");
 }
+__device__ __forceinline__ void dma16(const void* base, uint32_t offset, uint32_t lds_addr) {      // the same from a common base
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds_addr), "v"(offset), "s"(base) : "memory", "m0");
+}
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(size_t)(__attribute__((address_space(3))) const void*)p;
 }
@@ -118,6 +123,30 @@ __device__ __forceinline__ uint32_t split3(const float (&x)[8], bf16x8 (&t)[3]) 
 #pragma unroll
   for (int k = 0; k < 3; ++k) t[k] = __builtin_bit_cast(bf16x8, make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]));
   return rest;
+}
+// The same of a lane's numbers x[0 .. 3], x[4 .. 7] with the differences taken by matrix instructions: x - term = x + A term, A[4 g + i][8 g + 4 u + i]
+// = -1 (u = 0: the first four numbers, u = 1: the others), which is exact like the subtraction.  Two of them take 16 cycles of the vector
+// issue port, 16 vector instructions 64.
+__device__ __forceinline__ bf16x8 minus_ones(int u, int r16, int g) {
+  const uint32_t one = g == (r16 >> 2) ? 0xbf80u << (16 * (r16 & 1)) : 0u;
+  const uint32_t lo = r16 & 2 ? 0u : one, hi = r16 & 2 ? one : 0u;
+  return __builtin_bit_cast(bf16x8, u ? make_uint4(0u, 0u, lo, hi) : make_uint4(lo, hi, 0u, 0u));
+}
+__device__ __forceinline__ void split3(f32x4 x0, f32x4 x1, const bf16x8 (&minus)[2], bf16x8 (&t)[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const f32x4& x = e < 2 ? x0 : x1;
+      w[e] = __builtin_amdgcn_perm(__float_as_uint(x[2 * (e & 1) + 1]), __float_as_uint(x[2 * (e & 1)]), 0x07060302u);
+    }
+    t[k] = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
+    if (k < 2) {
+      x0 = mfma_bf(minus[0], t[k], x0);
+      x1 = mfma_bf(minus[1], t[k], x1);
+    }
+  }
 }
 
 }  // namespace
@@ -270,21 +299,36 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     at.bits = 3;
     if (at.nk <= 0) at.end = true;
   };
+  // Loads of a token tile: load i of a wave fetches RPL rows from (4 i + wave) RPL on.  A full tile's rows are at one offset per lane from
+  // scalar addresses: no vector instructions per load
+  constexpr int RPL = TERMS ? 64 / CP : 64 / CT, NL = TERMS ? D / 64 : NI;
+  const uint32_t lane_off = (uint32_t)((lane / (64 / RPL)) * (int)a.geo.stride_t + (TERMS ? lane % CP * 8 : ((lane % CT) ^ ((wave * RPL + lane / CT) & ST)) * (16 / (int)sizeof(T)))) * (uint32_t)sizeof(T);
+  auto is_full = [&](const Tile& t) { return t.nk == KTOK && a.geo.stride_t < (1 << 22); };
   // TERMS: one tensor (v or k) of tile t to its place.  16-byte piece u of eight-channel chunk p at (u * 4 D + p) * 16: a lane takes
   // the same chunks apart again that it has fetched
   auto issue_terms = [&](const Tile& t, const auto mean_c, const bool value) {
     constexpr bool mean = decltype(mean_c)::value;
+    const uint32_t dst = lds_addr(lds) + (value ? TILE : 0) + wave * 1024;
+    if (!mean && is_full(t)) {
+      const float* src = (const float*)(value ? a.v : a.k) + tbase + ((long long)t.start + wave * RPL) * a.geo.stride_t;
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        dma16(src, lane_off, dst + i * 4096);
+        dma16(src + 4, lane_off, dst + i * 4096 + TILE / 2);
+        src += 4 * RPL * a.geo.stride_t;
+      }
+      return;
+    }
     int li = lane;
     asm volatile("" : "+v"(li));
 #pragma unroll
-    for (int i = 0; i < D / 64; ++i) {
-      const int p = wave * D + i * 64 + li, row = min(p / CP, t.nk - 1), ch = p % CP * 8;
+    for (int i = 0; i < NL; ++i) {
+      const int row = min((4 * i + wave) * RPL + li / CP, t.nk - 1), ch = li % CP * 8;
       const float* src;
       if constexpr (!mean) src = (const float*)(value ? a.v : a.k) + tbase + (long long)(t.start + row) * a.geo.stride_t + ch;
       else src = (value ? a.vc : a.kc) + (bh * T_max + block_in_range(kvl[t.start + row], c.T)) * D + ch;
-      const uint32_t dst = lds_addr(lds) + (value ? TILE : 0) + (wave * D + i * 64) * 16;
-      dma16(src, dst);
-      dma16(src + 4, dst + TILE / 2);
+      dma16(src, dst + i * 4096);
+      dma16(src + 4, dst + i * 4096 + TILE / 2);
     }
   };
   // the weights of a mean tile's slots: slot tid % 32 as block tid / 32 of the item sees it: n_j, or 0
@@ -296,33 +340,44 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       wts[stage * 64 + tid] = w;
     }
   };
-  auto issue = [&](const Tile& t, int stage) {
-    unsigned char* const kdst = lds + stage * 2 * TILE;
+  auto issue = [&](const Tile& t, const auto mean_c, int stage) {
+    constexpr bool mean = decltype(mean_c)::value;
+    const uint32_t kdst = lds_addr(lds) + stage * 2 * TILE;
+    if (BF && !mean && is_full(t)) {
+      const long long off = tbase + ((long long)t.start + wave * RPL) * a.geo.stride_t;
+      const T *k = (const T*)a.k + off, *v = (const T*)a.v + off;
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        dma16(k, lane_off, kdst + (4 * i + wave) * 1024);
+        dma16(v, lane_off, kdst + (4 * i + wave) * 1024 + TILE);
+        k += 4 * RPL * a.geo.stride_t;
+        v += 4 * RPL * a.geo.stride_t;
+      }
+      return;
+    }
     int li = lane;
     asm volatile("" : "+v"(li));                       // worked out for every tile, not kept in registers
-    if (!t.mean) {
 #pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const int p = (wave * NI + i) * 64 + li, row = p / CT, ch = (p % CT) ^ (row & ST);
+    for (int i = 0; i < NI; ++i) {
+      const int p = (4 * i + wave) * 64 + li;
+      const uint32_t dst = kdst + (4 * i + wave) * 1024;
+      if constexpr (!mean) {
+        const int row = p / CT, ch = (p % CT) ^ (row & ST);
         const long long off = tbase + (long long)(t.start + min(row, t.nk - 1)) * a.geo.stride_t + ch * (16 / (int)sizeof(T));
-        const uint32_t dst = lds_addr(kdst) + (wave * NI + i) * 1024;
         dma16((const T*)a.k + off, dst);
         dma16((const T*)a.v + off, dst + TILE);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const int p = (wave * NI + i) * 64 + li, row = p / CM, ch = (p % CM) ^ (row & SM);
+      } else {
+        const int row = p / CM, ch = (p % CM) ^ (row & SM);
         const int j = block_in_range(kvl[t.start + min(row, t.nk - 1)], c.T);
         const long long off = (bh * T_max + j) * D + ch * 4;
-        const uint32_t dst = lds_addr(kdst) + (wave * NI + i) * 1024;
         dma16(a.kc + off, dst);
         dma16(a.vc + off, dst + TILE);
       }
-      mean_weights(t, stage);
     }
+    if (mean) mean_weights(t, stage);
   };
 
+  const bf16x8 minus[2] = {minus_ones(0, r16, g), minus_ones(1, r16, g)};
   f32x4 acc[NT][QT];                                   // element i: channel 16 ct + 4 g + i; on fp32 matrix instructions: see the store
   constexpr float NONE = WIDE ? INFINITY : -M_INIT;    // minus the maximum of no score
   float neg_m[QT], l_run[QT];                          // minus the running maximum (log2 domain; WIDE bf16: as the score is); sums per lane
@@ -338,7 +393,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   }
   auto factor = [&](float diff) { return __builtin_amdgcn_exp2f(WIDE && BF ? diff * cscale : diff); };      // between two maxima, from their difference
 
-  // ---- a half tile: 32 keys from row `r0` of the stage; `nk` of them real; wt: weights of a mean tile's 32 slots.  TERMS: kb and vb are the
+  // ---- 16 KT keys from row `r0` of the stage: a half tile, or a whole one of tokens in the first pass over bf16 rows; `nk` of them real; wt: weights of a mean tile's 32 slots.  TERMS: kb and vb are the
   // same place, filled with the terms of the keys and, while `between` runs, with those of the values
   auto half = [&](const unsigned char* kb, const unsigned char* vb, const int r0, const int nk, const auto mean_c, const float* wt, const auto between)
       __attribute__((always_inline)) {
@@ -347,9 +402,10 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     // are used instead of being kept in registers through the loop
     int rm = r16, gm = g;
     if (BF || TERMS) asm volatile("" : "+v"(rm), "+v"(gm));
-    f32x4 s[2][QT];
+    constexpr int KT = BF && !FULL32 && !mean ? 4 : 2;
+    f32x4 s[KT][QT];
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
+    for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) s[kt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
     if constexpr (TERMS) {
@@ -418,10 +474,11 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) s[kt][qt] += s_odd[kt][qt];
     } else if constexpr (!mean) {
+      if constexpr (BF && D == 64) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int ks = 0; ks < D / 32; ++ks)
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
+        for (int kt = 0; kt < KT; ++kt) {
           const bf16x8 k8 = *reinterpret_cast<const bf16x8*>(kb + ((r0 + 16 * kt + r16) * CT + ((4 * ks + g) ^ (r16 & ST))) * 16);
 #pragma unroll
           for (int qt = 0; qt < QT; ++qt) s[kt][qt] = mfma_bf(k8, qb[qt][ks], s[kt][qt]);
@@ -459,6 +516,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
           }
         }
     }
+    if constexpr (BF && D == 64) __builtin_amdgcn_s_setprio(0);
     // masks: slots past the end, mean slots with weight 0
     f32x4 w4[2];
     if constexpr (mean) {
@@ -470,9 +528,9 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 #pragma unroll
           for (int i = 0; i < 4; ++i) s[kt][qt][i] = w4[kt][i] > 0.f ? s[kt][qt][i] : -INFINITY;
       }
-    } else if (nk < 32) {
+    } else if (nk < 16 * KT) {
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
@@ -486,8 +544,8 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     for (int qt = 0; qt < QT; ++qt) {
       mx[qt] = s[0][qt][0];
 #pragma unroll
-      for (int e = 1; e < 7; e += 2) mx[qt] = fmaxf(fmaxf(mx[qt], s[e >> 2][qt][e & 3]), s[(e + 1) >> 2][qt][(e + 1) & 3]);
-      mx[qt] = fmaxf(mx[qt], s[1][qt][3]) * (WIDE ? 1.f : cscale);
+      for (int e = 1; e < 4 * KT - 1; e += 2) mx[qt] = fmaxf(fmaxf(mx[qt], s[e >> 2][qt][e & 3]), s[(e + 1) >> 2][qt][(e + 1) & 3]);
+      mx[qt] = fmaxf(mx[qt], s[KT - 1][qt][3]) * (WIDE ? 1.f : cscale);
       raise |= __ballot((mx[qt] + neg_m[qt]) * (WIDE && BF ? cscale : 1.f) > (FULL32 ? 0.f : RESCALE_TAU));
     }
     if (raise != 0ull) {
@@ -503,143 +561,148 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         for (int ct = 0; ct < NT; ++ct) acc[ct][qt] *= alpha;
       }
     }
-    float p[QT][8];                                    // element 4 kt + i
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-      const float sh = shift(neg_m[qt]);
+    for (int k0 = 0; k0 < KT; k0 += 2) {
+      f32x4 p[QT][2];                                    // [kt % 2]
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int qt = 0; qt < QT; ++qt) {
+        const float sh = shift(neg_m[qt]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          p[qt][4 * kt + i] = __builtin_amdgcn_exp2f(WIDE ? (s[kt][qt][i] + sh) * (BF ? cscale : 1.f) : fmaf(s[kt][qt][i], cscale, sh));
-    }
-    if constexpr (mean) {                              // Eq. 4: a mean key weighs its block's token count
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            p[qt][kt][i] = __builtin_amdgcn_exp2f(WIDE ? (s[k0 + kt][qt][i] + sh) * (BF ? cscale : 1.f) : fmaf(s[k0 + kt][qt][i], cscale, sh));
+      }
+      if constexpr (mean) {                              // Eq. 4: a mean key weighs its block's token count
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+          for (int kt = 0; kt < 2; ++kt) p[qt][kt] *= w4[kt];
+      }
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) p[qt][e] *= w4[e >> 2][e & 3];
-    }
+        for (int e = 0; e < 8; ++e) l_run[qt] += p[qt][e >> 2][e & 3];
+      // O^T += V^T P^T
+      if constexpr (TERMS) {
+        bf16x8 p3[QT][3];
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) l_run[qt] += p[qt][e];
-    // O^T += V^T P^T
-    if constexpr (TERMS) {
-      bf16x8 p3[QT][3];
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) {
-        split3(p[qt], p3[qt]);
-        asm volatile("" : "+v"(p3[qt][0]), "+v"(p3[qt][1]), "+v"(p3[qt][2]), "+v"(l_run[qt]));      // before the barriers, not where they are used
-      }
-      ISA_GEN_FENCE();
-      between();
-      asm volatile("" : "+v"(rm), "+v"(gm));
-      const int tr_row = 4 * gm + (rm >> 2);
-      constexpr int GR = 2;                            // (one at a time 4 % slower, four alike)
-#pragma unroll
-      for (int c0 = 0; c0 < NT; c0 += GR) {
-        ISA_GEN_FENCE();
-        bf16x8 v3[GR][3];
-#pragma unroll
-        for (int n = 0; n < GR; ++n)
-#pragma unroll
-          for (int u = 0; u < 3; ++u) {
-            const unsigned char* src = vb + u * PLANE + (tr_row * CP + ((2 * (c0 + n) + ((rm & 3) >> 1)) ^ (tr_row & SP))) * 16 + (rm & 1) * 8;
-            const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src));
-            const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src + 16 * CP * 16));
-            v3[n][u] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-          }
-#pragma unroll
-        for (int u = 2; u >= 0; --u)
-#pragma unroll
-          for (int w = 2 - u; w >= 0; --w)
-#pragma unroll
-            for (int n = 0; n < GR; ++n)
-#pragma unroll
-              for (int qt = 0; qt < QT; ++qt) acc[c0 + n][qt] = mfma_bf(v3[n][u], p3[qt][w], acc[c0 + n][qt]);
-      }
-    } else if constexpr (FM) {
-      f32x4 v4[2][NT / 4];                             // tiles 4 u + e: output row m is channel 64 u + 4 m + e
-      auto v_load = [&](int n) {                       // key slot 16 kt + 4 g + i, n = 4 kt + i
-        const int row = 4 * (n & 4) + 4 * g + (n & 3);
-#pragma unroll
-        for (int u = 0; u < NT / 4; ++u) {
-          v4[n & 1][u] = *reinterpret_cast<const f32x4*>(vb + (row * CM + ((16 * u + r16) ^ (row & SM))) * 16);
-          if (mean ? w4[n >> 2][n & 3] == 0.f : nk < 32 && row >= nk) v4[n & 1][u] = f32x4{0.f, 0.f, 0.f, 0.f};      // what is masked may hold anything
+        for (int qt = 0; qt < QT; ++qt) {
+          split3(p[qt][0], p[qt][1], minus, p3[qt]);
+          asm volatile("" : "+v"(p3[qt][0]), "+v"(p3[qt][1]), "+v"(p3[qt][2]), "+v"(l_run[qt]));      // before the barriers, not where they are used
         }
-      };
-      v_load(0);
-#pragma unroll
-      for (int n = 0; n < 8; ++n) {
         ISA_GEN_FENCE();
-        if (n + 1 < 8) v_load(n + 1);
-#pragma unroll
-        for (int u = 0; u < NT / 4; ++u)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int qt = 0; qt < QT; ++qt) acc[4 * u + e][qt] = mfma_f(v4[n & 1][u][e], p[qt][n], acc[4 * u + e][qt]);
-      }
-    } else if constexpr (FULL32) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
+        between();
         asm volatile("" : "+v"(rm), "+v"(gm));
-        const int row = (e & 4) * 4 + 4 * gm + (e & 3);
-#pragma unroll
-        for (int ct = 0; ct < NT; ++ct) {
-          ISA_GEN_FENCE();
-          float v;
-          if constexpr (mean) v = *reinterpret_cast<const float*>(vb + (row * CM + ((4 * ct + (rm >> 2)) ^ (row & SM))) * 16 + (rm & 3) * 4);
-          else v = bits_f((uint32_t)*reinterpret_cast<const uint16_t*>(vb + ((r0 + row) * CT + ((2 * ct + (rm >> 3)) ^ (row & ST))) * 16 + (rm & 7) * 2) << 16);
-          if (mean ? w4[e >> 2][e & 3] == 0.f : row >= nk) v = 0.f;
-#pragma unroll
-          for (int qt = 0; qt < QT; ++qt) acc[ct][qt] = mfma_f(v, p[qt][e], acc[ct][qt]);
-        }
-      }
-    } else {
-      bf16x8 p3[QT][3];
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt) split3(p[qt], p3[qt]);
-      if constexpr (!mean) {
-        const int tr_row = 4 * g + (r16 >> 2);         // see the transposed reads of the backward kernel
-        constexpr int GR = 4;                          // output tiles whose V^T fragments are held at a time
+        const int tr_row = 4 * gm + (rm >> 2);
+        constexpr int GR = 2;                            // (one at a time 4 % slower, four alike)
 #pragma unroll
         for (int c0 = 0; c0 < NT; c0 += GR) {
-          bf16x8 v8[GR];
-#pragma unroll
-          for (int n = 0; n < GR; ++n) {
-            const unsigned char* src = vb + ((r0 + tr_row) * CT + ((2 * (c0 + n) + ((r16 & 3) >> 1)) ^ (tr_row & ST))) * 16 + (r16 & 1) * 8;
-            const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src));
-            const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src + 16 * CT * 16));
-            v8[n] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-          }
-#pragma unroll
-          for (int u = 2; u >= 0; --u)                 // the small terms first
-#pragma unroll
-            for (int n = 0; n < GR; ++n)
-#pragma unroll
-              for (int qt = 0; qt < QT; ++qt) acc[c0 + n][qt] = mfma_bf(v8[n], p3[qt][u], acc[c0 + n][qt]);
-        }
-      } else {
-#pragma unroll
-        for (int ct = 0; ct < NT; ++ct) {
           ISA_GEN_FENCE();
-          float x[8];
+          bf16x8 v3[GR][3];
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int row = (e & 4) * 4 + 4 * gm + (e & 3);
-            x[e] = *reinterpret_cast<const float*>(vb + (row * CM + ((4 * ct + (rm >> 2)) ^ (row & SM))) * 16 + (rm & 3) * 4);
-          }
-          bf16x8 v3[3];
-          split3(x, v3);
+          for (int n = 0; n < GR; ++n)
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+              const unsigned char* src = vb + u * PLANE + (tr_row * CP + ((2 * (c0 + n) + ((rm & 3) >> 1)) ^ (tr_row & SP))) * 16 + (rm & 1) * 8;
+              const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src));
+              const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src + 16 * CP * 16));
+              v3[n][u] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
 #pragma unroll
           for (int u = 2; u >= 0; --u)
 #pragma unroll
-            for (int w = 2; w >= 0; --w)
-              if (u + w < 4) {
+            for (int w = 2 - u; w >= 0; --w)
 #pragma unroll
-                for (int qt = 0; qt < QT; ++qt) acc[ct][qt] = mfma_bf(v3[u], p3[qt][w], acc[ct][qt]);
-              }
+              for (int n = 0; n < GR; ++n)
+#pragma unroll
+                for (int qt = 0; qt < QT; ++qt) acc[c0 + n][qt] = mfma_bf(v3[n][u], p3[qt][w], acc[c0 + n][qt]);
+        }
+      } else if constexpr (FM) {
+        f32x4 v4[2][NT / 4];                             // tiles 4 u + e: output row m is channel 64 u + 4 m + e
+        auto v_load = [&](int n) {                       // key slot 16 kt + 4 g + i, n = 4 kt + i
+          const int row = 4 * (n & 4) + 4 * g + (n & 3);
+#pragma unroll
+          for (int u = 0; u < NT / 4; ++u) {
+            v4[n & 1][u] = *reinterpret_cast<const f32x4*>(vb + (row * CM + ((16 * u + r16) ^ (row & SM))) * 16);
+            if (mean ? w4[n >> 2][n & 3] == 0.f : nk < 32 && row >= nk) v4[n & 1][u] = f32x4{0.f, 0.f, 0.f, 0.f};      // what is masked may hold anything
+          }
+        };
+        v_load(0);
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+          ISA_GEN_FENCE();
+          if (n + 1 < 8) v_load(n + 1);
+#pragma unroll
+          for (int u = 0; u < NT / 4; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+              for (int qt = 0; qt < QT; ++qt) acc[4 * u + e][qt] = mfma_f(v4[n & 1][u][e], p[qt][n >> 2][n & 3], acc[4 * u + e][qt]);
+        }
+      } else if constexpr (FULL32) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          asm volatile("" : "+v"(rm), "+v"(gm));
+          const int row = (e & 4) * 4 + 4 * gm + (e & 3);
+#pragma unroll
+          for (int ct = 0; ct < NT; ++ct) {
+            ISA_GEN_FENCE();
+            float v;
+            if constexpr (mean) v = *reinterpret_cast<const float*>(vb + (row * CM + ((4 * ct + (rm >> 2)) ^ (row & SM))) * 16 + (rm & 3) * 4);
+            else v = bits_f((uint32_t)*reinterpret_cast<const uint16_t*>(vb + ((r0 + row) * CT + ((2 * ct + (rm >> 3)) ^ (row & ST))) * 16 + (rm & 7) * 2) << 16);
+            if (mean ? w4[e >> 2][e & 3] == 0.f : row >= nk) v = 0.f;
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt) acc[ct][qt] = mfma_f(v, p[qt][e >> 2][e & 3], acc[ct][qt]);
+          }
+        }
+      } else {
+        bf16x8 p3[QT][3];
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) split3(p[qt][0], p[qt][1], minus, p3[qt]);
+        if constexpr (!mean) {
+          const int tr_row = 4 * g + (r16 >> 2);         // see the transposed reads of the backward kernel
+          if constexpr (D == 64) __builtin_amdgcn_s_setprio(1);
+          constexpr int GR = 4;                          // output tiles whose V^T fragments are held at a time
+#pragma unroll
+          for (int c0 = 0; c0 < NT; c0 += GR) {
+            bf16x8 v8[GR];
+#pragma unroll
+            for (int n = 0; n < GR; ++n) {
+              const unsigned char* src = vb + ((r0 + 16 * k0 + tr_row) * CT + ((2 * (c0 + n) + ((r16 & 3) >> 1)) ^ (tr_row & ST))) * 16 + (r16 & 1) * 8;
+              const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src));
+              const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(src + 16 * CT * 16));
+              v8[n] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+#pragma unroll
+            for (int u = 2; u >= 0; --u)                 // the small terms first
+#pragma unroll
+              for (int n = 0; n < GR; ++n)
+#pragma unroll
+                for (int qt = 0; qt < QT; ++qt) acc[c0 + n][qt] = mfma_bf(v8[n], p3[qt][u], acc[c0 + n][qt]);
+          }
+          if constexpr (D == 64) __builtin_amdgcn_s_setprio(0);
+        } else {
+#pragma unroll
+          for (int ct = 0; ct < NT; ++ct) {
+            ISA_GEN_FENCE();
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const int row = (e & 4) * 4 + 4 * gm + (e & 3);
+              x[e] = *reinterpret_cast<const float*>(vb + (row * CM + ((4 * ct + (rm >> 2)) ^ (row & SM))) * 16 + (rm & 3) * 4);
+            }
+            bf16x8 v3[3];
+            split3(x, v3);
+#pragma unroll
+            for (int u = 2; u >= 0; --u)
+#pragma unroll
+              for (int w = 2; w >= 0; --w)
+                if (u + w < 4) {
+#pragma unroll
+                  for (int qt = 0; qt < QT; ++qt) acc[ct][qt] = mfma_bf(v3[u], p3[qt][w], acc[ct][qt]);
+                }
+          }
         }
       }
     }
@@ -663,7 +726,6 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   };
   Tile cur = next_mine();
   int stage = 0;
-  if (!TERMS && !cur.end) issue(cur, 0);
   // TERMS: this wave's share of a tile of keys or values, which it has fetched itself, taken apart into the common place
   auto take_apart = [&](const bool value) {
     const unsigned char* const src = lds + (value ? TILE : 0);
@@ -672,7 +734,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 #pragma unroll
     for (int i = 0; i < D / 64; ++i) {
       ISA_GEN_FENCE();
-      const int p = wave * D + i * 64 + li, row = p / CP;
+      const int p = (4 * i + wave) * 64 + li, row = p / CP;
       float x[8];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -727,15 +789,21 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       ISA_GEN_BARRIER();                               // everybody has left the weights of the last tile
       return;
     }
-    for (; !cur.end && cur.mean == mean; stage ^= 1) {
+    if (cur.end || cur.mean != mean) return;
+    issue(cur, mean_c, stage);
+    for (bool more = true; more; stage ^= 1) {
       const Tile nxt = next_mine();                    // its table reads wait together with the tile loads
+      more = !nxt.end && nxt.mean == mean;
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();                                 // the tile is complete; everybody has left the one before, whose stage is filled next
-      if (!nxt.end) issue(nxt, stage ^ 1);
+      if (more) issue(nxt, mean_c, stage ^ 1);
       const unsigned char* kb = lds + stage * 2 * TILE;
-      if ((cur.bits >> own) & 1) {                     // wave-uniform
+      const int n_own = (cur.bits >> own) & 1 ? cur.nk : 0;      // a tile of the other block's exact set has no keys for this wave
+      if constexpr (BF && !FULL32) {
+        if (n_own > 0) half(kb, kb + TILE, 0, n_own, mean_c, wts + stage * 64 + own * 32, [] {});
+      } else {
 #pragma unroll 1
-        for (int r0 = 0; r0 < cur.nk; r0 += 32) half(kb, kb + TILE, r0, cur.nk - r0, mean_c, wts + stage * 64 + own * 32, [] {});
+        for (int r0 = 0; r0 < n_own; r0 += 32) half(kb, kb + TILE, r0, n_own - r0, mean_c, wts + stage * 64 + own * 32, [] {});
       }
       cur = nxt;
       ++n_mine;
@@ -1023,30 +1091,29 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
   // rows, plus its exact set's share (x `shared` in two groups); Taylor items fill what the long ones leave idle, so the time is that of the
   // long items' rounds or that of all items with the chip full, whichever is longer; not so beside two groups, which leave little idle.  A bf16
   // part has at least 256 tokens, an fp32 one may be a single block (D = 128, 1 head, 300 tokens: 46 whole, 35 in parts).
-  // The numbers are fitted to 1094 calls (1 to 40 heads, 300 to 15 600 tokens, dense and sparse, ragged batches; fp32 to 522) with every form and number of
-  // parts measured: the choice costs 0.7 to 1.3 % more than the best one on the geometric average.  Measured, whole calls, us, keep 0.5, full 0.25, whole
-  // items of 128 rows / of 64 / in two groups / as chosen: bf16, 15 600 tokens, blocks of 64: D = 64, 1 head 387 / 281 / 231 / 88, 4 heads 404 / 302 /
-  // 240 / 175, 8 417 / 342 / 347 / 299, 12 505 / 469 / 490 / 402, 16 531 / 581 / 641 / 531; D = 128: 2 heads 555 / 393 / 317 / 174, 4 562 / 402 / 392 / 282, 8
-  // 582 / 554 / 749 / 478, 12 756 / 812 / 1085 / 756 (the partial results have no room), 16 862 / 1051 / 1473 / 860; dense, 1980 tokens, 8 heads: D = 64
-  // 65 / 50 / 40 / 40, D = 128 93 / 67 / 54 / 54.  fp32, 64 rows / 128 / as chosen: 4800 tokens, D = 128, 4 heads 341 / 434 / 109, 12 351 / 448 / 192, D = 64, 4 heads 213 / 269 / 75.
+  // The numbers are fitted to 1200 calls (1 to 40 heads, 300 to 15 600 tokens, dense and sparse, ragged batches) with every form and number of
+  // parts measured: the choice costs 0.7 to 1.5 % more than the best one on the geometric average.  Measured, whole calls, us, keep 0.5, full 0.25, whole
+  // items of 128 rows / of 64 / in two groups / as chosen: bf16, 15 600 tokens, blocks of 64: D = 64, 1 head 325 / 247 / 203 / 77, 4 heads 340 / 266 /
+  // 212 / 150, 8 349 / 282 / 295 / 250, 12 391 / 383 / 419 / 355, 16 442 / 482 / 545 / 442; D = 128: 2 heads 491 / 342 / 281 / 163, 4 505 / 353 / 358 / 253, 8
+  // 513 / 477 / 671 / 428, 12 659 / 709 / 952 / 658 (the partial results have no room), 16 772 / 901 / 1257 / 770; dense, 1980 tokens, 8 heads: D = 64
+  // 55 / 42 / 36 / 36, D = 128 84 / 56 / 51 / 52.  fp32, 64 rows / 128 / as chosen: 4800 tokens, D = 128, 4 heads 341 / 434 / 109, 12 351 / 448 / 192, D = 64, 4 heads 213 / 269 / 75.
   struct Form { int rows, groups, resident; double pace[4], start; };
   struct Kind { double taylor, shared, merge, rate; Form form[3]; };
   static const Kind kinds[2][2] = {                    // [bf16][D = 64]
       {{.0086, 1, 6.3, 4.7, {{64, 1, 2, {4.1, 4.8}, 40}, {128, 1, 2, {5.13, 6.52}, 30}}},
        {.013, 1, 3.7, 4.3, {{64, 1, 4, {2.15, 2.6, 3.04, 4.75}, 16}, {128, 1, 3, {3.15, 3.27, 5.25}, 14.5}}}},
       {{.075, 1.4, 6.0, 5.4, {{64, 1, 2, {1.63, 2.52}, 185}, {128, 1, 2, {2.67, 3.87}, 180}, {64, 2, 1, {2.77}, 145}}},
-       {.050, 2.0, 4.5, 4.1, {{64, 1, 4, {1.25, 1.75, 2.17, 3.03}, 320}, {128, 1, 3, {1.86, 2.91, 3.29}, 340}, {64, 2, 2, {1.97, 2.97}, 240}}}}};
+       {.0436, 1.68, 5.75, 3.7, {{64, 1, 4, {1.285, 1.57, 2.13, 3.04}, 257}, {128, 1, 3, {1.73, 2.5, 3.29}, 349}, {64, 2, 2, {1.85, 3.58}, 209}}}}};
   const Kind& kind = kinds[bf][d64];
   bool two = false, groups = false;
   Cut chosen = {};
   ga.parts = 1;
   if (n_long == 0) {
-    // Taylor items alone, 128 rows / 64: D = 64, 24, 4, 2 heads (2928, 488, 244 items of 128 rows) 186 / 226, 67 / 73, 61 / 58; D = 128, 24, 2 heads
-    // 351 / 465, 82 / 79.  With exact sets a pair of blocks of 64 reads both blocks' sets, which Taylor items do not make up for at D = 64:
-    // 24, 8 heads 435 / 396, 192 / 171 (D = 128: 797 / 814, 302 / 305).
-    // fp32: D = 128, 24 heads (2928) 430 / 524, 8 (976) 151 / 184, 24 (288) 39 / 41, 2 (244) 63 / 61; D = 64 (2928) 202 / 221, (912) 60.3 / 60.4, (304)
-    // 39.4 / 38.8; pairs with exact sets (every wave multiplies both blocks' tiles) D = 128 2424 / 1946, D = 64 1207 / 885.
-    two = !(set_share > 0.0 && (d64 || !bf) && pr.p.block == 64) && items(n_taylor, 128) >= chip * (bf ? (d64 ? 1.75 : 1.25) : d64 ? 3.5 : 1.0);
+    // Taylor items alone, 128 rows / 64, us by items of 128 rows: bf16, D = 64: 2928 179 / 219, 912 53 / 57, 304 35.7 / 35.4; D = 128: 2928
+    // 341 / 457, 304 50 / 57, 288 33 / 37, 244 79 / 78; fp32, D = 64: 2928 202 / 221, 912 60.3 / 60.4, 304 39.4 / 38.8; D = 128: 2928 430 / 524,
+    // 288 39 / 41, 244 63 / 61.  With exact sets a pair of blocks of 64 reads both blocks' sets: bf16, 2928: D = 64 496 / 452, D = 128
+    // 958 / 900; fp32 1207 / 885, 2424 / 1946.
+    two = !(set_share > 0.0 && pr.p.block == 64) && items(n_taylor, 128) >= chip * (bf ? (d64 ? 1.75 : 1.0) : d64 ? 3.5 : 1.0);
   } else {
     double best = INFINITY;
     for (int f = 0; f < (bf ? 3 : 2); ++f) {

@@ -434,3 +434,31 @@ def test_fp32_infinities_in_wide_workgroups(I, shape):
     others = [c for c in range(wl.D) if c != 3]
     diff = (outs[1][..., others] - outs[0][..., others]).norm() / outs[0][..., others].norm()
     assert diff <= 30 * 2.0 ** -24, diff
+
+
+# bf16: a tile of 64 keys is weighed at once, its last keys masked (tails around its 32-key halves in every block), and fetched row by row where it is not
+# full or where rows are 2^22 elements apart or more (a view of one head of many)
+@pytest.mark.parametrize("tail", [1, 33, 47, 48, 63])
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[2] == 64], ids=[i for i in SHAPE_IDS if i[-3:] == "b64"])
+def test_full_and_ragged_tiles_of_one_list(I, shape, tail):
+    wl = _wl(shape, 2, (1, 1, 192 + tail), (((1, 1, 64 + tail), (1, 1, 128), (1, 1, tail)),), keep_ratio=1.0, full_frac=0.5, seed=817 + tail)
+    check_end_to_end(I, wl, *gen(wl))
+
+
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[4]], ids=[SHAPE_IDS[0], SHAPE_IDS[4]])
+def test_rows_far_apart(I, shape):
+    D, n, stride = shape[1], 140, 2 ** 22
+    wl = _wl(shape, 1, (1, 1, n), ((),), seed=823)
+    g = torch.Generator().manual_seed(wl.seed)
+    x = [torch.randn((1, 1, n, D), generator=g).to(W.torch_dtype(wl.dtype)) for _ in range(3)]
+    far = torch.zeros((4, D + (n - 1) * stride), dtype=x[0].dtype, device="cuda").as_strided((4, 1, 1, n, D), (D + (n - 1) * stride, 8, 8, stride, 1))
+    for i, t in enumerate(x):
+        far[i].copy_(t)
+    near = torch.empty((1, 1, n, D), dtype=x[0].dtype, device="cuda")
+    kw = dict(H=1, D=D, dtype=shape[0], block=shape[2], seg_len=[[n]], keep_ratio=1.0, full_frac=1.0)
+    pr = I.Problem(**kw)
+    I.isa_dense_attention(pr, *(t.cuda() for t in x), near, I.new_workspace(pr))
+    pr = I.Problem(**kw)
+    I.isa_dense_attention(pr, far[0], far[1], far[2], far[3], I.new_workspace(pr))
+    torch.cuda.synchronize()
+    assert torch.equal(far[3], near)
