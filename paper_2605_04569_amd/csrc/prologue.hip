@@ -22,6 +22,7 @@
 namespace isa {
 
 constexpr int PBLOCK = 128;   // largest block
+constexpr int ENTRIES = 4096; // sines and cosines that a workgroup has room for
 
 struct GridDesc {             // passed to kernels by value
   int grid[ISA_MAX_SEGMENTS][3];
@@ -82,6 +83,23 @@ __device__ inline void tile_coords(int p, int t, int h, int w, int tt, int th, i
   *cw = c * tw + (p - lh * sw);
 }
 
+// Stores, and loads of more than the last-level cache holds, are streamed (nontemporal): nothing of them is found there again before it is
+// pushed out, and what they would push out is.  isa_prologue, isa_untile and isa_prologue_backward together, us, neither / stores /
+// both: 40 heads of 39 680 tokens (1.2 GB of queries, keys and values) 1030 / 1003 / 926, 20 heads of 15 600 (240 MB) 217 / 184 / 198.
+constexpr long long CACHE_BYTES = 256ll << 20;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store16(void* p, uint32_t x, uint32_t y, uint32_t z, uint32_t w) {
+  __builtin_nontemporal_store(u32x4{x, y, z, w}, reinterpret_cast<u32x4*>(p));
+}
+template <bool STREAM> __device__ __forceinline__ uint4 load16(const void* p) {
+  const u32x4* const q = reinterpret_cast<const u32x4*>(p);
+  u32x4 r;
+  if constexpr (STREAM) r = __builtin_nontemporal_load(q);
+  else r = *q;
+  return make_uint4(r.x, r.y, r.z, r.w);
+}
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 template <typename T> struct Row16;      // 16 bytes of a token row
 template <> struct Row16<float> {
   static constexpr int N = 4;
@@ -89,7 +107,7 @@ template <> struct Row16<float> {
     o[0] = __uint_as_float(v.x); o[1] = __uint_as_float(v.y); o[2] = __uint_as_float(v.z); o[3] = __uint_as_float(v.w);
   }
   __device__ static void store(float* p, float* o) {       // o is left holding the stored values
-    *reinterpret_cast<float4*>(p) = make_float4(o[0], o[1], o[2], o[3]);
+    store16(p, __float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3]));
   }
 };
 template <> struct Row16<uint16_t> {   // bf16 storage
@@ -102,29 +120,24 @@ template <> struct Row16<uint16_t> {   // bf16 storage
       o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
   }
-  __device__ static uint32_t round_bf16(float f) {         // round to nearest even, NaN kept quiet
-    const uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-  }
   __device__ static void store(uint16_t* p, float* o) {    // o is left holding the rounded values
     uint32_t w[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t lo = round_bf16(o[2 * i]), hi = round_bf16(o[2 * i + 1]);
-      w[i] = lo | (hi << 16);
-      o[2 * i] = __uint_as_float(lo << 16);
-      o[2 * i + 1] = __uint_as_float(hi << 16);
+      const bf16x2 r = {(__bf16)o[2 * i], (__bf16)o[2 * i + 1]};         // one instruction, to nearest even
+      w[i] = __builtin_bit_cast(uint32_t, r);
+      o[2 * i] = __uint_as_float(w[i] << 16);
+      o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
-    *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+    store16(p, w[0], w[1], w[2], w[3]);
   }
 };
 
 // Loads the thread's 16-byte piece of TPT token rows (all in flight together).
-template <typename T, int TPT>
+template <typename T, int TPT, bool STREAM>
 __device__ __forceinline__ void load_rows(uint4 (&raw)[TPT], const T* ip, const int (&src)[TPT], long long stride_t) {
 #pragma unroll
-  for (int tk = 0; tk < TPT; ++tk) raw[tk] = *reinterpret_cast<const uint4*>(ip + (long long)src[tk] * stride_t);
+  for (int tk = 0; tk < TPT; ++tk) raw[tk] = load16<STREAM>(ip + (long long)src[tk] * stride_t);
 }
 
 // Rotates (if asked), stores and sums the rows that load_rows brought in; acc receives the column sums of what was stored.
@@ -154,7 +167,30 @@ __device__ __forceinline__ void finish_rows(const uint4 (&raw)[TPT], const float
   }
 }
 
-template <typename T, int D>
+// The smallest / largest of a wave's 64 numbers, in every lane.
+template <bool MAX>
+__device__ __forceinline__ int wave_extreme(int x) {
+  auto both = [](int a, int b) { return MAX ? max(a, b) : min(a, b); };
+  const auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  x = both(s[0], s[1]);
+  const auto t = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = both(t[0], t[1]);
+  x = both(x, __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, true));         // row_ror 8, 4, 2, 1
+  x = both(x, __builtin_amdgcn_update_dpp(0, x, 0x124, 0xf, 0xf, true));
+  x = both(x, __builtin_amdgcn_update_dpp(0, x, 0x122, 0xf, 0xf, true));
+  return both(x, __builtin_amdgcn_update_dpp(0, x, 0x121, 0xf, 0xf, true));
+}
+
+// A long launch is HBM-bound (see the top), a short one waits for a workgroup's own chain: coordinates, frequencies, sines and cosines, then
+// a pass per tensor.
+// TABLE: a block's tokens have few coordinates (a tile of 2 x 8 x 8: 2 frames, 8 rows, 8 columns), so the workgroup works the sines and
+// cosines of each coordinate out once, one channel pair a thread, and hands them out through LDS: 380 in place of 8192, and 11 KB less
+// code to fetch.  Without: a thread works out its own, for grids whose coordinates have no room and where it has 8 (D = 64, blocks of 64).
+// SPLIT: a workgroup takes one of the three tensors.  PB: the block, so that a thread has no rows that a block of 64 has not.
+// All three, and roundings of one instruction, us (isa_prologue; before / after): bf16, 5 heads of 440 tokens 19.3 / 9.7, 16 of 1848 22.1 /
+// 15.9, 8 of 15 600 47 / 35.5; blocks of 64, 12 of 2704 28 / 17, D = 64 12 of 7920 25 / 19; fp32, 4 of 39 680 117 / 101.
+// STREAM: load16, above.
+template <typename T, int D, int PB, bool TABLE, bool SPLIT, bool STREAM>
 __global__ __launch_bounds__(256) void k_prologue(const T* __restrict__ q_in, const T* __restrict__ k_in,
                                                   const T* __restrict__ v_in, T* __restrict__ q_out,
                                                   T* __restrict__ k_out, T* __restrict__ v_out,
@@ -164,19 +200,34 @@ __global__ __launch_bounds__(256) void k_prologue(const T* __restrict__ q_in, co
   constexpr int VEC = Row16<T>::N;
   constexpr int CH = D / VEC;            // 16-byte chunks per row
   constexpr int RP = 256 / CH;           // rows covered per pass
-  constexpr int TPT = PBLOCK / RP;       // rows per thread
+  constexpr int TPT = PB / RP;           // rows per thread
   constexpr int NP = VEC / 2;            // channel pairs per thread
-  __shared__ int s_src[PBLOCK];
-  __shared__ int s_pos[PBLOCK][3];
-  __shared__ float red[2][RP][D];
-  const int j = blockIdx.x, b = blockIdx.z, h0 = blockIdx.y * hpw;
+  __shared__ int s_src[PB];
+  __shared__ int s_pos[PB][3];
+  constexpr int RED = 2 * RP * D, SHARED = TABLE && 2 * ENTRIES > RED ? 2 * ENTRIES : RED;
+  __shared__ __attribute__((aligned(16))) float shared[SHARED];
+  float (&red)[2][RP][D] = *reinterpret_cast<float (*)[2][RP][D]>(shared);
+  float2* const table = reinterpret_cast<float2*>(shared);             // until the passes begin
+  __shared__ int s_lo[4][3], s_hi[4][3];
+  const int j = blockIdx.x, b = blockIdx.z, h0 = SPLIT ? blockIdx.y / 3 : blockIdx.y * hpw;
   const BlockPos bp = locate_block(seg, gd, b, j, g.block);
   if (bp.n == 0) return;
-  if (threadIdx.x < bp.n) {
-    int ct, ch, cw;
-    tile_coords(bp.p0 + threadIdx.x, bp.t, bp.h, bp.w, gd.tile[0], gd.tile[1], gd.tile[2], &ct, &ch, &cw);
-    s_src[threadIdx.x] = bp.seg_start + (ct * bp.h + ch) * bp.w + cw;
-    s_pos[threadIdx.x][0] = ct; s_pos[threadIdx.x][1] = ch; s_pos[threadIdx.x][2] = cw;
+  if (TABLE || threadIdx.x < bp.n) {
+    int co[3];
+    const int i = min((int)threadIdx.x, bp.n - 1);     // (the others repeat the last token's)
+    tile_coords(bp.p0 + i, bp.t, bp.h, bp.w, gd.tile[0], gd.tile[1], gd.tile[2], &co[0], &co[1], &co[2]);
+    if (threadIdx.x < bp.n) {
+      s_src[i] = bp.seg_start + (co[0] * bp.h + co[1]) * bp.w + co[2];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) s_pos[i][a] = co[a];
+    }
+    if constexpr (TABLE) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        s_lo[threadIdx.x >> 6][a] = wave_extreme<false>(co[a]);
+        s_hi[threadIdx.x >> 6][a] = wave_extreme<true>(co[a]);
+      }
+    }
   }
   __syncthreads();
 
@@ -194,40 +245,91 @@ __global__ __launch_bounds__(256) void k_prologue(const T* __restrict__ q_in, co
     dst[tk] = inverse ? raster : tiled;
     valid |= (r < bp.n ? 1u : 0u) << tk;
   }
-  const int n_it = 3 * min(hpw, g.H - h0);        // (head, tensor) passes of this workgroup, q, k, v of a head in turn
+  // (head, tensor) passes of this workgroup: q, k, v of a head in turn, or one of them
+  const int first_it = SPLIT ? blockIdx.y % 3 : 0, n_it = SPLIT ? first_it + 1 : 3 * min(hpw, g.H - h0);
   const long long base0 = (long long)b * g.stride_b + (long long)h0 * g.stride_h + c * VEC;
 
   // Two sets of landing registers: the rows of pass it + 1 are in flight while pass it is rotated and stored.
   uint4 raw0[TPT], raw1[TPT];
 #define ISA_IN_PTR(it) ((((it) % 3) == 0 ? q_in : ((it) % 3) == 1 ? k_in : v_in) + base0 + (long long)((it) / 3) * g.stride_h)
-  load_rows<T, TPT>(raw0, ISA_IN_PTR(0), src, g.stride_t);
+  load_rows<T, TPT, STREAM>(raw0, ISA_IN_PTR(first_it), src, g.stride_t);
 
   // the thread's channel pairs: which coordinate turns them, and how fast; then the sines and cosines of its rows
   // (computed while the first rows are on their way)
-  int axis[NP];
-  double freq[NP];
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    int pr = c * NP + i, d_a = 0;
-    axis[i] = -1;
-    if (pr < gd.rope_dims[0] / 2) { axis[i] = 0; d_a = gd.rope_dims[0]; }
-    else if ((pr -= gd.rope_dims[0] / 2) < gd.rope_dims[1] / 2) { axis[i] = 1; d_a = gd.rope_dims[1]; }
-    else if ((pr -= gd.rope_dims[1] / 2) < gd.rope_dims[2] / 2) { axis[i] = 2; d_a = gd.rope_dims[2]; }
-    freq[i] = axis[i] < 0 ? 0.0 : exp2(-2.0 * (double)pr / (double)d_a * gd.log2_theta);
-  }
   float cs[TPT][NP], sn[TPT][NP];
+  auto pair_axis = [&](int& pr) {                        // pr: from channel pair to pair of its axis
+    if (pr < gd.rope_dims[0] / 2) return 0;
+    if ((pr -= gd.rope_dims[0] / 2) < gd.rope_dims[1] / 2) return 1;
+    if ((pr -= gd.rope_dims[1] / 2) < gd.rope_dims[2] / 2) return 2;
+    return -1;
+  };
+  auto pick = [](int axis, int x0, int x1, int x2) { return axis == 0 ? x0 : axis == 1 ? x1 : x2; };
+  auto pair_freq = [&](int axis, int pr) {
+    return axis < 0 ? 0.0 : exp2(-2.0 * (double)pr / (double)pick(axis, gd.rope_dims[0], gd.rope_dims[1], gd.rope_dims[2]) * gd.log2_theta);
+  };
+  auto turn = [&](int pos, double freq, float* sine, float* cosine) {
+    double turns = (double)pos * freq * 0.1591549430918953357689;                  // angle / 2 pi
+    turns -= rint(turns);                                                          // into [-1/2, 1/2]
+    sincospif((float)(2.0 * turns), sine, cosine);
+    if (inverse) *sine = -*sine;                                                   // turn back
+  };
+  if constexpr (TABLE) {
+    int lo[3], n[3];
 #pragma unroll
-  for (int tk = 0; tk < TPT; ++tk) {
-    const int r = rg + tk * RP;
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = min(min(s_lo[0][a], s_lo[1][a]), min(s_lo[2][a], s_lo[3][a]));
+      n[a] = max(max(s_hi[0][a], s_hi[1][a]), max(s_hi[2][a], s_hi[3][a])) - lo[a] + 1;
+    }
+    const int p0 = gd.rope_dims[0] / 2, p1 = gd.rope_dims[1] / 2, p2 = gd.rope_dims[2] / 2;
+    const bool rotates = !SPLIT || first_it < 2;
+    if (rotates) {
+      int pr = threadIdx.x % (D / 2);
+      const int axis = pair_axis(pr);
+      if (axis >= 0) {
+        const double freq = pair_freq(axis, pr);
+        const int count = pick(axis, n[0], n[1], n[2]), from = pick(axis, lo[0], lo[1], lo[2]), pairs = pick(axis, p0, p1, p2);
+        float2* const out = table + pick(axis, 0, n[0] * p0, n[0] * p0 + n[1] * p1) + pr;
+#pragma unroll 1
+        for (int k = threadIdx.x / (D / 2); k < count; k += 256 / (D / 2)) {
+          float2 t;
+          turn(from + k, freq, &t.x, &t.y);
+          out[k * pairs] = t;
+        }
+      }
+      __syncthreads();
+    }
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-      cs[tk][i] = 1.f; sn[tk][i] = 0.f;
-      if (r < bp.n && axis[i] >= 0) {
-        const int pos = axis[i] == 0 ? s_pos[r][0] : axis[i] == 1 ? s_pos[r][1] : s_pos[r][2];
-        double turns = (double)pos * freq[i] * 0.1591549430918953357689;          // angle / 2 pi
-        turns -= rint(turns);                                                        // into [-1/2, 1/2]
-        sincospif((float)(2.0 * turns), &sn[tk][i], &cs[tk][i]);
-        if (inverse) sn[tk][i] = -sn[tk][i];                                         // turn back
+      int pr = c * NP + i;
+      const int axis = pair_axis(pr);
+      const bool turned = rotates && axis >= 0;
+      const int pairs = pick(axis, p0, p1, p2), a = max(axis, 0);
+      const int at = pick(axis, 0, n[0] * p0, n[0] * p0 + n[1] * p1) + pr - pick(axis, lo[0], lo[1], lo[2]) * pairs;
+#pragma unroll
+      for (int tk = 0; tk < TPT; ++tk) {
+        const int r = rg + tk * RP;
+        const float2 t = table[turned ? at + s_pos[r < bp.n ? r : 0][a] * pairs : 0];
+        sn[tk][i] = turned ? t.x : 0.f;
+        cs[tk][i] = turned ? t.y : 1.f;
+      }
+    }
+    if (rotates) __syncthreads();                        // from here on the place is the block means'
+  } else {
+    int axis[NP];
+    double freq[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      int pr = c * NP + i;
+      axis[i] = pair_axis(pr);
+      freq[i] = pair_freq(axis[i], pr);
+    }
+#pragma unroll
+    for (int tk = 0; tk < TPT; ++tk) {
+      const int r = rg + tk * RP;
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        cs[tk][i] = 1.f; sn[tk][i] = 0.f;
+        if (r < bp.n && axis[i] >= 0) turn(pick(axis[i], s_pos[r][0], s_pos[r][1], s_pos[r][2]), freq[i], &sn[tk][i], &cs[tk][i]);
       }
     }
   }
@@ -254,11 +356,11 @@ __global__ __launch_bounds__(256) void k_prologue(const T* __restrict__ q_in, co
       }                                                                                                               \
     }                                                                                                                 \
   }
-  for (int it = 0; it < n_it; it += 2) {
-    if (it + 1 < n_it) load_rows<T, TPT>(raw1, ISA_IN_PTR(it + 1), src, g.stride_t);
+  for (int it = first_it; it < n_it; it += 2) {
+    if (it + 1 < n_it) load_rows<T, TPT, STREAM>(raw1, ISA_IN_PTR(it + 1), src, g.stride_t);
     ISA_PASS(raw0, 0, it)
     if (it + 1 < n_it) {
-      if (it + 2 < n_it) load_rows<T, TPT>(raw0, ISA_IN_PTR(it + 2), src, g.stride_t);
+      if (it + 2 < n_it) load_rows<T, TPT, STREAM>(raw0, ISA_IN_PTR(it + 2), src, g.stride_t);
       ISA_PASS(raw1, 1, it + 1)
     }
   }
@@ -267,14 +369,14 @@ __global__ __launch_bounds__(256) void k_prologue(const T* __restrict__ q_in, co
 }
 
 // Inverse reordering of one tensor: token p of the tile order goes back to its row-major place.
-template <typename T, int D>
+template <typename T, int D, int PB, bool STREAM>
 __global__ __launch_bounds__(256) void k_untile(const T* __restrict__ x_tiled, T* __restrict__ x_raster, SegDesc seg,
                                                 GridDesc gd, Geometry g, int hpw) {
   constexpr int VEC = Row16<T>::N;
   constexpr int CH = D / VEC;
   constexpr int RP = 256 / CH;
-  constexpr int TPT = PBLOCK / RP;
-  __shared__ int s_src[PBLOCK];
+  constexpr int TPT = PB / RP;
+  __shared__ int s_src[PB];
   const int j = blockIdx.x, b = blockIdx.z, h0 = blockIdx.y * hpw;
   const BlockPos bp = locate_block(seg, gd, b, j, g.block);
   if (bp.n == 0) return;
@@ -296,11 +398,11 @@ __global__ __launch_bounds__(256) void k_untile(const T* __restrict__ x_tiled, T
 #pragma unroll
     for (int tk = 0; tk < TPT; ++tk) {      // rows past the block's end re-read its first row and are not stored
       const int row = src[tk] >= 0 ? bp.start + rg + tk * RP : bp.start;
-      x[tk] = *reinterpret_cast<const uint4*>(x_tiled + base + (long long)row * g.stride_t);
+      x[tk] = load16<STREAM>(x_tiled + base + (long long)row * g.stride_t);
     }
 #pragma unroll
     for (int tk = 0; tk < TPT; ++tk)
-      if (src[tk] >= 0) *reinterpret_cast<uint4*>(x_raster + base + (long long)src[tk] * g.stride_t) = x[tk];
+      if (src[tk] >= 0) store16(x_raster + base + (long long)src[tk] * g.stride_t, x[tk].x, x[tk].y, x[tk].z, x[tk].w);
   }
 }
 
@@ -314,6 +416,13 @@ static int heads_per_wg(const Problem& pr) {
   return (int)hpw;
 }
 
+// Whether `tensors` of the problem's tensors are more than the last-level cache holds.
+static bool exceeds_cache(const Problem& pr, int tensors) {
+  long long rows = 0;
+  for (int b = 0; b < pr.p.B; ++b) rows += pr.cnt.b[b].S;
+  return tensors * rows * pr.p.H * pr.p.D * (pr.p.dtype == ISA_BF16 ? 2 : 4) >= CACHE_BYTES;
+}
+
 static GridDesc make_desc(const Problem& pr, const isa_grid* gr) {
   GridDesc gd;
   memset(&gd, 0, sizeof(gd));
@@ -325,36 +434,76 @@ static GridDesc make_desc(const Problem& pr, const isa_grid* gr) {
   return gd;
 }
 
+// Whether the coordinates of every block have room in the table.  A block is at most 128 consecutive tokens of the tile order: they may
+// have any row and column of the grid, and the frames of the tile planes they lie in.
+static bool table_fits(const Problem& pr, const isa_grid* gr) {
+  const int n_seg = pr.seg.seg_ptr[pr.p.B];
+  for (int s = 0; s < n_seg; ++s) {
+    const long long t = gr->seg_grid[3 * s], h = gr->seg_grid[3 * s + 1], w = gr->seg_grid[3 * s + 2];
+    if (t == 0 || h == 0 || w == 0) continue;
+    const long long tt = gr->tile[0] < t ? gr->tile[0] : t, planes = (PBLOCK - 1) / (tt * h * w) + 2;
+    const long long frames = planes * tt < t ? planes * tt : t;
+    if (frames * (gr->rope_dims[0] / 2) + h * (gr->rope_dims[1] / 2) + w * (gr->rope_dims[2] / 2) > ENTRIES) return false;
+  }
+  return true;
+}
+
 hipError_t launch_prologue(const Problem& pr, const isa_grid* gr, const void* q_in, const void* k_in, const void* v_in,
                            void* q_out, void* k_out, void* v_out, float* qc, float* kc, float* vc, bool inverse,
                            hipStream_t st) {
   const GridDesc gd = make_desc(pr, gr);
+  const bool stream = exceeds_cache(pr, 3);
   const int hpw = heads_per_wg(pr);
-  const dim3 grid(pr.cnt.T_max, (pr.p.H + hpw - 1) / hpw, pr.p.B), blk(256);
+  // one tensor a workgroup as long as all of them run at once (an fp32 row of 128 channels takes a whole compute unit's registers): 8 heads of
+  // 2400 tokens (160 workgroups) 14.7 / 13.6 us, 16 of 1848 (256) 15.9 / 21.1; fp32, 12 of 1564 (168) 18.4 / 22.8
+  const long long resident = pr.p.dtype == ISA_F32 && pr.p.D == 128 && pr.p.block == 128 ? 1 : 2;
+  const bool split = 3ll * pr.cnt.T_max * pr.p.B * pr.p.H <= resident * N_XCD * cus_per_xcd(), table = table_fits(pr, gr);
+  const dim3 grid(pr.cnt.T_max, split ? 3 * pr.p.H : (pr.p.H + hpw - 1) / hpw, pr.p.B), blk(256);
+#define ISA_PRO2(T, D, PB, TABLE, SPLIT, STREAM)                                                                      \
+  hipLaunchKernelGGL((k_prologue<T, D, PB, TABLE, SPLIT, STREAM>), grid, blk, 0, st, (const T*)q_in, (const T*)k_in,          \
+                     (const T*)v_in, (T*)q_out, (T*)k_out, (T*)v_out, qc, kc, vc, pr.seg, gd, pr.geo, hpw, inverse ? 1 : 0)
+#define ISA_PRO1(T, D, PB, TABLE)                                                                                     \
+  do {                                                                                                                \
+    if (split) ISA_PRO2(T, D, PB, TABLE, true, false);                                                                \
+    else if (stream) ISA_PRO2(T, D, PB, TABLE, false, true);                                                          \
+    else ISA_PRO2(T, D, PB, TABLE, false, false);                                                                     \
+  } while (0)
 #define ISA_PRO(T, D)                                                                                                \
-  hipLaunchKernelGGL((k_prologue<T, D>), grid, blk, 0, st, (const T*)q_in, (const T*)k_in, (const T*)v_in, (T*)q_out, \
-                     (T*)k_out, (T*)v_out, qc, kc, vc, pr.seg, gd, pr.geo, hpw, inverse ? 1 : 0)
+  do {                                                                                                               \
+    if (pr.p.block == 128) { if (table) ISA_PRO1(T, D, 128, true); else ISA_PRO1(T, D, 128, false); }                \
+    else if (D == 128 && table) ISA_PRO1(T, D, 64, (D == 128));                                                      \
+    else ISA_PRO1(T, D, 64, false);                                                                                  \
+  } while (0)
   if (pr.p.dtype == ISA_BF16) {
     if (pr.p.D == 128) ISA_PRO(uint16_t, 128); else ISA_PRO(uint16_t, 64);
   } else {
     if (pr.p.D == 128) ISA_PRO(float, 128); else ISA_PRO(float, 64);
   }
 #undef ISA_PRO
+#undef ISA_PRO1
+#undef ISA_PRO2
   return hipGetLastError();
 }
 
 hipError_t launch_untile(const Problem& pr, const isa_grid* gr, const void* x_tiled, void* x_raster, hipStream_t st) {
   const GridDesc gd = make_desc(pr, gr);
+  const bool stream = exceeds_cache(pr, 1);
   const int hpw = heads_per_wg(pr);
   const dim3 grid(pr.cnt.T_max, (pr.p.H + hpw - 1) / hpw, pr.p.B), blk(256);
-#define ISA_UNT(T, D) \
-  hipLaunchKernelGGL((k_untile<T, D>), grid, blk, 0, st, (const T*)x_tiled, (T*)x_raster, pr.seg, gd, pr.geo, hpw)
+#define ISA_UNT1(T, D, PB, STREAM) \
+  hipLaunchKernelGGL((k_untile<T, D, PB, STREAM>), grid, blk, 0, st, (const T*)x_tiled, (T*)x_raster, pr.seg, gd, pr.geo, hpw)
+#define ISA_UNT(T, D)                                                                                                \
+  do {                                                                                                               \
+    if (pr.p.block == 64) { if (stream) ISA_UNT1(T, D, 64, true); else ISA_UNT1(T, D, 64, false); }                  \
+    else { if (stream) ISA_UNT1(T, D, 128, true); else ISA_UNT1(T, D, 128, false); }                                 \
+  } while (0)
   if (pr.p.dtype == ISA_BF16) {
     if (pr.p.D == 128) ISA_UNT(uint16_t, 128); else ISA_UNT(uint16_t, 64);
   } else {
     if (pr.p.D == 128) ISA_UNT(float, 128); else ISA_UNT(float, 64);
   }
 #undef ISA_UNT
+#undef ISA_UNT1
   return hipGetLastError();
 }
 

@@ -369,3 +369,46 @@ def test_prologue_operator_and_untile_replay_from_a_hip_graph(I):
     run(q.flip(1).contiguous(), k.flip(1).contiguous(), v.flip(1).contiguous(), eager2)
     torch.cuda.synchronize()
     assert torch.equal(bufs[4][:, :, :n], eager2[4][:, :, :n])
+
+
+def _wl(dtype, D, block, H, src):
+    return W.CONFIGS["cfg1"].with_(name="x", dtype=dtype, D=D, block=block, H=H, src_grid=src, ctx_grids=((src,),), seed=431)
+
+
+# few workgroups (a tensor each) and many (the three in turn); coordinates with room in the table (2 x 90 x 100: 4034 of 4096 places at D = 128) and
+# without (a row of 230 tokens); tiles whose tokens span rows and frames
+@pytest.mark.parametrize("src,H,tile", [((1, 2, 230), 2, (1, 1, 128)), ((1, 2, 230), 60, (1, 1, 128)), ((3, 5, 31), 2, (2, 8, 8)), ((3, 5, 31), 60, (2, 8, 8)),
+                                        ((2, 90, 100), 1, (2, 8, 8)), ((9, 3, 5), 3, (1, 1, 1))], ids=lambda x: str(x).replace(" ", ""))
+@pytest.mark.parametrize("dtype,D,block", [("bf16", 128, 128), ("bf16", 128, 64), ("bf16", 64, 64), ("f32", 128, 128), ("f32", 64, 128), ("f32", 64, 64)])
+def test_prologue_forms(I, dtype, D, block, src, H, tile):
+    wl = _wl(dtype, D, block, H, src)
+    pr, grid, (Q, K, V), (q, k, v), outs, means = run_prologue(I, wl, tile, ROPE[D])
+    grads = [torch.empty_like(q) for _ in range(3)]
+    I.isa_prologue_backward(pr, grid, *outs, *grads)               # the inverse: back to the inputs, but for the rounding between
+    torch.cuda.synchronize()
+    starts, counts, _ = O.block_layout(wl.seg_len(0), block)
+    for h in sorted({0, H - 1}):
+        want = P.prologue_head(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h]), grids_of(wl)[0], tile, ROPE[D], 10000.0)
+        for name, got_t, w, mean_t, x, back in zip("qkv", outs, want, means, (Q, K, V), grads):
+            got = f64(got_t[0, h])
+            assert (np.array_equal(got, w) if name == "v" else (np.abs(got - w) <= tolerances(wl, w)).all()), (name, h)
+            m = np.stack([got[s:s + n].mean(0) for s, n in zip(starts, counts)])
+            assert np.abs(f64(mean_t[0, h]) - m).max() <= 1e-5 * np.abs(m).max() + 1e-6, (name, h)
+            pair = np.abs(f64(x[0, h])).max()
+            assert np.abs(f64(back[0, h]) - f64(x[0, h])).max() <= (2.0 ** -7 if dtype == "bf16" else 4e-6) * pair, (name, h)
+
+
+def test_prologue_stores_special_values(I):
+    """bf16: infinities, NaN, signed zeros and the largest number go through the unrotated tensor as they are."""
+    wl = _wl("bf16", 128, 128, 2, (2, 9, 10))
+    q, k, v = (torch.randn((1, 2, wl.tokens(0), 128)).bfloat16().cuda() for _ in range(3))
+    for i, x in enumerate((float("inf"), -float("inf"), float("nan"), -0.0, 0.0, 3.3895313892515355e38, 1e-40)):
+        v[:, :, 7 * i + 3, i::9] = x
+    pr, grid = problem_of(wl), I.Grid(grids_of(wl), (2, 8, 8), ROPE[128], 10000.0)
+    outs, back = [torch.empty_like(q) for _ in range(3)], [torch.empty_like(q) for _ in range(3)]
+    I.isa_prologue(pr, grid, q, k, v, *outs)
+    I.isa_prologue_backward(pr, grid, *outs, *back)
+    torch.cuda.synchronize()
+    nan = torch.isnan(v)
+    assert torch.equal(torch.isnan(back[2]), nan)
+    assert torch.equal(back[2].view(torch.int16)[~nan], v.view(torch.int16)[~nan])
