@@ -66,8 +66,14 @@ __global__ __launch_bounds__(256) void k_pack_vt(const uint16_t* __restrict__ v,
 #pragma unroll
   for (int t = 0; t < NX; ++t)
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      val[t][i] = rg + 16 * i < n ? *reinterpret_cast<const uint4*>(src[t] + base + (long long)(rg + 16 * i) * g.stride_t) : make_uint4(0, 0, 0, 0);
+    for (int i = 0; i < 8; ++i) {
+      const uint16_t* const row = src[t] + base + (long long)(rg + 16 * i) * g.stride_t;
+      val[t][i] = make_uint4(0, 0, 0, 0);
+      if (rg + 16 * i < n) {              // the values are not read again: the attention kernels read the packed copy
+        if (t == 0) val[t][i] = stream_load(row);
+        else val[t][i] = *reinterpret_cast<const uint4*>(row);
+      }
+    }
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[rg + 16 * i][c * 8]);
