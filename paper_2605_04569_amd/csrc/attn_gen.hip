@@ -2,16 +2,19 @@
 // block = 128 kernels do not cover (and those too when they are switched off): exact online-softmax attention (Alg. 2
 // Part A), block-wise 0-th order Taylor attention with and without exact sets (Sec. 3, Eq. 3-4; Alg. 2 Parts A+B), dense.
 //
-// Precision: everything that a plain fp32 evaluation holds in fp32 keeps its 24 bits here.
+// Precision: every number that a plain fp32 evaluation holds in fp32 is held in 24 bits here, down to about 2^-110.
 //   fp32 tensors: queries, keys, values, means and weights are cut into three bf16 terms of 8 bits each whose sum is the number, and a
-//     product is the sum of six products of terms (v_mfma_f32_16x16x32_bf16; middle x low and low x low, below 2^-22 of it, are left
-//     out).  An item with a number whose terms have lost bits (below about 2^-110) is run again with v_mfma_f32_16x16x4_f32.  Error against 64
-//     bits on fp32 matrix instructions / in terms, 2-norm: 8 heads of 5280 tokens 5.8e-7 / 3.7e-7, dense 2.5e-6 / 2.1e-6, 24 heads of 15 600
-//     4.7e-6 / 4.1e-6, D = 64 4.6e-6 / 4.0e-6 (an instruction adds 32 products where one on fp32 adds 4).
+//     product is the sum of six products of terms (v_mfma_f32_16x16x32_bf16).  Left out are middle x low and low x low: the terms are rounded
+//     to nearest, so these are at most 2^-24 of the product of the leading bits, of either sign (with terms cut off up to 2^-21, always towards
+//     zero).  An item with a number whose terms have lost bits (below about 2^-110) is run again with v_mfma_f32_16x16x4_f32.  A weight that small,
+//     against the row's largest, loses less than 2^-133 of that one, unchecked: a part of the result only where the heavier keys' values are 0.
+//     Error against 64 bits of dense attention on fp32 matrix instructions / in terms, 2-norm: 2000 random tokens, D = 128, 9.2e-7 / 5.6e-7, D = 64
+//     6.6e-7 / 4.8e-7; one massive channel beside random ones 1.1e-5 / 6.0e-6; scores of a single channel's product 1.46e-6 / 1.44e-6 (with
+//     terms cut off 2.7e-6), 300 tokens 1.25e-6 / 1.30e-6 (an instruction adds 32 products where one on fp32 adds 4).
 //   bf16 tensors: scores of tokens with v_mfma_f32_16x16x32_bf16 (products of bf16 numbers are exact in fp32); the softmax
 //     weights and the fp32 block means are cut into three bf16 terms whose sum is the fp32 number (8 bits each), and
 //     the product is the sum of the terms' products: 3 matrix instructions for weights x tokens, 3 for queries x means, 8
-//     for weights x means (the term low x low, below 2^-32 of the result, is left out).
+//     for weights x means (the term low x low, below 2^-30 of the product, is left out; a mean below 2^-110 loses less than 2^-133, unchecked).
 //
 // Shape.  A workgroup of 4 waves owns 64 QT query rows, QT 16-query tiles per wave (QT = 1 when a launch has so few rows
 // that 128 a workgroup would leave compute units idle).  With r = lane % 16, g = lane / 16 the scores are computed
@@ -99,26 +102,33 @@ __device__ __forceinline__ f32x4 mfma_f(float a, float b, f32x4 c) {
 }
 __device__ __forceinline__ float bits_f(uint32_t u) { return __uint_as_float(u); }
 
-// Eight fp32 numbers as three bf16 fragments that add up to them: every term is the leading 8 bits of what the terms before it
-// left over (cut off, not rounded, so the differences are exact and the third term ends at bit 24).  Returns a word whose low half is 0
-// unless a number is so small that its third term has lost bits.
-__device__ __forceinline__ uint32_t split3(const float (&x)[8], bf16x8 (&t)[3]) {
+// Eight fp32 numbers as three bf16 fragments that add up to them: a term is the leading 8 bits of what the terms before it left over, so that the
+// differences are exact and the third term ends at bit 24.  ROUND: the first two terms are rounded to nearest instead of cut off: then the middle is at
+// most 2^-8 and the low 2^-17 of the leading bit, and of either sign (cut off: 2^-7 and 2^-15, of the number's sign), which is what products
+// need that leave out the smallest ones.  Returns a word whose low half is 0 unless a number is so small that its third term has lost bits.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+template <bool ROUND> __device__ __forceinline__ uint32_t lead8(float a, float b) {        // a below, b above
+  if constexpr (ROUND) {
+    const bf16x2 r = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, r);
+  } else {
+    return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+  }
+}
+template <bool ROUND> __device__ __forceinline__ uint32_t split3(const float (&x)[8], bf16x8 (&t)[3]) {
 #pragma clang fp contract(off)                         // of the numbers as they are, not of a product they come from
   uint32_t w[3][4], rest = 0;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     float a = x[2 * e], b = x[2 * e + 1];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-      w[k][e] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);              // high halves: a below, b above
-      if (k < 2) {
-        a -= bits_f(ua & 0xffff0000u);
-        b -= bits_f(ub & 0xffff0000u);
-      } else {
-        rest |= ua | ub;
-      }
+    for (int k = 0; k < 2; ++k) {
+      w[k][e] = lead8<ROUND>(a, b);
+      a -= bits_f(ROUND ? w[k][e] << 16 : __float_as_uint(a) & 0xffff0000u);
+      b -= bits_f((ROUND ? w[k][e] : __float_as_uint(b)) & 0xffff0000u);
     }
+    w[2][e] = lead8<false>(a, b);
+    rest |= __float_as_uint(a) | __float_as_uint(b);
   }
 #pragma unroll
   for (int k = 0; k < 3; ++k) t[k] = __builtin_bit_cast(bf16x8, make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]));
@@ -132,14 +142,14 @@ __device__ __forceinline__ bf16x8 minus_ones(int u, int r16, int g) {
   const uint32_t lo = r16 & 2 ? 0u : one, hi = r16 & 2 ? one : 0u;
   return __builtin_bit_cast(bf16x8, u ? make_uint4(0u, 0u, lo, hi) : make_uint4(lo, hi, 0u, 0u));
 }
-__device__ __forceinline__ void split3(f32x4 x0, f32x4 x1, const bf16x8 (&minus)[2], bf16x8 (&t)[3]) {
+template <bool ROUND> __device__ __forceinline__ void split3(f32x4 x0, f32x4 x1, const bf16x8 (&minus)[2], bf16x8 (&t)[3]) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     uint32_t w[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const f32x4& x = e < 2 ? x0 : x1;
-      w[e] = __builtin_amdgcn_perm(__float_as_uint(x[2 * (e & 1) + 1]), __float_as_uint(x[2 * (e & 1)]), 0x07060302u);
+      const float a = (e < 2 ? x0 : x1)[2 * (e & 1)], b = (e < 2 ? x0 : x1)[2 * (e & 1) + 1];
+      w[e] = k < 2 ? lead8<ROUND>(a, b) : lead8<false>(a, b);
     }
     t[k] = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
     if (k < 2) {
@@ -248,7 +258,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 #pragma unroll
           for (int i = 0; i < 4; ++i) x[4 * u + i] = y[i];
         }
-        cut_off |= split3(x, q3[qt][ks]);
+        cut_off |= split3<true>(x, q3[qt][ks]);
       }
     } else {
 #pragma unroll
@@ -424,7 +434,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
           for (int u = 0; u < 3; ++u)
             k3[kt][u] = *reinterpret_cast<const bf16x8*>(kb + u * PLANE + ((16 * kt + rm) * CP + ((4 * ks + gm) ^ (rm & SP))) * 16);
 #pragma unroll
-        for (int u = 2; u >= 0; --u)                   // the smallest first; terms below 2^-22 of a product are left out
+        for (int u = 2; u >= 0; --u)                   // the smallest first
 #pragma unroll
           for (int w = 2 - u; w >= 0; --w)
 #pragma unroll
@@ -508,7 +518,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
             }
           } else {
             bf16x8 k3[3];
-            split3(x, k3);
+            split3<false>(x, k3);
 #pragma unroll
             for (int u = 2; u >= 0; --u)
 #pragma unroll
@@ -588,7 +598,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         bf16x8 p3[QT][3];
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) {
-          split3(p[qt][0], p[qt][1], minus, p3[qt]);
+          split3<true>(p[qt][0], p[qt][1], minus, p3[qt]);
           asm volatile("" : "+v"(p3[qt][0]), "+v"(p3[qt][1]), "+v"(p3[qt][2]), "+v"(l_run[qt]));      // before the barriers, not where they are used
         }
         ISA_GEN_FENCE();
@@ -659,7 +669,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
       } else {
         bf16x8 p3[QT][3];
 #pragma unroll
-        for (int qt = 0; qt < QT; ++qt) split3(p[qt][0], p[qt][1], minus, p3[qt]);
+        for (int qt = 0; qt < QT; ++qt) split3<false>(p[qt][0], p[qt][1], minus, p3[qt]);
         if constexpr (!mean) {
           const int tr_row = 4 * g + (r16 >> 2);         // see the transposed reads of the backward kernel
           if constexpr (D == 64) __builtin_amdgcn_s_setprio(1);
@@ -693,7 +703,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
               x[e] = *reinterpret_cast<const float*>(vb + (row * CM + ((4 * ct + (rm >> 2)) ^ (row & SM))) * 16 + (rm & 3) * 4);
             }
             bf16x8 v3[3];
-            split3(x, v3);
+            split3<false>(x, v3);
 #pragma unroll
             for (int u = 2; u >= 0; --u)
 #pragma unroll
@@ -743,7 +753,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         for (int e = 0; e < 4; ++e) x[4 * u + e] = y[e];
       }
       bf16x8 t[3];
-      cut_off |= split3(x, t);
+      cut_off |= split3<true>(x, t);
       asm volatile("" : "+v"(cut_off));                // here, not where it is read
 #pragma unroll
       for (int u = 0; u < 3; ++u) *reinterpret_cast<bf16x8*>(lds + 2 * TILE + u * PLANE + (row * CP + ((p % CP) ^ (row & SP))) * 16) = t[u];

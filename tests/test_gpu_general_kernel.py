@@ -383,6 +383,50 @@ F32 = [x for x in SHAPES if x[0] == "f32"]
 F32_IDS = [i for i in SHAPE_IDS if i[:3] == "f32"]
 
 
+# Numbers whose 24 bits leave much behind the first 8: 1 + 2^-7 - r 2^-23
+@pytest.mark.parametrize("H", [2, 300], ids=["narrow", "wide"])
+@pytest.mark.parametrize("shape", F32, ids=F32_IDS)
+def test_fp32_scores_of_one_channel(I, shape, H):
+    """Every other key has such a number in one channel, the others 1 in it and the rest in a second, so that all scores of a row are alike (63 to
+    127 in the log2 domain) and values of 1 and -1 cancel.  A score's sum is rounded once, by at most 2^-18, and the left-out terms are at most
+    2^-24 of a power of two of up to 64: three times 2^-18 between the two kinds of key, ln 2 / 2 of that in the result."""
+    D, n = shape[1], 300
+    g = torch.Generator().manual_seed(803)
+    q, k, v = (torch.zeros((1, H, n, D)) for _ in range(3))
+    odd = torch.arange(n) % 2 == 1
+    q[..., 0] = 44 * D ** 0.5 * (1 + 0.99 * torch.rand((1, H, n), generator=g))
+    q[..., 1] = q[..., 0]
+    r = torch.randint(1, 4096, (1, H, n // 2), generator=g) * 2.0 ** -23
+    k[:, :, odd, 0], k[:, :, ~odd, 0] = 1 + 2.0 ** -7 - r, 1.0
+    k[:, :, ~odd, 1] = 2.0 ** -7 - r
+    v[:, :, odd], v[:, :, ~odd] = 1.0, -1.0
+    pr = I.Problem(H=H, D=D, dtype="f32", block=shape[2], seg_len=[[n]], keep_ratio=1.0, full_frac=1.0)
+    out = torch.empty((1, H, n, D), device="cuda")
+    I.isa_dense_attention(pr, q.cuda(), k.cuda(), v.cuda(), out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    assert out.abs().max().item() <= 3 * 2.0 ** -18 * np.log(2.0) / 2
+
+
+@pytest.mark.parametrize("H", [2, 300], ids=["narrow", "wide"])
+@pytest.mark.parametrize("shape", F32, ids=F32_IDS)
+def test_fp32_weighted_values_of_one_key(I, shape, H):
+    """One key alone has values, 1 in channel 0 and such a number in channel 1: whatever its weights, the results have this ratio.  Off by the
+    roundings of the sum and of both results and by the left-out terms, at most 2^-24 each; on average by nothing."""
+    D, n = shape[1], 300
+    g = torch.Generator().manual_seed(805)
+    q, k = (torch.randn((1, H, n, D), generator=g) for _ in range(2))
+    v = torch.zeros((1, H, n, D))
+    v[:, :, 77, 0], v[:, :, 77, 1] = 1.0, 1 + 2.0 ** -7 - 2.0 ** -23
+    pr = I.Problem(H=H, D=D, dtype="f32", block=shape[2], seg_len=[[n]], keep_ratio=1.0, full_frac=1.0)
+    out = torch.empty((1, H, n, D), device="cuda")
+    I.isa_dense_attention(pr, q.cuda(), k.cuda(), v.cuda(), out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    o = f64(out)
+    off = o[..., 1] / o[..., 0] / v[0, 0, 77, 1].double().item() - 1
+    assert abs(off.mean()) <= 2.0 ** -24, off.mean()
+    assert np.abs(off).max() <= 4 * 2.0 ** -24, np.abs(off).max()
+
+
 # fp32, enough heads for 128-row workgroups: odd lists of blocks (a pair with one), short blocks, exact sets of both blocks of a pair, a ragged
 # batch; with full_frac 0 Taylor blocks alone
 @pytest.mark.parametrize("full_frac,exact_frac", [(0.6, 0.0), (0.6, 0.25), (0.0, 0.0), (0.0, 0.25)])
