@@ -83,13 +83,17 @@ __device__ inline void tile_coords(int p, int t, int h, int w, int tt, int th, i
   *cw = c * tw + (p - lh * sw);
 }
 
-// Stores, and loads of more than the last-level cache holds, are streamed (nontemporal): nothing of them is found there again before it is
-// pushed out, and what they would push out is.  isa_prologue, isa_untile and isa_prologue_backward together, us, neither / stores /
-// both: 40 heads of 39 680 tokens (1.2 GB of queries, keys and values) 1030 / 1003 / 926, 20 heads of 15 600 (240 MB) 217 / 184 / 198.
+// Rows of long calls are streamed (nontemporal): loads of more than the last-level cache holds, and stores of so much that little of it is found
+// there by what reads it next.  Chains, us, cached / streamed stores: copy into q, k, v - isa_prologue - isa_attention - isa_untile - copy of its
+// output, 40 heads of 3168 tokens (32 MB a tensor) 222 / 229, 24 of 10 400 (64) 543 / 542, 20 of 15 600 (80) 800 / 794, 40 of 15 600 (160)
+// 1540 / 1501; the same with inputs from memory 183 / 190, 464 / 480, 703 / 711, 1365 / 1334.  The three calls over and over on the same
+// buffers, whose outputs nothing reads: 20 of 6240 (32 MB) 83 / 79, 20 of 15 600 215 / 182, with streamed loads as well 198; 40 of 39 680 (1.2 GB of q, k, v)
+// 1030 / 1003 / 926.
 constexpr long long CACHE_BYTES = 256ll << 20;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void store16(void* p, uint32_t x, uint32_t y, uint32_t z, uint32_t w) {
-  __builtin_nontemporal_store(u32x4{x, y, z, w}, reinterpret_cast<u32x4*>(p));
+template <bool STREAM> __device__ __forceinline__ void store16(void* p, uint32_t x, uint32_t y, uint32_t z, uint32_t w) {
+  if constexpr (STREAM) __builtin_nontemporal_store(u32x4{x, y, z, w}, reinterpret_cast<u32x4*>(p));
+  else *reinterpret_cast<u32x4*>(p) = u32x4{x, y, z, w};
 }
 template <bool STREAM> __device__ __forceinline__ uint4 load16(const void* p) {
   const u32x4* const q = reinterpret_cast<const u32x4*>(p);
@@ -106,8 +110,8 @@ template <> struct Row16<float> {
   __device__ static void unpack(const uint4& v, float* o) {
     o[0] = __uint_as_float(v.x); o[1] = __uint_as_float(v.y); o[2] = __uint_as_float(v.z); o[3] = __uint_as_float(v.w);
   }
-  __device__ static void store(float* p, float* o) {       // o is left holding the stored values
-    store16(p, __float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3]));
+  template <bool STREAM> __device__ static void store(float* p, float* o) {       // o is left holding the stored values
+    store16<STREAM>(p, __float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3]));
   }
 };
 template <> struct Row16<uint16_t> {   // bf16 storage
@@ -120,7 +124,7 @@ template <> struct Row16<uint16_t> {   // bf16 storage
       o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
   }
-  __device__ static void store(uint16_t* p, float* o) {    // o is left holding the rounded values
+  template <bool STREAM> __device__ static void store(uint16_t* p, float* o) {    // o is left holding the rounded values
     uint32_t w[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -129,7 +133,7 @@ template <> struct Row16<uint16_t> {   // bf16 storage
       o[2 * i] = __uint_as_float(w[i] << 16);
       o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
-    store16(p, w[0], w[1], w[2], w[3]);
+    store16<STREAM>(p, w[0], w[1], w[2], w[3]);
   }
 };
 
@@ -141,7 +145,7 @@ __device__ __forceinline__ void load_rows(uint4 (&raw)[TPT], const T* ip, const 
 }
 
 // Rotates (if asked), stores and sums the rows that load_rows brought in; acc receives the column sums of what was stored.
-template <typename T, int TPT, int NP>
+template <typename T, int TPT, int NP, bool STREAM>
 __device__ __forceinline__ void finish_rows(const uint4 (&raw)[TPT], const float (&cs)[TPT][NP], const float (&sn)[TPT][NP],
                                             bool rotate, unsigned valid, T* op, const int (&dst)[TPT], long long stride_t,
                                             float (&acc)[2 * NP]) {
@@ -160,7 +164,7 @@ __device__ __forceinline__ void finish_rows(const uint4 (&raw)[TPT], const float
       }
     }
     if (valid >> tk & 1) {
-      Row16<T>::store(op + (long long)dst[tk] * stride_t, x);
+      Row16<T>::template store<STREAM>(op + (long long)dst[tk] * stride_t, x);
 #pragma unroll
       for (int i = 0; i < 2 * NP; ++i) acc[i] += x[i];
     }
@@ -189,8 +193,8 @@ __device__ __forceinline__ int wave_extreme(int x) {
 // SPLIT: a workgroup takes one of the three tensors.  PB: the block, so that a thread has no rows that a block of 64 has not.
 // All three, and roundings of one instruction, us (isa_prologue; before / after): bf16, 5 heads of 440 tokens 19.3 / 9.7, 16 of 1848 22.1 /
 // 15.9, 8 of 15 600 47 / 35.5; blocks of 64, 12 of 2704 28 / 17, D = 64 12 of 7920 25 / 19; fp32, 4 of 39 680 117 / 101.
-// STREAM: load16, above.
-template <typename T, int D, int PB, bool TABLE, bool SPLIT, bool STREAM>
+// LOADS, STORES: streamed, see load16 and store16.
+template <typename T, int D, int PB, bool TABLE, bool SPLIT, bool LOADS, bool STORES>
 __global__ __launch_bounds__(256) void k_prologue(const T* __restrict__ q_in, const T* __restrict__ k_in,
                                                   const T* __restrict__ v_in, T* __restrict__ q_out,
                                                   T* __restrict__ k_out, T* __restrict__ v_out,
@@ -252,7 +256,7 @@ __global__ __launch_bounds__(256) void k_prologue(const T* __restrict__ q_in, co
   // Two sets of landing registers: the rows of pass it + 1 are in flight while pass it is rotated and stored.
   uint4 raw0[TPT], raw1[TPT];
 #define ISA_IN_PTR(it) ((((it) % 3) == 0 ? q_in : ((it) % 3) == 1 ? k_in : v_in) + base0 + (long long)((it) / 3) * g.stride_h)
-  load_rows<T, TPT, STREAM>(raw0, ISA_IN_PTR(first_it), src, g.stride_t);
+  load_rows<T, TPT, LOADS>(raw0, ISA_IN_PTR(first_it), src, g.stride_t);
 
   // the thread's channel pairs: which coordinate turns them, and how fast; then the sines and cosines of its rows
   // (computed while the first rows are on their way)
@@ -342,7 +346,7 @@ __global__ __launch_bounds__(256) void k_prologue(const T* __restrict__ q_in, co
   {                                                                                                                   \
     const int t_ = (it) % 3, hh_ = (it) / 3;                                                                          \
     float acc_[VEC];                                                                                                  \
-    finish_rows<T, TPT, NP>(RAW, cs, sn, t_ < 2, valid,                                                               \
+    finish_rows<T, TPT, NP, STORES>(RAW, cs, sn, t_ < 2, valid,                                                       \
                             (t_ == 0 ? q_out : t_ == 1 ? k_out : v_out) + base0 + (long long)hh_ * g.stride_h,         \
                             dst, g.stride_t, acc_);                                                                    \
     if (means) {                                                                                                      \
@@ -357,10 +361,10 @@ __global__ __launch_bounds__(256) void k_prologue(const T* __restrict__ q_in, co
     }                                                                                                                 \
   }
   for (int it = first_it; it < n_it; it += 2) {
-    if (it + 1 < n_it) load_rows<T, TPT, STREAM>(raw1, ISA_IN_PTR(it + 1), src, g.stride_t);
+    if (it + 1 < n_it) load_rows<T, TPT, LOADS>(raw1, ISA_IN_PTR(it + 1), src, g.stride_t);
     ISA_PASS(raw0, 0, it)
     if (it + 1 < n_it) {
-      if (it + 2 < n_it) load_rows<T, TPT, STREAM>(raw0, ISA_IN_PTR(it + 2), src, g.stride_t);
+      if (it + 2 < n_it) load_rows<T, TPT, LOADS>(raw0, ISA_IN_PTR(it + 2), src, g.stride_t);
       ISA_PASS(raw1, 1, it + 1)
     }
   }
@@ -369,7 +373,7 @@ __global__ __launch_bounds__(256) void k_prologue(const T* __restrict__ q_in, co
 }
 
 // Inverse reordering of one tensor: token p of the tile order goes back to its row-major place.
-template <typename T, int D, int PB, bool STREAM>
+template <typename T, int D, int PB, bool LOADS, bool STORES>
 __global__ __launch_bounds__(256) void k_untile(const T* __restrict__ x_tiled, T* __restrict__ x_raster, SegDesc seg,
                                                 GridDesc gd, Geometry g, int hpw) {
   constexpr int VEC = Row16<T>::N;
@@ -398,11 +402,11 @@ __global__ __launch_bounds__(256) void k_untile(const T* __restrict__ x_tiled, T
 #pragma unroll
     for (int tk = 0; tk < TPT; ++tk) {      // rows past the block's end re-read its first row and are not stored
       const int row = src[tk] >= 0 ? bp.start + rg + tk * RP : bp.start;
-      x[tk] = load16<STREAM>(x_tiled + base + (long long)row * g.stride_t);
+      x[tk] = load16<LOADS>(x_tiled + base + (long long)row * g.stride_t);
     }
 #pragma unroll
     for (int tk = 0; tk < TPT; ++tk)
-      if (src[tk] >= 0) store16(x_raster + base + (long long)src[tk] * g.stride_t, x[tk].x, x[tk].y, x[tk].z, x[tk].w);
+      if (src[tk] >= 0) store16<STORES>(x_raster + base + (long long)src[tk] * g.stride_t, x[tk].x, x[tk].y, x[tk].z, x[tk].w);
   }
 }
 
@@ -416,7 +420,9 @@ static int heads_per_wg(const Problem& pr) {
   return (int)hpw;
 }
 
-// Whether `tensors` of the problem's tensors are more than the last-level cache holds.
+// Stores are streamed from tensors of 64 MB on (see store16)
+constexpr int STORE_TENSORS = 4;
+// Whether `tensors` of the problem's tensors have more bytes than the last-level cache.
 static bool exceeds_cache(const Problem& pr, int tensors) {
   long long rows = 0;
   for (int b = 0; b < pr.p.B; ++b) rows += pr.cnt.b[b].S;
@@ -452,21 +458,22 @@ hipError_t launch_prologue(const Problem& pr, const isa_grid* gr, const void* q_
                            void* q_out, void* k_out, void* v_out, float* qc, float* kc, float* vc, bool inverse,
                            hipStream_t st) {
   const GridDesc gd = make_desc(pr, gr);
-  const bool stream = exceeds_cache(pr, 3);
+  const bool loads = exceeds_cache(pr, 3), stores = exceeds_cache(pr, STORE_TENSORS);
   const int hpw = heads_per_wg(pr);
   // one tensor a workgroup as long as all of them run at once (an fp32 row of 128 channels takes a whole compute unit's registers): 8 heads of
   // 2400 tokens (160 workgroups) 14.7 / 13.6 us, 16 of 1848 (256) 15.9 / 21.1; fp32, 12 of 1564 (168) 18.4 / 22.8
   const long long resident = pr.p.dtype == ISA_F32 && pr.p.D == 128 && pr.p.block == 128 ? 1 : 2;
   const bool split = 3ll * pr.cnt.T_max * pr.p.B * pr.p.H <= resident * N_XCD * cus_per_xcd(), table = table_fits(pr, gr);
   const dim3 grid(pr.cnt.T_max, split ? 3 * pr.p.H : (pr.p.H + hpw - 1) / hpw, pr.p.B), blk(256);
-#define ISA_PRO2(T, D, PB, TABLE, SPLIT, STREAM)                                                                      \
-  hipLaunchKernelGGL((k_prologue<T, D, PB, TABLE, SPLIT, STREAM>), grid, blk, 0, st, (const T*)q_in, (const T*)k_in,          \
+#define ISA_PRO2(T, D, PB, TABLE, SPLIT, LOADS, STORES)                                                               \
+  hipLaunchKernelGGL((k_prologue<T, D, PB, TABLE, SPLIT, LOADS, STORES>), grid, blk, 0, st, (const T*)q_in, (const T*)k_in,   \
                      (const T*)v_in, (T*)q_out, (T*)k_out, (T*)v_out, qc, kc, vc, pr.seg, gd, pr.geo, hpw, inverse ? 1 : 0)
 #define ISA_PRO1(T, D, PB, TABLE)                                                                                     \
   do {                                                                                                                \
-    if (split) ISA_PRO2(T, D, PB, TABLE, true, false);                                                                \
-    else if (stream) ISA_PRO2(T, D, PB, TABLE, false, true);                                                          \
-    else ISA_PRO2(T, D, PB, TABLE, false, false);                                                                     \
+    if (split) ISA_PRO2(T, D, PB, TABLE, true, false, false);                                                         \
+    else if (loads) ISA_PRO2(T, D, PB, TABLE, false, true, true);                                                     \
+    else if (stores) ISA_PRO2(T, D, PB, TABLE, false, false, true);                                                   \
+    else ISA_PRO2(T, D, PB, TABLE, false, false, false);                                                              \
   } while (0)
 #define ISA_PRO(T, D)                                                                                                \
   do {                                                                                                               \
@@ -487,15 +494,20 @@ hipError_t launch_prologue(const Problem& pr, const isa_grid* gr, const void* q_
 
 hipError_t launch_untile(const Problem& pr, const isa_grid* gr, const void* x_tiled, void* x_raster, hipStream_t st) {
   const GridDesc gd = make_desc(pr, gr);
-  const bool stream = exceeds_cache(pr, 1);
+  const bool loads = exceeds_cache(pr, 1), stores = exceeds_cache(pr, STORE_TENSORS);
   const int hpw = heads_per_wg(pr);
   const dim3 grid(pr.cnt.T_max, (pr.p.H + hpw - 1) / hpw, pr.p.B), blk(256);
-#define ISA_UNT1(T, D, PB, STREAM) \
-  hipLaunchKernelGGL((k_untile<T, D, PB, STREAM>), grid, blk, 0, st, (const T*)x_tiled, (T*)x_raster, pr.seg, gd, pr.geo, hpw)
+#define ISA_UNT2(T, D, PB, LOADS, STORES) \
+  hipLaunchKernelGGL((k_untile<T, D, PB, LOADS, STORES>), grid, blk, 0, st, (const T*)x_tiled, (T*)x_raster, pr.seg, gd, pr.geo, hpw)
+#define ISA_UNT1(T, D, PB)                                                                                           \
+  do {                                                                                                               \
+    if (loads) ISA_UNT2(T, D, PB, true, true);                                                                       \
+    else if (stores) ISA_UNT2(T, D, PB, false, true);                                                                \
+    else ISA_UNT2(T, D, PB, false, false);                                                                           \
+  } while (0)
 #define ISA_UNT(T, D)                                                                                                \
   do {                                                                                                               \
-    if (pr.p.block == 64) { if (stream) ISA_UNT1(T, D, 64, true); else ISA_UNT1(T, D, 64, false); }                  \
-    else { if (stream) ISA_UNT1(T, D, 128, true); else ISA_UNT1(T, D, 128, false); }                                 \
+    if (pr.p.block == 64) ISA_UNT1(T, D, 64); else ISA_UNT1(T, D, 128);                                              \
   } while (0)
   if (pr.p.dtype == ISA_BF16) {
     if (pr.p.D == 128) ISA_UNT(uint16_t, 128); else ISA_UNT(uint16_t, 64);
@@ -504,6 +516,7 @@ hipError_t launch_untile(const Problem& pr, const isa_grid* gr, const void* x_ti
   }
 #undef ISA_UNT
 #undef ISA_UNT1
+#undef ISA_UNT2
   return hipGetLastError();
 }
 

@@ -398,6 +398,33 @@ def test_prologue_forms(I, dtype, D, block, src, H, tile):
             assert np.abs(f64(back[0, h]) - f64(x[0, h])).max() <= (2.0 ** -7 if dtype == "bf16" else 4e-6) * pair, (name, h)
 
 
+# rows cached (below 64 MB a tensor), stores streamed (prologue to 85 MB, isa_untile to 256 MB), loads too: the same bits as a call of one head; with the
+# table of sines and without
+@pytest.mark.parametrize("mb", [60, 72, 100, 270])
+@pytest.mark.parametrize("src,tile", [((3, 5, 31), (2, 8, 8)), ((1, 2, 230), (1, 1, 128))], ids=["table", "no_table"])
+@pytest.mark.parametrize("dtype,D,block", [("bf16", 128, 128), ("bf16", 128, 64), ("bf16", 64, 64), ("f32", 128, 128), ("f32", 64, 128), ("f32", 64, 64)])
+def test_streamed_rows_are_the_same(I, dtype, D, block, src, tile, mb):
+    wl = _wl(dtype, D, block, 1, src)
+    n = wl.tokens(0)
+    H = mb * 2 ** 20 // (n * D * (2 if dtype == "bf16" else 4))
+    g = torch.Generator(device="cuda").manual_seed(433)
+    one = [torch.randn((1, 1, n, D), generator=g, device="cuda").to(W.torch_dtype(dtype)) for _ in range(3)]
+    res = []
+    for h in (1, H):
+        x = [t.expand(1, h, n, D).contiguous() for t in one]
+        pr, grid = problem_of(wl, H=h), I.Grid(grids_of(wl), tile, ROPE[D], 10000.0)
+        outs, back = [torch.empty_like(t) for t in x], [torch.empty_like(t) for t in x]
+        raster = torch.empty_like(x[0])
+        means = [torch.empty((1, h, I.isa_get_counts(pr, 0)["T_max"], D), device="cuda") for _ in range(3)]
+        I.isa_prologue(pr, grid, *x, *outs, *means)
+        I.isa_untile(pr, grid, outs[0], raster)
+        I.isa_prologue_backward(pr, grid, *outs, *back)
+        res.append([*outs, raster, *back, *means])
+    torch.cuda.synchronize()
+    for i, (a, b) in enumerate(zip(*res)):
+        assert torch.equal(a.expand_as(b), b), i
+
+
 def test_prologue_stores_special_values(I):
     """bf16: infinities, NaN, signed zeros and the largest number go through the unrotated tensor as they are."""
     wl = _wl("bf16", 128, 128, 2, (2, 9, 10))
