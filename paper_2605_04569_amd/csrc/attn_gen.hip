@@ -915,9 +915,9 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         if (oc) r[i] = fmaf(a.gamma, oc[ch + i], r[i]);
       }
       if constexpr (BF) {
-        store_row(op + ch, make_uint2(f2bf(r[0]) | ((uint32_t)f2bf(r[1]) << 16), f2bf(r[2]) | ((uint32_t)f2bf(r[3]) << 16)), a.geo.stride_t == D);
+        *reinterpret_cast<uint2*>(op + ch) = make_uint2(f2bf(r[0]) | ((uint32_t)f2bf(r[1]) << 16), f2bf(r[2]) | ((uint32_t)f2bf(r[3]) << 16));
       } else {
-        store_row(op + ch, make_uint4(__float_as_uint(r[0]), __float_as_uint(r[1]), __float_as_uint(r[2]), __float_as_uint(r[3])), a.geo.stride_t == D);
+        *reinterpret_cast<float4*>(op + ch) = make_float4(r[0], r[1], r[2], r[3]);
       }
     }
   }

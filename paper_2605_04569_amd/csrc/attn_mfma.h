@@ -18,33 +18,15 @@ constexpr int V_TILE = MD * KT;   // bf16 elements of one V^T tile in LDS: 128 r
 constexpr float RESCALE_TAU = 8.0f;    // the running max is only raised when a tile exceeds it by 2^tau
 constexpr float M_INIT = -1.0e30f;
 
-// Rows that a call reads or writes once and nothing of it needs again go past the caches, where they would push out the keys and values that
-// other workgroups read: the values that are packed (whole calls, us, cached / streamed: 20 heads of 6240 tokens 124.8 / 122.8, 40 of 15 600 1082 /
-// 1072), and the output rows of k_attn_gen where a head's rows lie one after the other (40 heads of 64 channels, Taylor blocks, 467 / 460; fp32, 8
-// of 5280 189 / 187).  Left as they are: output rows of k_attn_sp (faster by 2 to 7 % where rows lie one after the other, slower by 1 to 2
-// where a token's stride lies between them, and both in one kernel spill 11 registers), of k_attn_mfma (20 heads of 15 600 at the paper's ratios
-// 784 / 818), gradients (40 of 15 600 4424 / 4462).
-typedef uint32_t u32x2_mem __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4_mem __attribute__((ext_vector_type(4)));
+// A load without a place in the caches: for the values that k_pack_vt packs, which would push out the keys that other workgroups read (the
+// attention kernels of the call read the packed copy).  Whole calls behind each other on changing inputs, us, cached / streamed: 20 heads of 6240 tokens
+// 189.5 / 186.8, 40 of 3168 146.5 / 142.9, 40 of 15 600 1166 / 1158; a training step, whose backward reads the values again: the same time.
+// Not so the output rows of k_attn_gen: alone, calls on contiguous heads were 1 to 2 % quicker past the caches, but what reads the output next finds
+// nothing there: with isa_untile and a copy behind it 24 heads of 3168, 64 channels, streamed / cached 89.6 / 88.2, fp32, 8 of 5280, 215.9 / 212.5.
 __device__ __forceinline__ uint4 stream_load(const void* p) {
+  typedef uint32_t u32x4_mem __attribute__((ext_vector_type(4)));
   const u32x4_mem r = __builtin_nontemporal_load(reinterpret_cast<const u32x4_mem*>(p));
   return make_uint4(r.x, r.y, r.z, r.w);
-}
-__device__ __forceinline__ void stream_store(void* p, uint4 x) {
-  __builtin_nontemporal_store(u32x4_mem{x.x, x.y, x.z, x.w}, reinterpret_cast<u32x4_mem*>(p));
-}
-__device__ __forceinline__ void stream_store(void* p, uint2 x) {
-  __builtin_nontemporal_store(u32x2_mem{x.x, x.y}, reinterpret_cast<u32x2_mem*>(p));
-}
-
-// stream: the same for every lane.  (The empty statement keeps the compiler from making one ordinary store of the two.)
-template <typename X> __device__ __forceinline__ void store_row(void* p, X x, bool stream) {
-  if (stream) {
-    stream_store(p, x);
-    asm volatile("");
-  } else {
-    *reinterpret_cast<X*>(p) = x;
-  }
 }
 
 __device__ inline uint16_t f2bf(float f) {     // round to nearest even
