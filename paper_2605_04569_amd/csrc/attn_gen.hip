@@ -6,7 +6,8 @@
 //   fp32 tensors: queries, keys, values, means and weights are cut into three bf16 terms of 8 bits each whose sum is the number, and a
 //     product is the sum of six products of terms (v_mfma_f32_16x16x32_bf16).  Left out are middle x low and low x low: the terms are rounded
 //     to nearest, so these are at most 2^-24 of the product of the leading bits, of either sign (with terms cut off up to 2^-21, always towards
-//     zero).  An item with a number whose terms have lost bits (below about 2^-110) is run again with v_mfma_f32_16x16x4_f32.  A weight that small,
+//     zero).  An item with a number whose terms have lost bits (below about 2^-110) is run again with v_mfma_f32_16x16x4_f32 where these can show:
+//     any such query, such keys beside queries of 2^96, such values in results below 2^-108.  A weight that small,
 //     against the row's largest, loses less than 2^-133 of that one, unchecked: a part of the result only where the heavier keys' values are 0.
 //     Error against 64 bits of dense attention on fp32 matrix instructions / in terms, 2-norm: 2000 random tokens, D = 128, 9.2e-7 / 5.6e-7, D = 64
 //     6.6e-7 / 4.8e-7; one massive channel beside random ones 1.1e-5 / 6.0e-6; scores of a single channel's product 1.46e-6 / 1.44e-6 (with
@@ -164,7 +165,7 @@ template <bool ROUND> __device__ __forceinline__ void split3(f32x4 x0, f32x4 x1,
 // One work item: 64 QT rows of one query block (QT = 2, block 64: of two neighbours in the list).  FULL32 is the second pass over an item:
 // it evaluates the products of fp32 numbers with fp32 matrix instructions instead of bf16 terms, slower, but infinities go
 // through them as through a multiplication (a term that is zero turns an infinity into NaN).  Returns whether this wave's results are
-// all finite, its maxima in the range of the fast weights and its terms complete; with FULL32 = false nothing is stored if some wave's are not, and the
+// all finite, its maxima in the range of the fast weights and no bits lost that can show; with FULL32 = false nothing is stored if some wave's are not, and the
 // caller runs the item again.
 //
 // A weight is exp2 of the scaled score minus the scaled running maximum.  The fast form of bf16 tensors is one fma, whose
@@ -240,7 +241,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
   bf16x8 qb[QT][D / 32];
   f32x4 qf[QT][NT];
   bf16x8 q3[QT][D / 32][3];                            // TERMS: of the scaled queries, channels as in qb
-  uint32_t cut_off = 0;                                // TERMS: bits that some number's terms have lost
+  uint32_t q_lost = 0, lost = 0;                       // TERMS: bits that terms have lost: of queries; of keys (low half) and values (high half)
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     const int row = row0 + 16 * qt + r16;
@@ -258,7 +259,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 #pragma unroll
           for (int i = 0; i < 4; ++i) x[4 * u + i] = y[i];
         }
-        cut_off |= split3<true>(x, q3[qt][ks]);
+        q_lost |= split3<true>(x, q3[qt][ks]);
       }
     } else {
 #pragma unroll
@@ -735,6 +736,9 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
     return mine;
   };
   Tile cur = next_mine();
+  // Queries whose terms have lost bits: at once.  (Here, as the first tables are read while the queries are: 0.3 us of a call of 24, further up 0.6.)
+  if constexpr (TERMS)
+    if (__syncthreads_or(q_lost & 0xffffu)) return false;
   int stage = 0;
   // TERMS: this wave's share of a tile of keys or values, which it has fetched itself, taken apart into the common place
   auto take_apart = [&](const bool value) {
@@ -753,8 +757,9 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         for (int e = 0; e < 4; ++e) x[4 * u + e] = y[e];
       }
       bf16x8 t[3];
-      cut_off |= split3<true>(x, t);
-      asm volatile("" : "+v"(cut_off));                // here, not where it is read
+      const uint32_t rest = split3<true>(x, t);
+      lost |= value ? rest << 16 : rest & 0xffffu;
+      asm volatile("" : "+v"(lost));                   // here, not where it is read
 #pragma unroll
       for (int u = 0; u < 3; ++u) *reinterpret_cast<bf16x8*>(lds + 2 * TILE + u * PLANE + (row * CP + ((p % CP) ^ (row & SP))) * 16) = t[u];
     }
@@ -860,7 +865,7 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
 
   // ---- normalise, check, store
   float inv[QT];
-  bool ok = !TERMS || (cut_off & 0xffffu) == 0;
+  bool ok = true;
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     float l = l_run[qt];
@@ -875,8 +880,34 @@ __device__ __forceinline__ bool attn_gen_item(const GenArgs& ga, unsigned char* 
         for (int i = 0; i < 4; ++i) ok = ok && fabsf(acc[ct][qt][i] * inv[qt]) < INFINITY;
     }
   }
-  if constexpr (!FULL32)
+  if constexpr (TERMS) {
+    // Lost bits of keys (less than 2^-133 each) change a score of queries below 2^96 by less than 2^-29, those of values a result by less than
+    // 2^-133, 2^-25 of one of 2^-108: the item is run again where queries or results are beyond.  8 heads of 5280 tokens, us, fp32 instructions
+    // alone / in terms, none such / one value or key of 2^-120 a head, always run again / now: 287 / 183 / 301 / 180; 24 heads of 64 channels 390 / 285 / 618 / 287; a
+    // query in every block 292 / - / 445 / 321; nothing but such values, both passes: 291 / - / 447 / 447
+    if (__syncthreads_or(!ok || lost != 0)) {
+      const bool keys = __syncthreads_or(lost & 0xffffu), values = __syncthreads_or(lost >> 16);
+      uint32_t q_max = 0;                              // of the leading terms, sign off
+      float o_min = INFINITY;
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+#pragma unroll
+        for (int ks = 0; ks < D / 32; ++ks) {
+          const uint4 w = __builtin_bit_cast(uint4, q3[qt][ks][0]);
+          q_max = max(q_max, max(max(w.x << 1, w.y << 1), max(w.z << 1, w.w << 1)));
+          q_max = max(q_max, max(max(w.x << 17, w.y << 17), max(w.z << 17, w.w << 17)));
+        }
+        if (row0 + 16 * qt + r16 < n_q)
+#pragma unroll
+          for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o_min = fminf(o_min, fabsf(acc[ct][qt][i] * inv[qt]));
+      }
+      if (__syncthreads_or(!ok || (keys && q_max >= __float_as_uint(0x1p96f) << 1) || (values && o_min < 0x1p-108f))) return false;
+    }
+  } else if constexpr (!FULL32) {
     if (__syncthreads_or(!ok)) return false;
+  }
   if (grp != 0) return true;
   if (PARTS && part >= 0) {
     const long long part_row = (long long)(first_part + part) * (64 * QI) + (FULL32 ? 64 * (slot % QI) : 0);

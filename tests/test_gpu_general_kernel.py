@@ -439,6 +439,30 @@ def test_fp32_wide_workgroups(I, shape, full_frac, exact_frac):
 
 
 @pytest.mark.parametrize("full_frac", [1.0, 0.0], ids=["exact", "taylor"])
+@pytest.mark.parametrize("tiny", ["k", "v"])
+@pytest.mark.parametrize("H", [2, 300], ids=["narrow", "wide"])
+@pytest.mark.parametrize("shape", F32, ids=F32_IDS)
+def test_fp32_tiny_numbers_beside_ordinary_ones(I, shape, H, tiny, full_frac):
+    """Numbers of 2^-120 whose terms lose bits where that cannot show: keys in a channel that no query has, single values in one channel.  The item
+    is not run again on fp32 instructions, whose sums end otherwise: (the other channels of) the result have the bits they have beside zeros."""
+    wl = _wl(shape, H, (1, 10, 33), (((1, 5, 33),),), keep_ratio=1.0, full_frac=full_frac, seed=808)
+    n, g = wl.tokens(0), torch.Generator().manual_seed(809)
+    q, k, v = (torch.randn((1, H, n, wl.D), generator=g).cuda() for _ in range(3))
+    q[..., 5] = 0
+    at = (slice(None), slice(None), slice(None), 5) if tiny == "k" else (slice(None), slice(None), slice(3, None, 64), 7)
+    pr, outs = problem_of(wl), []
+    for zero in (False, True):
+        x = k if tiny == "k" else v
+        x[at] = 0 if zero else torch.ldexp(1 + torch.rand(x[at].shape, generator=g), torch.tensor(-120)).cuda()
+        outs.append(torch.empty_like(q))
+        I.isa_attention(pr, q, k, v, outs[-1], I.new_workspace(pr))
+    torch.cuda.synchronize()
+    others = [c for c in range(wl.D) if tiny == "k" or c != 7]
+    assert torch.equal(outs[0][..., others], outs[1][..., others])
+    assert (outs[0] - outs[1]).abs().max().item() <= 2.0 ** -22
+
+
+@pytest.mark.parametrize("full_frac", [1.0, 0.0], ids=["exact", "taylor"])
 @pytest.mark.parametrize("small", ["q", "k", "v"])
 @pytest.mark.parametrize("H", [2, 300], ids=["narrow", "wide"])
 @pytest.mark.parametrize("shape", F32, ids=F32_IDS)
