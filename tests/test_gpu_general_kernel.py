@@ -264,8 +264,6 @@ def test_no_further_from_64_bits_than_the_storage_type(I, shape):
 @pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
 @pytest.mark.parametrize("H", [2, 520], ids=["narrow", "wide"])
 def test_infinities_pass_as_in_plain_arithmetic(I, shape, H):
-    if H == 520 and shape[0] == "f32":
-        pytest.skip("fp32 always takes 64-row workgroups")
     wl = _wl(shape, H, (1, 1, 4 * shape[2] + 17), (((1, 1, shape[2]),),), keep_ratio=1.0, full_frac=0.5, seed=771)
     Q, K, V, q, k, v = gen(wl)
     n = wl.tokens(0)
@@ -517,9 +515,29 @@ def test_full_and_ragged_tiles_of_one_list(I, shape, tail):
     check_end_to_end(I, wl, *gen(wl))
 
 
-@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[4]], ids=[SHAPE_IDS[0], SHAPE_IDS[4]])
-def test_rows_far_apart(I, shape):
-    D, n, stride = shape[1], 140, 2 ** 22
+# q, k, v and the result as a projection leaves them, [B, S, H, D]: a head's rows lie H D apart; 64- and 128-row workgroups, full and short tiles,
+# exact sets, the residual, batch items that differ, dense
+@pytest.mark.parametrize("H", [3, 150], ids=["narrow", "wide"])
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_token_layout(I, shape, H):
+    block = shape[2]
+    wl = _wl(shape, H, (1, 1, 5 * block + 40), (((1, 1, 4 * block + 9),), ((1, 1, 2 * block),)), B=2, keep_ratio=0.6, full_frac=0.6, exact_frac=0.25,
+             gamma=0.5, seed=821)
+    x = gen(wl)[3:]
+    xt = [t.transpose(1, 2).contiguous().transpose(1, 2) for t in x]
+    assert xt[0].stride(2) == H * wl.D
+    for f, pr in ((I.isa_attention, problem_of(wl)), (I.isa_attention, problem_of(wl, full_frac=0.0)), (I.isa_dense_attention, problem_of(wl))):
+        out, out_t = torch.zeros_like(x[0]), torch.zeros_like(xt[0])
+        f(pr, *x, out, I.new_workspace(pr))
+        f(pr, *xt, out_t, I.new_workspace(pr))
+        torch.cuda.synchronize()
+        assert torch.equal(out, out_t) and out.abs().max() > 0
+
+
+@pytest.mark.parametrize("stride", [2 ** 22 - 64, 2 ** 22])
+@pytest.mark.parametrize("shape", SHAPES, ids=SHAPE_IDS)
+def test_rows_far_apart(I, shape, stride):
+    D, n = shape[1], 140
     wl = _wl(shape, 1, (1, 1, n), ((),), seed=823)
     g = torch.Generator().manual_seed(wl.seed)
     x = [torch.randn((1, 1, n, D), generator=g).to(W.torch_dtype(wl.dtype)) for _ in range(3)]

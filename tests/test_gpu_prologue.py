@@ -398,6 +398,29 @@ def test_prologue_forms(I, dtype, D, block, src, H, tile):
             assert np.abs(f64(back[0, h]) - f64(x[0, h])).max() <= (2.0 ** -7 if dtype == "bf16" else 4e-6) * pair, (name, h)
 
 
+# [B, S, H, D] storage: the same bits as contiguous heads; a tensor a workgroup and the three in turn, streamed rows
+@pytest.mark.parametrize("H", [3, 60, 1300])
+@pytest.mark.parametrize("dtype,D,block", [("bf16", 128, 128), ("bf16", 128, 64), ("bf16", 64, 64), ("f32", 128, 128), ("f32", 64, 128), ("f32", 64, 64)])
+def test_prologue_token_layout(I, dtype, D, block, H):
+    wl = _wl(dtype, D, block, H, (3, 5, 31))
+    n = wl.tokens(0)
+    g = torch.Generator(device="cuda").manual_seed(435)
+    x = [torch.randn((1, H, n, D), generator=g, device="cuda").to(W.torch_dtype(dtype)) for _ in range(3)]
+    pr, grid = problem_of(wl), I.Grid(grids_of(wl), (2, 8, 8), ROPE[D], 10000.0)
+    res = []
+    for q, k, v in (x, [t.transpose(1, 2).contiguous().transpose(1, 2) for t in x]):
+        outs, back, raster = [torch.zeros_like(q) for _ in range(3)], [torch.zeros_like(q) for _ in range(3)], torch.zeros_like(q)
+        means = [torch.zeros((1, H, I.isa_get_counts(pr, 0)["T_max"], D), device="cuda") for _ in range(3)]
+        I.isa_prologue(pr, grid, q, k, v, *outs, *means)
+        I.isa_untile(pr, grid, outs[0], raster)
+        I.isa_prologue_backward(pr, grid, *outs, *back)
+        res.append([*outs, raster, *back, *means])
+    torch.cuda.synchronize()
+    assert res[1][0].stride(2) == H * D
+    for i, (a, b) in enumerate(zip(*res)):
+        assert torch.equal(a, b), i
+
+
 # rows cached (below 64 MB a tensor), stores streamed (prologue to 85 MB, isa_untile to 256 MB), loads too: the same bits as a call of one head; with the
 # table of sines and without
 @pytest.mark.parametrize("mb", [60, 72, 100, 270])
