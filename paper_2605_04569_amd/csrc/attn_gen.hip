@@ -1113,6 +1113,7 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
   GenArgs ga = {};
   ga.a = a;
   int n_long = 0, n_taylor = 0;
+  long long taylor_128 = 0;                            // Taylor items of 128 rows
   double set_share = 0.0;                              // of a long item's tokens, those a Taylor item reads for its exact set
   for (int b = 0; b < pr.p.B; ++b) {
     const BatchCounts& c = pr.cnt.b[b];
@@ -1120,11 +1121,11 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
     const int f = a.dense ? c.T : c.n_full, t = a.dense ? 0 : c.n_flat;
     n_long = f > n_long ? f : n_long;
     n_taylor = t > n_taylor ? t : n_taylor;
+    taylor_128 += pr.p.H * slots_of(pr.p.block, t, 128);
   }
   const long long bh = (long long)pr.p.B * pr.p.H;
   const bool d64 = pr.p.D == 64, bf = pr.p.dtype == ISA_BF16;
   const double chip = (double)N_XCD * cus_per_xcd();
-  auto items = [&](int n, int rows) { return bh * (pr.p.block >= rows ? n * (pr.p.block / rows) : (n + 1) / 2); };
   // The form of a workgroup (64 rows; 128, which read every LDS fragment once for two query tiles; bf16 also 64 in two groups of waves) and the parts per long item,
   // chosen together by a model of the call's time: with k workgroups per compute unit a block of 64 tokens takes each of them pace[k - 1]
   // us (k beyond what fits a compute unit: further rounds), and a workgroup spends `start` tokens' time on its start.  The merge of partial
@@ -1152,9 +1153,9 @@ hipError_t launch_attn_gen(const Problem& pr, const Workspace& ws, const AttnArg
   if (n_long == 0) {
     // Taylor items alone, 128 rows / 64, us by items of 128 rows: bf16, D = 64: 2928 179 / 219, 912 53 / 57, 304 35.7 / 35.4; D = 128: 2928
     // 341 / 457, 304 50 / 57, 288 33 / 37, 244 79 / 78; fp32, D = 64: 2928 202 / 221, 912 60.3 / 60.4, 304 39.4 / 38.8; D = 128: 2928 430 / 524,
-    // 288 39 / 41, 244 63 / 61.  With exact sets a pair of blocks of 64 reads both blocks' sets: bf16, 2928: D = 64 496 / 452, D = 128
+    // 288 39 / 41, 244 63 / 61; every batch item's own: 2 heads of 4977, 86 and 6481 tokens, bf16, D = 128, 182 items (306 if all were as long) 73 / 69.  With exact sets a pair of blocks of 64 reads both blocks' sets: bf16, 2928: D = 64 496 / 452, D = 128
     // 958 / 900; fp32 1207 / 885, 2424 / 1946.
-    two = !(set_share > 0.0 && pr.p.block == 64) && items(n_taylor, 128) >= chip * (bf ? (d64 ? 1.75 : 1.0) : d64 ? 3.5 : 1.0);
+    two = !(set_share > 0.0 && pr.p.block == 64) && taylor_128 >= chip * (bf ? (d64 ? 1.75 : 1.0) : d64 ? 3.5 : 1.0);
   } else {
     double best = INFINITY;
     for (int f = 0; f < (bf ? 3 : 2); ++f) {
