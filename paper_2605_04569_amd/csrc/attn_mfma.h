@@ -18,11 +18,13 @@ constexpr int V_TILE = MD * KT;   // bf16 elements of one V^T tile in LDS: 128 r
 constexpr float RESCALE_TAU = 8.0f;    // the running max is only raised when a tile exceeds it by 2^tau
 constexpr float M_INIT = -1.0e30f;
 
-// A load without a place in the caches: for the values that k_pack_vt packs, which would push out the keys that other workgroups read (the
-// attention kernels of the call read the packed copy).  Whole calls behind each other on changing inputs, us, cached / streamed: 20 heads of 6240 tokens
-// 189.5 / 186.8, 40 of 3168 146.5 / 142.9, 40 of 15 600 1166 / 1158; a training step, whose backward reads the values again: the same time.
-// Not so the output rows of k_attn_gen: alone, calls on contiguous heads were 1 to 2 % quicker past the caches, but what reads the output next finds
-// nothing there: with isa_untile and a copy behind it 24 heads of 3168, 64 channels, streamed / cached 89.6 / 88.2, fp32, 8 of 5280, 215.9 / 212.5.
+// A load without a place in the caches: for the values that the first kernel of a whole call packs, which would push out the queries and keys that
+// it reads beside them (the attention kernels read the packed copy).  Calls on changing inputs, with isa_untile and a copy of its output behind them, us,
+// cached / streamed: 20 heads of 6240 tokens 189.5 / 186.8, 40 of 3168 146.5 / 142.9, 40 of 15 600 1166 / 1158; a training step, whose backward
+// reads the values again, the same time.  Dense attention, which packs nothing but values, gains nothing and finds none that a call before has left:
+// 24 heads of 423 tokens 32.5 / 33.1, 16 of 6240 331 / 334.
+// Nor the output rows of k_attn_gen: alone, calls on contiguous heads were 1 to 2 % quicker past the caches, but what reads the output next finds
+// nothing there: with isa_untile and a copy 24 heads of 3168, 64 channels, cached / streamed 88.2 / 89.6, fp32, 8 of 5280, 212.5 / 215.9.
 __device__ __forceinline__ uint4 stream_load(const void* p) {
   typedef uint32_t u32x4_mem __attribute__((ext_vector_type(4)));
   const u32x4_mem r = __builtin_nontemporal_load(reinterpret_cast<const u32x4_mem*>(p));

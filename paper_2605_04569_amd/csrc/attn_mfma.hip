@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256) void k_pack_vt(const uint16_t* __restrict__ v,
       const uint16_t* const row = src[t] + base + (long long)(rg + 16 * i) * g.stride_t;
       val[t][i] = make_uint4(0, 0, 0, 0);
       if (rg + 16 * i < n) {
-        if (t == 0) val[t][i] = stream_load(row);
+        if (ALL && t == 0) val[t][i] = stream_load(row);
         else val[t][i] = *reinterpret_cast<const uint4*>(row);
       }
     }
