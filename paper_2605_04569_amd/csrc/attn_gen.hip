@@ -37,9 +37,10 @@
 // launch: vector instructions issuing in 94 -> 70 % of the cycles, matrix pipe busy 42 -> 62 %, no LDS bank conflicts.  Whole call 740 -> 651 us;
 // 128 channels 1271 -> 1133, dense attention of 8 such heads 1153 -> 977.  A kernel of one row per four lanes in scalar arithmetic took 11.6 ms.
 //
-// fp32 is bound by bf16 matrix instructions: six in place of eight fp32 ones that take twice as long each: 24 heads of 128 channels,
-// 15 600 tokens, 5.6 -> 3.2 ms a call (1.1 PFLOP/s of bf16 products), 64 channels in blocks of 64 2.97 -> 1.53 ms; 8 heads of 5280 tokens
-// 301 -> 190 us.  With 16 rows a wave the LDS reads take as long as the products, with 32 half of that.
+// fp32: six bf16 products in place of eight fp32 ones that take twice as long each: 24 heads of 128 channels, 15 600 tokens, 5.6 -> 3.2 ms a call (1.1
+// PFLOP/s of bf16 products), 64 channels in blocks of 64 2.96 -> 1.56 ms; 8 heads of 5280 tokens 301 -> 194 us.  Counters of the first / the last: matrix
+// pipe busy 54 / 49 % of the cycles, vector and matrix instructions at their port in 45 / 45 %; of the waves' cycles 40 / 39 % wait for a place there and
+// 22 / 25 % for data or at the four barriers of a tile.  With 16 rows a wave the LDS reads take as long as the products, with 32 half of that.
 #include <math.h>
 
 #include <type_traits>
