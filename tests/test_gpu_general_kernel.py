@@ -436,6 +436,27 @@ def test_fp32_wide_workgroups(I, shape, full_frac, exact_frac):
     check_end_to_end(I, wl, *gen(wl), heads=[0, 7, 150, 299])
 
 
+@pytest.mark.parametrize("H", [2, 300], ids=["narrow", "wide"])
+@pytest.mark.parametrize("shape", F32, ids=F32_IDS)
+def test_fp32_largest_number(I, shape, H):
+    """The largest number rounds to infinity in 8 bits: as a value, and as a key in a channel that no query has, it counts as in plain arithmetic."""
+    D, n = shape[1], 200
+    g = torch.Generator().manual_seed(810)
+    q, k, v = (torch.randn((1, H, n, D), generator=g) for _ in range(3))
+    top = torch.finfo(torch.float32).max
+    q[..., 9], k[:, :, 70:, 9] = 0, -top
+    v[:, :, 33, 3], v[:, :, 133, 4] = top, -top
+    pr = I.Problem(H=H, D=D, dtype="f32", block=shape[2], seg_len=[[n]], keep_ratio=1.0, full_frac=1.0)
+    out = torch.empty((1, H, n, D), device="cuda")
+    I.isa_dense_attention(pr, q.cuda(), k.cuda(), v.cuda(), out, I.new_workspace(pr))
+    torch.cuda.synchronize()
+    for h in (0, H - 1):
+        got, want = f64(out[0, h]), O.dense_attention(f64(q[0, h]), f64(k[0, h]), f64(v[0, h]))
+        for at in ([3, 4], [c for c in range(D) if c not in (3, 4)]):      # (norms of numbers of 2^120 are numbers in 64 bits)
+            rel = np.linalg.norm(got[:, at] - want[:, at]) / np.linalg.norm(want[:, at])
+            assert rel <= 30 * 2.0 ** -24, (h, rel)
+
+
 @pytest.mark.parametrize("full_frac", [1.0, 0.0], ids=["exact", "taylor"])
 @pytest.mark.parametrize("tiny", ["k", "v"])
 @pytest.mark.parametrize("H", [2, 300], ids=["narrow", "wide"])
